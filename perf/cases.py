@@ -70,7 +70,7 @@ def _log(rng, lo, hi):
     return max(lo, min(hi, int(round(float(lo) * (float(hi) / lo) ** rng.random()))))
 
 
-_IMAGES_AT_224 = 32     # no drawn net is larger than this many 224 x 224 images of the residual network
+_IMAGES_AT_224 = 32     # no drawn net does more than this many 224 x 224 images of the residual network, 80 % sparse
 
 
 def _draw_net(rng):
@@ -81,16 +81,16 @@ def _draw_net(rng):
         top //= 4
     size = {"vgg16": rng.randint(224, 255), "bottleneck": _log(rng, 7, 80), "inception_v3": rng.randint(150, 310)}.get(
         family, rng.randint(96, 288))
-    if family in ("resnet50", "inception_v3"):
-        top = max(1, min(top, int(_IMAGES_AT_224 // (1 if dtype == "f16" else 4) * 224 * 224 / (size * size))))
-    case = _net(family, dtype, _log(rng, 1, top), size)
+    options, kept = {}, 0.2
     if family == "resnet50":
-        case["recipe"] = rng.choice(["mixed", "uniform"])
-        if case["recipe"] == "uniform":
-            case["sparsity"] = round(rng.uniform(0.5, 0.95), 2)
-    elif family == "bottleneck":
-        case["sparsity"] = round(rng.uniform(0.5, 0.95), 2)
-    return case
+        options["recipe"] = rng.choice(["mixed", "uniform"])
+    if family == "bottleneck" or options.get("recipe") == "uniform":
+        options["sparsity"] = round(rng.uniform(0.5, 0.95), 2)
+        kept = max(0.2, 1.0 - options["sparsity"])
+    if family in ("resnet50", "inception_v3"):
+        room = _IMAGES_AT_224 / (1.0 if dtype == "f16" else 4.0) * 224 * 224 * 0.2 / kept
+        top = max(1, min(top, int(room / (size * size))))
+    return _net(family, dtype, _log(rng, 1, top), size, **options)
 
 
 def _draw_conv(rng):
