@@ -80,7 +80,7 @@ def layer_costs(ops, weights, in_shape, elem):
 
 
 KERNEL_OF_PREFIX = {"slinear": "sconv_linear_kernel", "squad": "sconv_quad_kernel", "stile": "sconv_stile_kernel", "sptile": "sconv_ptile_kernel",
-                    "swide": "sconv_wtile_kernel",
+                    "swide": "sconv_wtile_kernel", "cl": "cl_conv_kernel",
                     "sdirect": "sconv_direct_kernel", "sconv": "sconv_tile_kernel",
                     "dense": "dense_conv_kernel", "sfc": "sfc_kernel", "dwconv": "dwconv_kernel", "maxpool": "windowpool_kernel",
                     "avgpool": "avgpool_kernel", "avgpool2d": "windowpool_kernel", "concat": "windowpool_kernel",
@@ -94,7 +94,7 @@ def kernel_of(variant: str) -> str:
     return KERNEL_OF_PREFIX.get(variant.split("_")[0], variant)
 
 
-MFMA_KERNELS = ("dense_conv_kernel", "dense_wide_kernel")
+MFMA_KERNELS = ("dense_conv_kernel", "dense_wide_kernel", "cl_conv_kernel")
 
 
 def main() -> int:

@@ -452,7 +452,13 @@ class Net:
         """Pins every convolution op to the named variant (a saved tuning result: the list
         `variants()` returned).  An op that shares another op's launch here but had a launch of
         its own when the list was saved belongs to a group that tuning took apart: the group
-        is taken apart first."""
+        is taken apart first.  (A list made on plane layouts takes a channels-last net there, and the
+        other way round: the first name decides, before the groups are looked at.)"""
+        for i, (op, name) in enumerate(zip(self.ops, names)):
+            if op.kind == "conv" and name != "fused":
+                if name.startswith("cl_") != self.op_variant(i).startswith("cl_"):
+                    self.set_op_variant(i, name)
+                break
         infos = [self.op_info(i) for i in range(len(self.ops))]
         apart = sorted({infos[i]["fused_into"] for i, name in enumerate(names)
                         if infos[i]["launched_with"] and name != "fused"})

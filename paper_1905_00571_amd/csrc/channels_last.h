@@ -1,0 +1,85 @@
+// Channels-last tensors and the kernels that work on them (the net runner's matrix-core path).
+#pragma once
+
+#include "internal.h"
+
+namespace cadnn {
+
+// One image of a channels-last activation tensor: (h + 2 * ph) rows of (w + 2 * pw) pixels, the
+// channels of a pixel side by side.  A pixel holds `pix` elements, the tensor's own c channels first
+// (a slice of a concatenation has the pix of the whole); elements behind them and the halo are
+// kept at zero by whoever owns the buffer, like the halo of the plane layout.
+struct ClDesc {
+    int c, h, w;
+    int ph, pw;
+    int pix, row;       // elements from one pixel to the next, from one row to the next
+    int origin;         // element of pixel (0, 0)
+    int64_t image;      // elements from one image to the next
+};
+
+// A pixel's channels are read 64 or 128 bytes at a time, so regions pad them to 64 bytes.
+inline int cl_padded_channels(int c, size_t elem) {
+    const int unit = (int)(64 / elem);
+    return (c + unit - 1) / unit * unit;
+}
+inline ClDesc cl_desc(int c, int h, int w, int ph, int pw, int pix) {
+    ClDesc d;
+    d.c = c; d.h = h; d.w = w; d.ph = ph; d.pw = pw; d.pix = pix;
+    d.row = (w + 2 * pw) * pix;
+    d.origin = ph * d.row + pw * pix;
+    d.image = (int64_t)(h + 2 * ph) * d.row;
+    return d;
+}
+
+constexpr int kClMaxTaps = 64;
+
+// The weights of one layer as the matrix-core kernel reads them: K in steps of `rb` bytes per row
+// (rb / elem input channels of one filter tap, taps in order, only those that some filter uses; a
+// fused shortcut's channels follow), 64 output channels x one step side by side as [64][rb] with
+// the 16-byte pieces of a row in the order the kernel keeps them in LDS.
+struct ClPlan {
+    DevBuf w;
+    int rb = 0, steps = 0, steps_tap = 0, taps = 0, steps2 = 0;
+    int tap_r[kClMaxTaps], tap_c[kClMaxTaps];
+    bool stem = false;          // input packed 4 channels a pixel, a step is one filter row
+    // K split over workgroups: partial tiles and arrival counters
+    DevBuf part, count;
+};
+
+// Tiles a layer can be run with: 64 * mi output channels x 64 * ni output pixels.
+struct ClVariant {
+    const char* name;
+    int mi, ni, sk;
+};
+const std::vector<ClVariant>& all_cl_variants();
+
+struct ClConv {
+    const ClPlan* plan;
+    const void* x; ClDesc xd;
+    void* y; ClDesc yd;
+    const void* residual; ClDesc rd;
+    const void* x2; ClDesc x2d; int stride2;     // fused 1x1 shortcut (plan->steps2 > 0)
+    const float* bias; const float* bias2;
+    int n, cout, stride, pad, relu;
+};
+
+cadnn_status cl_build_plan(const cadnn_weights* w, const cadnn_weights* shortcut, int rb, bool stem, ClPlan* plan);
+// The tile the cost rule takes, and whether a variant can run the layer.
+const ClVariant* cl_pick(const cadnn_weights* w, const ClPlan& plan, int64_t pixels, bool f16);
+bool cl_variant_fits(const ClVariant& v, const ClPlan& plan, int64_t pixels, int cout);
+// Scratch of a split-K variant (no-op otherwise).
+cadnn_status cl_prepare_variant(const ClVariant& v, ClPlan* plan, int64_t pixels, int cout);
+cadnn_status launch_cl_conv(const ClConv& c, const ClVariant& v, bool f16, hipStream_t s);
+
+// [n][c][h][w] (the caller's input) -> channels-last.
+cadnn_status launch_cl_import(const void* x, int n, int c, int h, int w, void* y, const ClDesc& yd, bool f16, hipStream_t s);
+// channels-last -> [n][c][h][w].
+cadnn_status launch_cl_export(const void* x, const ClDesc& xd, void* y, int n, bool f16, hipStream_t s);
+// Window pools (kind 0: maximum, 1: mean over the in-image part); k = 1 copies.  flat: y is [n][c][h][w].
+cadnn_status launch_cl_pool(const void* x, const ClDesc& xd, void* y, const ClDesc& yd, bool flat, int n, int k, int stride,
+                            int pad, int kind, bool f16, hipStream_t s);
+cadnn_status launch_cl_gap(const void* x, const ClDesc& xd, void* y, int n, bool f16, hipStream_t s);
+cadnn_status launch_cl_depthwise(const cadnn_weights* w, const void* x, const ClDesc& xd, void* y, const ClDesc& yd, int n,
+                                 int stride, int pad, const float* bias, int relu, bool f16, hipStream_t s);
+
+}  // namespace cadnn

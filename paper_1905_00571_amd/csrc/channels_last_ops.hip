@@ -1,0 +1,293 @@
+// The layers between the convolutions of a channels-last net: import of the caller's [n][c][h][w]
+// tensor, export of the last map, window pools, global average pool, depthwise layers.
+//
+// All of them move each element once and are bound by memory; a thread works on 16 bytes of one
+// pixel's channels, neighbouring threads on neighbouring pieces, so every access is a run of whole
+// cache lines, and the taps of a window need no unaligned or 2-byte access at all.
+#include <algorithm>
+
+#include "channels_last.h"
+
+namespace cadnn {
+
+namespace {
+
+typedef _Float16 clo_h8 __attribute__((ext_vector_type(8)));
+typedef float clo_f4 __attribute__((ext_vector_type(4)));
+template <typename T> struct ClVec;
+template <> struct ClVec<_Float16> { typedef clo_h8 type; static constexpr int N = 8; };
+template <> struct ClVec<float> { typedef clo_f4 type; static constexpr int N = 4; };
+
+// Few channels (c <= 4, packed 4 to a pixel): one thread per pixel.
+template <typename T>
+__global__ __launch_bounds__(256) void cl_import4_kernel(const T* __restrict__ x, T* __restrict__ y, ClDesc yd, int c, int n) {
+    const int hw = yd.h * yd.w;
+    const int64_t i = (int64_t)blockIdx.x * 256 + threadIdx.x;
+    if (i >= (int64_t)n * hw) return;
+    const int img = (int)(i / hw), q = (int)(i - (int64_t)img * hw);
+    const int r = q / yd.w, col = q - r * yd.w;
+    typedef T v4 __attribute__((ext_vector_type(4)));
+    v4 v;
+#pragma unroll
+    for (int k = 0; k < 4; ++k) v[k] = k < c ? x[((int64_t)img * c + k) * hw + q] : (T)0.0f;
+    *(v4*)(y + (int64_t)img * yd.image + yd.origin + (int64_t)r * yd.row + (int64_t)col * yd.pix) = v;
+}
+
+// A tile of 64 pixels x 64 channels is transposed through LDS, in either direction.
+template <typename T>
+__global__ __launch_bounds__(256) void cl_import_kernel(const T* __restrict__ x, T* __restrict__ y, ClDesc yd, int c) {
+    constexpr int N = ClVec<T>::N, PITCH = 64 + N;
+    typedef typename ClVec<T>::type V;
+    __shared__ __attribute__((aligned(16))) T tile[64 * PITCH];      // [pixel][channel]
+    const int hw = yd.h * yd.w, lane = threadIdx.x & 63, wv = threadIdx.x >> 6;
+    const int q0 = blockIdx.x * 64, c0 = blockIdx.y * 64, img = blockIdx.z;
+#pragma unroll
+    for (int k = 0; k < 16; ++k) {
+        const int ch = wv + 4 * k;
+        const bool ok = c0 + ch < c && q0 + lane < hw;
+        tile[lane * PITCH + ch] = ok ? x[((int64_t)img * c + c0 + ch) * hw + q0 + lane] : (T)0.0f;
+    }
+    __syncthreads();
+    for (int i = threadIdx.x; i < 64 * (64 / N); i += 256) {
+        const int p = i / (64 / N), piece = i % (64 / N), q = q0 + p;
+        // (whole pieces: the channels behind the last one are the region's zeros)
+        if (q >= hw || c0 + piece * N >= c) continue;
+        const int r = q / yd.w, col = q - r * yd.w;
+        *(V*)(y + (int64_t)img * yd.image + yd.origin + (int64_t)r * yd.row + (int64_t)col * yd.pix + c0 + piece * N) =
+            *(const V*)(tile + p * PITCH + piece * N);
+    }
+}
+
+template <typename T>
+__global__ __launch_bounds__(256) void cl_export_kernel(const T* __restrict__ x, ClDesc xd, T* __restrict__ y) {
+    constexpr int N = ClVec<T>::N, PITCH = 64 + N;
+    typedef typename ClVec<T>::type V;
+    __shared__ __attribute__((aligned(16))) T tile[64 * PITCH];
+    const int hw = xd.h * xd.w, lane = threadIdx.x & 63, wv = threadIdx.x >> 6;
+    const int q0 = blockIdx.x * 64, c0 = blockIdx.y * 64, img = blockIdx.z;
+    for (int i = threadIdx.x; i < 64 * (64 / N); i += 256) {
+        const int p = i / (64 / N), piece = i % (64 / N), q = q0 + p;
+        if (q >= hw || c0 + piece * N >= xd.c) continue;
+        const int r = q / xd.w, col = q - r * xd.w;
+        *(V*)(tile + p * PITCH + piece * N) =
+            *(const V*)(x + (int64_t)img * xd.image + xd.origin + (int64_t)r * xd.row + (int64_t)col * xd.pix + c0 + piece * N);
+    }
+    __syncthreads();
+#pragma unroll
+    for (int k = 0; k < 16; ++k) {
+        const int ch = wv + 4 * k;
+        if (c0 + ch < xd.c && q0 + lane < hw) y[((int64_t)img * xd.c + c0 + ch) * hw + q0 + lane] = tile[lane * PITCH + ch];
+    }
+}
+
+// One thread per output pixel and 16-byte piece of channels.  KIND 0: maximum, 1: mean over the
+// in-image part of the window.
+template <typename T, int KIND>
+__global__ __launch_bounds__(256) void cl_pool_kernel(const T* __restrict__ x, ClDesc xd, T* __restrict__ y, ClDesc yd, int flat,
+                                                      int n, int k, int stride, int pad) {
+    constexpr int N = ClVec<T>::N;
+    typedef typename ClVec<T>::type V;
+    const int pieces = yd.c / N;
+    const int64_t i = (int64_t)blockIdx.x * 256 + threadIdx.x;
+    const int64_t px = i / pieces;
+    const int piece = (int)(i - px * pieces), hw = yd.h * yd.w;
+    if (px >= (int64_t)n * hw) return;
+    const int img = (int)(px / hw), q = (int)(px - (int64_t)img * hw);
+    const int oh = q / yd.w, ow = q - oh * yd.w;
+    const T* xp = x + (int64_t)img * xd.image + xd.origin + piece * N;
+    V m;
+    float sum[N];
+#pragma unroll
+    for (int j = 0; j < N; ++j) { m[j] = -(T)__builtin_inff(); sum[j] = 0.0f; }
+    int seen = 0;
+    for (int a = 0; a < k; ++a) {
+        const int ih = oh * stride + a - pad;
+        if (ih < 0 || ih >= xd.h) continue;
+        for (int b = 0; b < k; ++b) {
+            const int iw = ow * stride + b - pad;
+            if (iw < 0 || iw >= xd.w) continue;
+            const V v = *(const V*)(xp + (int64_t)ih * xd.row + (int64_t)iw * xd.pix);
+            if constexpr (KIND == 0) {
+                m = __builtin_elementwise_max(m, v);
+            } else {
+#pragma unroll
+                for (int j = 0; j < N; ++j) sum[j] += (float)v[j];
+            }
+            ++seen;
+        }
+    }
+    if constexpr (KIND == 1) {
+        const float d = seen ? (float)seen : 1.0f;
+#pragma unroll
+        for (int j = 0; j < N; ++j) m[j] = (T)(sum[j] / d);
+    } else if (!seen) {
+#pragma unroll
+        for (int j = 0; j < N; ++j) m[j] = (T)0.0f;
+    }
+    if (flat) {
+#pragma unroll
+        for (int j = 0; j < N; ++j) y[((int64_t)img * yd.c + piece * N + j) * hw + q] = m[j];
+    } else {
+        *(V*)(y + (int64_t)img * yd.image + yd.origin + (int64_t)oh * yd.row + (int64_t)ow * yd.pix + piece * N) = m;
+    }
+}
+
+// One workgroup per image and 8 pieces of channels: 32 threads share the pixels of a piece.
+template <typename T>
+__global__ __launch_bounds__(256) void cl_gap_kernel(const T* __restrict__ x, ClDesc xd, T* __restrict__ y) {
+    constexpr int N = ClVec<T>::N;
+    typedef typename ClVec<T>::type V;
+    __shared__ float part[32][8 * N + 1];
+    const int piece = threadIdx.x & 7, who = threadIdx.x >> 3, img = blockIdx.y;
+    const int c0 = (blockIdx.x * 8 + piece) * N, hw = xd.h * xd.w;
+    float s[N];
+#pragma unroll
+    for (int j = 0; j < N; ++j) s[j] = 0.0f;
+    if (c0 < xd.c) {
+        const T* xp = x + (int64_t)img * xd.image + xd.origin + c0;
+        for (int q = who; q < hw; q += 32) {
+            const int r = q / xd.w, col = q - r * xd.w;
+            const V v = *(const V*)(xp + (int64_t)r * xd.row + (int64_t)col * xd.pix);
+#pragma unroll
+            for (int j = 0; j < N; ++j) s[j] += (float)v[j];
+        }
+    }
+#pragma unroll
+    for (int j = 0; j < N; ++j) part[who][piece * N + j] = s[j];
+    __syncthreads();
+    const int ch = (int)threadIdx.x, first = (int)blockIdx.x * 8 * N;
+    if (ch < 8 * N && first + ch < xd.c) {
+        float t = 0.0f;
+        for (int k = 0; k < 32; ++k) t += part[k][ch];
+        y[(int64_t)img * xd.c + first + ch] = (T)(t / (float)hw);
+    }
+}
+
+// 3 x 3 depthwise layer on a tensor whose halo holds the padding: a thread keeps the filters of its
+// piece of channels and three columns of input in registers and walks R output rows down, so a new
+// row of output costs 3 (stride 1) or 6 (stride 2) loads instead of 9.
+template <typename T, int STRIDE>
+__global__ __launch_bounds__(256) void cl_dw3_kernel(const T* __restrict__ x, ClDesc xd, T* __restrict__ y, ClDesc yd,
+                                                     const float* __restrict__ w, const float* __restrict__ bias, int n, int pad,
+                                                     int relu, int rows) {
+    constexpr int N = ClVec<T>::N;
+    typedef typename ClVec<T>::type V;
+    const int pieces = yd.c / N, strips = (yd.h + rows - 1) / rows;
+    const int64_t i = (int64_t)blockIdx.x * 256 + threadIdx.x;
+    int64_t rest = i / pieces;
+    const int piece = (int)(i - rest * pieces);
+    const int ow = (int)(rest % yd.w);
+    rest /= yd.w;
+    const int strip = (int)(rest % strips), img = (int)(rest / strips);
+    if (img >= n) return;
+    const int oh0 = strip * rows, oh1 = min(oh0 + rows, yd.h);
+    float wt[9][N], b[N];
+    const float* wp = w + (size_t)piece * N * 9;
+#pragma unroll
+    for (int j = 0; j < N; ++j) {
+#pragma unroll
+        for (int t = 0; t < 9; ++t) wt[t][j] = wp[j * 9 + t];
+        b[j] = bias ? bias[piece * N + j] : 0.0f;
+    }
+    const T* xp = x + (int64_t)img * xd.image + xd.origin - (int64_t)pad * xd.row + (int64_t)(ow * STRIDE - pad) * xd.pix + piece * N;
+    T* yp = y + (int64_t)img * yd.image + yd.origin + (int64_t)ow * yd.pix + piece * N;
+    V in[3][3];
+    auto load_row = [&](int slot, int ir) __attribute__((always_inline)) {
+#pragma unroll
+        for (int k = 0; k < 3; ++k) in[slot][k] = *(const V*)(xp + (int64_t)ir * xd.row + (int64_t)k * xd.pix);
+    };
+#pragma unroll
+    for (int r = 0; r < 3 - STRIDE; ++r) load_row(r, oh0 * STRIDE + r);
+    for (int oh = oh0; oh < oh1; ++oh) {
+#pragma unroll
+        for (int r = 3 - STRIDE; r < 3; ++r) load_row(r, oh * STRIDE + r);
+        float s[N];
+#pragma unroll
+        for (int j = 0; j < N; ++j) s[j] = 0.0f;
+#pragma unroll
+        for (int r = 0; r < 3; ++r)
+#pragma unroll
+            for (int k = 0; k < 3; ++k)
+#pragma unroll
+                for (int j = 0; j < N; ++j) s[j] = fmaf(wt[r * 3 + k][j], (float)in[r][k][j], s[j]);
+        V o;
+#pragma unroll
+        for (int j = 0; j < N; ++j) {
+            float v = s[j] + b[j];
+            if (relu) v = v > 0.0f ? v : 0.0f;
+            o[j] = (T)v;
+        }
+        *(V*)(yp + (int64_t)oh * yd.row) = o;
+#pragma unroll
+        for (int r = 0; r < 3 - STRIDE; ++r)
+#pragma unroll
+            for (int k = 0; k < 3; ++k) in[r][k] = in[r + STRIDE][k];
+    }
+}
+
+}  // namespace
+
+cadnn_status launch_cl_import(const void* x, int n, int c, int h, int w, void* y, const ClDesc& yd, bool f16, hipStream_t s) {
+    if (yd.pix == 4) {
+        const unsigned blocks = (unsigned)(((int64_t)n * h * w + 255) / 256);
+        if (f16) CADNN_LAUNCH(cl_import4_kernel<_Float16>, dim3(blocks), dim3(256), 0, s, (const _Float16*)x, (_Float16*)y, yd, c, n);
+        else CADNN_LAUNCH(cl_import4_kernel<float>, dim3(blocks), dim3(256), 0, s, (const float*)x, (float*)y, yd, c, n);
+    } else {
+        const dim3 grid((unsigned)((h * w + 63) / 64), (unsigned)((c + 63) / 64), (unsigned)n);
+        if (f16) CADNN_LAUNCH(cl_import_kernel<_Float16>, grid, dim3(256), 0, s, (const _Float16*)x, (_Float16*)y, yd, c);
+        else CADNN_LAUNCH(cl_import_kernel<float>, grid, dim3(256), 0, s, (const float*)x, (float*)y, yd, c);
+    }
+    CADNN_HIP(hipGetLastError());
+    return CADNN_OK;
+}
+
+cadnn_status launch_cl_export(const void* x, const ClDesc& xd, void* y, int n, bool f16, hipStream_t s) {
+    const dim3 grid((unsigned)((xd.h * xd.w + 63) / 64), (unsigned)((xd.c + 63) / 64), (unsigned)n);
+    if (f16) CADNN_LAUNCH(cl_export_kernel<_Float16>, grid, dim3(256), 0, s, (const _Float16*)x, xd, (_Float16*)y);
+    else CADNN_LAUNCH(cl_export_kernel<float>, grid, dim3(256), 0, s, (const float*)x, xd, (float*)y);
+    CADNN_HIP(hipGetLastError());
+    return CADNN_OK;
+}
+
+cadnn_status launch_cl_pool(const void* x, const ClDesc& xd, void* y, const ClDesc& yd, bool flat, int n, int k, int stride,
+                            int pad, int kind, bool f16, hipStream_t s) {
+    const int64_t items = (int64_t)n * yd.h * yd.w * (yd.c / (f16 ? 8 : 4));
+    const dim3 grid((unsigned)((items + 255) / 256)), block(256);
+    const int fl = flat ? 1 : 0;
+    if (f16 && kind == 0) CADNN_LAUNCH((cl_pool_kernel<_Float16, 0>), grid, block, 0, s, (const _Float16*)x, xd, (_Float16*)y, yd, fl, n, k, stride, pad);
+    else if (f16) CADNN_LAUNCH((cl_pool_kernel<_Float16, 1>), grid, block, 0, s, (const _Float16*)x, xd, (_Float16*)y, yd, fl, n, k, stride, pad);
+    else if (kind == 0) CADNN_LAUNCH((cl_pool_kernel<float, 0>), grid, block, 0, s, (const float*)x, xd, (float*)y, yd, fl, n, k, stride, pad);
+    else CADNN_LAUNCH((cl_pool_kernel<float, 1>), grid, block, 0, s, (const float*)x, xd, (float*)y, yd, fl, n, k, stride, pad);
+    CADNN_HIP(hipGetLastError());
+    return CADNN_OK;
+}
+
+cadnn_status launch_cl_gap(const void* x, const ClDesc& xd, void* y, int n, bool f16, hipStream_t s) {
+    const int per = f16 ? 64 : 32;
+    const dim3 grid((unsigned)((xd.c + per - 1) / per), (unsigned)n);
+    if (f16) CADNN_LAUNCH(cl_gap_kernel<_Float16>, grid, dim3(256), 0, s, (const _Float16*)x, xd, (_Float16*)y);
+    else CADNN_LAUNCH(cl_gap_kernel<float>, grid, dim3(256), 0, s, (const float*)x, xd, (float*)y);
+    CADNN_HIP(hipGetLastError());
+    return CADNN_OK;
+}
+
+cadnn_status launch_cl_depthwise(const cadnn_weights* w, const void* x, const ClDesc& xd, void* y, const ClDesc& yd, int n,
+                                 int stride, int pad, const float* bias, int relu, bool f16, hipStream_t s) {
+    // rows a thread walks: as many as still leave the chip a few workgroups per CU
+    const int64_t columns = (int64_t)n * yd.w * (yd.c / (f16 ? 8 : 4));
+    int rows = 14;
+    while (rows > 2 && columns * ((yd.h + rows - 1) / rows) < 256 * 1024) rows = (rows + 1) / 2;
+    const int64_t items = columns * ((yd.h + rows - 1) / rows);
+    const dim3 grid((unsigned)((items + 255) / 256)), block(256);
+    const float* wt = (const float*)w->d_dw.p;
+#define CADNN_CL_DW(T, S) CADNN_LAUNCH((cl_dw3_kernel<T, S>), grid, block, 0, s, (const T*)x, xd, (T*)y, yd, wt, bias, n, pad, relu, rows)
+    if (f16 && stride == 1) CADNN_CL_DW(_Float16, 1);
+    else if (f16) CADNN_CL_DW(_Float16, 2);
+    else if (stride == 1) CADNN_CL_DW(float, 1);
+    else CADNN_CL_DW(float, 2);
+#undef CADNN_CL_DW
+    CADNN_HIP(hipGetLastError());
+    return CADNN_OK;
+}
+
+}  // namespace cadnn

@@ -7,78 +7,11 @@
 
 #include <iterator>
 
-#include "internal.h"
+#include "net.h"
 
 using namespace cadnn;
 
 namespace {
-
-enum OpKind { OP_CONV, OP_FC, OP_MAXPOOL, OP_AVGPOOL, OP_DEPTHWISE, OP_AVGPOOL2D, OP_CONCAT };
-
-struct Shape {
-    int n = 0, c = 0, h = 0, w = 0;
-    size_t elems() const { return (size_t)n * c * h * w; }
-    bool operator==(const Shape& o) const { return n == o.n && c == o.c && h == o.h && w == o.w; }
-};
-
-// Where a tensor lives: -1 = the caller's x, -2 = the caller's y, otherwise the output of
-// op `inst` inside the workspace.  Every op output has a region of its own, so a halo
-// that is zeroed once stays zero (kernels only write the image proper).
-struct NetOp {
-    OpKind kind;
-    const cadnn_weights* w = nullptr;
-    const void* bias = nullptr;
-    int stride = 1, pad = 0, relu = 0, k = 0;
-    int src = 0, dst = 0, res = -1;          // buffer ids as given by the caller
-    Shape in, out;
-    int src_inst = -1, res_inst = -1;        // producing op of each input (-1 = net input)
-    TensorDesc xd, yd, rd;
-    size_t y_off = 0;                        // byte offset of this op's output region
-    int shortcut = -1;                       // conv: the 1x1 projection op fused into this one
-    int pool_op = -1;                        // conv: the global average pool op fused into this one
-    int dw_op = -1;                          // conv: the depthwise op fused into this one
-    int fused_into = -1;                     // projection / pool / depthwise: the op that now computes it (it is skipped)
-    // concatenation: its sources (src / src_inst repeat the first), the first output channel of
-    // each, and whether the source's producer writes its slice of this op's region itself
-    std::vector<int> srcs, src_insts, ch_off;
-    std::vector<char> in_place;
-    int slice_of = -1;                       // producer: the concatenation whose region it writes into ...
-    int slice_ch = 0;                        // ... starting at this channel
-    // 1x1 layers that read the same tensor pixel by pixel are merged into ONE launch with the
-    // rows of all of them (a horizontal fusion): the first carries the others as `siblings`
-    // and writes a region with the channels of all; a sibling is skipped (fused_into = the
-    // first) and its output is the channel slice [sib_ch, sib_ch + cout) of that region
-    std::vector<int> siblings;
-    int sibling_of = -1, sib_ch = 0, launch_c = 0;   // launch_c: channels the launch writes (own + siblings')
-    // Independent layers (different inputs, different weights) whose inputs are all ready when
-    // the first of them runs are launched with it as ONE kernel: the first carries the others
-    // as `comates`; a comate is skipped (fused_into = colaunch_of = the first).  Its tensors are
-    // its own, untouched by this.
-    std::vector<int> comates;
-    int colaunch_of = -1;
-    // A window pool is launched right after the op that completes its input (hoisted_to; that op
-    // lists it in `hoisted`) instead of at its place in the op list, so that the layer reading
-    // it can join the launch of layers that come before the pool in the list.  The members of
-    // a group that tuning disbanded stay behind its first op the same way.
-    int hoisted_to = -1;
-    std::vector<int> hoisted;
-    // A large stride-2 layer with a filter wider than 1x1 whose input could not be kept
-    // de-interleaved where it is produced (odd sizes, other readers, a concatenation) reads a
-    // de-interleaved copy made right before it: xd describes the copy at x_off, src_d the
-    // tensor it is made from.
-    bool restaged = false;
-    size_t x_off = 0;
-    TensorDesc src_d;
-};
-
-// The one kernel of a group of co-launched layers: the variant that serves them all and the
-// members' launch records in device memory (with the plans they point into).
-struct CoLaunch {
-    const ConvVariant* v = nullptr;
-    DevBuf table;
-    std::vector<std::shared_ptr<ConvPlan>> plans;
-    std::vector<ConvLaunch> records;   // host copy of the table (the launch derives the grid from it)
-};
 
 // Weights, bias and output layout an op is launched with: its own, or -- first op of a sibling
 // group -- the merged ones.
@@ -125,30 +58,6 @@ cadnn_status static_workspace(void** ptr) {
     return CADNN_OK;
 }
 }  // namespace
-
-struct cadnn_net {
-    cadnn_dtype dtype = CADNN_F32;
-    Shape input;
-    std::vector<NetOp> ops;
-    std::map<int, Shape> cur;        // shape currently held by each buffer id while building
-    std::map<int, int> producer;     // op that last wrote each buffer id (-1 = net input)
-    size_t ws_bytes = 0;
-    bool laid_out = false;
-    bool finalized = false;
-    bool use_graph = false;
-    bool want_tune = false;
-    bool allow_s2d = true;
-    bool allow_fusion = true;
-    char* ws = nullptr;
-    bool static_ws = false;          // the workspace is the library's static array (CADNN_NET_STATIC_WORKSPACE)
-    std::map<int, std::unique_ptr<cadnn_weights>> merged_w;   // per first op of a sibling group
-    std::map<int, std::unique_ptr<DevBuf>> merged_bias;
-    std::map<int, std::unique_ptr<CoLaunch>> colaunch;        // per first op of a group of co-launched layers
-    hipGraphExec_t exec = nullptr;
-    const void* cap_x = nullptr;
-    void* cap_y = nullptr;
-    size_t elem() const { return dtype == CADNN_F16 ? 2 : 4; }
-};
 
 namespace {
 
@@ -542,19 +451,29 @@ struct Layout {
         }
     }
 
+    void run() {
+        choose_halos();
+        place_concat_slices();
+        merge_siblings();
+        choose_deinterleaved();
+        place_regions();
+        fuse();
+        share_launches();
+        net->ws_bytes = off;
+    }
 };
 
 void layout(cadnn_net* net) {
     Layout l(net);
-    l.choose_halos();
-    l.place_concat_slices();
-    l.merge_siblings();
-    l.choose_deinterleaved();
-    l.place_regions();
-    l.fuse();
-    l.share_launches();
-    net->ws_bytes = l.off;
+    l.run();
     net->laid_out = true;
+    // channels-last execution, where it is expected to be the faster one (the plane layouts above
+    // stay: pinning one of their variants takes the net back to them, so the workspace holds either)
+    net->cl.reset();
+    if (net->allow_s2d && net->allow_fusion && cl_expected_faster(net)) {
+        net->cl = cl_layout(net);
+        if (net->cl) net->ws_bytes = std::max(net->ws_bytes, net->cl->ws_bytes);
+    }
 }
 
 int out_s2d(const NetOp& op) {
@@ -689,6 +608,7 @@ cadnn_status restage_input(cadnn_net* net, const NetOp& op, const void* x, hipSt
 }
 
 cadnn_status launch_one(cadnn_net* net, size_t i, const void* x, void* y, hipStream_t s) {
+    if (net->cl) return cl_launch_one(net, i, x, y, s);
     const NetOp& op = net->ops[i];
     if (op.fused_into >= 0) return CADNN_OK;     // computed inside (or launched with) another op
     cadnn_status rs = restage_input(net, op, x, s);
@@ -740,12 +660,19 @@ cadnn_status launch_one(cadnn_net* net, size_t i, const void* x, void* y, hipStr
 }
 
 // The ops in launch order: the op list's, but for the hoisted pools.
-cadnn_status launch_all(cadnn_net* net, const void* x, void* y, hipStream_t s) {
+std::vector<size_t> launch_order(const cadnn_net* net) {
+    std::vector<size_t> order;
     for (size_t i = 0; i < net->ops.size(); ++i) {
-        if (net->ops[i].hoisted_to >= 0) continue;
+        if (!net->cl && net->ops[i].hoisted_to >= 0) continue;
+        order.push_back(i);
+        if (!net->cl) for (int h : net->ops[i].hoisted) order.push_back((size_t)h);
+    }
+    return order;
+}
+
+cadnn_status launch_all(cadnn_net* net, const void* x, void* y, hipStream_t s) {
+    for (size_t i : launch_order(net)) {
         cadnn_status st = launch_one(net, i, x, y, s);
-        for (size_t k = 0; k < net->ops[i].hoisted.size() && st == CADNN_OK; ++k)
-            st = launch_one(net, (size_t)net->ops[i].hoisted[k], x, y, s);
         if (st != CADNN_OK) return st;
     }
     return CADNN_OK;
@@ -762,6 +689,7 @@ void drop_graph(cadnn_net* net) {
 // the data an ordinary pass leaves in its input region, then every group of co-launched layers
 // as a whole; a group stays only if it beats its layers launched apart.
 cadnn_status tune_net(cadnn_net* net, const void* x, void* y, hipStream_t s) {
+    if (net->cl) return cl_tune(net, x, y, s);
     // every layer is timed on the data an ordinary pass leaves in its input region
     cadnn_status st = launch_all(net, x, y, s);
     std::vector<float> alone_us(net->ops.size(), 0.0f);
@@ -996,6 +924,10 @@ extern "C" cadnn_status cadnn_net_op_info(cadnn_net* net, int op_index, int flag
     } else {
         layout_for(net, flags);
     }
+    if (net->cl) {
+        cl_op_info(net, (size_t)op_index, out);
+        return CADNN_OK;
+    }
     const NetOp& op = net->ops[op_index];
     out->halo_h = op.yd.ph;
     out->halo_w = op.yd.pw;
@@ -1013,30 +945,8 @@ extern "C" cadnn_status cadnn_net_op_info(cadnn_net* net, int op_index, int flag
     return CADNN_OK;
 }
 
-extern "C" cadnn_status cadnn_net_finalize(cadnn_net* net, void* ws, size_t bytes, int flags) {
-    if (!net) return fail(CADNN_EINVAL, "cadnn_net_finalize: NULL net");
-    if (net->ops.empty()) return fail(CADNN_EINVAL, "cadnn_net_finalize: empty net");
-    // (a plain layout never needs more room than the de-interleaved one that
-    // cadnn_net_workspace_bytes reports)
-    layout_for(net, flags);
-    net->static_ws = (flags & CADNN_NET_STATIC_WORKSPACE) != 0;
-    if (net->static_ws) {
-        if (net->ws_bytes > kStaticWorkspaceBytes)
-            return fail(CADNN_EUNSUPPORTED, "cadnn_net_finalize: the net needs %zu bytes of workspace, the static workspace holds %zu",
-                        net->ws_bytes, kStaticWorkspaceBytes);
-        cadnn_status st = static_workspace(&ws);
-        if (st != CADNN_OK) return st;
-        bytes = kStaticWorkspaceBytes;
-    }
-    if (net->ws_bytes > 0 && !ws) return fail(CADNN_EINVAL, "cadnn_net_finalize: NULL workspace");
-    if (bytes < net->ws_bytes) return fail(CADNN_EINVAL, "cadnn_net_finalize: workspace of %zu bytes, %zu needed", bytes, net->ws_bytes);
-    drop_graph(net);
-    net->ws = (char*)ws;
-    // halos are read as the zero padding of the consumer layers and are never written again
-    if (net->ws_bytes) {
-        CADNN_HIP(hipMemset(ws, 0, net->ws_bytes));
-        CADNN_HIP(hipDeviceSynchronize());
-    }
+// Everything the layers of a net on plane layouts need on the device.
+static cadnn_status prepare_planes(cadnn_net* net) {
     // biases of a sibling group, stacked like the rows of its merged weights
     net->merged_bias.clear();
     for (size_t i = 0; i < net->ops.size(); ++i) {
@@ -1068,6 +978,76 @@ extern "C" cadnn_status cadnn_net_finalize(cadnn_net* net, void* ws, size_t byte
         cadnn_status st = set_colaunch_variant(net, i, nullptr);
         if (st != CADNN_OK) return st;
     }
+    return CADNN_OK;
+}
+
+// The net leaves the channels-last execution for the plane layouts (a variant of theirs is pinned).
+static cadnn_status leave_channels_last(cadnn_net* net) {
+    if (net->exec) (void)hipGraphExecDestroy(net->exec);
+    net->exec = nullptr;
+    CADNN_HIP(hipDeviceSynchronize());
+    net->cl.reset();
+    if (net->cl_ws.p) {         // (the plane layouts' own workspace was left as it was)
+        net->cl_ws.release();
+        net->ws = net->planes_ws;
+        return CADNN_OK;
+    }
+    if (net->ws_bytes) CADNN_HIP(hipMemset(net->ws, 0, net->ws_bytes));
+    CADNN_HIP(hipDeviceSynchronize());
+    return prepare_planes(net);
+}
+
+// ... and the way there: a channels-last variant is pinned on a net that the rule left on planes (a saved
+// choice replays whichever execution it was made with).  The workspace is the library's own then.
+static cadnn_status enter_channels_last(cadnn_net* net) {
+    std::unique_ptr<ClNet> cl = (net->allow_s2d && net->allow_fusion && !net->static_ws) ? cl_layout(net) : nullptr;
+    if (!cl) return fail(CADNN_EUNSUPPORTED, "cadnn_net_set_op_variant: the net has no channels-last execution");
+    if (net->exec) (void)hipGraphExecDestroy(net->exec);
+    net->exec = nullptr;
+    CADNN_HIP(hipDeviceSynchronize());
+    cadnn_status st = net->cl_ws.alloc(cl->ws_bytes, true);
+    if (st != CADNN_OK) return st;
+    net->planes_ws = net->ws;
+    net->ws = (char*)net->cl_ws.p;
+    net->cl = std::move(cl);
+    if ((st = cl_prepare(net)) == CADNN_OK) return CADNN_OK;
+    net->cl.reset();
+    net->cl_ws.release();
+    net->ws = net->planes_ws;
+    return st;
+}
+
+extern "C" cadnn_status cadnn_net_finalize(cadnn_net* net, void* ws, size_t bytes, int flags) {
+    if (!net) return fail(CADNN_EINVAL, "cadnn_net_finalize: NULL net");
+    if (net->ops.empty()) return fail(CADNN_EINVAL, "cadnn_net_finalize: empty net");
+    // (a plain layout never needs more room than the de-interleaved one that
+    // cadnn_net_workspace_bytes reports)
+    layout_for(net, flags);
+    net->static_ws = (flags & CADNN_NET_STATIC_WORKSPACE) != 0;
+    if (net->static_ws) {
+        if (net->cl) {          // (nets that fit the static workspace stay on the plane layouts)
+            net->cl.reset();
+            Layout l(net);
+            l.run();
+        }
+        if (net->ws_bytes > kStaticWorkspaceBytes)
+            return fail(CADNN_EUNSUPPORTED, "cadnn_net_finalize: the net needs %zu bytes of workspace, the static workspace holds %zu",
+                        net->ws_bytes, kStaticWorkspaceBytes);
+        cadnn_status st = static_workspace(&ws);
+        if (st != CADNN_OK) return st;
+        bytes = kStaticWorkspaceBytes;
+    }
+    if (net->ws_bytes > 0 && !ws) return fail(CADNN_EINVAL, "cadnn_net_finalize: NULL workspace");
+    if (bytes < net->ws_bytes) return fail(CADNN_EINVAL, "cadnn_net_finalize: workspace of %zu bytes, %zu needed", bytes, net->ws_bytes);
+    drop_graph(net);
+    net->ws = (char*)ws;
+    // halos are read as the zero padding of the consumer layers and are never written again
+    if (net->ws_bytes) {
+        CADNN_HIP(hipMemset(ws, 0, net->ws_bytes));
+        CADNN_HIP(hipDeviceSynchronize());
+    }
+    cadnn_status st = net->cl ? cl_prepare(net) : prepare_planes(net);
+    if (st != CADNN_OK) return st;
     net->use_graph = (flags & CADNN_NET_GRAPH) != 0;
     net->want_tune = (flags & CADNN_NET_TUNE) != 0;
     net->finalized = true;
@@ -1182,12 +1162,7 @@ extern "C" cadnn_status cadnn_net_profile_in_order(cadnn_net* net, const void* x
     if (repeats <= 0) return fail(CADNN_EINVAL, "cadnn_net_profile_in_order: repeats must be positive");
     hipStream_t s = (hipStream_t)stream;
     const size_t nops = net->ops.size();
-    std::vector<size_t> order;
-    for (size_t i = 0; i < nops; ++i) {
-        if (net->ops[i].hoisted_to >= 0) continue;
-        order.push_back(i);
-        for (int h : net->ops[i].hoisted) order.push_back((size_t)h);
-    }
+    const std::vector<size_t> order = launch_order(net);
     std::vector<LaunchTimer> timers(order.size());
     cadnn_status st = CADNN_OK;
     for (LaunchTimer& t : timers)
@@ -1229,6 +1204,11 @@ extern "C" cadnn_status cadnn_net_op_variant(const cadnn_net* net, int op_index,
     if (op_index < 0 || op_index >= (int)net->ops.size()) return fail(CADNN_EINVAL, "cadnn_net_op_variant: no op %d", op_index);
     const NetOp& op = net->ops[op_index];
     const char* name = "";
+    if (net->cl) {
+        std::strncpy(buf, cl_op_variant(net, (size_t)op_index), len - 1);
+        buf[len - 1] = '\0';
+        return CADNN_OK;
+    }
     switch (op.kind) {
         case OP_CONV: {
             ConvExtra ex;
@@ -1260,6 +1240,18 @@ extern "C" cadnn_status cadnn_net_op_candidates(const cadnn_net* net, int op_ind
     if (op_index < 0 || op_index >= (int)net->ops.size()) return fail(CADNN_EINVAL, "cadnn_net_op_candidates: no op %d", op_index);
     const NetOp& op = net->ops[op_index];
     if (op.kind != OP_CONV) return fail(CADNN_EINVAL, "cadnn_net_op_candidates: op %d is not a convolution", op_index);
+    if (net->cl) {
+        const int into = net->cl->ops[(size_t)op_index]->fused_into;
+        if (into >= 0) return fail(CADNN_EINVAL, "cadnn_net_op_candidates: op %d is computed inside op %d", op_index, into);
+        std::string all;
+        for (const ClVariant* v : cl_candidates(net, (size_t)op_index)) {
+            if (!all.empty()) all += "\n";
+            all += v->name;
+        }
+        if (all.size() + 1 > len) return fail(CADNN_EINVAL, "cadnn_net_op_candidates: buffer of %zu bytes, %zu needed", len, all.size() + 1);
+        std::memcpy(buf, all.c_str(), all.size() + 1);
+        return CADNN_OK;
+    }
     if (op.fused_into >= 0) return fail(CADNN_EINVAL, "cadnn_net_op_candidates: op %d is computed inside op %d", op_index, op.fused_into);
     if (!op.comates.empty()) {
         // the variants that serve the whole group
@@ -1285,6 +1277,28 @@ extern "C" cadnn_status cadnn_net_set_op_variant(cadnn_net* net, int op_index, c
     if (op_index < 0 || op_index >= (int)net->ops.size()) return fail(CADNN_EINVAL, "cadnn_net_set_op_variant: no op %d", op_index);
     const NetOp& op = net->ops[op_index];
     if (op.kind != OP_CONV) return fail(CADNN_EINVAL, "cadnn_net_set_op_variant: op %d is not a convolution", op_index);
+    const std::vector<ClVariant>& cls = all_cl_variants();
+    if (!net->cl && name && std::any_of(cls.begin(), cls.end(), [&](const ClVariant& v) { return std::strcmp(v.name, name) == 0; })) {
+        cadnn_status entered = enter_channels_last(net);
+        if (entered != CADNN_OK) return entered;
+    }
+    if (net->cl) {
+        ClOp& c = *net->cl->ops[(size_t)op_index];
+        if (c.fused_into >= 0) return CADNN_OK;
+        const ClVariant* v = nullptr;
+        for (const ClVariant* k : cl_candidates(net, (size_t)op_index)) if (name && std::strcmp(k->name, name) == 0) v = k;
+        const int64_t pixels = (int64_t)op.out.n * op.out.h * op.out.w;
+        if (!name || !*name) v = cl_pick(op.w, c.plan, pixels, net->dtype == CADNN_F16);
+        if (v) {
+            drop_graph(net);
+            CADNN_HIP(hipDeviceSynchronize());
+            c.v = v;
+            return cl_prepare_variant(*v, &c.plan, pixels, op.out.c);
+        }
+        if (std::strncmp(name, "cl_", 3) == 0) return fail(CADNN_EINVAL, "cadnn_net_set_op_variant: '%s' does not serve op %d", name, op_index);
+        cadnn_status left = leave_channels_last(net);
+        if (left != CADNN_OK) return left;
+    }
     if (op.fused_into >= 0) return CADNN_OK;     // nothing to pin: computed inside, or launched with, another op
     if (!op.comates.empty() && name && std::strcmp(name, "apart") == 0) {
         // the group's layers one launch each from now on (what tuning does to a group that loses)
@@ -1321,6 +1335,10 @@ extern "C" cadnn_status cadnn_net_read_buffer(cadnn_net* net, int buf, void* hos
     if (it == net->producer.end() || it->second < 0 || it->second + 1 == (int)net->ops.size())
         return fail(CADNN_EINVAL, "cadnn_net_read_buffer: buffer %d is not in the workspace", buf);
     const NetOp& op = net->ops[it->second];
+    if (net->cl) {
+        CADNN_HIP(hipStreamSynchronize((hipStream_t)stream));
+        return cl_read_buffer(net, (size_t)it->second, host_out, bytes);
+    }
     // (a fused pool's vector is written, by the convolution; a fused projection's map is not)
     if (op.fused_into >= 0 && op.kind == OP_CONV && op.sibling_of < 0 && op.colaunch_of < 0)
         return fail(CADNN_EINVAL, "cadnn_net_read_buffer: buffer %d is never materialised (its op is computed inside op %d)", buf, op.fused_into);

@@ -1,0 +1,416 @@
+// Channels-last execution of a net: every activation tensor [row][column][channel] with a zero halo,
+// every convolution an implicit GEMM over the zero-filled weight matrix on the matrix cores.  The
+// paper's per-layer choice between dense and compressed execution (Section 5 compares them, Section
+// 4 selects parameters by measurement) is taken here for the net as a whole, because the
+// two kinds of kernels want different memory layouts.
+#include <algorithm>
+#include <cstdlib>
+#include <cstring>
+#include <functional>
+
+#include "net.h"
+
+namespace cadnn {
+
+namespace {
+
+struct Reader { int op; bool residual; };
+
+bool is_pool(const NetOp& o) { return o.kind == OP_MAXPOOL || o.kind == OP_AVGPOOL2D; }
+
+// A first layer of few channels: its input is packed 4 channels to a pixel and one K step is a whole
+// filter row.
+bool stem_conv(const NetOp& o, size_t e) {
+    return o.kind == OP_CONV && o.src_inst < 0 && o.w->cin <= 4 && o.w->kw * 4 * (int)e <= 128 && o.w->kh <= kClMaxTaps;
+}
+
+const void* region(const cadnn_net* net, size_t off) { return net->ws + off; }
+
+// Tensor of op k's output as a cl tensor lives at this offset (k < 0: the imported input).
+size_t tensor_off_of(const cadnn_net* net, int k) { return k < 0 ? net->cl->in_off : net->cl->ops[(size_t)k]->y_off; }
+
+const NetOp* shortcut_op(const cadnn_net* net, const ClOp& c) { return c.shortcut >= 0 ? &net->ops[(size_t)c.shortcut] : nullptr; }
+
+ClConv conv_args(const cadnn_net* net, size_t i, void* y_region) {
+    const NetOp& op = net->ops[i];
+    const ClOp& c = *net->cl->ops[i];
+    ClConv a{};
+    a.plan = &c.plan;
+    a.x = region(net, c.x_stem ? c.x_off : tensor_off_of(net, op.src_inst));
+    a.xd = c.xd;
+    a.y = y_region;
+    a.yd = c.yd;
+    if (op.res >= 0 && c.shortcut < 0) {
+        a.residual = region(net, tensor_off_of(net, op.res_inst));
+        a.rd = c.rd;
+    }
+    if (const NetOp* p = shortcut_op(net, c)) {
+        const ClOp& pc = *net->cl->ops[(size_t)c.shortcut];
+        a.x2 = region(net, tensor_off_of(net, p->src_inst));
+        a.x2d = pc.xd;
+        a.stride2 = p->stride;
+        a.bias2 = (const float*)p->bias;
+    }
+    a.bias = (const float*)op.bias;
+    a.n = op.out.n;
+    a.cout = op.out.c;
+    a.stride = op.stride;
+    a.pad = op.pad;
+    a.relu = op.relu;
+    return a;
+}
+
+int64_t out_pixels(const NetOp& op) { return (int64_t)op.out.n * op.out.h * op.out.w; }
+
+}  // namespace
+
+std::unique_ptr<ClNet> cl_layout(const cadnn_net* net) {
+    const int nops = (int)net->ops.size();
+    const size_t e = net->elem();
+    const int epp = (int)(16 / e);
+    std::vector<std::vector<Reader>> readers((size_t)nops);
+    for (int k = 0; k < nops; ++k) {
+        const NetOp& o = net->ops[(size_t)k];
+        if (o.kind == OP_CONCAT) { for (int j : o.src_insts) if (j >= 0) readers[(size_t)j].push_back({k, false}); }
+        else if (o.src_inst >= 0) readers[(size_t)o.src_inst].push_back({k, false});
+        if (o.res_inst >= 0) readers[(size_t)o.res_inst].push_back({k, true});
+    }
+    std::unique_ptr<ClNet> cl(new ClNet());
+    for (int k = 0; k < nops; ++k) cl->ops.emplace_back(new ClOp());
+
+    // which outputs are plain [n][c][h][w], and whether every op can run
+    bool import = false;
+    int in_halo = 0;
+    std::vector<int> halo((size_t)nops, 0);
+    auto flat = [&](int k) { return k >= 0 && cl->ops[(size_t)k]->flat; };
+    for (int k = 0; k < nops; ++k) {
+        const NetOp& o = net->ops[(size_t)k];
+        ClOp& c = *cl->ops[(size_t)k];
+        bool to_fc = false;
+        for (const Reader& r : readers[(size_t)k]) to_fc = to_fc || net->ops[(size_t)r.op].kind == OP_FC;
+        c.flat = o.kind == OP_FC || o.kind == OP_AVGPOOL || (is_pool(o) && (to_fc || k == nops - 1));
+        if (c.flat)
+            for (const Reader& r : readers[(size_t)k]) if (net->ops[(size_t)r.op].kind != OP_FC) return nullptr;
+        if (o.kind == OP_FC) {
+            if (o.src_inst >= 0 && !flat(o.src_inst)) return nullptr;
+            continue;
+        }
+        if (flat(o.src_inst) || flat(o.res_inst)) return nullptr;
+        const bool stem = stem_conv(o, e);
+        if (o.src_inst < 0 && !stem) import = true;
+        if (o.res >= 0 && o.res_inst < 0) import = true;
+        if (o.kind == OP_CONV) {
+            if (o.out.c % epp || o.w->kh * o.w->kw > kClMaxTaps || o.pad > 64) return nullptr;
+        } else if (o.kind == OP_DEPTHWISE) {
+            if (o.out.c % epp || o.w->kh != 3 || o.w->kw != 3 || o.stride > 2 || o.pad > 1) return nullptr;
+        } else if (o.kind == OP_CONCAT) {
+            for (size_t j = 0; j < o.src_insts.size(); ++j) {
+                const int p = o.src_insts[j];
+                if (flat(p) || o.ch_off[j] % epp) return nullptr;
+                if (p < 0) import = true;
+                if ((p < 0 ? net->input.c : net->ops[(size_t)p].out.c) % epp) return nullptr;
+            }
+        } else if (o.in.c % epp) {
+            return nullptr;
+        }
+        if (o.kind == OP_CONV || o.kind == OP_DEPTHWISE) {
+            if (o.src_inst >= 0) halo[(size_t)o.src_inst] = std::max(halo[(size_t)o.src_inst], o.pad);
+            else if (!stem) in_halo = std::max(in_halo, o.pad);
+        }
+    }
+
+    // projection shortcuts become more of K of the layer that adds them
+    for (int k = 0; k < nops; ++k) {
+        const NetOp& o = net->ops[(size_t)k];
+        if (o.kind != OP_CONV || o.res_inst < 0 || o.res_inst == nops - 1) continue;
+        const NetOp& p = net->ops[(size_t)o.res_inst];
+        if (p.kind != OP_CONV || p.w->kh != 1 || p.w->kw != 1 || p.pad != 0 || p.relu || p.res >= 0 || stem_conv(p, e) ||
+            readers[(size_t)o.res_inst].size() != 1 || stem_conv(o, e))
+            continue;
+        cl->ops[(size_t)k]->shortcut = o.res_inst;
+        cl->ops[(size_t)o.res_inst]->fused_into = k;
+    }
+
+    // sources of concatenations that nothing else reads are written in place
+    for (int k = 0; k + 1 < nops; ++k) {
+        const NetOp& o = net->ops[(size_t)k];
+        if (o.kind != OP_CONCAT) continue;
+        for (int p : o.src_insts) {
+            if (p < 0 || readers[(size_t)p].size() != 1 || net->ops[(size_t)p].kind == OP_CONCAT) continue;
+            cl->ops[(size_t)p]->slice_of = k;
+        }
+    }
+
+    size_t off = 0;
+    bool fits = true;
+    auto place = [&](const ClDesc& d, int n) {
+        const size_t at = off, bytes = (size_t)n * (size_t)d.image * e;
+        if (bytes >= 0x7fff0000ull) fits = false;
+        off += (bytes + 255) / 256 * 256;
+        return at;
+    };
+    if (import) {
+        cl->in_d = cl_desc(net->input.c, net->input.h, net->input.w, in_halo, in_halo, cl_padded_channels(net->input.c, e));
+        cl->in_off = place(cl->in_d, net->input.n);
+    }
+    for (int k = 0; k < nops; ++k) {
+        const NetOp& o = net->ops[(size_t)k];
+        ClOp& c = *cl->ops[(size_t)k];
+        if (c.slice_of >= 0) continue;
+        if (c.flat) {
+            c.yd = cl_desc(o.out.c, o.out.h, o.out.w, 0, 0, o.out.c);
+            if (k != nops - 1) c.y_off = place(c.yd, o.out.n);
+            continue;
+        }
+        c.yd = cl_desc(o.out.c, o.out.h, o.out.w, halo[(size_t)k], halo[(size_t)k], cl_padded_channels(o.out.c, e));
+        if (c.fused_into < 0) c.y_off = place(c.yd, o.out.n);
+    }
+    for (int k = 0; k < nops; ++k) {
+        ClOp& c = *cl->ops[(size_t)k];
+        if (c.slice_of < 0) continue;
+        const NetOp& cat = net->ops[(size_t)c.slice_of];
+        const ClOp& cc = *cl->ops[(size_t)c.slice_of];
+        c.yd = cc.yd;
+        c.yd.c = net->ops[(size_t)k].out.c;
+        const size_t j = (size_t)(std::find(cat.src_insts.begin(), cat.src_insts.end(), k) - cat.src_insts.begin());
+        c.yd.origin += cat.ch_off[j];
+        c.y_off = cc.y_off;
+    }
+    for (int k = 0; k < nops; ++k) {
+        const NetOp& o = net->ops[(size_t)k];
+        ClOp& c = *cl->ops[(size_t)k];
+        if (o.kind == OP_FC) continue;
+        if (stem_conv(o, e)) {
+            c.x_stem = true;
+            c.xd = cl_desc(o.in.c, o.in.h, o.in.w, o.pad, o.pad, 4);
+            c.x_off = place(c.xd, o.in.n);
+        } else {
+            c.xd = o.src_inst < 0 ? cl->in_d : cl->ops[(size_t)o.src_inst]->yd;
+            const bool reads_input = o.src_inst < 0 ||
+                                     (o.kind == OP_CONCAT && std::find(o.src_insts.begin(), o.src_insts.end(), -1) != o.src_insts.end());
+            if (reads_input && cl->import_at < 0) cl->import_at = k;
+        }
+        if (o.res >= 0) {
+            c.rd = o.res_inst < 0 ? cl->in_d : cl->ops[(size_t)o.res_inst]->yd;
+            if (o.res_inst < 0 && cl->import_at < 0) cl->import_at = k;
+        }
+    }
+    if (!fits) return nullptr;
+    cl->ws_bytes = off;
+    return cl;
+}
+
+// Which execution a net takes unless a variant of the other is pinned.  Both are modelled as a fixed cost
+// per launch plus multiply-adds at a rate: the compressed kernels of the plane layouts do the nonzero
+// ones at 8.5 TFLOP/s (ResNet-50, 80 % sparse, fp16 / mixed, fp32: 7-8.7 measured at batch 2 to 32), the
+// matrix cores all of them at 430 (fp16) or 80 (fp32).  Measured around the line (us, planes /
+// channels-last): ResNet-50 fp16 batch 1 417 / 369, 2 633 / 383, 8 1841 / 513, 32 6789 / 972; fp32
+// batch 2 539 / 637, 8 1521 / 1124; VGG-16 batch 1 fp16 394 / 194, fp32 428 / 484; Inception-V3 fp16 batch 2
+// 967 / 803, fp32 batch 1 556 / 1175; MobileNet-V2 fp16 batch 2 227 / 304, 16 613 / 471.  Near the line
+// the plane layouts keep the net: tuning gains them more (10-20 %) than it gains these kernels.
+bool cl_expected_faster(const cadnn_net* net) {
+    double nonzero = 0.0, dense = 0.0;
+    int planes_launches = 0, cl_launches = 0;
+    for (const NetOp& o : net->ops) {
+        if (o.kind != OP_CONCAT) ++cl_launches;
+        if (o.fused_into < 0 && o.kind != OP_CONCAT) ++planes_launches;
+        if (!o.w) continue;
+        const double pixels = (double)o.out.n * o.out.h * o.out.w;
+        nonzero += 2.0 * (double)o.w->nnz * pixels;
+        if (o.kind == OP_CONV) dense += 2.0 * (double)o.w->cout * o.w->cin * o.w->kh * o.w->kw * pixels;
+    }
+    const double planes_us = 4.5 * planes_launches + nonzero / 8.5e6;
+    const double cl_us = 6.7 * cl_launches + dense / (net->dtype == CADNN_F16 ? 430e6 : 80e6);
+    return cl_us < 0.8 * planes_us;
+}
+
+cadnn_status cl_prepare(cadnn_net* net) {
+    const size_t e = net->elem();
+    for (size_t i = 0; i < net->ops.size(); ++i) {
+        const NetOp& op = net->ops[i];
+        ClOp& c = *net->cl->ops[i];
+        cadnn_status st = CADNN_OK;
+        if (op.kind == OP_FC) st = cadnn_fc_prepare(op.w);
+        if (op.kind == OP_DEPTHWISE) st = ensure_dw_device(op.w);
+        if (op.kind == OP_CONV && c.fused_into < 0 && !c.plan.w.p) {
+            int rb = 128;
+            const NetOp* p = shortcut_op(net, c);
+            if (c.x_stem) {
+                if (op.w->kw * 4 * (int)e <= 64) rb = 64;
+            } else if (((size_t)cl_padded_channels(op.in.c, e) * e) % 128 ||
+                       (p && ((size_t)cl_padded_channels(p->in.c, e) * e) % 128)) {
+                rb = 64;
+            }
+            try {
+                st = cl_build_plan(op.w, p ? p->w : nullptr, rb, c.x_stem, &c.plan);
+            } catch (const std::bad_alloc&) {
+                st = fail(CADNN_ENOMEM, "out of host memory building a conv plan");
+            }
+            if (st != CADNN_OK) return st;
+            c.v = cl_pick(op.w, c.plan, out_pixels(op), e == 2);
+            st = cl_prepare_variant(*c.v, &c.plan, out_pixels(op), op.out.c);
+        }
+        if (st != CADNN_OK) return st;
+    }
+    return CADNN_OK;
+}
+
+cadnn_status cl_launch_one(cadnn_net* net, size_t i, const void* x, void* y, hipStream_t s) {
+    const NetOp& op = net->ops[i];
+    const ClOp& c = *net->cl->ops[i];
+    const bool f16 = net->dtype == CADNN_F16, last = i + 1 == net->ops.size();
+    cadnn_status st = CADNN_OK;
+    if ((int)i == net->cl->import_at)
+        st = launch_cl_import(x, net->input.n, net->input.c, net->input.h, net->input.w, net->ws + net->cl->in_off, net->cl->in_d, f16, s);
+    if (st == CADNN_OK && c.x_stem)
+        st = launch_cl_import(x, op.in.n, op.in.c, op.in.h, op.in.w, net->ws + c.x_off, c.xd, f16, s);
+    if (st != CADNN_OK || c.fused_into >= 0) return st;
+    void* dst = (last && c.flat) ? y : (void*)(net->ws + c.y_off);
+    const void* src = region(net, tensor_off_of(net, op.src_inst));
+    switch (op.kind) {
+        case OP_CONV:
+            st = launch_cl_conv(conv_args(net, i, dst), *c.v, f16, s);
+            break;
+        case OP_DEPTHWISE:
+            st = launch_cl_depthwise(op.w, src, c.xd, dst, c.yd, op.out.n, op.stride, op.pad, (const float*)op.bias, op.relu, f16, s);
+            break;
+        case OP_FC:
+            return launch_fc(op.w, op.src_inst < 0 ? x : src, dst, op.in.n, (const float*)op.bias, op.relu, s);
+        case OP_MAXPOOL:
+        case OP_AVGPOOL2D:
+            st = launch_cl_pool(src, c.xd, dst, c.yd, c.flat, op.out.n, op.k, op.stride, op.pad, op.kind == OP_MAXPOOL ? 0 : 1, f16, s);
+            break;
+        case OP_AVGPOOL:
+            return launch_cl_gap(src, c.xd, dst, op.in.n, f16, s);
+        case OP_CONCAT:
+            for (size_t j = 0; j < op.srcs.size() && st == CADNN_OK; ++j) {
+                const int p = op.src_insts[j];
+                if (p >= 0 && net->cl->ops[(size_t)p]->slice_of == (int)i) continue;
+                const ClDesc from = p < 0 ? net->cl->in_d : net->cl->ops[(size_t)p]->yd;
+                ClDesc to = c.yd;
+                to.c = from.c;
+                to.origin += op.ch_off[j];
+                st = launch_cl_pool(region(net, tensor_off_of(net, p)), from, dst, to, false, op.out.n, 1, 1, 0, 0, f16, s);
+            }
+            break;
+    }
+    if (st == CADNN_OK && last && !c.flat) st = launch_cl_export(region(net, c.y_off), c.yd, y, op.out.n, f16, s);
+    return st;
+}
+
+// Every convolution's tiles timed on the net's own buffers, the op that produces its input launched
+// ahead of each timed launch and the caches swept before that.
+cadnn_status cl_tune(cadnn_net* net, const void* x, void* y, hipStream_t s) {
+    cadnn_status st = CADNN_OK;
+    for (size_t i = 0; i < net->ops.size() && st == CADNN_OK; ++i) st = cl_launch_one(net, i, x, y, s);
+    if (st != CADNN_OK) return st;
+    DevBuf sweep;
+    const size_t sweep_bytes = (size_t)64 << 20;
+    if ((st = sweep.alloc(2 * sweep_bytes, true)) != CADNN_OK) return st;
+    hipEvent_t e0 = nullptr, e1 = nullptr;
+    CADNN_HIP(hipEventCreate(&e0));
+    if (hipEventCreate(&e1) != hipSuccess) { (void)hipEventDestroy(e0); return fail(CADNN_EHIP, "hipEventCreate failed"); }
+    constexpr int kReps = 20;
+    for (size_t i = 0; i < net->ops.size() && st == CADNN_OK; ++i) {
+        const NetOp& op = net->ops[i];
+        ClOp& c = *net->cl->ops[i];
+        if (op.kind != OP_CONV || c.fused_into >= 0) continue;
+        const ClVariant* best = nullptr;
+        float best_ms = 0.0f;
+        for (const ClVariant* v : cl_candidates(net, i)) {
+            if ((st = cl_prepare_variant(*v, &c.plan, out_pixels(op), op.out.c)) != CADNN_OK) break;
+            c.v = v;
+            float total = 0.0f;
+            for (int r = 0; r < kReps + 1 && st == CADNN_OK; ++r) {
+                if ((st = launch_copy(sweep.p, (char*)sweep.p + sweep_bytes, sweep_bytes, s)) != CADNN_OK) break;
+                if (op.src_inst >= 0) st = cl_launch_one(net, (size_t)op.src_inst, x, y, s);
+                if (st != CADNN_OK) break;
+                if (hipEventRecord(e0, s) != hipSuccess) { st = fail(CADNN_EHIP, "hipEventRecord failed"); break; }
+                if ((st = launch_cl_conv(conv_args(net, i, net->ws + c.y_off), *v, net->dtype == CADNN_F16, s)) != CADNN_OK) break;
+                float ms = 0.0f;
+                if (hipEventRecord(e1, s) != hipSuccess || hipEventSynchronize(e1) != hipSuccess ||
+                    hipEventElapsedTime(&ms, e0, e1) != hipSuccess) { st = fail(CADNN_EHIP, "event timing failed"); break; }
+                if (r > 0) total += ms;             // (the first launch of a kernel pays for its upload)
+            }
+            if (st != CADNN_OK) break;
+            if (std::getenv("CADNN_TUNE_LOG"))
+                std::fprintf(stderr, "[cadnn tune] cl cin=%d cout=%d k=%d s=%d out=%dx%dx%d steps=%d rb=%d %-20s %8.2f us\n", op.w->cin, op.w->cout,
+                             op.w->kh, op.stride, op.out.n, op.out.h, op.out.w, c.plan.steps, c.plan.rb, v->name, total * 1e3f / kReps);
+            if (!best || total < best_ms) { best = v; best_ms = total; }
+        }
+        if (best) c.v = best;
+    }
+    (void)hipEventDestroy(e0);
+    (void)hipEventDestroy(e1);
+    return st;
+}
+
+void cl_op_info(const cadnn_net* net, size_t i, cadnn_op_info* out) {
+    const ClOp& c = *net->cl->ops[i];
+    out->halo_h = c.yd.ph;
+    out->halo_w = c.yd.pw;
+    out->pitch = c.flat ? c.yd.w : c.yd.row;
+    out->plane = c.flat ? (int64_t)c.yd.h * c.yd.w : 1;
+    out->image = c.yd.image;
+    out->deinterleaved = 0;
+    out->offset = (int64_t)c.y_off + (int64_t)c.yd.origin * (int64_t)net->elem();
+    out->fused_into = c.fused_into;
+    out->slice_of = c.slice_of;
+    out->slice_channel = c.slice_of >= 0 ? c.yd.origin - net->cl->ops[(size_t)c.slice_of]->yd.origin : 0;
+    out->launched_with = 0;
+    out->launched_after = -1;
+    out->input_copy = c.x_stem ? (int64_t)c.x_off : -1;
+}
+
+const char* cl_op_variant(const cadnn_net* net, size_t i) {
+    const NetOp& op = net->ops[i];
+    const ClOp& c = *net->cl->ops[i];
+    switch (op.kind) {
+        case OP_CONV: return c.fused_into >= 0 ? "fused" : c.v->name;
+        case OP_FC: return "sfc";
+        case OP_DEPTHWISE: return "dwconv";
+        case OP_MAXPOOL: return "maxpool";
+        case OP_AVGPOOL: return "avgpool";
+        case OP_AVGPOOL2D: return "avgpool2d";
+        case OP_CONCAT: break;
+    }
+    for (int p : op.src_insts)
+        if (p < 0 || net->cl->ops[(size_t)p]->slice_of != (int)i) return "concat";
+    return "in place";
+}
+
+std::vector<const ClVariant*> cl_candidates(const cadnn_net* net, size_t i) {
+    std::vector<const ClVariant*> out;
+    const NetOp& op = net->ops[i];
+    for (const ClVariant& v : all_cl_variants())
+        if (cl_variant_fits(v, net->cl->ops[i]->plan, out_pixels(op), op.out.c)) out.push_back(&v);
+    return out;
+}
+
+cadnn_status cl_read_buffer(cadnn_net* net, size_t i, void* host_out, size_t bytes) {
+    const NetOp& op = net->ops[i];
+    const ClOp& c = *net->cl->ops[i];
+    const size_t e = net->elem();
+    if (c.fused_into >= 0)
+        return fail(CADNN_EINVAL, "cadnn_net_read_buffer: the buffer is never materialised (its op is computed inside op %d)", c.fused_into);
+    if (bytes != op.out.elems() * e) return fail(CADNN_EINVAL, "cadnn_net_read_buffer: the buffer holds %zu bytes, %zu asked", op.out.elems() * e, bytes);
+    if (c.flat) {
+        CADNN_HIP(hipMemcpy(host_out, net->ws + c.y_off, bytes, hipMemcpyDeviceToHost));
+        return CADNN_OK;
+    }
+    // the region whole, the channels gathered on the host
+    const ClDesc& whole = c.slice_of >= 0 ? net->cl->ops[(size_t)c.slice_of]->yd : c.yd;
+    const size_t total = (size_t)op.out.n * (size_t)whole.image * e;
+    std::vector<char> raw(total);
+    CADNN_HIP(hipMemcpy(raw.data(), net->ws + c.y_off, total, hipMemcpyDeviceToHost));
+    for (int n = 0; n < op.out.n; ++n)
+        for (int r = 0; r < op.out.h; ++r)
+            for (int q = 0; q < op.out.w; ++q) {
+                const char* src = raw.data() + ((size_t)n * (size_t)c.yd.image + (size_t)c.yd.origin + (size_t)r * (size_t)c.yd.row + (size_t)q * (size_t)c.yd.pix) * e;
+                for (int ch = 0; ch < op.out.c; ++ch)
+                    std::memcpy((char*)host_out + ((((size_t)n * op.out.c + ch) * op.out.h + r) * op.out.w + q) * e, src + (size_t)ch * e, e);
+            }
+    return CADNN_OK;
+}
+
+}  // namespace cadnn

@@ -1,0 +1,149 @@
+"""GPU parity of the channels-last execution (matrix-core convolutions over [row][column][channel]
+tensors) on small nets chosen for its edges: tiles that are not full, channel counts that are not
+whole K steps, first layers of few channels, strides, residuals, fused projections, in-place and copied
+concatenations, flat outputs, every tile and K split.  Buffers and outputs against the oracle with the
+propagated bound of a forward error analysis (util.chain_bounds)."""
+import numpy as np
+import pytest
+
+import oracle
+import workloads as wl
+from util import chain_bounds, assert_within_bound
+
+pytestmark = pytest.mark.gpu
+
+torch = pytest.importorskip("torch")
+
+Op = wl.Op
+
+
+@pytest.fixture(scope="module")
+def cad():
+    if not torch.cuda.is_available():
+        pytest.skip("no GPU")
+    import paper_1905_00571_amd as cad
+    cad.lib()
+    return cad
+
+
+def stem_net():
+    """7x7/2 first layer on 3 channels, max pool, depthwise, a strided block with projection, an
+    identity block, a concatenation with one in-place, one pooled and one copied source, a fully
+    connected layer on a map of several pixels."""
+    return [
+        Op("conv", "stem", 0, 1, 3, 24, 7, 2, 3, 0.0, True),
+        Op("maxpool", "pool", 1, 2, k=3, stride=2, pad=1),
+        Op("conv", "expand", 2, 3, 24, 72, 1, 1, 0, 0.5, True),
+        Op("dwconv", "dw1", 3, 4, 72, 72, 3, 1, 1, 0.0, True),
+        Op("conv", "project", 4, 5, 72, 40, 1, 1, 0, 0.5, False),
+        Op("conv", "a", 5, 6, 40, 16, 1, 1, 0, 0.5, True),
+        Op("conv", "b", 6, 7, 16, 16, 3, 2, 1, 0.5, True),
+        Op("conv", "p", 5, 8, 40, 136, 1, 2, 0, 0.5, False),
+        Op("conv", "c", 7, 9, 16, 136, 1, 1, 0, 0.5, True, 8),
+        Op("dwconv", "dw2", 9, 10, 136, 136, 3, 2, 1, 0.0, False),
+        Op("conv", "d", 10, 11, 136, 64, 3, 1, 1, 0.8, True),
+        Op("conv", "e", 11, 12, 64, 64, 3, 1, 1, 0.8, True, 11),
+        Op("avgpool2d", "mean", 12, 13, k=3, stride=1, pad=1),
+        Op("conv", "f", 13, 14, 64, 24, 1, 1, 0, 0.5, True),
+        Op("concat", "cat", 12, 15, srcs=(12, 14)),
+        Op("maxpool", "last", 15, 16, k=2, stride=1, pad=0),
+        Op("fc", "fc", 16, 17, 88 * 2 * 3, 30, sparsity=0.5, relu=False),
+    ], (3, 3, 43, 51)
+
+
+def deep_net():
+    """An input of many channels (brought in by a transposition, read as a residual too), a long K on few
+    pixels (K splits), a rectangular filter in a square bank, an output that is a feature map."""
+    return [
+        Op("conv", "in", 0, 1, 264, 72, 1, 1, 0, 0.8, True),
+        Op("conv", "long", 1, 2, 72, 200, 3, 1, 1, 0.8, True),
+        Op("conv", "rect", 2, 3, 200, 136, 7, 1, 3, 0.5, True, kh=1, kw=7),
+        Op("conv", "back", 3, 4, 136, 264, 1, 1, 0, 0.8, False, 0),
+        Op("conv", "out", 4, 5, 264, 72, 5, 2, 2, 0.9, True),
+    ], (5, 264, 6, 5)
+
+
+def mean_net():
+    """A 3x3 first layer, one image, the global average pool in front of the classifier."""
+    return [
+        Op("conv", "stem", 0, 1, 3, 8, 3, 2, 1, 0.0, True),
+        Op("conv", "wide", 1, 2, 8, 136, 3, 2, 0, 0.5, True),
+        Op("avgpool", "gap", 2, 3),
+        Op("fc", "fc", 3, 4, 136, 12, sparsity=0.5, relu=True),
+    ], (1, 3, 20, 23)
+
+
+@pytest.mark.parametrize("dtype_name", ["f32", "f16"])
+@pytest.mark.parametrize("make", [stem_net, deep_net, mean_net], ids=lambda f: f.__name__)
+def test_channels_last_net(cad, make, dtype_name):
+    f16 = dtype_name == "f16"
+    dtype, npdt = (cad.F16, np.float16) if f16 else (cad.F32, np.float32)
+    ops, shape = make()
+    x, ws, bs = wl.net_tensors(ops, make.__name__, shape, input_relu=True)
+    xs = x.astype(npdt)
+    ref, ins, outs = oracle.run_net(ops, xs, ws, bs, dtype=npdt)
+    bounds = chain_bounds(ops, ins, outs, ws, bs, f16)
+    xs2 = wl.activation(shape, make.__name__, 99, relu=True).astype(npdt)
+    ref2, ins2, outs2 = oracle.run_net(ops, xs2, ws, bs, dtype=npdt)
+    bound2 = chain_bounds(ops, ins2, outs2, ws, bs, f16)[-1]
+
+    net = cad.build_net(ops, ws, bs, shape, dtype, use_graph=True)
+    planes = net.variants()
+    convs = [i for i, o in enumerate(ops) if o.kind == "conv"]
+    net.set_op_variant(convs[0], "cl_mfma_64x64")          # the whole net goes channels-last
+
+    def check(what):
+        for inp, want, lim in ((xs, ref, bounds[-1]), (xs2, ref2, bound2), (xs, ref, bounds[-1])):
+            y = net.run(torch.from_numpy(inp).cuda())
+            torch.cuda.synchronize()
+            assert_within_bound(y.cpu().numpy(), want, lim, f"{make.__name__} {what}")
+        checked = 0
+        for i, o in enumerate(ops[:-1]):
+            if net.op_variant(i) == "fused":
+                with pytest.raises(cad.CadnnError):
+                    net.read_buffer(o.dst, outs[i].shape)
+                continue
+            assert_within_bound(net.read_buffer(o.dst, outs[i].shape), outs[i], bounds[i], f"{make.__name__} {what} {o.name}")
+            checked += 1
+        return checked
+
+    check("default tiles")
+    names = {i: net.op_candidates(i) for i in convs if net.op_variant(i) != "fused"}
+    every = sorted(set(sum(names.values(), [])))
+    for name in every:
+        for i, have in names.items():
+            net.set_op_variant(i, name if name in have else None)
+            assert name not in have or net.op_variant(i) == name
+        check(name)
+    if make is deep_net:
+        assert {"cl_mfma_128x128", "cl_mfma_64x64_k8", "cl_mfma_128x64_k4"} <= set(every), every
+    with pytest.raises(cad.CadnnError):
+        net.set_op_variant(convs[0], "cl_no_such_tile")
+    saved = net.variants()
+    net.set_variants(planes)                                # and back
+    assert net.variants() == planes
+    y = net.run(torch.from_numpy(xs).cuda())
+    torch.cuda.synchronize()
+    assert_within_bound(y.cpu().numpy(), ref, bounds[-1], f"{make.__name__} back on planes")
+    net.set_variants(saved)
+    assert net.variants() == saved
+    check("saved choice replayed")
+    net.free()
+
+
+def test_channels_last_tuned(cad):
+    """A net the rule takes channels-last by itself (enough multiply-adds), tuned on its first run."""
+    ops = wl.resnet50_ops(uniform=0.8)
+    shape = (8, 3, 128, 127)
+    x, ws, bs = wl.net_tensors(ops, "cl-tuned", shape)
+    xs = x.astype(np.float16)
+    ref, _, _ = oracle.run_net(ops, xs, ws, bs, dtype=np.float16)
+    net = cad.build_net(ops, ws, bs, shape, cad.F16, use_graph=True, tune=True)
+    for _ in range(2):
+        y = net.run(torch.from_numpy(xs).cuda())
+        torch.cuda.synchronize()
+        got = y.float().cpu().numpy()
+        # 1e-2: the stated bar of whole nets in fp16 storage
+        assert np.abs(got - ref).max() <= 1e-2 * np.abs(ref).max()
+    assert all(n.startswith("cl_") or n == "fused" for n, o in zip(net.variants(), ops) if o.kind == "conv")
+    net.free()
