@@ -304,13 +304,24 @@ static const ConvVariant* heuristic_variant(const cadnn_weights* w, const ConvGe
     return best;
 }
 
+// The model runs over some two hundred instantiations, which takes the host longer than a small
+// layer takes the GPU: its pick is kept on the handle, per geometry.  (A fused shortcut's own geometry is
+// not part of the key, so those picks are not kept.)
 static const ConvVariant* pick_variant(const cadnn_weights* w, const ConvGeom& g) {
+    const GeomKey key = g.key();
+    const bool keep = !(g.ex && g.ex->w);
     {
         std::lock_guard<std::mutex> lock(w->mu);
-        auto it = w->chosen.find(g.key());
+        auto it = w->chosen.find(key);
         if (it != w->chosen.end()) return it->second;
+        if (keep && (it = w->modelled.find(key)) != w->modelled.end()) return it->second;
     }
-    return heuristic_variant(w, g);
+    const ConvVariant* v = heuristic_variant(w, g);
+    if (keep && v) {
+        std::lock_guard<std::mutex> lock(w->mu);
+        w->modelled[key] = v;
+    }
+    return v;
 }
 
 // The launch record of variant v on the layer (builds and uploads the variant's plan on first use).
