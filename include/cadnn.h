@@ -289,8 +289,8 @@ cadnn_status cadnn_net_add_fc(cadnn_net* net, const cadnn_weights* w, const void
  * cadnn_net_op_info has been called with other flags since the last op was added; finalize
  * refuses a workspace smaller than its own flags need. */
 cadnn_status cadnn_net_workspace_bytes(const cadnn_net* net, size_t* bytes);
-/* flags: CADNN_NET_GRAPH -- cadnn_run_net replays a captured HIP graph (re-captured
- * when x / y change between calls); CADNN_NET_TUNE -- the first cadnn_run_net call
+/* flags: CADNN_NET_GRAPH -- cadnn_run_net replays a captured HIP graph (of the launches that
+ * touch neither x nor y, which may be other tensors on every call); CADNN_NET_TUNE -- the first cadnn_run_net call
  * first runs cadnn_conv2d_tune on every convolution with the net's own buffers, the
  * op that produces its input launched before every timed launch so that the caches are
  * as they will be (that first call synchronises and takes a fraction of a second);

@@ -681,8 +681,35 @@ cadnn_status launch_all(cadnn_net* net, const void* x, void* y, hipStream_t s) {
 void drop_graph(cadnn_net* net) {
     if (net->exec) (void)hipGraphExecDestroy(net->exec);
     net->exec = nullptr;
-    net->cap_x = nullptr;
-    net->cap_y = nullptr;
+}
+
+// Whether launching op i reads the caller's x or writes the caller's y.
+bool touches_caller(const cadnn_net* net, size_t i) {
+    const NetOp& op = net->ops[i];
+    auto last = [&](int k) { return k >= 0 && (size_t)k + 1 == net->ops.size(); };
+    if (op.src_inst < 0 || (op.res >= 0 && op.res_inst < 0) || last((int)i)) return true;
+    for (int p : op.src_insts) if (op.kind == OP_CONCAT && p < 0) return true;
+    if (net->cl) {
+        const ClOp& c = *net->cl->ops[i];
+        return net->cl->import_at == (int)i || (c.shortcut >= 0 && net->ops[(size_t)c.shortcut].src_inst < 0);
+    }
+    return last(op.pool_op) || last(op.dw_op) || (op.shortcut >= 0 && net->ops[(size_t)op.shortcut].src_inst < 0);
+}
+
+// The part of a pass that is replayed as a graph: the longest run of launches, in launch order, that touch
+// neither x nor y, so that the graph serves whatever tensors a call brings.  (A graph that holds
+// their addresses has to be captured and instantiated again for every new input or output buffer:
+// 1.2 ms for ResNet-50, 0.1 ms for a three-layer block that runs in 0.03.)
+struct GraphRange { size_t first = 0, last = 0; };
+GraphRange graph_range(const cadnn_net* net, const std::vector<size_t>& order) {
+    GraphRange best;
+    size_t start = 0;
+    for (size_t k = 0; k <= order.size(); ++k) {
+        if (k < order.size() && !touches_caller(net, order[k])) continue;
+        if (k - start > best.last - best.first) { best.first = start; best.last = k; }
+        start = k + 1;
+    }
+    return best;
 }
 
 // Live tuning (CADNN_NET_TUNE, on the first run): every convolution's candidates are timed on
@@ -1065,8 +1092,11 @@ extern "C" cadnn_status cadnn_run_net(cadnn_net* net, const void* x, void* y, vo
         drop_graph(net);
     }
     if (!net->use_graph) return launch_all(net, x, y, s);
-    if (!net->exec || net->cap_x != x || net->cap_y != y) {
-        drop_graph(net);
+    const std::vector<size_t> order = launch_order(net);
+    const GraphRange range = graph_range(net, order);
+    // (a couple of launches are cheaper one by one)
+    if (range.last - range.first < 4) return launch_all(net, x, y, s);
+    if (!net->exec) {
         hipStream_t cs = nullptr;
         CADNN_HIP(hipStreamCreateWithFlags(&cs, hipStreamNonBlocking));
         hipGraph_t graph = nullptr;
@@ -1075,7 +1105,7 @@ extern "C" cadnn_status cadnn_run_net(cadnn_net* net, const void* x, void* y, vo
         if (e != hipSuccess) {
             st = fail(CADNN_EHIP, "hipStreamBeginCapture failed: %s", hipGetErrorString(e));
         } else {
-            st = launch_all(net, x, y, cs);
+            for (size_t k = range.first; k < range.last && st == CADNN_OK; ++k) st = launch_one(net, order[k], x, y, cs);
             e = hipStreamEndCapture(cs, &graph);
             if (st == CADNN_OK && e != hipSuccess)
                 st = fail(CADNN_EHIP, "hipStreamEndCapture failed: %s", hipGetErrorString(e));
@@ -1090,10 +1120,16 @@ extern "C" cadnn_status cadnn_run_net(cadnn_net* net, const void* x, void* y, vo
         if (graph) (void)hipGraphDestroy(graph);
         (void)hipStreamDestroy(cs);
         if (st != CADNN_OK) return st;
-        net->cap_x = x;
-        net->cap_y = y;
+    }
+    for (size_t k = 0; k < range.first; ++k) {
+        cadnn_status st = launch_one(net, order[k], x, y, s);
+        if (st != CADNN_OK) return st;
     }
     CADNN_HIP(hipGraphLaunch(net->exec, s));
+    for (size_t k = range.last; k < order.size(); ++k) {
+        cadnn_status st = launch_one(net, order[k], x, y, s);
+        if (st != CADNN_OK) return st;
+    }
     return CADNN_OK;
 }
 

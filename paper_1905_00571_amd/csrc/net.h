@@ -118,8 +118,6 @@ struct cadnn_net {
     std::unique_ptr<cadnn::ClNet> cl;   // set: the net runs channels-last
     cadnn::DevBuf cl_ws;                // workspace of a net that was taken there by pinning a variant
     hipGraphExec_t exec = nullptr;
-    const void* cap_x = nullptr;
-    void* cap_y = nullptr;
     size_t elem() const { return dtype == CADNN_F16 ? 2 : 4; }
 };
 
