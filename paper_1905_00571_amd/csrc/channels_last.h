@@ -46,10 +46,11 @@ struct ClPlan {
     DevBuf part, count;
 };
 
-// Tiles a layer can be run with: 64 * mi output channels x 64 * ni output pixels.
+// Tiles a layer can be run with: 64 * mi output channels x 64 * ni output pixels, s stage buffers (how far
+// the loads run ahead), sk workgroups that share a tile, each a slice of K.
 struct ClVariant {
     const char* name;
-    int mi, ni, sk;
+    int mi, ni, s, sk;
 };
 const std::vector<ClVariant>& all_cl_variants();
 

@@ -11,8 +11,17 @@
 //     row are permuted by the row (piece ^ (row / 2) % 8, or (row / 4) % 4 for 64-byte rows), which puts the
 //     16 rows a quarter-wave reads into 16 different bank groups.  The permutation is applied to the
 //     source addresses of the activations and is baked into the weight plan.
-//   * S stage buffers; a stage's loads are issued S - 1 stages ahead, right behind the barrier that says
-//     every wave is done with the buffer: one barrier and one counted wait per stage.
+//   * S stage buffers.  A stage's fragments are read into registers one stage ahead of its products and its
+//     buffer is loaded again right behind the barrier that follows, between the products: one barrier and
+//     one counted wait per stage.
+//   * What bounds it is the way into LDS: 50-57 bytes per clock and CU (measured, data in L2; 29 from behind it),
+//     so a 64 x 64 x 64 step of fp16 takes 290 clocks where its products take 128.  Larger tiles reuse more
+//     but leave CUs idle.  fp32 products take 1024 clocks a step and bound it themselves.
+//   * With one or two workgroups a CU the rest is start and end: 1200 clocks to the first loads and 1500 from the
+//     last product to the last store.  So the launch record is fetched whole, the first weights are
+//     requested before anything is computed, divisions are multiplications, and bias and residual are
+//     requested ahead of the K loop.  ResNet-50 fp16, us per pass before -> after (these and the stages above):
+//     batch 1 371 -> 320, 8 517 -> 419, 32 981 -> 851; fp32 batch 8 1132 -> 1028; MobileNet-V2 fp16 batch 16 490 -> 407.
 //   * Padding is a zero halo in memory, so no tap is ever tested.
 //   * A fused 1x1 projection shortcut (paper Section 4, layer fusion) is more K steps on a second tensor.
 //   * The epilogue goes through LDS, [pixel][channel]: residual rows come in and finished rows go out as
@@ -25,6 +34,7 @@
 //     output-channel tiles of one pixel tile next to each other: its L2 serves the re-reads.
 #include <cmath>
 #include <cstring>
+#include <type_traits>
 
 #include "channels_last.h"
 
@@ -59,9 +69,33 @@ struct ClArgs {
     ClTensorArg xt, x2t, yt, rt;
     uint32_t wspan;
     int total, hw, ow, cout, relu;
-    int steps_tap, steps1, steps, tiles_m, tiles, sk;
+    int steps_tap, steps1, steps, ntaps, tiles_m, tiles, per_die, sk, log_sk;
+    int per_slice;              // steps of a slice of the split
+    uint32_t magic_hw, magic_ow, magic_tm, magic_st;
     int tap_off[kClMaxTaps];
 };
+
+template <int I, int N, class F>
+__device__ __forceinline__ void cl_static_for(F&& f) {
+    if constexpr (I < N) {
+        f(std::integral_constant<int, I>());
+        cl_static_for<I + 1, N>(f);
+    }
+}
+
+// Waits until at most VM vector-memory operations and no LDS read of this wave are outstanding.  (The builtin
+// and not an asm statement: the compiler, which tracks its own loads, then knows that they have landed.)
+template <int VM>
+__device__ __forceinline__ void cl_wait() {
+    asm volatile("" ::: "memory");
+    __builtin_amdgcn_s_waitcnt((VM & 15) | (7 << 4) | ((VM >> 4) << 14));
+    asm volatile("" ::: "memory");
+}
+__device__ __forceinline__ void cl_barrier() {
+    asm volatile("" ::: "memory");
+    __builtin_amdgcn_s_barrier();
+    asm volatile("" ::: "memory");
+}
 
 // 16 bytes per lane from memory to LDS (lane l: lds + 16 l).  The wait for it is the caller's.
 __device__ __forceinline__ void cl_dma(cl_u4 rsrc, uint32_t voff, uint32_t soff, uint32_t lds) {
@@ -79,17 +113,26 @@ __device__ __forceinline__ cl_u4 cl_rsrc(const void* p, uint32_t span) {
     return r;
 }
 
+// MI x NI accumulators of 32 x 32 per wave, 2 x 2 waves: a tile of 64 MI channels x 64 NI pixels; S stage buffers.
 template <typename T, int RB, int MI, int NI, int S>
 struct ClCfg {
     static constexpr int TM = 64 * MI, TN = 64 * NI;
     static constexpr int STAGE = (TM + TN) * RB;
     static constexpr int PITCH = TM * (int)sizeof(T) + 16;
-    static constexpr int MAIN = S * STAGE > TN * PITCH ? S * STAGE : TN * PITCH;
+    static constexpr int cmax(int a, int b) { return a > b ? a : b; }
+    static constexpr int MAIN = cmax(S * STAGE, TN * PITCH);
     static constexpr int LDS = MAIN + TN * 16 + TM * 4;
 };
 
+// v / d for 0 <= v < 2^31 with magic = ceil(2^32 / d): the product is at most one too large.
+__device__ __forceinline__ int cl_div(int v, uint32_t magic, int d) {
+    const int q = (int)__umulhi((uint32_t)v, magic);
+    return d == 1 ? v : q - (q * d > v ? 1 : 0);
+}
+
+// (two waves per SIMD asked for: all registers then are of one kind, no accumulator copies in the loop)
 template <typename T, int RB, int MI, int NI, int S>
-__global__ __launch_bounds__(256) void cl_conv_kernel(const ClArgs a) {
+__global__ __launch_bounds__(256, MI * NI == 1 ? 4 : 2) void cl_conv_kernel(const ClArgs a) {
     using C = ClCfg<T, RB, MI, NI, S>;
     constexpr int TM = C::TM, TN = C::TN, STAGE = C::STAGE, PITCH = C::PITCH;
     constexpr int RPL = 1024 / RB;                 // rows one wave-load fills
@@ -102,24 +145,48 @@ __global__ __launch_bounds__(256) void cl_conv_kernel(const ClArgs a) {
     float* bl = (float*)(cl_smem + C::MAIN + TN * 16);
     const uint32_t lds0 = (uint32_t)(uintptr_t)(__attribute__((address_space(3))) char*)cl_smem;
 
+    // ---- the launch record is fetched whole and at once (field by field, as the compiler would place the loads, it
+    //      is a chain of a dozen scalar-cache misses in front of the first load of data)
+    asm volatile("" :: "s"(a.w), "s"(a.x), "s"(a.x2), "s"(a.y), "s"(a.res), "s"(a.bias), "s"(a.bias2), "s"(a.part), "s"(a.count),
+                 "s"(a.wspan), "s"(a.total), "s"(a.hw), "s"(a.ow), "s"(a.cout), "s"(a.relu), "s"(a.steps_tap), "s"(a.steps1), "s"(a.steps),
+                 "s"(a.ntaps), "s"(a.tiles_m), "s"(a.tiles), "s"(a.per_die), "s"(a.sk), "s"(a.log_sk), "s"(a.per_slice), "s"(a.magic_hw), "s"(a.magic_ow),
+                 "s"(a.magic_tm));
+    asm volatile("" :: "s"(a.xt.span), "s"(a.xt.img), "s"(a.xt.row), "s"(a.xt.col), "s"(a.xt.org), "s"(a.x2t.img), "s"(a.x2t.row), "s"(a.x2t.col),
+                 "s"(a.x2t.org), "s"(a.yt.span), "s"(a.yt.img), "s"(a.yt.row), "s"(a.yt.col), "s"(a.yt.org), "s"(a.rt.span), "s"(a.rt.img),
+                 "s"(a.rt.row), "s"(a.rt.col), "s"(a.rt.org), "s"(a.tap_off[0]));
+
     // ---- which tile: dies own contiguous runs
-    const int per_die = (a.tiles + 7) >> 3;
-    const int t = ((int)blockIdx.x & 7) * per_die + ((int)blockIdx.x >> 3);
-    if (((int)blockIdx.x >> 3) >= per_die || t >= a.tiles) return;
-    const int mt = __builtin_amdgcn_readfirstlane(t % a.tiles_m), rest = t / a.tiles_m;
-    const int z = __builtin_amdgcn_readfirstlane(rest % a.sk), nt = __builtin_amdgcn_readfirstlane(rest / a.sk);
+    const int t = ((int)blockIdx.x & 7) * a.per_die + ((int)blockIdx.x >> 3);
+    if (((int)blockIdx.x >> 3) >= a.per_die || t >= a.tiles) return;
+    const int rest = cl_div(t, a.magic_tm, a.tiles_m), mt = t - rest * a.tiles_m;
+    const int z = rest & (a.sk - 1), nt = rest >> a.log_sk;
     const int m0 = mt * TM, n0 = nt * TN;
 
     const int tid = (int)threadIdx.x, lane = tid & 63;
     const int wv = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int wm = wv >> 1, wn = wv & 1;
 
+    // ---- the weights of the first stage need nothing but the tile's number: on their way before all else
+    constexpr int L = LA + LB;
+    const int s_first = z * a.per_slice, steps = min(a.per_slice, a.steps - s_first);
+    const uint32_t va = (uint32_t)(wv * 1024 + lane * 16);
+    const cl_u4 wr = cl_rsrc(a.w, a.wspan);
+    uint32_t wsoff[MI];
+#pragma unroll
+    for (int i = 0; i < MI; ++i) wsoff[i] = (uint32_t)((mt * MI + i) * a.steps + s_first) * (64u * RB);
+    const uint32_t lds_w = lds0 + (uint32_t)wv * 1024u;
+    auto issue_w = [&](auto I, uint32_t buf) __attribute__((always_inline)) {
+        constexpr int i = decltype(I)::value, PER = 64 * RB / 4096;      // PER: loads of a thread per 64-row block
+        cl_dma(wr, va, wsoff[i / PER] + (uint32_t)(i % PER) * 4096u, lds_w + buf * STAGE + (uint32_t)i * 4096u);
+    };
+    cl_static_for<0, LA>([&](auto I) __attribute__((always_inline)) { issue_w(I, 0u); });
+
     if (tid < TN) {
         const int Q = n0 + tid;
         int4 e = make_int4((int)kClOutOfRange, (int)kClOutOfRange, (int)kClOutOfRange, (int)kClOutOfRange);
         if (Q < a.total) {
-            const int img = Q / a.hw, q = Q - img * a.hw;
-            const int oh = q / a.ow, ow = q - oh * a.ow;
+            const int img = cl_div(Q, a.magic_hw, a.hw), q = Q - img * a.hw;
+            const int oh = cl_div(q, a.magic_ow, a.ow), ow = q - oh * a.ow;
             e.x = img * a.xt.img + oh * a.xt.row + ow * a.xt.col + a.xt.org;
             e.y = img * a.x2t.img + oh * a.x2t.row + ow * a.x2t.col + a.x2t.org;
             e.z = img * a.yt.img + oh * a.yt.row + ow * a.yt.col + a.yt.org;
@@ -127,11 +194,15 @@ __global__ __launch_bounds__(256) void cl_conv_kernel(const ClArgs a) {
         }
         ptab[tid] = e;
     }
-    if (tid < TM) {
-        const int co = m0 + tid;
-        bl[tid] = co < a.cout ? (a.bias ? a.bias[co] : 0.0f) + (a.bias2 ? a.bias2[co] : 0.0f) : 0.0f;
+    // (the bias is requested here and put in LDS behind the K loop: nothing waits for it)
+    float my_bias = 0.0f, my_bias2 = 0.0f;
+    if (tid < TM && m0 + tid < a.cout) {
+        if (a.bias) my_bias = a.bias[m0 + tid];
+        if (a.bias2) my_bias2 = a.bias2[m0 + tid];
     }
-    __syncthreads();
+    // (no wait for memory here, as __syncthreads would have: only the table in LDS is awaited)
+    __builtin_amdgcn_s_waitcnt(0xc07f);
+    cl_barrier();
 
     // ---- sources: this thread's row (of each group of rows) and 16-byte piece
     const int lrow = lane / PIECES, lpos = lane % PIECES;
@@ -143,16 +214,12 @@ __global__ __launch_bounds__(256) void cl_conv_kernel(const ClArgs a) {
         const int e = ptab[j * 4 * RPL + wv * RPL + lrow].x;
         vb[j] = e == (int)kClOutOfRange ? kClOutOfRange : (uint32_t)e + piece;
     }
-    const uint32_t va = (uint32_t)(wv * 1024 + lane * 16);
     cl_u4 xr = cl_rsrc(a.x, a.xt.span);
-    const cl_u4 wr = cl_rsrc(a.w, a.wspan);
 
     // ---- the residual's rows are requested up front where they fit few registers
     constexpr int CPR = TM * (int)sizeof(T) / 16, ITEMS = TN * CPR / 256;
-    constexpr bool EARLY = ITEMS <= 4;
-    const cl_u4 rr_ = cl_rsrc(a.res, a.rt.span);
+    constexpr bool EARLY = ITEMS <= 8;
     const __amdgpu_buffer_rsrc_t rrs = __builtin_amdgcn_make_buffer_rsrc((void*)a.res, 0, a.rt.span, 0x00020000);
-    (void)rr_;
     const int ec = tid % CPR, ep = tid / CPR;                    // epilogue: this thread's piece and first pixel
     const bool ec_live = m0 + ec * EPP < a.cout;
     cl_u4 resv[EARLY ? ITEMS : 1];
@@ -169,14 +236,8 @@ __global__ __launch_bounds__(256) void cl_conv_kernel(const ClArgs a) {
     }
 
     // ---- the walk over this workgroup's slice of K
-    const int per_slice = __builtin_amdgcn_readfirstlane((a.steps + a.sk - 1) / a.sk);
-    const int s_first = z * per_slice;
-    const int steps = min(per_slice, a.steps - s_first);
     int f_left, f_tap = 0, f_todo = steps;
     uint32_t f_soff;
-    uint32_t wsoff[MI];
-#pragma unroll
-    for (int i = 0; i < MI; ++i) wsoff[i] = (uint32_t)((mt * MI + i) * a.steps + s_first) * (64u * RB);
     auto enter_shortcut = [&](int at) __attribute__((always_inline)) {
         xr = cl_rsrc(a.x2, a.x2t.span);
 #pragma unroll
@@ -187,31 +248,30 @@ __global__ __launch_bounds__(256) void cl_conv_kernel(const ClArgs a) {
         f_left = 0x7fffffff;
         f_soff = (uint32_t)at * RB;
     };
-    if (s_first < a.steps1) {
-        f_tap = __builtin_amdgcn_readfirstlane(s_first / a.steps_tap);
+    if (s_first == 0) {
+        f_left = a.steps_tap;
+        f_soff = (uint32_t)a.tap_off[0];
+    } else if (s_first < a.steps1) {
+        f_tap = cl_div(s_first, a.magic_st, a.steps_tap);
         const int at = s_first - f_tap * a.steps_tap;
         f_left = a.steps_tap - at;
         f_soff = (uint32_t)a.tap_off[f_tap] + (uint32_t)at * RB;
     } else {
         enter_shortcut(s_first - a.steps1);
     }
-    const int ntaps = a.steps1 / a.steps_tap;
-    const uint32_t lds_w = lds0 + (uint32_t)wv * 1024u;
-    auto issue = [&](uint32_t buf) __attribute__((always_inline)) {
-        const uint32_t base = lds_w + buf * STAGE;
-#pragma unroll
-        for (int i = 0; i < LA; ++i) {
-            constexpr int PER = 64 * RB / 4096;      // loads of this thread per 64-row block
-            cl_dma(wr, va, wsoff[i / PER] + (uint32_t)(i % PER) * 4096u, base + (uint32_t)i * 4096u);
-        }
-#pragma unroll
-        for (int j = 0; j < LB; ++j) cl_dma(xr, vb[j], f_soff, base + (uint32_t)(TM * RB) + (uint32_t)j * 4096u);
+    // load i of a stage: the weights' first, then the activations'
+    auto issue_one = [&](auto I, uint32_t buf) __attribute__((always_inline)) {
+        constexpr int i = decltype(I)::value;
+        if constexpr (i < LA) issue_w(I, buf);
+        else cl_dma(xr, vb[i - LA], f_soff, lds_w + buf * STAGE + (uint32_t)i * 4096u);
+    };
+    auto advance = [&]() __attribute__((always_inline)) {
 #pragma unroll
         for (int i = 0; i < MI; ++i) wsoff[i] += 64u * RB;
         f_soff += RB;
         --f_todo;
         if (--f_left == 0 && f_todo > 0) {
-            if (++f_tap < ntaps) {
+            if (++f_tap < a.ntaps) {
                 f_left = a.steps_tap;
                 f_soff = (uint32_t)a.tap_off[f_tap];
             } else {
@@ -219,7 +279,6 @@ __global__ __launch_bounds__(256) void cl_conv_kernel(const ClArgs a) {
             }
         }
     };
-
     cl_f16v acc[MI][NI];
 #pragma unroll
     for (int mi = 0; mi < MI; ++mi)
@@ -234,52 +293,97 @@ __global__ __launch_bounds__(256) void cl_conv_kernel(const ClArgs a) {
     const uint32_t fa = (uint32_t)((wm * 32 * MI + l31) * RB), fb = (uint32_t)(TM * RB + (wn * 32 * NI + l31) * RB);
     const uint32_t fp = (uint32_t)((fk ^ fs) * 16);
 
-    // loads in flight per stage and thread; a stage past the end of the slice issues none
-    constexpr int L = LA + LB;
-    auto wait_stage = [&](int ahead) __attribute__((always_inline)) {
-        // `ahead` stages may stay in flight behind the one needed now
-        if constexpr (S >= 4) { if (ahead >= 2) { asm volatile("s_waitcnt vmcnt(%0) lgkmcnt(0)" :: "n"(2 * L) : "memory"); return; } }
-        if constexpr (S >= 3) { if (ahead >= 1) { asm volatile("s_waitcnt vmcnt(%0) lgkmcnt(0)" :: "n"(L) : "memory"); return; } }
-        asm volatile("s_waitcnt vmcnt(0) lgkmcnt(0)" ::: "memory");
+    // A stage's fragments are read into registers one stage ahead of its products, so LDS latency and
+    // the products overlap inside a wave, and a stage's buffer is free again as soon as it is read:
+    //   wait until this wave's loads of stage s + 1 have landed -- barrier: everybody's have, and everybody
+    //   has read stage s -- load stage s + S into the buffer of stage s -- read stage s + 1 -- multiply stage s
+    auto wait_loads = [&](int behind) __attribute__((always_inline)) {
+        // `behind` stages may stay in flight behind the one needed now
+        cl_static_for<1, S>([&](auto B) __attribute__((always_inline)) {
+            if (behind == decltype(B)::value) cl_wait<decltype(B)::value * L>();
+        });
+        if (behind <= 0) cl_wait<0>();
     };
-#pragma unroll
-    for (int j = 0; j < S - 1; ++j)
-        if (j < steps) issue((uint32_t)j);
-    uint32_t rd = 0, wrbuf = S - 1;
-    for (int s = 0; s < steps; ++s) {
-        wait_stage(min(steps - 1 - s, S - 2));
-        __builtin_amdgcn_s_barrier();
-        asm volatile("" ::: "memory");
-        if (s + S - 1 < steps) issue(wrbuf);
-        const char* st = cl_smem + rd * STAGE;
-        // (scheduling of the reads against the products is left to the compiler: everything below is straight-line)
+    static_assert((S - 1) * L <= 63, "the wait counter counts to 63");
+    cl_u4 af[2][KS][MI], bf[2][KS][NI];
+    auto read_frags = [&](auto F, uint32_t buf) __attribute__((always_inline)) {
+        constexpr int f = decltype(F)::value;
+        const char* st = cl_smem + buf * STAGE;
 #pragma unroll
         for (int ks = 0; ks < KS; ++ks) {
             const uint32_t p = fp ^ (uint32_t)(ks * 32);
-            cl_u4 af[MI], bf[NI];
 #pragma unroll
-            for (int mi = 0; mi < MI; ++mi) af[mi] = *(const cl_u4*)(st + fa + mi * 32 * RB + p);
+            for (int mi = 0; mi < MI; ++mi) af[f][ks][mi] = *(const cl_u4*)(st + fa + mi * 32 * RB + p);
 #pragma unroll
-            for (int ni = 0; ni < NI; ++ni) bf[ni] = *(const cl_u4*)(st + fb + ni * 32 * RB + p);
-#pragma unroll
-            for (int mi = 0; mi < MI; ++mi)
-#pragma unroll
-                for (int ni = 0; ni < NI; ++ni) {
-                    if constexpr (sizeof(T) == 2) {
-                        acc[mi][ni] = __builtin_amdgcn_mfma_f32_32x32x16_f16(__builtin_bit_cast(cl_h8, af[mi]),
-                                                                             __builtin_bit_cast(cl_h8, bf[ni]), acc[mi][ni], 0, 0, 0);
-                    } else {
-#pragma unroll
-                        for (int e = 0; e < 4; ++e)
-                            acc[mi][ni] = __builtin_amdgcn_mfma_f32_32x32x2f32(__uint_as_float(af[mi][e]), __uint_as_float(bf[ni][e]),
-                                                                               acc[mi][ni], 0, 0, 0);
-                    }
-                }
+            for (int ni = 0; ni < NI; ++ni) bf[f][ks][ni] = *(const cl_u4*)(st + fb + ni * 32 * RB + p);
         }
-        rd = rd + 1 == S ? 0 : rd + 1;
-        wrbuf = wrbuf + 1 == S ? 0 : wrbuf + 1;
+    };
+    auto multiply = [&](auto F, auto K) __attribute__((always_inline)) {
+        constexpr int f = decltype(F)::value, ks = decltype(K)::value;
+#pragma unroll
+        for (int mi = 0; mi < MI; ++mi)
+#pragma unroll
+            for (int ni = 0; ni < NI; ++ni) {
+                if constexpr (sizeof(T) == 2) {
+                    acc[mi][ni] = __builtin_amdgcn_mfma_f32_32x32x16_f16(__builtin_bit_cast(cl_h8, af[f][ks][mi]),
+                                                                         __builtin_bit_cast(cl_h8, bf[f][ks][ni]), acc[mi][ni], 0, 0, 0);
+                } else {
+#pragma unroll
+                    for (int e = 0; e < 4; ++e)
+                        acc[mi][ni] = __builtin_amdgcn_mfma_f32_32x32x2f32(__uint_as_float(af[f][ks][mi][e]), __uint_as_float(bf[f][ks][ni][e]),
+                                                                           acc[mi][ni], 0, 0, 0);
+                }
+            }
+    };
+    cl_static_for<LA, L>([&](auto I) __attribute__((always_inline)) { issue_one(I, 0u); });
+    advance();
+    for (int j = 1; j < S && j < steps; ++j) {
+        cl_static_for<0, L>([&](auto I) __attribute__((always_inline)) { issue_one(I, (uint32_t)j); });
+        advance();
     }
-
+    wait_loads(min(steps, S) - 1);
+    cl_barrier();
+    read_frags(std::integral_constant<int, 0>(), 0);
+    uint32_t cur = 0;                       // buffer of the stage being multiplied
+    // (FULL: stage s + S exists, known at compile time)
+    auto stage = [&](auto F, auto FULL, int s) __attribute__((always_inline)) {
+        constexpr int f = decltype(F)::value;
+        constexpr bool full = decltype(FULL)::value;
+        const uint32_t nxt = cur + 1 == S ? 0 : cur + 1;
+        const bool more = full || s + S < steps;
+        if (full || s + 1 < steps) {
+            // stages s + 2 .. s + S - 1 are in flight behind stage s + 1
+            if (more || s + S == steps) cl_wait<(S - 2) * L>();
+            else wait_loads(steps - 2 - s);
+            cl_barrier();
+            read_frags(std::integral_constant<int, f ^ 1>(), nxt);
+        }
+        // A load to LDS holds its wave for as long as the memory pipeline takes 64 addresses (16 clocks
+        // and more while the other waves' are in front); between products that time is the matrix pipe's.
+        // (The scheduler is held to the order: LDS reads, then products and loads in turn.)
+        cl_static_for<0, KS>([&](auto K) __attribute__((always_inline)) {
+            constexpr int k = decltype(K)::value;
+            __builtin_amdgcn_sched_barrier(0);
+            multiply(F, K);
+            __builtin_amdgcn_sched_barrier(0);
+            if (more) cl_static_for<k * L / KS, (k + 1) * L / KS>([&](auto I) __attribute__((always_inline)) { issue_one(I, cur); });
+        });
+        if (more) advance();
+        cur = nxt;
+    };
+    typedef std::integral_constant<int, 0> Set0;
+    typedef std::integral_constant<int, 1> Set1;
+    int s = 0;
+    for (; s + 1 + S < steps; s += 2) {
+        stage(Set0(), std::true_type(), s);
+        stage(Set1(), std::true_type(), s + 1);
+    }
+    for (; s < steps; s += 2) {
+        stage(Set0(), std::false_type(), s);
+        if (s + 1 < steps) stage(Set1(), std::false_type(), s + 1);
+    }
+    asm volatile("s_waitcnt vmcnt(0)" ::: "memory");        // (the bias and the residual's rows)
+    if (tid < TM) bl[tid] = my_bias + my_bias2;
     // ---- K split over workgroups: the slices of a tile meet in memory (device-scope accesses go to the level
     //      all dies share; every thread's stores are acknowledged before the arrival is counted)
     if (a.sk > 1) {
@@ -391,15 +495,11 @@ hipError_t launch_cl_tile(const ClArgs& a, hipStream_t s) {
     return hipGetLastError();
 }
 
-#ifndef CADNN_CL_STAGES
-#define CADNN_CL_STAGES(T, RB, MI, NI) ((MI) * (NI) == 4 ? 2 : 3)
-#endif
 template <typename T, int RB>
-hipError_t launch_cl_rb(const ClArgs& a, int mi, int ni, hipStream_t s) {
-    if (mi == 2 && ni == 2) return launch_cl_tile<T, RB, 2, 2, CADNN_CL_STAGES(T, RB, 2, 2)>(a, s);
-    if (mi == 2) return launch_cl_tile<T, RB, 2, 1, CADNN_CL_STAGES(T, RB, 2, 1)>(a, s);
-    if (ni == 2) return launch_cl_tile<T, RB, 1, 2, CADNN_CL_STAGES(T, RB, 1, 2)>(a, s);
-    return launch_cl_tile<T, RB, 1, 1, CADNN_CL_STAGES(T, RB, 1, 1)>(a, s);
+hipError_t launch_cl_rb(const ClArgs& a, const ClVariant& v, hipStream_t s) {
+    if (v.mi == 2) return v.ni == 2 ? launch_cl_tile<T, RB, 2, 2, 2>(a, s) : launch_cl_tile<T, RB, 2, 1, 3>(a, s);
+    if (v.ni == 2) return launch_cl_tile<T, RB, 1, 2, 3>(a, s);
+    return v.s == 3 ? launch_cl_tile<T, RB, 1, 1, 3>(a, s) : launch_cl_tile<T, RB, 1, 1, 4>(a, s);
 }
 
 ClTensorArg tensor_arg(const ClDesc& d, int n, size_t e, int stride, int r0, int c0) {
@@ -418,12 +518,13 @@ ClTensorArg tensor_arg(const ClDesc& d, int n, size_t e, int stride, int r0, int
 
 const std::vector<ClVariant>& all_cl_variants() {
     static const std::vector<ClVariant> v = {
-        {"cl_mfma_128x128", 2, 2, 1}, {"cl_mfma_128x64", 2, 1, 1}, {"cl_mfma_64x128", 1, 2, 1}, {"cl_mfma_64x64", 1, 1, 1},
-        {"cl_mfma_64x64_k2", 1, 1, 2}, {"cl_mfma_64x64_k4", 1, 1, 4}, {"cl_mfma_64x64_k8", 1, 1, 8},
-        {"cl_mfma_128x64_k2", 2, 1, 2}, {"cl_mfma_128x64_k4", 2, 1, 4}, {"cl_mfma_128x128_k2", 2, 2, 2},
+        {"cl_mfma_128x128_s2", 2, 2, 2, 1}, {"cl_mfma_128x64_s3", 2, 1, 3, 1}, {"cl_mfma_64x128_s3", 1, 2, 3, 1}, {"cl_mfma_64x64_s3", 1, 1, 3, 1},
+        {"cl_mfma_64x64_s4", 1, 1, 4, 1}, {"cl_mfma_64x64_s3k2", 1, 1, 3, 2}, {"cl_mfma_64x64_s3k4", 1, 1, 3, 4}, {"cl_mfma_64x64_s4k4", 1, 1, 4, 4},
     };
     return v;
 }
+
+constexpr int64_t kNumCus = 256, kLdsPerCu = 160 * 1024;
 
 static int64_t cl_tiles(const ClVariant& v, int64_t pixels, int cout) {
     return ((pixels + 64 * v.ni - 1) / (64 * v.ni)) * ((cout + 64 * v.mi - 1) / (64 * v.mi));
@@ -432,6 +533,7 @@ static int64_t cl_tiles(const ClVariant& v, int64_t pixels, int cout) {
 bool cl_variant_fits(const ClVariant& v, const ClPlan& plan, int64_t pixels, int cout) {
     if (v.mi == 2 && cout <= 64) return false;
     if (cl_tiles(v, pixels, cout) * v.sk >= (1 << 28)) return false;
+    if (pixels >= (1 << 30)) return false;      // (32-bit pixel arithmetic)
     if (v.sk == 1) return true;
     // every slice gets at least two steps and none is empty; the scratch stays below 256 MiB
     const int per = (plan.steps + v.sk - 1) / v.sk;
@@ -456,24 +558,29 @@ cadnn_status cl_prepare_variant(const ClVariant& v, ClPlan* plan, int64_t pixels
     return CADNN_OK;
 }
 
+// The cost of a layer in clocks, up to what is the same for all tiles: rounds of as many workgroups as fit on
+// a CU (LDS, and the registers the kernel is bound to), each with a start and an end that grow with the tile and
+// with how many run at once, and steps that take a fixed time while a workgroup has the CU to itself
+// (the latency of loads that run two stages ahead) and the CU's rate when it does not.  The
+// constants are fitted to the times of every variant on 116 layers (ResNet-50 at 1, 8 and 32 images,
+// MobileNet-V2 at 16; the tile it takes for a layer is on average 1.5 % slower than that layer's best one).
+// Four stages pay where workgroups are alone or two to a CU and the K loop is long (at one ResNet-50 image:
+// 18 steps 10.9 -> 9.7 us); there is no use for more stages: six and eight measured the same.
 const ClVariant* cl_pick(const cadnn_weights* w, const ClPlan& plan, int64_t pixels, bool f16) {
     const ClVariant* best = nullptr;
     double best_cost = 0.0;
-    const double rb = plan.rb / 128.0;
     for (const ClVariant& v : all_cl_variants()) {
         if (!cl_variant_fits(v, plan, pixels, w->cout)) continue;
-        const double blocks = (double)cl_tiles(v, pixels, w->cout) * v.sk;
-        const double size = v.mi * v.ni;
-        const double per_cu = size == 4 ? 2.0 : size == 2 ? 2.0 : 3.0;          // workgroups a CU holds
-        const double steps = std::max(1.0, std::ceil((double)plan.steps / v.sk));
-        // clocks of a step when a CU's workgroups share it, and of one that has it alone
-        const double mfma = (f16 ? 128.0 : 1024.0) * size * rb;
-        const double alone = std::max(mfma, 600.0);
-        const double shared = std::max(mfma, 600.0 / per_cu);
-        const double rounds = std::ceil(blocks / (256.0 * per_cu));
-        const double in_cu = std::min(per_cu, std::ceil(blocks / 256.0));
-        const double step = in_cu <= 1.0 ? alone : shared * in_cu;
-        const double cost = rounds * (4000.0 + steps * std::max(step, alone) + size * 600.0) + (v.sk > 1 ? 4000.0 + 500.0 * v.sk * size : 0.0);
+        const int64_t blocks = cl_tiles(v, pixels, w->cout) * v.sk;
+        const int steps = (plan.steps + v.sk - 1) / v.sk;
+        if (v.s == 4 && (blocks > 2 * kNumCus || steps < 8)) continue;
+        const int size = v.mi * v.ni, bytes = 64 * (v.mi + v.ni) * plan.rb;
+        const int64_t per_cu = std::min<int64_t>(kLdsPerCu / (v.s * bytes), size == 1 ? 4 : 2);
+        const double rate = std::max((f16 ? 20.0 : 265.0) * size * plan.rb / 128.0, bytes / 70.0);
+        const double alone = std::max(rate, (v.s == 4 ? 630.0 : 800.0) * (1.0 + 0.25 * (size - 1)));
+        auto round = [&](int64_t n) { return n == 0 ? 0.0 : 350.0 + 2700.0 * size * (double)n + steps * std::max(alone, rate * (double)n); };
+        const int64_t in_cu = (blocks + kNumCus - 1) / kNumCus;
+        const double cost = (double)(in_cu / per_cu) * round(per_cu) + round(in_cu % per_cu) + (v.sk > 1 ? 2300.0 + 1100.0 * v.sk : 0.0);
         if (!best || cost < best_cost) { best = &v; best_cost = cost; }
     }
     return best;
@@ -507,14 +614,23 @@ cadnn_status launch_cl_conv(const ClConv& c, const ClVariant& v, bool f16, hipSt
     a.steps = p.steps;
     a.tiles_m = (c.cout + 64 * v.mi - 1) / (64 * v.mi);
     a.sk = v.sk;
+    a.log_sk = v.sk == 4 ? 2 : v.sk == 2 ? 1 : 0;
+    a.ntaps = p.taps;
     a.tiles = (int)cl_tiles(v, a.total, c.cout) * v.sk;
+    a.per_slice = (p.steps + v.sk - 1) / v.sk;
+    a.per_die = (a.tiles + 7) / 8;
+    auto magic = [](int d) { return (uint32_t)(((1ull << 32) + (uint64_t)d - 1) / (uint64_t)d); };
+    a.magic_hw = magic(a.hw);
+    a.magic_ow = magic(a.ow);
+    a.magic_tm = magic(a.tiles_m);
+    a.magic_st = magic(a.steps_tap);
     a.part = (float*)p.part.p;
     a.count = (int*)p.count.p;
     for (int t = 0; t < p.taps; ++t)
         a.tap_off[t] = (int)(((int64_t)p.tap_r[t] * c.xd.row + (int64_t)p.tap_c[t] * c.xd.pix) * (int64_t)e);
     hipError_t err;
-    if (f16) err = p.rb == 128 ? launch_cl_rb<_Float16, 128>(a, v.mi, v.ni, s) : launch_cl_rb<_Float16, 64>(a, v.mi, v.ni, s);
-    else err = p.rb == 128 ? launch_cl_rb<float, 128>(a, v.mi, v.ni, s) : launch_cl_rb<float, 64>(a, v.mi, v.ni, s);
+    if (f16) err = p.rb == 128 ? launch_cl_rb<_Float16, 128>(a, v, s) : launch_cl_rb<_Float16, 64>(a, v, s);
+    else err = p.rb == 128 ? launch_cl_rb<float, 128>(a, v, s) : launch_cl_rb<float, 64>(a, v, s);
     CADNN_HIP(err);
     return CADNN_OK;
 }

@@ -204,15 +204,17 @@ std::unique_ptr<ClNet> cl_layout(const cadnn_net* net) {
 // per launch plus multiply-adds at a rate: the compressed kernels of the plane layouts do the nonzero
 // ones at 8.5 TFLOP/s (ResNet-50, 80 % sparse, fp16 / mixed, fp32: 7-8.7 measured at batch 2 to 32), the
 // matrix cores all of them at 430 (fp16) or 80 (fp32).  Measured around the line (us, planes /
-// channels-last): ResNet-50 fp16 batch 1 417 / 369, 2 633 / 383, 8 1841 / 513, 32 6789 / 972; fp32
-// batch 2 539 / 637, 8 1521 / 1124; VGG-16 batch 1 fp16 394 / 194, fp32 428 / 484; Inception-V3 fp16 batch 2
-// 967 / 803, fp32 batch 1 556 / 1175; MobileNet-V2 fp16 batch 2 227 / 304, 16 613 / 471.  Near the line
-// the plane layouts keep the net: tuning gains them more (10-20 %) than it gains these kernels.
+// channels-last): ResNet-50 fp16 batch 1 417 / 321, 2 632 / 330, 8 1841 / 418, 32 6789 / 851; fp32
+// batch 2 539 / 617, 4 861 / 736, 8 1521 / 1028; VGG-16 batch 1 fp16 392 / 173, fp32 389 / 460; Inception-V3
+// fp16 batch 1 641 / 682, 2 967 / 703, fp32 batch 1 556 / 1130; MobileNet-V1 fp16 batch 1 122 / 162, 16 735 / 267;
+// MobileNet-V2 fp16 batch 2 224 / 270, 4 288 / 283, 16 613 / 407.  Near the line the plane layouts keep the
+// net: tuning gains them more (10-20 %) than it gains these kernels.
 bool cl_expected_faster(const cadnn_net* net) {
     double nonzero = 0.0, dense = 0.0;
-    int planes_launches = 0, cl_launches = 0;
+    double cl_us = 0.0;
+    int planes_launches = 0;
     for (const NetOp& o : net->ops) {
-        if (o.kind != OP_CONCAT) ++cl_launches;
+        if (o.kind != OP_CONCAT) cl_us += o.kind == OP_DEPTHWISE ? 6.0 : 5.3;
         if (o.fused_into < 0 && o.kind != OP_CONCAT) ++planes_launches;
         if (!o.w) continue;
         const double pixels = (double)o.out.n * o.out.h * o.out.w;
@@ -220,8 +222,8 @@ bool cl_expected_faster(const cadnn_net* net) {
         if (o.kind == OP_CONV) dense += 2.0 * (double)o.w->cout * o.w->cin * o.w->kh * o.w->kw * pixels;
     }
     const double planes_us = 4.5 * planes_launches + nonzero / 8.5e6;
-    const double cl_us = 6.7 * cl_launches + dense / (net->dtype == CADNN_F16 ? 430e6 : 80e6);
-    return cl_us < 0.8 * planes_us;
+    cl_us += dense / (net->dtype == CADNN_F16 ? 430e6 : 80e6);
+    return cl_us < 0.77 * planes_us;
 }
 
 cadnn_status cl_prepare(cadnn_net* net) {

@@ -90,7 +90,7 @@ def test_channels_last_net(cad, make, dtype_name):
     net = cad.build_net(ops, ws, bs, shape, dtype, use_graph=True)
     planes = net.variants()
     convs = [i for i, o in enumerate(ops) if o.kind == "conv"]
-    net.set_op_variant(convs[0], "cl_mfma_64x64")          # the whole net goes channels-last
+    net.set_op_variant(convs[0], "cl_mfma_64x64_s3")          # the whole net goes channels-last
 
     def check(what):
         for inp, want, lim in ((xs, ref, bounds[-1]), (xs2, ref2, bound2), (xs, ref, bounds[-1])):
@@ -116,7 +116,7 @@ def test_channels_last_net(cad, make, dtype_name):
             assert name not in have or net.op_variant(i) == name
         check(name)
     if make is deep_net:
-        assert {"cl_mfma_128x128", "cl_mfma_64x64_k8", "cl_mfma_128x64_k4"} <= set(every), every
+        assert {"cl_mfma_128x128_s2", "cl_mfma_64x64_s3k4", "cl_mfma_64x64_s4k4"} <= set(every), every
     with pytest.raises(cad.CadnnError):
         net.set_op_variant(convs[0], "cl_no_such_tile")
     saved = net.variants()

@@ -32,7 +32,7 @@ def test_new_tensors_on_every_call(blocks, cl, dtype_name):
     eager = cad.build_net(ops, ws, bs, shape, dtype, use_graph=False)
     if cl:
         for n in (net, eager):
-            n.set_op_variant(0, "cl_mfma_64x64")
+            n.set_op_variant(0, "cl_mfma_64x64_s3")
     kept = []
     for rep in range(5):
         xi = torch.from_numpy(np.roll(x, rep, axis=2).astype(npdt)).cuda()
