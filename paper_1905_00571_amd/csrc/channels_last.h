@@ -80,7 +80,8 @@ cadnn_status launch_cl_export(const void* x, const ClDesc& xd, void* y, int n, b
 cadnn_status launch_cl_pool(const void* x, const ClDesc& xd, void* y, const ClDesc& yd, bool flat, int n, int k, int stride,
                             int pad, int kind, bool f16, hipStream_t s);
 cadnn_status launch_cl_gap(const void* x, const ClDesc& xd, void* y, int n, bool f16, hipStream_t s);
-cadnn_status launch_cl_depthwise(const cadnn_weights* w, const void* x, const ClDesc& xd, void* y, const ClDesc& yd, int n,
+// 3 x 3, `taps` [9][channels].
+cadnn_status launch_cl_depthwise(const float* taps, const void* x, const ClDesc& xd, void* y, const ClDesc& yd, int n,
                                  int stride, int pad, const float* bias, int relu, bool f16, hipStream_t s);
 
 }  // namespace cadnn

@@ -165,30 +165,36 @@ __global__ __launch_bounds__(256) void cl_gap_kernel(const T* __restrict__ x, Cl
 
 // 3 x 3 depthwise layer on a tensor whose halo holds the padding: a thread keeps the filters of its
 // piece of channels and three columns of input in registers and walks R output rows down, so a new
-// row of output costs 3 (stride 1) or 6 (stride 2) loads instead of 9.
+// row of output costs 3 (stride 1) or 6 (stride 2) loads instead of 9.  The filters come [tap][channel], so
+// neighbouring pieces read neighbouring bytes of them too ([channel][tap], as the layer kernel on planes has them,
+// is 72 4-byte loads per thread, 288 bytes from lane to lane: as long as everything else the thread does).
 template <typename T, int STRIDE>
 __global__ __launch_bounds__(256) void cl_dw3_kernel(const T* __restrict__ x, ClDesc xd, T* __restrict__ y, ClDesc yd,
                                                      const float* __restrict__ w, const float* __restrict__ bias, int n, int pad,
                                                      int relu, int rows) {
     constexpr int N = ClVec<T>::N;
     typedef typename ClVec<T>::type V;
-    const int pieces = yd.c / N, strips = (yd.h + rows - 1) / rows;
-    const int64_t i = (int64_t)blockIdx.x * 256 + threadIdx.x;
-    int64_t rest = i / pieces;
+    // (all of an activation tensor is less than 2 GiB: its 16-byte pieces are counted in 32 bits)
+    const uint32_t pieces = (uint32_t)yd.c / N, strips = (uint32_t)((yd.h + rows - 1) / rows), width = (uint32_t)yd.w;
+    const uint32_t i = blockIdx.x * 256u + threadIdx.x;
+    uint32_t rest = i / pieces;
     const int piece = (int)(i - rest * pieces);
-    const int ow = (int)(rest % yd.w);
-    rest /= yd.w;
-    const int strip = (int)(rest % strips), img = (int)(rest / strips);
+    const uint32_t up = rest / width;
+    const int ow = (int)(rest - up * width);
+    const int img = (int)(up / strips), strip = (int)(up - (uint32_t)img * strips);
     if (img >= n) return;
     const int oh0 = strip * rows, oh1 = min(oh0 + rows, yd.h);
     float wt[9][N], b[N];
-    const float* wp = w + (size_t)piece * N * 9;
 #pragma unroll
-    for (int j = 0; j < N; ++j) {
+    for (int t = 0; t < 9; ++t)
 #pragma unroll
-        for (int t = 0; t < 9; ++t) wt[t][j] = wp[j * 9 + t];
-        b[j] = bias ? bias[piece * N + j] : 0.0f;
-    }
+        for (int j = 0; j < N; j += 4) {
+            const clo_f4 q = *(const clo_f4*)(w + (size_t)t * yd.c + piece * N + j);
+#pragma unroll
+            for (int k = 0; k < 4; ++k) wt[t][j + k] = q[k];
+        }
+#pragma unroll
+    for (int j = 0; j < N; ++j) b[j] = bias ? bias[piece * N + j] : 0.0f;
     const T* xp = x + (int64_t)img * xd.image + xd.origin - (int64_t)pad * xd.row + (int64_t)(ow * STRIDE - pad) * xd.pix + piece * N;
     T* yp = y + (int64_t)img * yd.image + yd.origin + (int64_t)ow * yd.pix + piece * N;
     V in[3][3];
@@ -271,7 +277,7 @@ cadnn_status launch_cl_gap(const void* x, const ClDesc& xd, void* y, int n, bool
     return CADNN_OK;
 }
 
-cadnn_status launch_cl_depthwise(const cadnn_weights* w, const void* x, const ClDesc& xd, void* y, const ClDesc& yd, int n,
+cadnn_status launch_cl_depthwise(const float* taps, const void* x, const ClDesc& xd, void* y, const ClDesc& yd, int n,
                                  int stride, int pad, const float* bias, int relu, bool f16, hipStream_t s) {
     // rows a thread walks: as many as still leave the chip a few workgroups per CU
     const int64_t columns = (int64_t)n * yd.w * (yd.c / (f16 ? 8 : 4));
@@ -279,8 +285,7 @@ cadnn_status launch_cl_depthwise(const cadnn_weights* w, const void* x, const Cl
     while (rows > 2 && columns * ((yd.h + rows - 1) / rows) < 256 * 1024) rows = (rows + 1) / 2;
     const int64_t items = columns * ((yd.h + rows - 1) / rows);
     const dim3 grid((unsigned)((items + 255) / 256)), block(256);
-    const float* wt = (const float*)w->d_dw.p;
-#define CADNN_CL_DW(T, S) CADNN_LAUNCH((cl_dw3_kernel<T, S>), grid, block, 0, s, (const T*)x, xd, (T*)y, yd, wt, bias, n, pad, relu, rows)
+#define CADNN_CL_DW(T, S) CADNN_LAUNCH((cl_dw3_kernel<T, S>), grid, block, 0, s, (const T*)x, xd, (T*)y, yd, taps, bias, n, pad, relu, rows)
     if (f16 && stride == 1) CADNN_CL_DW(_Float16, 1);
     else if (f16) CADNN_CL_DW(_Float16, 2);
     else if (stride == 1) CADNN_CL_DW(float, 1);

@@ -84,6 +84,7 @@ struct ClOp {
     int shortcut = -1;                       // projection op fused into this convolution
     int fused_into = -1;                     // projection: the convolution that computes it
     ClPlan plan;
+    DevBuf dw;                               // depthwise: the filters, [tap][channel]
     const ClVariant* v = nullptr;
 };
 struct ClNet {

@@ -233,7 +233,17 @@ cadnn_status cl_prepare(cadnn_net* net) {
         ClOp& c = *net->cl->ops[i];
         cadnn_status st = CADNN_OK;
         if (op.kind == OP_FC) st = cadnn_fc_prepare(op.w);
-        if (op.kind == OP_DEPTHWISE) st = ensure_dw_device(op.w);
+        if (op.kind == OP_DEPTHWISE && !c.dw.p) {
+            try {
+                std::vector<float> taps((size_t)op.w->cout * 9, 0.0f);
+                for (int r = 0; r < op.w->cout; ++r)
+                    for (int32_t j = op.w->row_ptr[(size_t)r]; j < op.w->row_ptr[(size_t)r + 1]; ++j)
+                        taps[(size_t)op.w->col_idx[(size_t)j] * (size_t)op.w->cout + (size_t)op.w->perm[(size_t)r]] = op.w->vals[(size_t)j];
+                st = c.dw.upload(taps.data(), taps.size() * 4);
+            } catch (const std::bad_alloc&) {
+                st = fail(CADNN_ENOMEM, "out of host memory building the depthwise filter table");
+            }
+        }
         if (op.kind == OP_CONV && c.fused_into < 0 && !c.plan.w.p) {
             int rb = 128;
             const NetOp* p = shortcut_op(net, c);
@@ -274,7 +284,7 @@ cadnn_status cl_launch_one(cadnn_net* net, size_t i, const void* x, void* y, hip
             st = launch_cl_conv(conv_args(net, i, dst), *c.v, f16, s);
             break;
         case OP_DEPTHWISE:
-            st = launch_cl_depthwise(op.w, src, c.xd, dst, c.yd, op.out.n, op.stride, op.pad, (const float*)op.bias, op.relu, f16, s);
+            st = launch_cl_depthwise((const float*)c.dw.p, src, c.xd, dst, c.yd, op.out.n, op.stride, op.pad, (const float*)op.bias, op.relu, f16, s);
             break;
         case OP_FC:
             return launch_fc(op.w, op.src_inst < 0 ? x : src, dst, op.in.n, (const float*)op.bias, op.relu, s);
