@@ -55,7 +55,10 @@ struct ClVariant {
 const std::vector<ClVariant>& all_cl_variants();
 
 struct ClConv {
-    const ClPlan* plan;
+    const ClPlan* plan;                          // the shape of K; its buffers are named below
+    const void* w; size_t w_bytes;
+    float* part; int* count;
+    bool planes;                                 // y and residual are [n][c][h][w]; of yd only h and w are read
     const void* x; ClDesc xd;
     void* y; ClDesc yd;
     const void* residual; ClDesc rd;
@@ -66,11 +69,17 @@ struct ClConv {
 
 cadnn_status cl_build_plan(const cadnn_weights* w, const cadnn_weights* shortcut, int rb, bool stem, ClPlan* plan);
 // The tile the cost rule takes, and whether a variant can run the layer.
-const ClVariant* cl_pick(const cadnn_weights* w, const ClPlan& plan, int64_t pixels, bool f16);
+const ClVariant* cl_pick(int cout, const ClPlan& plan, int64_t pixels, bool f16);
 bool cl_variant_fits(const ClVariant& v, const ClPlan& plan, int64_t pixels, int cout);
 // Scratch of a split-K variant (no-op otherwise).
 cadnn_status cl_prepare_variant(const ClVariant& v, ClPlan* plan, int64_t pixels, int cout);
+void cl_split_scratch(const ClVariant& v, int64_t pixels, int cout, size_t* part_bytes, size_t* count_bytes);
 cadnn_status launch_cl_conv(const ClConv& c, const ClVariant& v, bool f16, hipStream_t s);
+
+// One unpruned layer on [n][c][h][w] tensors from raw weights [cout][cin][kh][kw].
+bool dense_cl_serves(bool f16, int n, int cin, int h, int w, int cout, int kh, int kw, int stride, int pad);
+cadnn_status dense_cl_conv2d(const void* w_dev, const void* x, void* y, const void* residual, int n, int cin, int h, int w,
+                             int cout, int kh, int kw, int stride, int pad, const void* bias, int relu, bool f16, hipStream_t s);
 
 // [n][c][h][w] (the caller's input) -> channels-last.
 cadnn_status launch_cl_import(const void* x, int n, int c, int h, int w, void* y, const ClDesc& yd, bool f16, hipStream_t s);

@@ -71,6 +71,7 @@ struct ClArgs {
     int total, hw, ow, cout, relu;
     int steps_tap, steps1, steps, ntaps, tiles_m, tiles, per_die, sk, log_sk;
     int per_slice;              // steps of a slice of the split
+    int plane;                  // PLANES: bytes from one channel to the next
     uint32_t magic_hw, magic_ow, magic_tm, magic_st;
     int tap_off[kClMaxTaps];
 };
@@ -131,7 +132,10 @@ __device__ __forceinline__ int cl_div(int v, uint32_t magic, int d) {
 }
 
 // (two waves per SIMD asked for: all registers then are of one kind, no accumulator copies in the loop)
-template <typename T, int RB, int MI, int NI, int S>
+// PLANES: y and the residual are [n][c][h][w] (a layer called on its own).  A lane then stores its pixel of each
+// channel straight from the accumulators: 32 lanes write 64 (fp16) or 128 contiguous bytes, which
+// costs less than a pass of its own over y (a launch, 4 us at the least).
+template <typename T, int RB, int MI, int NI, int S, bool PLANES>
 __global__ __launch_bounds__(256, MI * NI == 1 ? 4 : 2) void cl_conv_kernel(const ClArgs a) {
     using C = ClCfg<T, RB, MI, NI, S>;
     constexpr int TM = C::TM, TN = C::TN, STAGE = C::STAGE, PITCH = C::PITCH;
@@ -218,7 +222,7 @@ __global__ __launch_bounds__(256, MI * NI == 1 ? 4 : 2) void cl_conv_kernel(cons
 
     // ---- the residual's rows are requested up front where they fit few registers
     constexpr int CPR = TM * (int)sizeof(T) / 16, ITEMS = TN * CPR / 256;
-    constexpr bool EARLY = ITEMS <= 8;
+    constexpr bool EARLY = ITEMS <= 8 && !PLANES;
     const __amdgpu_buffer_rsrc_t rrs = __builtin_amdgcn_make_buffer_rsrc((void*)a.res, 0, a.rt.span, 0x00020000);
     const int ec = tid % CPR, ep = tid / CPR;                    // epilogue: this thread's piece and first pixel
     const bool ec_live = m0 + ec * EPP < a.cout;
@@ -428,6 +432,45 @@ __global__ __launch_bounds__(256, MI * NI == 1 ? 4 : 2) void cl_conv_kernel(cons
 
     // ---- epilogue.  Lane l holds, per accumulator, pixel l % 32 and channels 8 g + 4 (l / 32) + i, g, i < 4.
     __syncthreads();                        // the stage buffers are free: every wave is past its last read
+    const __amdgpu_buffer_rsrc_t yrs = __builtin_amdgcn_make_buffer_rsrc((void*)a.y, 0, a.yt.span, 0x00020000);
+    if constexpr (PLANES) {
+#pragma unroll
+        for (int ni = 0; ni < NI; ++ni) {
+            const int4 e = ptab[wn * 32 * NI + ni * 32 + l31];
+#pragma unroll
+            for (int mi = 0; mi < MI; ++mi) {
+                const int cl = wm * 32 * MI + mi * 32 + fk * 4;
+                uint32_t off[16];
+                float v[16];
+#pragma unroll
+                for (int i = 0; i < 16; ++i) {
+                    const int ch = cl + (i >> 2) * 8 + (i & 3);
+                    const bool live = m0 + ch < a.cout && e.z != (int)kClOutOfRange;
+                    off[i] = live ? (uint32_t)(e.z + (m0 + ch) * a.plane) : kClOutOfRange;
+                    v[i] = acc[mi][ni][i] + bl[ch];
+                }
+                if (a.res) {
+                    T r[16];
+#pragma unroll
+                    for (int i = 0; i < 16; ++i) {
+                        const int ch = cl + (i >> 2) * 8 + (i & 3);
+                        const uint32_t ro = off[i] == kClOutOfRange ? kClOutOfRange : (uint32_t)(e.w + (m0 + ch) * a.plane);
+                        if constexpr (sizeof(T) == 2) r[i] = __builtin_bit_cast(T, (uint16_t)__builtin_amdgcn_raw_buffer_load_b16(rrs, ro, 0u, 0));
+                        else r[i] = __builtin_bit_cast(T, (uint32_t)__builtin_amdgcn_raw_buffer_load_b32(rrs, ro, 0u, 0));
+                    }
+#pragma unroll
+                    for (int i = 0; i < 16; ++i) v[i] += (float)r[i];
+                }
+#pragma unroll
+                for (int i = 0; i < 16; ++i) {
+                    const T o = (T)((a.relu && !(v[i] > 0.0f)) ? 0.0f : v[i]);
+                    if constexpr (sizeof(T) == 2) __builtin_amdgcn_raw_buffer_store_b16(__builtin_bit_cast(uint16_t, o), yrs, off[i], 0u, 0);
+                    else __builtin_amdgcn_raw_buffer_store_b32(__builtin_bit_cast(uint32_t, o), yrs, off[i], 0u, 0);
+                }
+            }
+        }
+        return;
+    }
     if (a.res) {
 #pragma unroll
         for (int k = 0; k < ITEMS; ++k) {
@@ -471,7 +514,6 @@ __global__ __launch_bounds__(256, MI * NI == 1 ? 4 : 2) void cl_conv_kernel(cons
                 }
             }
     __syncthreads();
-    const __amdgpu_buffer_rsrc_t yrs = __builtin_amdgcn_make_buffer_rsrc((void*)a.y, 0, a.yt.span, 0x00020000);
 #pragma unroll
     for (int k = 0; k < ITEMS; ++k) {
         const int p = ep + k * (256 / CPR);
@@ -482,24 +524,29 @@ __global__ __launch_bounds__(256, MI * NI == 1 ? 4 : 2) void cl_conv_kernel(cons
     }
 }
 
-template <typename T, int RB, int MI, int NI, int S>
+template <typename T, int RB, int MI, int NI, int S, bool PLANES>
 hipError_t launch_cl_tile(const ClArgs& a, hipStream_t s) {
     using C = ClCfg<T, RB, MI, NI, S>;
     // (more than 64 KB of dynamic LDS has to be asked for once per kernel)
     static const hipError_t attr = C::LDS <= 65536 ? hipSuccess
-                                                   : hipFuncSetAttribute((const void*)cl_conv_kernel<T, RB, MI, NI, S>,
+                                                   : hipFuncSetAttribute((const void*)cl_conv_kernel<T, RB, MI, NI, S, PLANES>,
                                                                          hipFuncAttributeMaxDynamicSharedMemorySize, C::LDS);
     if (attr != hipSuccess) return attr;
     const unsigned grid = (unsigned)((a.tiles + 7) / 8 * 8);
-    CADNN_LAUNCH((cl_conv_kernel<T, RB, MI, NI, S>), dim3(grid), dim3(256), (size_t)C::LDS, s, a);
+    CADNN_LAUNCH((cl_conv_kernel<T, RB, MI, NI, S, PLANES>), dim3(grid), dim3(256), (size_t)C::LDS, s, a);
     return hipGetLastError();
 }
 
-template <typename T, int RB>
+template <typename T, int RB, bool P>
 hipError_t launch_cl_rb(const ClArgs& a, const ClVariant& v, hipStream_t s) {
-    if (v.mi == 2) return v.ni == 2 ? launch_cl_tile<T, RB, 2, 2, 2>(a, s) : launch_cl_tile<T, RB, 2, 1, 3>(a, s);
-    if (v.ni == 2) return launch_cl_tile<T, RB, 1, 2, 3>(a, s);
-    return v.s == 3 ? launch_cl_tile<T, RB, 1, 1, 3>(a, s) : launch_cl_tile<T, RB, 1, 1, 4>(a, s);
+    if (v.mi == 2) return v.ni == 2 ? launch_cl_tile<T, RB, 2, 2, 2, P>(a, s) : launch_cl_tile<T, RB, 2, 1, 3, P>(a, s);
+    if (v.ni == 2) return launch_cl_tile<T, RB, 1, 2, 3, P>(a, s);
+    return v.s == 3 ? launch_cl_tile<T, RB, 1, 1, 3, P>(a, s) : launch_cl_tile<T, RB, 1, 1, 4, P>(a, s);
+}
+
+template <typename T, bool P>
+hipError_t launch_cl_type(const ClArgs& a, const ClVariant& v, int rb, hipStream_t s) {
+    return rb == 128 ? launch_cl_rb<T, 128, P>(a, v, s) : launch_cl_rb<T, 64, P>(a, v, s);
 }
 
 ClTensorArg tensor_arg(const ClDesc& d, int n, size_t e, int stride, int r0, int c0) {
@@ -542,10 +589,16 @@ bool cl_variant_fits(const ClVariant& v, const ClPlan& plan, int64_t pixels, int
     return tiles <= 512 && tiles * v.sk * v.mi * v.ni * 16384 <= (256ll << 20);
 }
 
+void cl_split_scratch(const ClVariant& v, int64_t pixels, int cout, size_t* part_bytes, size_t* count_bytes) {
+    const int64_t tiles = v.sk > 1 ? cl_tiles(v, pixels, cout) : 0;
+    *part_bytes = (size_t)(tiles * v.sk * v.mi * v.ni * 16384);
+    *count_bytes = (size_t)tiles * 4;
+}
+
 cadnn_status cl_prepare_variant(const ClVariant& v, ClPlan* plan, int64_t pixels, int cout) {
     if (v.sk <= 1) return CADNN_OK;
-    const int64_t tiles = cl_tiles(v, pixels, cout);
-    const size_t part = (size_t)(tiles * v.sk * v.mi * v.ni * 16384), count = (size_t)tiles * 4;
+    size_t part = 0, count = 0;
+    cl_split_scratch(v, pixels, cout, &part, &count);
     cadnn_status st = CADNN_OK;
     if (plan->part.bytes < part) {
         plan->part.release();
@@ -566,12 +619,12 @@ cadnn_status cl_prepare_variant(const ClVariant& v, ClPlan* plan, int64_t pixels
 // MobileNet-V2 at 16; the tile it takes for a layer is on average 1.5 % slower than that layer's best one).
 // Four stages pay where workgroups are alone or two to a CU and the K loop is long (at one ResNet-50 image:
 // 18 steps 10.9 -> 9.7 us); there is no use for more stages: six and eight measured the same.
-const ClVariant* cl_pick(const cadnn_weights* w, const ClPlan& plan, int64_t pixels, bool f16) {
+const ClVariant* cl_pick(int cout, const ClPlan& plan, int64_t pixels, bool f16) {
     const ClVariant* best = nullptr;
     double best_cost = 0.0;
     for (const ClVariant& v : all_cl_variants()) {
-        if (!cl_variant_fits(v, plan, pixels, w->cout)) continue;
-        const int64_t blocks = cl_tiles(v, pixels, w->cout) * v.sk;
+        if (!cl_variant_fits(v, plan, pixels, cout)) continue;
+        const int64_t blocks = cl_tiles(v, pixels, cout) * v.sk;
         const int steps = (plan.steps + v.sk - 1) / v.sk;
         if (v.s == 4 && (blocks > 2 * kNumCus || steps < 8)) continue;
         const int size = v.mi * v.ni, bytes = 64 * (v.mi + v.ni) * plan.rb;
@@ -590,20 +643,20 @@ cadnn_status launch_cl_conv(const ClConv& c, const ClVariant& v, bool f16, hipSt
     const ClPlan& p = *c.plan;
     const size_t e = f16 ? 2 : 4;
     ClArgs a{};
-    a.w = (const char*)p.w.p;
+    a.w = (const char*)c.w;
     a.x = (const char*)c.x;
     a.y = (char*)c.y;
     a.res = (const char*)c.residual;
     a.bias = c.bias;
     a.xt = tensor_arg(c.xd, c.n, e, c.stride, -c.pad, -c.pad);
-    a.yt = tensor_arg(c.yd, c.n, e, 1, 0, 0);
-    if (c.residual) a.rt = tensor_arg(c.rd, c.n, e, 1, 0, 0);
+    if (!c.planes) a.yt = tensor_arg(c.yd, c.n, e, 1, 0, 0);
+    if (c.residual && !c.planes) a.rt = tensor_arg(c.rd, c.n, e, 1, 0, 0);
     if (p.steps2 > 0) {
         a.x2 = (const char*)c.x2;
         a.bias2 = c.bias2;
         a.x2t = tensor_arg(c.x2d, c.n, e, c.stride2, 0, 0);
     }
-    a.wspan = (uint32_t)p.w.bytes;
+    a.wspan = (uint32_t)c.w_bytes;
     a.hw = c.yd.h * c.yd.w;
     a.total = c.n * a.hw;
     a.ow = c.yd.w;
@@ -624,13 +677,24 @@ cadnn_status launch_cl_conv(const ClConv& c, const ClVariant& v, bool f16, hipSt
     a.magic_ow = magic(a.ow);
     a.magic_tm = magic(a.tiles_m);
     a.magic_st = magic(a.steps_tap);
-    a.part = (float*)p.part.p;
-    a.count = (int*)p.count.p;
+    a.part = c.part;
+    a.count = c.count;
     for (int t = 0; t < p.taps; ++t)
         a.tap_off[t] = (int)(((int64_t)p.tap_r[t] * c.xd.row + (int64_t)p.tap_c[t] * c.xd.pix) * (int64_t)e);
     hipError_t err;
-    if (f16) err = p.rb == 128 ? launch_cl_rb<_Float16, 128>(a, v, s) : launch_cl_rb<_Float16, 64>(a, v, s);
-    else err = p.rb == 128 ? launch_cl_rb<float, 128>(a, v, s) : launch_cl_rb<float, 64>(a, v, s);
+    if (c.planes) {
+        // one pixel of one channel after the other; images follow each other
+        a.yt.img = (int)((int64_t)c.cout * a.hw * (int64_t)e);
+        a.yt.row = (int)(a.ow * e);
+        a.yt.col = (int)e;
+        a.yt.org = 0;
+        a.yt.span = (uint32_t)((int64_t)c.n * a.yt.img);
+        a.plane = (int)(a.hw * (int64_t)e);
+        if (c.residual) a.rt = a.yt;
+        err = f16 ? launch_cl_type<_Float16, true>(a, v, p.rb, s) : launch_cl_type<float, true>(a, v, p.rb, s);
+    } else {
+        err = f16 ? launch_cl_type<_Float16, false>(a, v, p.rb, s) : launch_cl_type<float, false>(a, v, p.rb, s);
+    }
     CADNN_HIP(err);
     return CADNN_OK;
 }

@@ -13,7 +13,7 @@
 // the weight chunk and the gathered activation chunk are staged in LDS (k fastest, rows
 // padded against bank conflicts); global loads of chunk c+1 are issued before the MFMAs of
 // chunk c and written to the other LDS buffer afterwards, one barrier per chunk.
-#include "internal.h"
+#include "channels_last.h"
 
 namespace cadnn {
 
@@ -228,6 +228,8 @@ cadnn_status dense_conv2d_impl(const void* w_dev, const void* x, void* y, int n,
     if (desc_too_large(make_desc(cin, h, wdt)) || desc_too_large(yd) || (int64_t)cin * h * wdt * elem >= 0x7ffffff0ll ||
         yd.image * elem >= 0x7ffffff0ll)
         return fail(CADNN_EUNSUPPORTED, "cadnn_dense_conv2d: one image of a tensor is 2 GiB or more");
+    if (dense_cl_serves(dtype == CADNN_F16, n, cin, h, wdt, cout, kh, kw, stride, pad))
+        return dense_cl_conv2d(w_dev, x, y, residual, n, cin, h, wdt, cout, kh, kw, stride, pad, bias, relu, dtype == CADNN_F16, s);
     // fp16 storage with whole 32-channel steps takes the 128 x 128-tile kernel
     if (cin % 32 == 0 && dense_wide_serves(dtype == CADNN_F16, cin, kh * kw, (int64_t)cin * h * wdt * elem * n, yd.image * elem * n,
                           (int64_t)n * hout * wout))

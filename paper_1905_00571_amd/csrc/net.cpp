@@ -1324,7 +1324,7 @@ extern "C" cadnn_status cadnn_net_set_op_variant(cadnn_net* net, int op_index, c
         const ClVariant* v = nullptr;
         for (const ClVariant* k : cl_candidates(net, (size_t)op_index)) if (name && std::strcmp(k->name, name) == 0) v = k;
         const int64_t pixels = (int64_t)op.out.n * op.out.h * op.out.w;
-        if (!name || !*name) v = cl_pick(op.w, c.plan, pixels, net->dtype == CADNN_F16);
+        if (!name || !*name) v = cl_pick(op.w->cout, c.plan, pixels, net->dtype == CADNN_F16);
         if (v) {
             drop_graph(net);
             CADNN_HIP(hipDeviceSynchronize());

@@ -36,6 +36,10 @@ ClConv conv_args(const cadnn_net* net, size_t i, void* y_region) {
     const ClOp& c = *net->cl->ops[i];
     ClConv a{};
     a.plan = &c.plan;
+    a.w = c.plan.w.p;
+    a.w_bytes = c.plan.w.bytes;
+    a.part = (float*)c.plan.part.p;
+    a.count = (int*)c.plan.count.p;
     a.x = region(net, c.x_stem ? c.x_off : tensor_off_of(net, op.src_inst));
     a.xd = c.xd;
     a.y = y_region;
@@ -259,7 +263,7 @@ cadnn_status cl_prepare(cadnn_net* net) {
                 st = fail(CADNN_ENOMEM, "out of host memory building a conv plan");
             }
             if (st != CADNN_OK) return st;
-            c.v = cl_pick(op.w, c.plan, out_pixels(op), e == 2);
+            c.v = cl_pick(op.w->cout, c.plan, out_pixels(op), e == 2);
             st = cl_prepare_variant(*c.v, &c.plan, out_pixels(op), op.out.c);
         }
         if (st != CADNN_OK) return st;

@@ -1,0 +1,67 @@
+"""cadnn_dense_conv2d over the sizes where its two routes and their tiles end: channels and pixels
+around the 64 and 128 of a tile and the 64 bytes of a step, halos, strides, rectangular filters, K
+long enough to be split, too few channels for the channels-last route.  The bound holds for any
+order of fp32 sums of K products: (K + 3) 2^-24 (sum |w| |x| + |b| + |r|), plus one rounding to storage."""
+import numpy as np
+import pytest
+
+pytestmark = pytest.mark.gpu
+
+torch = pytest.importorskip("torch")
+
+#        n  cin cout  h   w  kh kw stride pad residual
+CASES = [(1, 16, 1, 1, 1, 1, 1, 1, 0, False),
+         (2, 17, 65, 9, 5, 3, 3, 1, 1, True),
+         (3, 33, 130, 7, 7, 1, 1, 1, 0, True),
+         (1, 64, 64, 8, 8, 3, 3, 1, 1, False),
+         (1, 512, 64, 7, 7, 3, 3, 1, 1, True),      # K split over workgroups
+         (2, 100, 24, 13, 11, 5, 5, 1, 2, False),
+         (1, 40, 40, 17, 17, 7, 7, 2, 3, True),
+         (4, 48, 129, 31, 33, 1, 7, 1, 3, False),
+         (2, 96, 72, 14, 10, 3, 3, 2, 0, False),
+         (32, 64, 128, 14, 14, 3, 3, 1, 1, True),   # the large tiles
+         (2, 3, 24, 21, 21, 7, 7, 2, 3, False),     # the kernel on planes
+         (1, 15, 8, 6, 6, 9, 9, 1, 4, True)]
+
+
+@pytest.mark.parametrize("dtype", ["f32", "f16"])
+@pytest.mark.parametrize("case", CASES)
+def test_dense_layer_against_64_bits(case, dtype):
+    if not torch.cuda.is_available():
+        pytest.skip("no GPU")
+    import paper_1905_00571_amd as cad
+    n, cin, cout, h, w, kh, kw, stride, pad, residual = case
+    tt = torch.float16 if dtype == "f16" else torch.float32
+    gen = torch.Generator().manual_seed(cin * 131 + cout)
+    x = torch.randn(n, cin, h, w, generator=gen).to(tt)
+    wt = (torch.randn(cout, cin, kh, kw, generator=gen) * (2.0 / (cin * kh * kw)) ** 0.5).to(tt)
+    b = torch.randn(cout, generator=gen)
+    conv = torch.nn.functional.conv2d
+    ref = conv(x.double(), wt.double(), b.double(), stride, pad)
+    size = conv(x.double().abs(), wt.double().abs(), b.double().abs(), stride, pad)
+    r = None
+    if residual:
+        r = torch.randn(ref.shape, generator=gen).to(tt)
+        ref, size = ref + r.double(), size + r.double().abs()
+    ref = ref.clamp_min(0.0)
+    got = cad.cadnn_dense_conv2d(wt.cuda(), x.cuda(), stride, pad, b.cuda(), None if r is None else r.cuda(), True)
+    got = got.cpu().double()
+    bound = (cin * kh * kw + 3) * 2.0 ** -24 * size
+    if dtype == "f16":
+        bound = bound + 2.0 ** -11 * ref.abs() + 2.0 ** -25
+    excess = ((got - ref).abs() - bound).max().item()
+    assert got.shape == ref.shape and excess <= 0.0, f"{case} {dtype}: {excess:.3e} above the bound"
+
+
+def test_dense_layer_repeats_and_follows_new_weights():
+    """Nothing of a call is kept for the next: new weights and inputs in the same tensors."""
+    if not torch.cuda.is_available():
+        pytest.skip("no GPU")
+    import paper_1905_00571_amd as cad
+    x, wt = torch.randn(2, 64, 14, 14).cuda(), torch.randn(64, 64, 3, 3).cuda()
+    first = cad.cadnn_dense_conv2d(wt, x, 1, 1).clone()
+    assert torch.equal(first, cad.cadnn_dense_conv2d(wt, x, 1, 1))
+    wt.mul_(2.0)
+    assert torch.equal(2.0 * first, cad.cadnn_dense_conv2d(wt, x, 1, 1))
+    x.mul_(0.5)
+    assert torch.equal(first, cad.cadnn_dense_conv2d(wt, x, 1, 1))
