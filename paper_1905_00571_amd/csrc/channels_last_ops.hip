@@ -5,6 +5,7 @@
 // pixel's channels, neighbouring threads on neighbouring pieces, so every access is a run of whole
 // cache lines, and the taps of a window need no unaligned or 2-byte access at all.
 #include <algorithm>
+#include <type_traits>
 
 #include "channels_last.h"
 
@@ -164,49 +165,71 @@ __global__ __launch_bounds__(256) void cl_gap_kernel(const T* __restrict__ x, Cl
 }
 
 // 3 x 3 depthwise layer on a tensor whose halo holds the padding: a thread keeps the filters of its
-// piece of channels and three columns of input in registers and walks R output rows down, so a new
+// piece of channels and three columns of input in registers and walks `rows` output rows down, so a new
 // row of output costs 3 (stride 1) or 6 (stride 2) loads instead of 9.  The filters come [tap][channel], so
 // neighbouring pieces read neighbouring bytes of them too ([channel][tap], as the layer kernel on planes has them,
 // is 72 4-byte loads per thread, 288 bytes from lane to lane: as long as everything else the thread does).
+// What bounds it at the sizes of these nets is the chain of waits, not the 1 to 13 MB of a layer: the launch
+// record is fetched whole, and the rows of the next output are requested before this one is computed (a row
+// awaited where it is used also awaits the store before it).  14 x 14 x 384 at batch 16, fp16, us: 9.3 with
+// [channel][tap], 8.4 with [tap][channel], 4.9 with the rows ahead; 56 x 56 x 144: 22 / 16.6 / 13.
+template <typename T>
+struct ClDwArgs {
+    const T* x;
+    T* y;
+    const float* w;
+    const float* bias;
+    int64_t x_image, y_image, x_first, y_first;     // elements; x_first: tap (0, 0) of output pixel (0, 0)
+    int x_row, x_pix, y_row, y_pix;
+    int c, height, width, n, relu, rows, strips;
+};
+
 template <typename T, int STRIDE>
-__global__ __launch_bounds__(256) void cl_dw3_kernel(const T* __restrict__ x, ClDesc xd, T* __restrict__ y, ClDesc yd,
-                                                     const float* __restrict__ w, const float* __restrict__ bias, int n, int pad,
-                                                     int relu, int rows) {
+__global__ __launch_bounds__(256) void cl_dw3_kernel(const ClDwArgs<T> a) {
     constexpr int N = ClVec<T>::N;
     typedef typename ClVec<T>::type V;
+    asm volatile("" :: "s"(a.x), "s"(a.y), "s"(a.w), "s"(a.bias), "s"(a.x_image), "s"(a.y_image), "s"(a.x_first), "s"(a.y_first), "s"(a.x_row),
+                 "s"(a.x_pix), "s"(a.y_row), "s"(a.y_pix), "s"(a.c), "s"(a.height), "s"(a.width), "s"(a.n), "s"(a.relu), "s"(a.rows), "s"(a.strips));
     // (all of an activation tensor is less than 2 GiB: its 16-byte pieces are counted in 32 bits)
-    const uint32_t pieces = (uint32_t)yd.c / N, strips = (uint32_t)((yd.h + rows - 1) / rows), width = (uint32_t)yd.w;
+    const uint32_t pieces = (uint32_t)a.c / N, strips = (uint32_t)a.strips, width = (uint32_t)a.width;
     const uint32_t i = blockIdx.x * 256u + threadIdx.x;
     uint32_t rest = i / pieces;
     const int piece = (int)(i - rest * pieces);
     const uint32_t up = rest / width;
     const int ow = (int)(rest - up * width);
     const int img = (int)(up / strips), strip = (int)(up - (uint32_t)img * strips);
-    if (img >= n) return;
-    const int oh0 = strip * rows, oh1 = min(oh0 + rows, yd.h);
+    if (img >= a.n) return;
+    const int oh0 = strip * a.rows, oh1 = min(oh0 + a.rows, a.height);
+    const T* xp = a.x + (int64_t)img * a.x_image + a.x_first + (int64_t)(oh0 * STRIDE) * a.x_row + (int64_t)(ow * STRIDE) * a.x_pix + piece * N;
+    T* yp = a.y + (int64_t)img * a.y_image + a.y_first + (int64_t)oh0 * a.y_row + (int64_t)ow * a.y_pix + piece * N;
+    V in[3][3], next[STRIDE][3];
+#pragma unroll
+    for (int r = 0; r < 3; ++r)
+#pragma unroll
+        for (int k = 0; k < 3; ++k) in[r][k] = *(const V*)(xp + (int64_t)r * a.x_row + k * a.x_pix);
     float wt[9][N], b[N];
 #pragma unroll
     for (int t = 0; t < 9; ++t)
 #pragma unroll
         for (int j = 0; j < N; j += 4) {
-            const clo_f4 q = *(const clo_f4*)(w + (size_t)t * yd.c + piece * N + j);
+            const clo_f4 q = *(const clo_f4*)(a.w + (size_t)t * a.c + piece * N + j);
 #pragma unroll
             for (int k = 0; k < 4; ++k) wt[t][j + k] = q[k];
         }
 #pragma unroll
-    for (int j = 0; j < N; ++j) b[j] = bias ? bias[piece * N + j] : 0.0f;
-    const T* xp = x + (int64_t)img * xd.image + xd.origin - (int64_t)pad * xd.row + (int64_t)(ow * STRIDE - pad) * xd.pix + piece * N;
-    T* yp = y + (int64_t)img * yd.image + yd.origin + (int64_t)ow * yd.pix + piece * N;
-    V in[3][3];
-    auto load_row = [&](int slot, int ir) __attribute__((always_inline)) {
+    for (int j = 0; j < N; ++j) b[j] = 0.0f;
+    if (a.bias) {
 #pragma unroll
-        for (int k = 0; k < 3; ++k) in[slot][k] = *(const V*)(xp + (int64_t)ir * xd.row + (int64_t)k * xd.pix);
-    };
-#pragma unroll
-    for (int r = 0; r < 3 - STRIDE; ++r) load_row(r, oh0 * STRIDE + r);
+        for (int j = 0; j < N; ++j) b[j] = a.bias[piece * N + j];
+    }
+    xp += (int64_t)3 * a.x_row;
     for (int oh = oh0; oh < oh1; ++oh) {
+        if (oh + 1 < oh1) {
 #pragma unroll
-        for (int r = 3 - STRIDE; r < 3; ++r) load_row(r, oh * STRIDE + r);
+            for (int r = 0; r < STRIDE; ++r)
+#pragma unroll
+                for (int k = 0; k < 3; ++k) next[r][k] = *(const V*)(xp + (int64_t)r * a.x_row + k * a.x_pix);
+        }
         float s[N];
 #pragma unroll
         for (int j = 0; j < N; ++j) s[j] = 0.0f;
@@ -220,14 +243,16 @@ __global__ __launch_bounds__(256) void cl_dw3_kernel(const T* __restrict__ x, Cl
 #pragma unroll
         for (int j = 0; j < N; ++j) {
             float v = s[j] + b[j];
-            if (relu) v = v > 0.0f ? v : 0.0f;
+            if (a.relu) v = v > 0.0f ? v : 0.0f;
             o[j] = (T)v;
         }
-        *(V*)(yp + (int64_t)oh * yd.row) = o;
+        *(V*)yp = o;
+        yp += a.y_row;
+        xp += (int64_t)STRIDE * a.x_row;
 #pragma unroll
-        for (int r = 0; r < 3 - STRIDE; ++r)
+        for (int r = 0; r < 3; ++r)
 #pragma unroll
-            for (int k = 0; k < 3; ++k) in[r][k] = in[r + STRIDE][k];
+            for (int k = 0; k < 3; ++k) in[r][k] = r + STRIDE < 3 ? in[r + STRIDE < 3 ? r + STRIDE : 0][k] : next[r + STRIDE >= 3 ? r + STRIDE - 3 : 0][k];
     }
 }
 
@@ -283,13 +308,25 @@ cadnn_status launch_cl_depthwise(const float* taps, const void* x, const ClDesc&
     const int64_t columns = (int64_t)n * yd.w * (yd.c / (f16 ? 8 : 4));
     int rows = 14;
     while (rows > 2 && columns * ((yd.h + rows - 1) / rows) < 256 * 1024) rows = (rows + 1) / 2;
-    const int64_t items = columns * ((yd.h + rows - 1) / rows);
-    const dim3 grid((unsigned)((items + 255) / 256)), block(256);
-#define CADNN_CL_DW(T, S) CADNN_LAUNCH((cl_dw3_kernel<T, S>), grid, block, 0, s, (const T*)x, xd, (T*)y, yd, taps, bias, n, pad, relu, rows)
-    if (f16 && stride == 1) CADNN_CL_DW(_Float16, 1);
-    else if (f16) CADNN_CL_DW(_Float16, 2);
-    else if (stride == 1) CADNN_CL_DW(float, 1);
-    else CADNN_CL_DW(float, 2);
+    const int strips = (yd.h + rows - 1) / rows;
+    const dim3 grid((unsigned)((columns * strips + 255) / 256)), block(256);
+    auto fill = [&](auto& a) {
+        typedef typename std::remove_const<typename std::remove_pointer<decltype(a.x)>::type>::type T;
+        a.x = (const T*)x; a.y = (T*)y; a.w = taps; a.bias = bias;
+        a.x_image = xd.image; a.y_image = yd.image;
+        a.x_first = xd.origin - (int64_t)pad * xd.row - (int64_t)pad * xd.pix;
+        a.y_first = yd.origin;
+        a.x_row = xd.row; a.x_pix = xd.pix; a.y_row = yd.row; a.y_pix = yd.pix;
+        a.c = yd.c; a.height = yd.h; a.width = yd.w; a.n = n; a.relu = relu; a.rows = rows; a.strips = strips;
+    };
+    ClDwArgs<_Float16> h{};
+    ClDwArgs<float> f{};
+    if (f16) fill(h); else fill(f);
+#define CADNN_CL_DW(T, S, A) CADNN_LAUNCH((cl_dw3_kernel<T, S>), grid, block, 0, s, A)
+    if (f16 && stride == 1) CADNN_CL_DW(_Float16, 1, h);
+    else if (f16) CADNN_CL_DW(_Float16, 2, h);
+    else if (stride == 1) CADNN_CL_DW(float, 1, f);
+    else CADNN_CL_DW(float, 2, f);
 #undef CADNN_CL_DW
     CADNN_HIP(hipGetLastError());
     return CADNN_OK;
