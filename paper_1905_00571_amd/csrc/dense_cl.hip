@@ -5,7 +5,7 @@
 // [n][c][h][w] from its accumulators.  Both tensors are moved once more than a kernel on planes
 // moves them (256 channels of 14 x 14 at batch 32, fp16: 6.4 MB and 1.2 MB of weights), which buys
 // 16-byte loads straight to LDS for 2-byte gathers and a transposition in registers.  us per call, one launch on
-// planes / this: that layer 52.9 / 27.5; fp16 192 -> 192 5x5 on 8 x 42 77 / 21, 29 -> 36 5x5 on two 100 x 100 images
+// planes / this: that layer 52.9 / 24.1; fp16 192 -> 192 5x5 on 8 x 42 77 / 21, 29 -> 36 5x5 on two 100 x 100 images
 // 45 / 17; fp32 62 -> 188 7x7 on 71 x 71 189 / 76, 107 -> 25 7x7 / 2 on 43 x 43 316 / 39.
 #include <algorithm>
 #include <mutex>
@@ -76,7 +76,20 @@ __global__ __launch_bounds__(256) void cl_arrange_kernel(const ClArrange a) {
         T* mine = lds + wv * all;
         if (co < a.cout) {
             const T* src = (const T*)a.w + ((int64_t)co * a.cin + c0) * a.taps;
-            for (int i = lane; i < all; i += 64) mine[i] = i < have ? src[i] : (T)0.0f;
+            // (nine loads in flight: a 3x3 filter's step of 64 channels at once)
+            for (int i0 = 0; i0 < all; i0 += 9 * 64) {
+                T v[9];
+#pragma unroll
+                for (int u = 0; u < 9; ++u) {
+                    const int i = i0 + u * 64 + lane;
+                    v[u] = i < have ? src[i] : (T)0.0f;
+                }
+#pragma unroll
+                for (int u = 0; u < 9; ++u) {
+                    const int i = i0 + u * 64 + lane;
+                    if (i < all) mine[i] = v[u];
+                }
+            }
         }
         __syncthreads();
         if (co >= a.cout) return;
