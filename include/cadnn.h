@@ -319,7 +319,11 @@ cadnn_status cadnn_net_workspace_bytes(const cadnn_net* net, size_t* bytes);
  *     whole group.  Tuning (CADNN_NET_TUNE) keeps a group only if it beats its layers
  *     launched apart.
  *   - a window pool that rides on no launch moves up in the launch order to where its input
- *     completes (launched_after). */
+ *     completes (launched_after).
+ * A net with enough work (a model of its launches and multiply-adds decides, unless a variant is pinned) runs with
+ * channels-last tensors on the matrix cores instead, over zero-filled weights: there a pruned weight meets its
+ * activation, so an infinity or NaN that arises in a map reaches every output channel of its windows, not only those
+ * with a nonzero weight on it.  Pinning a convolution to a variant of the other kind changes the whole net over. */
 #define CADNN_NET_GRAPH 1
 #define CADNN_NET_TUNE 2
 #define CADNN_NET_PLAIN_LAYOUT 4

@@ -221,65 +221,176 @@ static std::vector<const ConvVariant*> candidates(const cadnn_weights* w, const 
     return out;
 }
 
-// Default choice when nothing was tuned or pinned: a model of one launch on 256 CUs x 4
-// SIMDs, in cycles.  For the staging-free families it is the largest of three terms --
-// a wave's own latency chain times the rounds of waves the chip needs, the vector issue
-// slots all waves consume (prologue + instructions per nonzero), and the L1 cache-line
-// traffic (32 bytes per cycle per CU; a stride-2 lane pattern touches twice the lines) --
-// with constants fitted to the tuner's timings of every variant on ResNet-50, VGG-16,
-// MobileNet-V1 and Inception-V3 at batch 1 and ResNet-50 at batch 8 (its pick costs 8-15 %
-// over the tuned choice; the fit leaves the L1 term almost no weight).
-// Modelled cycles of one launch of variant v on the layer; negative: not modelled (the
-// LDS-staged families, chosen by tuning only).
+// Default choice when nothing was tuned or pinned: a model of one launch in microseconds.  Every
+// family's time is a sum of non-negative multiples of the same few quantities of a launch:
+//   1, the rounds of workgroups a CU runs one after the other, and per round the channel chunks staged, the nonzeros a
+//   wave walks and the LDS words it stages (a wave's own latency); the waves of the launch per SIMD, times the
+//   nonzeros, times the words (what all waves together issue); the levels of a split row's reduction.
+// The staging-free families have cache lines read in place of the words, the matrix-core kernels K steps.
+// The multiples are fitted per family and pixels per lane (non-negative least squares on relative errors)
+// to the tuner's times of every variant on 230 layers of 16 to 512 channels, 1x1 to 7x7, both storage types, batch 1
+// to 16, and on the layers of VGG-16, Inception-V3 and ResNet-50 in fp32 at batch 1 to 3.  Its pick takes 1.12 times
+// (nets: 1.08 times) the best variant's time in the geometric mean; a model of the staging-free families
+// alone, with the staged ones as a last resort, took 1.61 times on the single layers.
+struct VariantCost { int family, p, kind, f16; float c[9]; };
+constexpr VariantCost kVariantCosts[] = {
+    {FAM_DENSE, 1, 0, 0, {4.1f, 3.92f, 1.81f, 0.357f, 0.0f, 0.0f, 0.0f, 0.0f, 0.0f}},
+    {FAM_DENSE, 1, 0, 1, {8.76f, 0.398f, 1.88f, 0.0f, 0.0f, 0.0f, 0.0f, 0.0f, 0.0f}},
+    {FAM_DIRECT, 1, 0, 0, {9.23f, 0.0f, 0.0f, 0.0486f, 0.156f, 0.0f, 0.0319f, 0.0f, 0.0f}},
+    {FAM_DIRECT, 1, 0, 1, {10.3f, 0.0f, 0.0f, 0.0414f, 0.132f, 0.0f, 0.0964f, 0.0f, 0.0f}},
+    {FAM_DIRECT, 2, 0, 0, {11.3f, 0.0f, 0.0f, 0.0691f, 0.375f, 0.0f, 0.115f, 0.0f, 0.0f}},
+    {FAM_DIRECT, 2, 0, 1, {12.0f, 0.0f, 0.0f, 0.0643f, 0.0f, 0.0f, 0.165f, 0.0f, 0.0f}},
+    {FAM_DIRECT, 4, 0, 0, {11.3f, 3.36f, 0.0f, 0.0805f, 0.0f, 0.0f, 0.268f, 0.0f, 0.0f}},
+    {FAM_DIRECT, 4, 0, 1, {16.6f, 0.0f, 0.0f, 0.0755f, 0.0f, 0.0f, 0.333f, 0.0f, 0.0f}},
+    {FAM_DENSE, 1, 1, 1, {11.8f, 0.846f, 0.474f, 0.0656f, 0.0f, 0.0f, 0.0f, 0.0f, 0.0f}},
+    {FAM_LINEAR, 1, 0, 0, {5.93f, 0.0f, 0.0156f, 0.0183f, 0.117f, 0.0f, 0.222f, 0.0173f, 0.0f}},
+    {FAM_LINEAR, 1, 0, 1, {5.76f, 0.0f, 0.0f, 0.0343f, 0.143f, 0.0f, 0.03f, 0.0f, 0.0f}},
+    {FAM_LINEAR, 2, 0, 0, {5.99f, 0.0f, 0.0204f, 0.0295f, 0.136f, 0.0f, 0.237f, 0.0f, 0.0f}},
+    {FAM_LINEAR, 2, 0, 1, {5.5f, 0.493f, 0.0569f, 0.0237f, 0.0f, 0.0f, 0.167f, 0.0f, 0.0f}},
+    {FAM_LINEAR, 2, 1, 0, {5.91f, 0.0f, 0.0119f, 0.0228f, 0.144f, 0.0183f, 0.0f, 0.0f, 0.0f}},
+    {FAM_LINEAR, 2, 1, 1, {5.75f, 0.0f, 0.0147f, 0.0319f, 0.157f, 0.00247f, 0.0f, 0.0f, 0.0f}},
+    {FAM_LINEAR, 4, 0, 0, {7.44f, 0.0873f, 0.0935f, 0.00873f, 0.611f, 0.0f, 0.219f, 0.0f, 0.0f}},
+    {FAM_LINEAR, 4, 0, 1, {6.71f, 0.18f, 0.127f, 0.0f, 0.733f, 0.0f, 0.272f, 0.0f, 0.0f}},
+    {FAM_LINEAR, 4, 1, 0, {6.22f, 0.0f, 0.0159f, 0.0245f, 0.26f, 0.0188f, 0.0f, 0.0f, 0.0f}},
+    {FAM_LINEAR, 4, 1, 1, {6.08f, 0.0f, 0.0f, 0.0844f, 0.191f, 0.0143f, 0.0f, 0.0708f, 0.0f}},
+    {FAM_PTILE, 1, 0, 0, {6.99f, 1.28f, 1.19f, 0.0412f, 0.0f, 0.111f, 0.00049f, 0.0236f, 0.0464f}},
+    {FAM_PTILE, 1, 1, 0, {7.03f, 1.55f, 0.472f, 0.0452f, 0.127f, 0.107f, 0.0f, 0.0f, 0.0f}},
+    {FAM_PTILE, 1, 0, 1, {6.6f, 3.17f, 0.0f, 0.0419f, 0.128f, 0.0f, 0.00136f, 0.0267f, 0.0f}},
+    {FAM_PTILE, 1, 1, 1, {6.78f, 0.857f, 1.4f, 0.0476f, 0.263f, 0.105f, 0.0f, 0.0f, 0.277f}},
+    {FAM_PTILE, 2, 0, 0, {8.59f, 0.901f, 0.894f, 0.0436f, 0.0986f, 0.0f, 0.00271f, 0.0f, 0.0f}},
+    {FAM_PTILE, 2, 1, 0, {7.97f, 0.953f, 0.73f, 0.0547f, 0.09f, 0.0625f, 0.0f, 0.0f, 0.0f}},
+    {FAM_PTILE, 2, 0, 1, {7.21f, 2.21f, 1.85f, 0.0428f, 0.223f, 0.0f, 0.00453f, 0.0f, 0.0f}},
+    {FAM_PTILE, 2, 1, 1, {8.27f, 1.97f, 0.0381f, 0.052f, 0.25f, 0.32f, 0.00166f, 0.0f, 0.0f}},
+    {FAM_PTILE, 4, 0, 0, {8.72f, 3.53f, 1.18f, 0.0832f, 0.0286f, 0.0f, 0.0246f, 0.0f, 0.0f}},
+    {FAM_PTILE, 4, 1, 0, {7.89f, 1.67f, 1.63f, 0.0567f, 0.0f, 0.556f, 0.00774f, 0.0f, 0.0f}},
+    {FAM_PTILE, 4, 0, 1, {9.59f, 1.48f, 3.89f, 0.0743f, 0.147f, 0.0f, 0.0322f, 0.0f, 0.0f}},
+    {FAM_PTILE, 4, 1, 1, {8.39f, 0.0f, 5.39f, 0.0577f, 0.109f, 0.0f, 0.0108f, 0.00608f, 0.0f}},
+    {FAM_LINEAR, 2, 2, 0, {5.85f, 0.517f, 0.0f, 0.0218f, 0.541f, 0.0217f, 0.0f, 0.0f, 0.0f}},
+    {FAM_LINEAR, 4, 2, 0, {5.54f, 0.7f, 0.0f, 0.0354f, 0.286f, 0.0163f, 0.0287f, 0.342f, 0.0f}},
+    {FAM_STILE, 1, 0, 0, {5.97f, 0.729f, 1.06f, 0.0268f, 0.0f, 0.565f, 0.00592f, 0.0189f, 0.0f}},
+    {FAM_STILE, 1, 0, 1, {6.38f, 1.3f, 1.17f, 0.0268f, 0.0f, 0.198f, 0.00616f, 0.0277f, 0.0f}},
+    {FAM_STILE, 2, 0, 0, {0.0f, 0.628f, 1.32f, 0.0206f, 0.0f, 0.461f, 0.0148f, 0.0f, 1.88f}},
+    {FAM_STILE, 2, 0, 1, {0.0f, 0.0222f, 2.21f, 0.0113f, 0.0f, 0.318f, 0.0176f, 0.0f, 2.04f}},
+    {FAM_STILE, 4, 0, 0, {0.0f, 1.66f, 0.71f, 0.0455f, 5.68e-05f, 0.996f, 0.0167f, 0.0107f, 1.97f}},
+    {FAM_STILE, 4, 0, 1, {0.0f, 0.786f, 1.35f, 0.0364f, 0.0f, 1.07f, 0.0177f, 0.00839f, 2.42f}},
+    {FAM_TILE, 1, 0, 0, {5.5f, 2.13f, 1.4f, 0.0491f, 0.0128f, 2.14f, 0.0f, 0.031f, 0.0f}},
+    {FAM_TILE, 1, 0, 1, {11.4f, 0.0f, 0.0f, 0.0537f, 0.0253f, 1.96f, 0.0f, 0.128f, 0.0f}},
+    {FAM_TILE, 2, 0, 0, {5.33f, 3.03f, 1.41f, 0.0698f, 0.00986f, 2.56f, 0.0f, 0.00169f, 0.0f}},
+    {FAM_TILE, 2, 0, 1, {16.5f, 0.0f, 0.0f, 0.0566f, 0.041f, 0.0f, 0.00895f, 0.0299f, 0.0f}},
+    {FAM_TILE, 4, 0, 0, {8.05f, 0.0f, 4.19f, 0.0555f, 0.00753f, 3.71f, 0.0105f, 0.00554f, 0.0f}},
+    {FAM_TILE, 4, 0, 1, {0.0f, 10.0f, 1.25f, 0.0496f, 0.234f, 3.36f, 0.0203f, 0.01f, 0.0f}},
+    {FAM_WTILE, 4, 16, 0, {8.59f, 0.0f, 1.18f, 0.0245f, 0.0662f, 0.526f, 0.00741f, 0.0f, 0.0f}},
+    {FAM_WTILE, 4, 4, 0, {8.32f, 0.0f, 1.22f, 0.0204f, 0.0805f, 0.293f, 0.00506f, 0.0f, 0.0f}},
+    {FAM_WTILE, 4, 64, 0, {7.92f, 0.307f, 0.717f, 0.0456f, 0.0614f, 0.592f, 0.0f, 0.0f, 0.0f}},
+    {FAM_WTILE, 4, 8, 0, {8.78f, 0.0f, 1.15f, 0.0239f, 0.0765f, 0.345f, 0.00688f, 0.0f, 0.0f}},
+    {FAM_WTILE, 4, 16, 1, {8.69f, 0.87f, 0.975f, 0.0175f, 0.113f, 0.0f, 0.00935f, 0.0f, 0.0f}},
+    {FAM_WTILE, 4, 4, 1, {8.0f, 0.687f, 1.78f, 0.0154f, 0.0849f, 0.0f, 0.0071f, 0.0f, 0.0f}},
+    {FAM_WTILE, 4, 64, 1, {8.9f, 0.0f, 1.5f, 0.0367f, 0.035f, 0.341f, 0.0f, 0.00752f, 0.0f}},
+    {FAM_WTILE, 4, 8, 1, {9.29f, 0.267f, 1.57f, 0.0164f, 0.0964f, 0.0f, 0.00959f, 0.0f, 0.0f}},
+};
+
 static double variant_cost(const cadnn_weights* w, const ConvGeom& g, const ConvVariant* v) {
-    const double nnz_row = w->cout ? (double)w->nnz / w->cout : 0.0;
-    const double pixels = (double)g.hout * g.wout;
-    double cost;
-    if (v->family == FAM_DENSE && v->tw == 128) {
-        // large tiles, two workgroups per CU; for a pruned layer, and for K split over
-        // workgroups, the measured selection decides
-        if ((double)w->nnz < 0.25 * (double)w->cout * w->cin * w->kh * w->kw || v->splitk > 1) return -1.0;
-        const double tm = v->rows_per_block(), tn = 64.0 * v->p;
-        const double blocks = std::ceil(pixels * g.n / tn) * std::ceil(w->cout / tm);
-        const double K = (double)w->cin * w->kh * w->kw;
-        cost = 4000.0 + std::ceil(blocks / 512.0) * std::ceil(K / 32.0) * (300.0 + 1200.0 * tm * tn / 16384.0);
-    } else if (v->family == FAM_DENSE) {
-        // matrix cores: 64 x 64 tiles, ~1024 cycles per 32-deep chunk of K per tile
-        if ((double)w->nnz < 0.25 * (double)w->cout * w->cin * w->kh * w->kw) return -1.0;   // by measurement only
-        const double blocks = std::ceil(pixels / 64.0) * g.n * std::ceil(w->cout / 64.0);
-        const double K = (double)w->cin * w->kh * w->kw;
-        cost = 2500.0 + std::ceil(blocks / 256.0) * std::ceil(K / 32.0) * 1100.0;
-    } else if (v->family == FAM_STILE || v->family == FAM_PTILE || v->family == FAM_WTILE) {
-        return -1.0;
-    } else if (v->quad) {
-        return -1.0;
-    } else if (v->family != FAM_TILE) {
-        const int P = v->p;
-        const double walked = v->adjacent == 2 ? (double)g.hout * ((g.wout + P - 1) / P * P) : pixels;
-        const double tiles = std::ceil(walked / (64.0 * P)) * g.n;
-        const double blocks = tiles * std::ceil((double)w->cout / v->rows_per_block());
-        const double waves = blocks * v->nw;
-        const double iters = v->rpw * nnz_row / v->ks;
-        const double line_bytes = 256.0 * P * ((g.stride == 2 && !g.xd.s2d) ? 2.0 : 1.0);
-        const double t_l1 = waves * iters * line_bytes / 32.0 / 256.0;
-        const double instrs = v->adjacent ? 3.0 + P : 2.0 + 2.0 * P;
-        const double t_issue = waves * (1787.0 + iters * instrs * 1.21) / 1024.0;
-        const double per_nz = 77.4 * (1.0 + 0.51 * (P - 1)) / (1.0 + 0.079 * std::log2(v->unroll / 4.0));
-        const double t_wave = 382.0 + iters * per_nz + (v->ks > 1 ? 338.0 * std::log2((double)v->ks) : 0.0);
-        const double rounds = std::ceil(waves / (1024.0 * 2.3));
-        cost = std::max(std::max(t_wave * rounds, t_issue), 0.078 * t_l1);
-        if (v->family == FAM_DIRECT) cost *= 1.3;   // per-lane tap offsets, bounds by range check
+    auto up = [](int64_t a, int64_t b) { return (a + b - 1) / b; };
+    const int taps = w->kh * w->kw, S = g.stride;
+    const bool dense = v->family == FAM_DENSE, free = v->family == FAM_LINEAR || v->family == FAM_DIRECT;
+    // for a pruned layer (whose zeros would meet every activation), and for K split over workgroups, the measured
+    // selection decides on the matrix cores
+    if (dense && ((double)w->nnz < 0.25 * (double)w->cout * w->cin * taps || v->splitk > 1)) return -1.0;
+    const int kind = dense ? v->tw == 128 : v->family == FAM_PTILE ? v->tw == 16 : v->family == FAM_WTILE ? v->rw
+                     : v->family == FAM_LINEAR ? (v->quad ? 2 : v->adjacent != 0) : 0;
+    const VariantCost* m = nullptr;
+    for (const VariantCost& c : kVariantCosts)
+        if (c.family == v->family && (dense || c.p == v->p) && c.kind == kind && (c.f16 != 0) == v->is_f16) m = &c;
+    if (!m) return -1.0;
+    double x[9] = {1.0};
+    if (dense) {
+        const bool wide = v->tw == 128;
+        const int tm = wide ? v->rows_per_block() : 64, tn = wide ? 64 * v->p : 64;
+        const int64_t pixels = (int64_t)g.hout * g.wout;
+        const double blocks = (double)((wide ? up(pixels * g.n, tn) : up(pixels, tn) * g.n) * up(w->cout, tm));
+        const double steps = (double)(wide && w->cin % 32 == 0 ? (int64_t)w->cin / 32 * taps : up((int64_t)w->cin * taps, 32));
+        x[1] = std::max(1.0, blocks / 512.0);
+        x[2] = x[1] * steps;
+        x[3] = blocks / 256.0 * steps * (tm * tn / 4096.0);
     } else {
-        const double tiles = std::ceil((double)g.wout / v->tw) * std::ceil((double)g.hout / v->th) * g.n;
-        const double blocks = tiles * std::ceil((double)w->cout / v->rows_per_block());
-        const double nchunks = std::ceil((double)w->cin / v->cch);
-        const double stage = nchunks * (1500.0 + (double)std::min(w->cin, v->cch) * v->plane / (v->nw * 64.0) * 24.0);
-        const double iters = v->rpw * nnz_row;
-        const double t_block = stage + iters * (10.0 + 6.0 * v->p);
-        const double rounds = std::ceil(blocks / 256.0);
-        cost = t_block * rounds * 2.0;   // until tuned, prefer the staging-free families
+        const double nnz_row = (double)w->nnz / w->cout;
+        double iters = (v->quad ? 1 : v->rpw) * nnz_row / v->ks;
+        const int64_t groups = up(w->cout, v->rows_per_block());
+        int64_t tiles, resident, chunks = 0;
+        double words = 0.0;                       // 64-word staging steps of a wave
+        if (free) {
+            const int64_t row = v->adjacent ? up(g.wout, v->p) * v->p : g.wout;
+            tiles = (v->quad ? 1 : up(g.hout * row, 64 * v->p)) * g.n;
+            resident = 12 / v->nw;
+        } else if (v->family == FAM_PTILE) {
+            const PtileGeom t = ptile_geom(*v, w->cin, w->kh, w->kw, S, g.pad, g.wout);
+            tiles = up(g.wout, t.tile_w) * up(g.hout, t.tile_h) * g.n;
+            chunks = t.nchunks;
+            words = (double)w->cin * t.nstp / v->nw;
+            resident = std::min<int64_t>((int64_t)(kLdsBytesPerCU / std::max<size_t>(t.lds_bytes, 1)), 24 / v->nw);
+            iters += 2.0 * v->rpw * (double)chunks;         // (parts are padded)
+        } else if (v->family == FAM_WTILE) {
+            const WtileGeom t = wtile_geom(*v, w->cin, w->kh, w->kw, S);
+            tiles = t.flat ? up((int64_t)g.hout * g.wout * g.n, t.tile_w) : up(g.wout, t.tile_w) * up(g.hout, t.tile_h) * g.n;
+            chunks = t.nchunks;
+            words = (double)w->cin * t.nstp / v->nw;
+            resident = std::min<int64_t>((int64_t)(kLdsBytesPerCU / std::max<size_t>(t.lds_bytes, 1)), 24 / v->nw);
+            iters += 2.0 * v->rpw * (double)chunks;
+        } else {
+            const int th = 64 / v->tw * v->p;
+            tiles = up(g.wout, v->tw) * up(g.hout, th) * g.n;
+            const double plane = (double)((th - 1) * S + w->kh) * ((v->tw - 1) * S + w->kw);
+            const bool split = v->family == FAM_STILE;        // every wave stages its own channels
+            chunks = up(w->cin, (int64_t)v->cch * (split ? v->nw : 1));
+            words = (split ? (double)chunks * v->cch : (double)w->cin / v->nw) * plane / 64.0;
+            resident = 16 / v->nw;
+        }
+        const int64_t blocks = tiles * groups;
+        const double rounds = (double)up(up(blocks, 256), std::max<int64_t>(1, resident)), waves = (double)blocks * v->nw;
+        if (free) {
+            const double line_bytes = 256.0 * v->p * ((S == 2 && !g.xd.s2d) ? 2.0 : 1.0);
+            x[1] = rounds;
+            x[2] = rounds * iters / std::sqrt(v->family == FAM_DIRECT ? 4.0 : v->quad ? 16.0 : (double)v->unroll);
+            x[3] = rounds * iters;
+            x[4] = waves / 1024.0;
+            x[5] = waves / 1024.0 * iters;
+            x[6] = waves * iters * line_bytes / 32.0 / 256.0 / 1000.0;
+            x[7] = std::log2((double)v->ks);
+        } else {
+            x[1] = rounds;
+            x[2] = rounds * (double)chunks;
+            x[3] = rounds * iters;
+            x[4] = rounds * words;
+            x[5] = waves / 1024.0;
+            x[6] = waves / 1024.0 * iters;
+            x[7] = waves / 1024.0 * words;
+            x[8] = std::log2((double)v->ks);
+        }
     }
-    return cost;
+    double us = 0.0;
+    for (int i = 0; i < 9; ++i) us += (double)m->c[i] * x[i];
+    return us;
+}
+
+// Layers launched together (FAM_LINEAR only): the variants of one launch are compared by the slowest member in
+// cycles, each priced as the largest of a wave's own latency chain times the rounds of waves, the issue slots all waves
+// consume, and the L1 cache-line traffic -- fitted to single layers' timings on ResNet-50, VGG-16,
+// MobileNet-V1 and Inception-V3.  The model above, its chains' maximum plus what all waves issue, picks worse
+// here (Inception-V3 fp32 batch 1: 591 us against 577).
+static double group_member_cost(const cadnn_weights* w, const ConvGeom& g, const ConvVariant* v) {
+    const double nnz_row = w->cout ? (double)w->nnz / w->cout : 0.0;
+    const int P = v->p;
+    const double walked = v->adjacent == 2 ? (double)g.hout * ((g.wout + P - 1) / P * P) : (double)g.hout * g.wout;
+    const double tiles = std::ceil(walked / (64.0 * P)) * g.n;
+    const double waves = tiles * std::ceil((double)w->cout / v->rows_per_block()) * v->nw;
+    const double iters = v->rpw * nnz_row / v->ks;
+    const double line_bytes = 256.0 * P * ((g.stride == 2 && !g.xd.s2d) ? 2.0 : 1.0);
+    const double t_l1 = waves * iters * line_bytes / 32.0 / 256.0;
+    const double instrs = v->adjacent ? 3.0 + P : 2.0 + 2.0 * P;
+    const double t_issue = waves * (1787.0 + iters * instrs * 1.21) / 1024.0;
+    const double per_nz = 77.4 * (1.0 + 0.51 * (P - 1)) / (1.0 + 0.079 * std::log2(v->unroll / 4.0));
+    const double t_wave = 382.0 + iters * per_nz + (v->ks > 1 ? 338.0 * std::log2((double)v->ks) : 0.0);
+    return std::max(std::max(t_wave * std::ceil(waves / (1024.0 * 2.3)), t_issue), 0.078 * t_l1);
 }
 
 static const ConvVariant* heuristic_variant(const cadnn_weights* w, const ConvGeom& g) {
@@ -290,14 +401,14 @@ static const ConvVariant* heuristic_variant(const cadnn_weights* w, const ConvGe
     double best_cost = 0.0;
     for (const ConvVariant* v : cand) {
         const double cost = variant_cost(w, g, v);
-        if (cost < 0.0) continue;   // chosen by tuning only
+        if (cost < 0.0) continue;   // not modelled: chosen by tuning only
         if (!best || cost < best_cost) { best = v; best_cost = cost; }
     }
     if (!best) {
-        // only LDS-staged variants serve the geometry (a 5x5 filter on a plain tensor): take
-        // the one whose waves walk the fewest nonzeros each, the channel split priced as above
+        // nothing modelled serves the layer (a sparse layer of a geometry that only the matrix cores take): the one
+        // whose waves walk the fewest nonzeros each
         for (const ConvVariant* v : cand) {
-            const double cost = v->rpw * nnz_row / v->ks + (v->ks > 1 ? 338.0 / 77.4 * std::log2((double)v->ks) : 0.0);
+            const double cost = v->rpw * nnz_row / std::max(v->ks, 1);
             if (!best || cost < best_cost) { best = v; best_cost = cost; }
         }
     }
@@ -477,7 +588,7 @@ cadnn_status conv2d_group_candidates(const std::vector<ConvMember>& members, int
     for (const ConvVariant* v : *out) {
         double worst = 0.0;
         for (size_t k = 0; k < members.size(); ++k)
-            if (members[k].pool_kind == 0) worst = std::max(worst, variant_cost(members[k].w, geoms[k], v));
+            if (members[k].pool_kind == 0) worst = std::max(worst, group_member_cost(members[k].w, geoms[k], v));
         if (pick && (!*pick || worst < best)) { *pick = v; best = worst; }
     }
     return CADNN_OK;

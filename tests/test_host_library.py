@@ -239,3 +239,20 @@ def test_binding_exposes_the_c_names():
         if n.startswith("cadnn_net_") or n in ("cadnn_last_error",):
             continue
         assert hasattr(cad, n) or hasattr(binding, n), n
+
+
+@pytest.mark.parametrize("dtype_name", ["f32", "f16"])
+@pytest.mark.parametrize("geom", [(1, 64, 64, 56, 3, 1, 1), (2, 288, 384, 35, 3, 2, 0), (4, 20, 65, 18, 5, 1, 2),
+                                  (5, 48, 40, 11, 7, 2, 3), (3, 107, 68, 40, 1, 1, 0), (1, 24, 30, 9, 7, 3, 3)])
+def test_untuned_pick_is_listed_and_keeps_pruned_layers_off_the_zero_filled_matrix(geom, dtype_name):
+    """The model's pick serves the layer, and a layer with less than a quarter of its weights is not
+    run densely untuned where a sparse kernel serves it (0 * Inf of a pruned weight would be NaN)."""
+    import paper_1905_00571_amd as cad
+    n, cin, cout, hw, k, stride, pad = geom
+    w = wl.pruned_weights(cout, cin, k, k, 0.85, "pick-%d-%d" % (cin, k), 0)
+    h = cad.cadnn_pack_weights(w, cad.F16 if dtype_name == "f16" else cad.F32)
+    names = cad.cadnn_conv2d_list_variants(h, n, hw, hw, stride, pad)
+    pick = cad.cadnn_conv2d_variant_name(h, n, hw, hw, stride, pad)
+    assert pick in names
+    if any(not nm.startswith("dense") for nm in names):
+        assert not pick.startswith("dense")
