@@ -111,8 +111,8 @@ __global__ __launch_bounds__(256) void cl_arrange_kernel(const ClArrange a) {
 // the kernels of most layers, so blocks are kept: taken under the lock, owned by one call until it returns
 // them, and handed on with an event that the next user's stream waits for (8.6 us in all).  At most
 // kKeep blocks of at most kKeepBytes together are held; one that no longer fits goes back to the device, in the order
-// of the stream that takes its place.  While a stream is captured, and for larger workspaces, every call
-// allocates for itself in stream order.
+// of the stream that takes its place.  For larger workspaces every call allocates for itself in stream
+// order.  (No captured stream comes here.)
 struct Workspace {
     char* p = nullptr;
     size_t bytes = 0;
@@ -123,12 +123,10 @@ struct Workspace {
 class WorkspacePool {
   public:
     hipError_t take(size_t bytes, hipStream_t s, Workspace* out) {
-        hipStreamCaptureStatus capture = hipStreamCaptureStatusNone;
-        hipError_t e = hipStreamIsCapturing(s, &capture);
-        if (e != hipSuccess) return e;
+        hipError_t e;
         *out = Workspace{};
         out->bytes = bytes;
-        if (capture != hipStreamCaptureStatusNone || bytes > kKeepBytes / 2) return hipMallocAsync((void**)&out->p, bytes, s);
+        if (bytes > kKeepBytes / 2) return hipMallocAsync((void**)&out->p, bytes, s);
         int device = 0;
         if ((e = hipGetDevice(&device)) != hipSuccess) return e;
         Workspace found, old;

@@ -228,7 +228,10 @@ cadnn_status dense_conv2d_impl(const void* w_dev, const void* x, void* y, int n,
     if (desc_too_large(make_desc(cin, h, wdt)) || desc_too_large(yd) || (int64_t)cin * h * wdt * elem >= 0x7ffffff0ll ||
         yd.image * elem >= 0x7ffffff0ll)
         return fail(CADNN_EUNSUPPORTED, "cadnn_dense_conv2d: one image of a tensor is 2 GiB or more");
-    if (dense_cl_serves(dtype == CADNN_F16, n, cin, h, wdt, cout, kh, kw, stride, pad))
+    // (a captured graph keeps to the kernels that need no workspace, or whose own one is recorded with them)
+    hipStreamCaptureStatus capture = hipStreamCaptureStatusNone;
+    CADNN_HIP(hipStreamIsCapturing(s, &capture));
+    if (capture == hipStreamCaptureStatusNone && dense_cl_serves(dtype == CADNN_F16, n, cin, h, wdt, cout, kh, kw, stride, pad))
         return dense_cl_conv2d(w_dev, x, y, residual, n, cin, h, wdt, cout, kh, kw, stride, pad, bias, relu, dtype == CADNN_F16, s);
     // fp16 storage with whole 32-channel steps takes the 128 x 128-tile kernel
     if (cin % 32 == 0 && dense_wide_serves(dtype == CADNN_F16, cin, kh * kw, (int64_t)cin * h * wdt * elem * n, yd.image * elem * n,

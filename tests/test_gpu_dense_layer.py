@@ -65,3 +65,56 @@ def test_dense_layer_repeats_and_follows_new_weights():
     assert torch.equal(2.0 * first, cad.cadnn_dense_conv2d(wt, x, 1, 1))
     x.mul_(0.5)
     assert torch.equal(first, cad.cadnn_dense_conv2d(wt, x, 1, 1))
+
+
+def test_dense_layer_workspaces_on_two_streams_threads_and_under_capture():
+    """Workspaces are handed from call to call: calls that alternate between streams and threads, with
+    growing and shrinking sizes, and a captured graph's replays give what calls one by one give."""
+    if not torch.cuda.is_available():
+        pytest.skip("no GPU")
+    import threading
+    import paper_1905_00571_amd as cad
+    gen = torch.Generator().manual_seed(3)
+    layers = []
+    for cin, cout, hw, k in ((64, 64, 28, 3), (256, 128, 14, 3), (32, 48, 56, 5), (512, 64, 7, 3)):
+        x = torch.randn(4, cin, hw, hw, generator=gen).half().cuda()
+        w = (torch.randn(cout, cin, k, k, generator=gen) * 0.05).half().cuda()
+        layers.append((w, x, k // 2))
+    want = []
+    for w, x, pad in layers:
+        want.append(cad.cadnn_dense_conv2d(w, x, 1, pad).clone())
+        torch.cuda.synchronize()
+    failures = []
+
+    def work(seed):
+        stream = torch.cuda.Stream()
+        with torch.cuda.stream(stream):
+            for i in range(40):
+                j = (i * (seed + 1) + seed) % len(layers)
+                w, x, pad = layers[j]
+                y = cad.cadnn_dense_conv2d(w, x, 1, pad)
+                if not torch.equal(y, want[j]):
+                    failures.append((seed, i, j))
+        stream.synchronize()
+
+    threads = [threading.Thread(target=work, args=(s,)) for s in range(3)]
+    for t in threads:
+        t.start()
+    for t in threads:
+        t.join()
+    assert not failures
+    # a captured graph keeps to the kernels on planes (another order of the same fp32 sums)
+    w, x, pad = layers[0][0].float(), layers[0][1].float(), layers[0][2]
+    eager = cad.cadnn_dense_conv2d(w, x, 1, pad).clone()
+    y = torch.empty_like(eager)
+    torch.cuda.synchronize()
+    graph = torch.cuda.CUDAGraph()
+    with torch.cuda.graph(graph):
+        cad.cadnn_dense_conv2d(w, x, 1, pad, out=y)
+    bound = 2 * (w[0].numel() + 3) * 2.0 ** -24 * torch.nn.functional.conv2d(x.double().abs().cpu(), w.double().abs().cpu(), None, 1, pad)
+    for _ in range(3):
+        y.zero_()
+        graph.replay()
+        cad.cadnn_dense_conv2d(layers[1][0], layers[1][1], 1, layers[1][2])
+        torch.cuda.synchronize()
+        assert bool(((y.double() - eager.double()).abs().cpu() <= bound).all())
