@@ -615,9 +615,10 @@ cadnn_status cl_prepare_variant(const ClVariant& v, ClPlan* plan, int64_t pixels
 // a CU (LDS, and the registers the kernel is bound to), each with a start and an end that grow with the tile and
 // with how many run at once, and steps that take a fixed time while a workgroup has the CU to itself
 // (the latency of loads that run two stages ahead) and the CU's rate when it does not.  The
-// constants are fitted to the times of every variant on 116 layers (ResNet-50 at 1, 8 and 32 images,
-// MobileNet-V2 at 16; the tile it takes for a layer is on average 1.5 % slower than that layer's best one).
-// Four stages pay where workgroups are alone or two to a CU and the K loop is long (at one ResNet-50 image:
+// constants are fitted to the times of every variant on 387 layers (ResNet-50 at 1, 8, 16 and 32 images, MobileNet-V2
+// at 16, VGG-16 at 1, Inception-V3 at 4 in fp16, ResNet-50 at 4 and 8 in fp32): the tiles it takes are 1.7 % slower in sum than each layer's
+// best (one ResNet-50 image 0.9 %; with constants from 116 of these layers 2.5 % and 4 %: 332 -> 317 us a pass).
+// Splitting K of the larger tiles, or in eight, wins none or three of the 387.  Four stages pay where workgroups are alone or two to a CU and the K loop is long (at one ResNet-50 image:
 // 18 steps 10.9 -> 9.7 us); there is no use for more stages: six and eight measured the same.
 const ClVariant* cl_pick(int cout, const ClPlan& plan, int64_t pixels, bool f16) {
     const ClVariant* best = nullptr;
@@ -626,14 +627,14 @@ const ClVariant* cl_pick(int cout, const ClPlan& plan, int64_t pixels, bool f16)
         if (!cl_variant_fits(v, plan, pixels, cout)) continue;
         const int64_t blocks = cl_tiles(v, pixels, cout) * v.sk;
         const int steps = (plan.steps + v.sk - 1) / v.sk;
-        if (v.s == 4 && (blocks > 2 * kNumCus || steps < 8)) continue;
+        if (v.s == 4 && (blocks > 2 * kNumCus || steps < 4)) continue;
         const int size = v.mi * v.ni, bytes = 64 * (v.mi + v.ni) * plan.rb;
         const int64_t per_cu = std::min<int64_t>(kLdsPerCu / (v.s * bytes), size == 1 ? 4 : 2);
-        const double rate = std::max((f16 ? 20.0 : 265.0) * size * plan.rb / 128.0, bytes / 70.0);
-        const double alone = std::max(rate, (v.s == 4 ? 630.0 : 800.0) * (1.0 + 0.25 * (size - 1)));
-        auto round = [&](int64_t n) { return n == 0 ? 0.0 : 350.0 + 2700.0 * size * (double)n + steps * std::max(alone, rate * (double)n); };
+        const double rate = std::max((f16 ? 21.5 : 211.0) * size * plan.rb / 128.0, bytes / 47.0);
+        const double alone = std::max(rate, (v.s == 4 ? 630.0 : 642.0) * (1.0 + 0.25 * (size - 1)));
+        auto round = [&](int64_t n) { return n == 0 ? 0.0 : 367.0 + 3370.0 * size * (double)n + steps * std::max(alone, rate * (double)n); };
         const int64_t in_cu = (blocks + kNumCus - 1) / kNumCus;
-        const double cost = (double)(in_cu / per_cu) * round(per_cu) + round(in_cu % per_cu) + (v.sk > 1 ? 2300.0 + 1100.0 * v.sk : 0.0);
+        const double cost = (double)(in_cu / per_cu) * round(per_cu) + round(in_cu % per_cu) + (v.sk > 1 ? 4960.0 + 871.0 * v.sk : 0.0);
         if (!best || cost < best_cost) { best = &v; best_cost = cost; }
     }
     return best;
