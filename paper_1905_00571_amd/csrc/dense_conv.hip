@@ -228,12 +228,17 @@ cadnn_status dense_conv2d_impl(const void* w_dev, const void* x, void* y, int n,
     if (desc_too_large(make_desc(cin, h, wdt)) || desc_too_large(yd) || (int64_t)cin * h * wdt * elem >= 0x7ffffff0ll ||
         yd.image * elem >= 0x7ffffff0ll)
         return fail(CADNN_EUNSUPPORTED, "cadnn_dense_conv2d: one image of a tensor is 2 GiB or more");
-    // (a captured graph keeps to the kernels that need no workspace, or whose own one is recorded with them)
+    // (a captured graph keeps to the kernels that need no kept workspace: one handed on between calls must not be
+    // read by a replay)
     hipStreamCaptureStatus capture = hipStreamCaptureStatusNone;
-    CADNN_HIP(hipStreamIsCapturing(s, &capture));
+    if (hipStreamIsCapturing(s, &capture) != hipSuccess) {
+        (void)hipGetLastError();
+        capture = hipStreamCaptureStatusActive;
+    }
     if (capture == hipStreamCaptureStatusNone && dense_cl_serves(dtype == CADNN_F16, n, cin, h, wdt, cout, kh, kw, stride, pad))
         return dense_cl_conv2d(w_dev, x, y, residual, n, cin, h, wdt, cout, kh, kw, stride, pad, bias, relu, dtype == CADNN_F16, s);
-    // fp16 storage with whole 32-channel steps takes the 128 x 128-tile kernel
+    // fp16 storage with whole 32-channel steps takes the 128 x 128-tile kernel where that route is not taken (a captured
+    // stream, more than 64 taps, a halo that brings the tensor to 2 GiB)
     if (cin % 32 == 0 && dense_wide_serves(dtype == CADNN_F16, cin, kh * kw, (int64_t)cin * h * wdt * elem * n, yd.image * elem * n,
                           (int64_t)n * hout * wout))
         return dense_wide_conv2d_raw(w_dev, x, make_desc(cin, h, wdt), y, yd, residual, yd, n, cout, kh, kw, stride, pad,
