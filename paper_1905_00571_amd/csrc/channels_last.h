@@ -41,7 +41,8 @@ struct ClPlan {
     DevBuf w;
     int rb = 0, steps = 0, steps_tap = 0, taps = 0, steps2 = 0;
     int tap_r[kClMaxTaps], tap_c[kClMaxTaps];
-    bool stem = false;          // input packed 4 channels a pixel, a step is one filter row
+    bool stem = false;          // input packed 4 channels a pixel, a step is one filter row ...
+    int row_bytes = 0;          // ... of this many bytes, the rest of the step being padding of the weights alone
     // K split over workgroups: partial tiles and arrival counters
     DevBuf part, count;
 };

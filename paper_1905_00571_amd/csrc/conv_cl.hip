@@ -71,6 +71,7 @@ struct ClArgs {
     int total, hw, ow, cout, relu;
     int steps_tap, steps1, steps, ntaps, tiles_m, tiles, per_die, sk, log_sk;
     int per_slice;              // steps of a slice of the split
+    int row_bytes;              // bytes of a step that are the pixel's own; what lies behind them is not used
     int plane;                  // PLANES: bytes from one channel to the next
     uint32_t magic_hw, magic_ow, magic_tm, magic_st;
     int tap_off[kClMaxTaps];
@@ -131,13 +132,22 @@ __device__ __forceinline__ int cl_div(int v, uint32_t magic, int d) {
     return d == 1 ? v : q - (q * d > v ? 1 : 0);
 }
 
+// What a launch is, beside a layer between channels-last tensors.
+enum ClMode { CL_MAPS = 0, CL_PLANES = 1, CL_ODD_ROW = 2 };
+
 // (two waves per SIMD asked for: all registers then are of one kind, no accumulator copies in the loop)
-// PLANES: y and the residual are [n][c][h][w] (a layer called on its own).  A lane then stores its pixel of each
+// CL_PLANES: y and the residual are [n][c][h][w] (a layer called on its own).  A lane then stores its pixel of each
 // channel straight from the accumulators: 32 lanes write 64 (fp16) or 128 contiguous bytes, which
 // costs less than a pass of its own over y (a launch, 4 us at the least).
-template <typename T, int RB, int MI, int NI, int S, bool PLANES>
+// CL_ODD_ROW: a first layer in 2-byte storage whose filter rows have an odd number of pixels, 8 bytes each.  A step is
+// wider than such a row.  Whole pieces behind it are not requested at all (that goes for every first
+// layer); the piece that is half the next pixel's loses that half in the registers, because a zero weight does not
+// undo an infinity or a NaN.  (Four more instructions a step; other layers take the kernels without them.)
+template <typename T, int RB, int MI, int NI, int S, int MODE>
 __global__ __launch_bounds__(256, MI * NI == 1 ? 4 : 2) void cl_conv_kernel(const ClArgs a) {
     using C = ClCfg<T, RB, MI, NI, S>;
+    constexpr bool PLANES = MODE == CL_PLANES;
+    static_assert(MODE != CL_ODD_ROW || sizeof(T) == 2, "a pixel of 4-byte storage is a whole piece");
     constexpr int TM = C::TM, TN = C::TN, STAGE = C::STAGE, PITCH = C::PITCH;
     constexpr int RPL = 1024 / RB;                 // rows one wave-load fills
     constexpr int LA = TM * RB / 4096, LB = TN * RB / 4096;      // loads per thread and stage
@@ -154,7 +164,7 @@ __global__ __launch_bounds__(256, MI * NI == 1 ? 4 : 2) void cl_conv_kernel(cons
     asm volatile("" :: "s"(a.w), "s"(a.x), "s"(a.x2), "s"(a.y), "s"(a.res), "s"(a.bias), "s"(a.bias2), "s"(a.part), "s"(a.count),
                  "s"(a.wspan), "s"(a.total), "s"(a.hw), "s"(a.ow), "s"(a.cout), "s"(a.relu), "s"(a.steps_tap), "s"(a.steps1), "s"(a.steps),
                  "s"(a.ntaps), "s"(a.tiles_m), "s"(a.tiles), "s"(a.per_die), "s"(a.sk), "s"(a.log_sk), "s"(a.per_slice), "s"(a.magic_hw), "s"(a.magic_ow),
-                 "s"(a.magic_tm));
+                 "s"(a.magic_tm), "s"(a.row_bytes));
     asm volatile("" :: "s"(a.xt.span), "s"(a.xt.img), "s"(a.xt.row), "s"(a.xt.col), "s"(a.xt.org), "s"(a.x2t.img), "s"(a.x2t.row), "s"(a.x2t.col),
                  "s"(a.x2t.org), "s"(a.yt.span), "s"(a.yt.img), "s"(a.yt.row), "s"(a.yt.col), "s"(a.yt.org), "s"(a.rt.span), "s"(a.rt.img),
                  "s"(a.rt.row), "s"(a.rt.col), "s"(a.rt.org), "s"(a.tap_off[0]));
@@ -216,7 +226,7 @@ __global__ __launch_bounds__(256, MI * NI == 1 ? 4 : 2) void cl_conv_kernel(cons
 #pragma unroll
     for (int j = 0; j < LB; ++j) {
         const int e = ptab[j * 4 * RPL + wv * RPL + lrow].x;
-        vb[j] = e == (int)kClOutOfRange ? kClOutOfRange : (uint32_t)e + piece;
+        vb[j] = e == (int)kClOutOfRange || (int)piece >= a.row_bytes ? kClOutOfRange : (uint32_t)e + piece;
     }
     cl_u4 xr = cl_rsrc(a.x, a.xt.span);
 
@@ -320,6 +330,14 @@ __global__ __launch_bounds__(256, MI * NI == 1 ? 4 : 2) void cl_conv_kernel(cons
             for (int mi = 0; mi < MI; ++mi) af[f][ks][mi] = *(const cl_u4*)(st + fa + mi * 32 * RB + p);
 #pragma unroll
             for (int ni = 0; ni < NI; ++ni) bf[f][ks][ni] = *(const cl_u4*)(st + fb + ni * 32 * RB + p);
+            if constexpr (MODE == CL_ODD_ROW) {
+                const uint32_t own = 2 * ks + fk == a.row_bytes / 16 ? 0u : ~0u;
+#pragma unroll
+                for (int ni = 0; ni < NI; ++ni) {
+                    bf[f][ks][ni][2] &= own;
+                    bf[f][ks][ni][3] &= own;
+                }
+            }
         }
     };
     auto multiply = [&](auto F, auto K) __attribute__((always_inline)) {
@@ -524,35 +542,35 @@ __global__ __launch_bounds__(256, MI * NI == 1 ? 4 : 2) void cl_conv_kernel(cons
     }
 }
 
-template <typename T, int RB, int MI, int NI, int S, bool PLANES>
+template <typename T, int RB, int MI, int NI, int S, int MODE>
 hipError_t launch_cl_tile(const ClArgs& a, hipStream_t s) {
     using C = ClCfg<T, RB, MI, NI, S>;
     // (more than 64 KB of dynamic LDS has to be asked for once per kernel)
     static const hipError_t attr = C::LDS <= 65536 ? hipSuccess
-                                                   : hipFuncSetAttribute((const void*)cl_conv_kernel<T, RB, MI, NI, S, PLANES>,
+                                                   : hipFuncSetAttribute((const void*)cl_conv_kernel<T, RB, MI, NI, S, MODE>,
                                                                          hipFuncAttributeMaxDynamicSharedMemorySize, C::LDS);
     if (attr != hipSuccess) return attr;
     const unsigned grid = (unsigned)((a.tiles + 7) / 8 * 8);
-    CADNN_LAUNCH((cl_conv_kernel<T, RB, MI, NI, S, PLANES>), dim3(grid), dim3(256), (size_t)C::LDS, s, a);
+    CADNN_LAUNCH((cl_conv_kernel<T, RB, MI, NI, S, MODE>), dim3(grid), dim3(256), (size_t)C::LDS, s, a);
     return hipGetLastError();
 }
 
-template <typename T, int RB, bool P>
+template <typename T, int RB, int MODE>
 hipError_t launch_cl_rb(const ClArgs& a, const ClVariant& v, hipStream_t s) {
-    if (v.mi == 2) return v.ni == 2 ? launch_cl_tile<T, RB, 2, 2, 2, P>(a, s) : launch_cl_tile<T, RB, 2, 1, 3, P>(a, s);
-    if (v.ni == 2) return launch_cl_tile<T, RB, 1, 2, 3, P>(a, s);
-    return v.s == 3 ? launch_cl_tile<T, RB, 1, 1, 3, P>(a, s) : launch_cl_tile<T, RB, 1, 1, 4, P>(a, s);
+    if (v.mi == 2) return v.ni == 2 ? launch_cl_tile<T, RB, 2, 2, 2, MODE>(a, s) : launch_cl_tile<T, RB, 2, 1, 3, MODE>(a, s);
+    if (v.ni == 2) return launch_cl_tile<T, RB, 1, 2, 3, MODE>(a, s);
+    return v.s == 3 ? launch_cl_tile<T, RB, 1, 1, 3, MODE>(a, s) : launch_cl_tile<T, RB, 1, 1, 4, MODE>(a, s);
 }
 
-template <typename T, bool P>
+template <typename T, int MODE>
 hipError_t launch_cl_type(const ClArgs& a, const ClVariant& v, int rb, hipStream_t s) {
-    return rb == 128 ? launch_cl_rb<T, 128, P>(a, v, s) : launch_cl_rb<T, 64, P>(a, v, s);
+    return rb == 128 ? launch_cl_rb<T, 128, MODE>(a, v, s) : launch_cl_rb<T, 64, MODE>(a, v, s);
 }
 
 ClTensorArg tensor_arg(const ClDesc& d, int n, size_t e, int stride, int r0, int c0) {
     ClTensorArg t;
-    // (a slice of a concatenation ends where its last pixel's own channels end; the slack behind a stem's
-    // packed image is part of its region)
+    // (every access lies inside: a slice of a concatenation ends with its last pixel, and a first layer's steps
+    // end with its filter rows, or 8 bytes behind them, which the region has room for)
     t.span = (uint32_t)((int64_t)n * d.image * (int64_t)e);
     t.img = (int)(d.image * (int64_t)e);
     t.row = (int)(d.row * (int64_t)e) * stride;
@@ -670,6 +688,7 @@ cadnn_status launch_cl_conv(const ClConv& c, const ClVariant& v, bool f16, hipSt
     a.sk = v.sk;
     a.log_sk = v.sk == 4 ? 2 : v.sk == 2 ? 1 : 0;
     a.ntaps = p.taps;
+    a.row_bytes = p.stem ? p.row_bytes : p.rb;
     a.tiles = (int)cl_tiles(v, a.total, c.cout) * v.sk;
     a.per_slice = (p.steps + v.sk - 1) / v.sk;
     a.per_die = (a.tiles + 7) / 8;
@@ -692,9 +711,11 @@ cadnn_status launch_cl_conv(const ClConv& c, const ClVariant& v, bool f16, hipSt
         a.yt.span = (uint32_t)((int64_t)c.n * a.yt.img);
         a.plane = (int)(a.hw * (int64_t)e);
         if (c.residual) a.rt = a.yt;
-        err = f16 ? launch_cl_type<_Float16, true>(a, v, p.rb, s) : launch_cl_type<float, true>(a, v, p.rb, s);
+        err = f16 ? launch_cl_type<_Float16, CL_PLANES>(a, v, p.rb, s) : launch_cl_type<float, CL_PLANES>(a, v, p.rb, s);
+    } else if (a.row_bytes % 16 != 0) {
+        err = launch_cl_type<_Float16, CL_ODD_ROW>(a, v, p.rb, s);
     } else {
-        err = f16 ? launch_cl_type<_Float16, false>(a, v, p.rb, s) : launch_cl_type<float, false>(a, v, p.rb, s);
+        err = f16 ? launch_cl_type<_Float16, CL_MAPS>(a, v, p.rb, s) : launch_cl_type<float, CL_MAPS>(a, v, p.rb, s);
     }
     CADNN_HIP(err);
     return CADNN_OK;
@@ -713,6 +734,7 @@ cadnn_status cl_build_plan(const cadnn_weights* w, const cadnn_weights* shortcut
         for (int r = 0; r < w->kh; ++r) { plan->tap_r[r] = r; plan->tap_c[r] = 0; }
         plan->taps = w->kh;
         plan->steps_tap = 1;
+        plan->row_bytes = w->kw * 4 * (int)e;
     } else {
         std::vector<char> used((size_t)taps_all, 0);
         for (int32_t k : w->col_idx) used[(size_t)(k % taps_all)] = 1;

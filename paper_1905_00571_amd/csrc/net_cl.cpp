@@ -147,8 +147,8 @@ std::unique_ptr<ClNet> cl_layout(const cadnn_net* net) {
 
     size_t off = 0;
     bool fits = true;
-    auto place = [&](const ClDesc& d, int n) {
-        const size_t at = off, bytes = (size_t)n * (size_t)d.image * e;
+    auto place = [&](const ClDesc& d, int n, size_t behind = 0) {
+        const size_t at = off, bytes = (size_t)n * (size_t)d.image * e + behind;
         if (bytes >= 0x7fff0000ull) fits = false;
         off += (bytes + 255) / 256 * 256;
         return at;
@@ -186,8 +186,9 @@ std::unique_ptr<ClNet> cl_layout(const cadnn_net* net) {
         if (o.kind == OP_FC) continue;
         if (stem_conv(o, e)) {
             c.x_stem = true;
+            // (the last 16-byte piece of a filter row may hold a pixel more than the row: room behind the last image)
             c.xd = cl_desc(o.in.c, o.in.h, o.in.w, o.pad, o.pad, 4);
-            c.x_off = place(c.xd, o.in.n);
+            c.x_off = place(c.xd, o.in.n, 16);
         } else {
             c.xd = o.src_inst < 0 ? cl->in_d : cl->ops[(size_t)o.src_inst]->yd;
             const bool reads_input = o.src_inst < 0 ||

@@ -147,3 +147,41 @@ def test_channels_last_tuned(cad):
         assert np.abs(got - ref).max() <= 1e-2 * np.abs(ref).max()
     assert all(n.startswith("cl_") or n == "fused" for n, o in zip(net.variants(), ops) if o.kind == "conv")
     net.free()
+
+
+@pytest.mark.parametrize("dtype_name", ["f32", "f16"])
+@pytest.mark.parametrize("k,stride,pad,h,w", [(3, 2, 0, 19, 23), (3, 1, 1, 9, 14), (7, 2, 3, 21, 20), (7, 2, 0, 15, 17), (5, 1, 0, 11, 9),
+                                              (5, 2, 2, 12, 13), (4, 2, 1, 12, 14), (1, 1, 0, 6, 7), (2, 2, 0, 10, 12)])
+def test_first_layer_reads_nothing_outside_its_windows(cad, k, stride, pad, h, w, dtype_name):
+    """A packed first layer's K step is wider than a filter row.  NaN and infinities in the middle image, at its
+    corners, edges and inside: every output whose window holds none of them (all of the other images') has the
+    bits it has without them, with every tile."""
+    dtype, npdt = (cad.F16, np.float16) if dtype_name == "f16" else (cad.F32, np.float32)
+    ops = [Op("conv", "stem", 0, 1, 3, 40, k, stride, pad, 0.0, False), Op("conv", "next", 1, 2, 40, 8, 1, 1, 0, 0.5, False)]
+    shape = (3, 3, h, w)
+    x, ws, bs = wl.net_tensors(ops, f"stem-{k}-{stride}-{pad}", shape)
+    bad = x.astype(npdt)
+    hit = np.zeros((3, h, w), bool)
+    for i, (r, c) in enumerate([(0, 0), (0, w - 1), (h - 1, 0), (h - 1, w - 1), (h // 2, 0), (h // 2, w // 2), (h // 2, w - 1)]):
+        bad[1, i % 3, r, c] = (np.nan, np.inf, -np.inf)[i % 3]
+        hit[1, r, c] = True
+    ho, wo = wl.conv_out_size(h, k, stride, pad), wl.conv_out_size(w, k, stride, pad)
+    padded = np.pad(hit, ((0, 0), (pad, pad + k), (pad, pad + k)))
+    touched = np.zeros((3, ho, wo), bool)
+    for a in range(k):
+        for b in range(k):
+            touched |= padded[:, a:a + ho * stride:stride, b:b + wo * stride:stride][:, :ho, :wo]
+    assert touched[1].any() and not touched[1].all()
+    net = cad.build_net(ops, ws, bs, shape, dtype, use_graph=False)
+    net.set_op_variant(0, "cl_mfma_64x64_s3")
+    keep = np.broadcast_to(~touched[:, None], (3, 40, ho, wo))
+    for name in net.op_candidates(0):
+        net.set_op_variant(0, name)
+        maps = []
+        for inp in (x.astype(npdt), bad):
+            net.run(torch.from_numpy(inp).cuda())
+            torch.cuda.synchronize()
+            maps.append(net.read_buffer(1, (3, 40, ho, wo)))
+        assert np.isfinite(maps[0]).all() and not np.isfinite(maps[1]).all()
+        assert np.array_equal(maps[0][keep], maps[1][keep]), name
+    net.free()

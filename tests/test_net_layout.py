@@ -282,3 +282,23 @@ def test_random_net_layouts_keep_their_invariants():
             for (a0, a1, an), (b0, b1, bn) in zip(regions, regions[1:]):
                 assert a1 <= b0, (seed, kw, an, bn)
     assert min(seen.values()) >= 20, seen         # the nets do contain what is being checked
+
+
+@pytest.mark.parametrize("family,n,size,first", [("inception_v3", 32, 299, (3, 2, 0)), ("mobilenet_v2", 32, 225, (3, 2, 1)),
+                                                 ("mobilenet_v1", 32, 224, (3, 2, 1)), ("resnet50", 8, 224, (7, 2, 3))])
+def test_first_layer_steps_end_inside_the_workspace(family, n, size, first):
+    """A channels-last net's packed first-layer input, 4 channels a pixel, is read in 16-byte pieces of filter
+    rows: the last piece of the last row of the last image, which may be half another pixel's, lies in the
+    workspace."""
+    ops = {"inception_v3": wl.inception_v3_ops, "mobilenet_v1": wl.mobilenet_v1_ops,
+           "mobilenet_v2": wl.mobilenet_v2_ops, "resnet50": lambda: wl.resnet50_ops(uniform=0.8)}[family]()
+    k, stride, pad = first
+    assert (ops[0].k, ops[0].stride, ops[0].pad) == first
+    infos, nbytes = plan(ops, (n, 3, size, size), "stem-end", dtype=cad.F16)
+    start = infos[0]["input_copy"]
+    assert start >= 0                                   # the net runs channels-last
+    out = wl.conv_out_size(size, k, stride, pad)
+    wide = size + 2 * pad
+    last_row = ((n - 1) * wide + (out - 1) * stride + k - 1) * wide * 8
+    end = start + last_row + (out - 1) * stride * 8 + (k * 8 + 15) // 16 * 16
+    assert end <= nbytes, (end, nbytes)
