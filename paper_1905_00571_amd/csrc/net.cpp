@@ -463,13 +463,20 @@ struct Layout {
     }
 };
 
+// The channels-last execution and, where a pin took the net there, the workspace that came with it.
+void drop_channels_last(cadnn_net* net) {
+    net->cl.reset();
+    net->cl_ws.release();
+    net->planes_ws = nullptr;
+}
+
 void layout(cadnn_net* net) {
     Layout l(net);
     l.run();
     net->laid_out = true;
     // channels-last execution, where it is expected to be the faster one (the plane layouts above
     // stay: pinning one of their variants takes the net back to them, so the workspace holds either)
-    net->cl.reset();
+    drop_channels_last(net);
     if (net->allow_s2d && net->allow_fusion && cl_expected_faster(net)) {
         net->cl = cl_layout(net);
         if (net->cl) net->ws_bytes = std::max(net->ws_bytes, net->cl->ws_bytes);
@@ -1053,9 +1060,10 @@ extern "C" cadnn_status cadnn_net_finalize(cadnn_net* net, void* ws, size_t byte
     net->static_ws = (flags & CADNN_NET_STATIC_WORKSPACE) != 0;
     if (net->static_ws) {
         if (net->cl) {          // (nets that fit the static workspace stay on the plane layouts)
-            net->cl.reset();
+            drop_channels_last(net);
             Layout l(net);
             l.run();
+            net->laid_out = false;      // (for a later call without the flag)
         }
         if (net->ws_bytes > kStaticWorkspaceBytes)
             return fail(CADNN_EUNSUPPORTED, "cadnn_net_finalize: the net needs %zu bytes of workspace, the static workspace holds %zu",
@@ -1067,13 +1075,21 @@ extern "C" cadnn_status cadnn_net_finalize(cadnn_net* net, void* ws, size_t byte
     if (net->ws_bytes > 0 && !ws) return fail(CADNN_EINVAL, "cadnn_net_finalize: NULL workspace");
     if (bytes < net->ws_bytes) return fail(CADNN_EINVAL, "cadnn_net_finalize: workspace of %zu bytes, %zu needed", bytes, net->ws_bytes);
     drop_graph(net);
+    net->finalized = false;             // (until everything below is done)
     net->ws = (char*)ws;
     // halos are read as the zero padding of the consumer layers and are never written again
-    if (net->ws_bytes) {
-        CADNN_HIP(hipMemset(ws, 0, net->ws_bytes));
-        CADNN_HIP(hipDeviceSynchronize());
+    if (net->ws_bytes) CADNN_HIP(hipMemset(ws, 0, net->ws_bytes));
+    cadnn_status st = CADNN_OK;
+    if (net->cl_ws.p) {
+        // a pin took the net channels-last, and pins outlive a second finalize: it goes on in the workspace
+        // that came with the pin; the caller's is the one that the plane layouts would return to
+        if ((st = prepare_planes(net)) != CADNN_OK) return st;
+        net->planes_ws = net->ws;
+        net->ws = (char*)net->cl_ws.p;
+        CADNN_HIP(hipMemset(net->ws, 0, net->cl_ws.bytes));
     }
-    cadnn_status st = net->cl ? cl_prepare(net) : prepare_planes(net);
+    CADNN_HIP(hipDeviceSynchronize());
+    st = net->cl ? cl_prepare(net) : prepare_planes(net);
     if (st != CADNN_OK) return st;
     net->use_graph = (flags & CADNN_NET_GRAPH) != 0;
     net->want_tune = (flags & CADNN_NET_TUNE) != 0;

@@ -111,7 +111,7 @@ struct cadnn_net {
     bool allow_s2d = true;
     bool allow_fusion = true;
     char* ws = nullptr;
-    char* planes_ws = nullptr;       // the caller's workspace while the net works in cl_ws
+    char* planes_ws = nullptr;       // the caller's (latest) workspace while the net works in cl_ws
     bool static_ws = false;          // the workspace is the library's static array (CADNN_NET_STATIC_WORKSPACE)
     std::map<int, std::unique_ptr<cadnn_weights>> merged_w;   // per first op of a sibling group
     std::map<int, std::unique_ptr<cadnn::DevBuf>> merged_bias;

@@ -185,3 +185,50 @@ def test_first_layer_reads_nothing_outside_its_windows(cad, k, stride, pad, h, w
         assert np.isfinite(maps[0]).all() and not np.isfinite(maps[1]).all()
         assert np.array_equal(maps[0][keep], maps[1][keep]), name
     net.free()
+
+
+def test_finalize_again_after_a_pin(cad):
+    """A net that a pin took channels-last is finalized a second time with a workspace of exactly the size asked
+    for (smaller than the channels-last tensors, whose few channels are padded): nothing behind it is written,
+    the first workspace is not used any more, the pin stays, and a plane variant takes the net to the new one."""
+    import ctypes
+    ops = [Op("conv", "stem", 0, 1, 3, 8, 3, 1, 1, 0.0, True), Op("conv", "a", 1, 2, 8, 8, 3, 1, 1, 0.5, True),
+           Op("conv", "b", 2, 3, 8, 4, 1, 1, 0, 0.5, False), Op("avgpool", "gap", 3, 4)]
+    shape = (2, 3, 40, 37)
+    x, ws, bs = wl.net_tensors(ops, "again", shape)
+    ref, ins, outs = oracle.run_net(ops, x, ws, bs, dtype=np.float32)
+    bound = chain_bounds(ops, ins, outs, ws, bs, False)[-1]
+    xd = torch.from_numpy(x).cuda()
+    net = cad.build_net(ops, ws, bs, shape, cad.F32, use_graph=False)
+    planes = net.variants()
+    net.set_op_variant(0, "cl_mfma_64x64_s3")
+    first = net._keep[-1]
+    size = first.numel()
+    assert not planes[0].startswith("cl_")
+
+    def check(what):
+        y = net.run(xd)
+        torch.cuda.synchronize()
+        assert_within_bound(y.cpu().numpy(), ref, bound, what)
+
+    check("pinned")
+    for again in range(2):
+        room = torch.full((size + (4 << 20),), 0x5A, dtype=torch.uint8, device="cuda")
+        torch.cuda.synchronize()
+        cad.binding._check(cad.lib().cadnn_net_finalize(net.handle, ctypes.c_void_p(room.data_ptr()), size, 0))
+        first.fill_(0x7F)                       # (what the caller does with a workspace it has taken back)
+        first = room
+        check("finalized again")
+        assert net.op_variant(0) == "cl_mfma_64x64_s3"
+        assert bool((room[size:] == 0x5A).all())
+    net.set_variants(planes)
+    check("back on planes")
+    assert net.variants() == planes and bool((first[size:] == 0x5A).all())
+    net.set_op_variant(0, "cl_mfma_64x64_s4")
+    check("channels-last once more")
+    # other flags lay the net out anew: no pin is left
+    room = torch.empty(size, dtype=torch.uint8, device="cuda")
+    cad.binding._check(cad.lib().cadnn_net_finalize(net.handle, ctypes.c_void_p(room.data_ptr()), size, 4))
+    check("plain layout")
+    assert not net.op_variant(0).startswith("cl_")
+    net.free()
