@@ -68,6 +68,10 @@ struct ClConv {
     int n, cout, stride, pad, relu;
 };
 
+// The shape of a layer's K (host work only; tap_of: per filter tap its place among the taps in use, or -1), and with
+// the weights on the device.
+cadnn_status cl_plan_shape(const cadnn_weights* w, const cadnn_weights* shortcut, int rb, bool stem, ClPlan* plan,
+                           std::vector<int>* tap_of = nullptr);
 cadnn_status cl_build_plan(const cadnn_weights* w, const cadnn_weights* shortcut, int rb, bool stem, ClPlan* plan);
 // The tile the cost rule takes, and whether a variant can run the layer.
 const ClVariant* cl_pick(int cout, const ClPlan& plan, int64_t pixels, bool f16);

@@ -721,7 +721,8 @@ cadnn_status launch_cl_conv(const ClConv& c, const ClVariant& v, bool f16, hipSt
     return CADNN_OK;
 }
 
-cadnn_status cl_build_plan(const cadnn_weights* w, const cadnn_weights* shortcut, int rb, bool stem, ClPlan* plan) {
+cadnn_status cl_plan_shape(const cadnn_weights* w, const cadnn_weights* shortcut, int rb, bool stem, ClPlan* plan,
+                           std::vector<int>* tap_of) {
     const size_t e = w->elem();
     const int taps_all = w->kh * w->kw, kpr = rb / (int)e;      // k per step
     plan->rb = rb;
@@ -755,6 +756,16 @@ cadnn_status cl_build_plan(const cadnn_weights* w, const cadnn_weights* shortcut
     }
     plan->steps2 = shortcut ? (shortcut->cin + kpr - 1) / kpr : 0;
     plan->steps = plan->taps * plan->steps_tap + plan->steps2;
+    if (tap_of) tap_of->swap(tap_index);
+    return CADNN_OK;
+}
+
+cadnn_status cl_build_plan(const cadnn_weights* w, const cadnn_weights* shortcut, int rb, bool stem, ClPlan* plan) {
+    const size_t e = w->elem();
+    const int taps_all = w->kh * w->kw, kpr = rb / (int)e;
+    std::vector<int> tap_index;
+    const cadnn_status st = cl_plan_shape(w, shortcut, rb, stem, plan, &tap_index);
+    if (st != CADNN_OK) return st;
     const size_t blocks = (size_t)(w->cout + 127) / 128 * 2;    // (64-row blocks, whole 128-row tiles)
     const size_t bytes = blocks * (size_t)plan->steps * 64 * (size_t)rb;
     if (bytes >= 0x7ffffff0ull) return fail(CADNN_EUNSUPPORTED, "cadnn_net: weight matrix of 2 GiB or more");

@@ -1015,6 +1015,28 @@ static cadnn_status prepare_planes(cadnn_net* net) {
     return CADNN_OK;
 }
 
+// Whether `name` may be pinned on convolution i of the plane layouts (host work only: the net may be running channels-last).
+static cadnn_status plane_variant_serves(const cadnn_net* net, size_t i, const char* name) {
+    const NetOp& op = net->ops[i];
+    if (!op.comates.empty() && std::strcmp(name, "apart") == 0) return CADNN_OK;
+    bool serves = false;
+    if (!op.comates.empty()) {
+        std::vector<const ConvVariant*> common;
+        cadnn_status st = conv2d_group_candidates(colaunch_members(net, i), op.in.n, &common, nullptr);
+        if (st != CADNN_OK) return st;
+        for (const ConvVariant* c : common) serves = serves || std::strcmp(c->name, name) == 0;
+    } else {
+        ConvExtra ex;
+        std::vector<char> names(1 << 16);
+        cadnn_status st = conv2d_list_variants_impl(eff_w(net, op), op.xd, op.in.n, op.stride, op.pad, names.data(), names.size(),
+                                                    out_s2d(op), shortcut_geom(net, op, &ex));
+        if (st != CADNN_OK) return st;
+        const std::string all = std::string("\n") + names.data() + "\n";
+        serves = all.find(std::string("\n") + name + "\n") != std::string::npos;
+    }
+    return serves ? CADNN_OK : fail(CADNN_EINVAL, "cadnn_net_set_op_variant: '%s' does not serve op %zu", name, i);
+}
+
 // The net leaves the channels-last execution for the plane layouts (a variant of theirs is pinned).
 static cadnn_status leave_channels_last(cadnn_net* net) {
     if (net->exec) (void)hipGraphExecDestroy(net->exec);
@@ -1033,9 +1055,12 @@ static cadnn_status leave_channels_last(cadnn_net* net) {
 
 // ... and the way there: a channels-last variant is pinned on a net that the rule left on planes (a saved
 // choice replays whichever execution it was made with).  The workspace is the library's own then.
-static cadnn_status enter_channels_last(cadnn_net* net) {
+// A variant that does not serve the op is refused before anything changes.
+static cadnn_status enter_channels_last(cadnn_net* net, size_t op, const ClVariant& v) {
     std::unique_ptr<ClNet> cl = (net->allow_s2d && net->allow_fusion && !net->static_ws) ? cl_layout(net) : nullptr;
     if (!cl) return fail(CADNN_EUNSUPPORTED, "cadnn_net_set_op_variant: the net has no channels-last execution");
+    if (cl->ops[op]->fused_into >= 0) return CADNN_OK;      // nothing to pin: the net stays as it is
+    if (!cl_would_serve(net, *cl, op, v)) return fail(CADNN_EINVAL, "cadnn_net_set_op_variant: '%s' does not serve op %zu", v.name, op);
     if (net->exec) (void)hipGraphExecDestroy(net->exec);
     net->exec = nullptr;
     CADNN_HIP(hipDeviceSynchronize());
@@ -1330,9 +1355,10 @@ extern "C" cadnn_status cadnn_net_set_op_variant(cadnn_net* net, int op_index, c
     const NetOp& op = net->ops[op_index];
     if (op.kind != OP_CONV) return fail(CADNN_EINVAL, "cadnn_net_set_op_variant: op %d is not a convolution", op_index);
     const std::vector<ClVariant>& cls = all_cl_variants();
-    if (!net->cl && name && std::any_of(cls.begin(), cls.end(), [&](const ClVariant& v) { return std::strcmp(v.name, name) == 0; })) {
-        cadnn_status entered = enter_channels_last(net);
-        if (entered != CADNN_OK) return entered;
+    const auto named = std::find_if(cls.begin(), cls.end(), [&](const ClVariant& v) { return name && std::strcmp(v.name, name) == 0; });
+    if (!net->cl && named != cls.end()) {
+        cadnn_status entered = enter_channels_last(net, (size_t)op_index, *named);
+        if (entered != CADNN_OK || !net->cl) return entered;
     }
     if (net->cl) {
         ClOp& c = *net->cl->ops[(size_t)op_index];
@@ -1348,7 +1374,9 @@ extern "C" cadnn_status cadnn_net_set_op_variant(cadnn_net* net, int op_index, c
             return cl_prepare_variant(*v, &c.plan, pixels, op.out.c);
         }
         if (std::strncmp(name, "cl_", 3) == 0) return fail(CADNN_EINVAL, "cadnn_net_set_op_variant: '%s' does not serve op %d", name, op_index);
-        cadnn_status left = leave_channels_last(net);
+        if (op.fused_into >= 0) return CADNN_OK;            // nothing to pin on planes either: the net stays as it is
+        cadnn_status left = plane_variant_serves(net, (size_t)op_index, name);
+        if (left == CADNN_OK) left = leave_channels_last(net);
         if (left != CADNN_OK) return left;
     }
     if (op.fused_into >= 0) return CADNN_OK;     // nothing to pin: computed inside, or launched with, another op

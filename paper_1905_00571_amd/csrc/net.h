@@ -133,5 +133,7 @@ cadnn_status cl_tune(cadnn_net* net, const void* x, void* y, hipStream_t s);
 void cl_op_info(const cadnn_net* net, size_t i, cadnn_op_info* out);
 const char* cl_op_variant(const cadnn_net* net, size_t i);
 std::vector<const ClVariant*> cl_candidates(const cadnn_net* net, size_t i);
+// Whether variant v would serve convolution i in the layout `cl` (host work only, before anything is prepared).
+bool cl_would_serve(const cadnn_net* net, const ClNet& cl, size_t i, const ClVariant& v);
 cadnn_status cl_read_buffer(cadnn_net* net, size_t i, void* host_out, size_t bytes);
 }  // namespace cadnn

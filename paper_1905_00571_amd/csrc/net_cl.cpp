@@ -64,6 +64,16 @@ ClConv conv_args(const cadnn_net* net, size_t i, void* y_region) {
     return a;
 }
 
+// Bytes of a K step of convolution i.
+int step_bytes(const cadnn_net* net, const ClNet& cl, size_t i) {
+    const NetOp& op = net->ops[i];
+    const ClOp& c = *cl.ops[i];
+    const size_t e = net->elem();
+    if (c.x_stem) return op.w->kw * 4 * (int)e <= 64 ? 64 : 128;
+    const NetOp* p = shortcut_op(net, c);
+    return ((size_t)cl_padded_channels(op.in.c, e) * e) % 128 || (p && ((size_t)cl_padded_channels(p->in.c, e) * e) % 128) ? 64 : 128;
+}
+
 int64_t out_pixels(const NetOp& op) { return (int64_t)op.out.n * op.out.h * op.out.w; }
 
 }  // namespace
@@ -250,16 +260,9 @@ cadnn_status cl_prepare(cadnn_net* net) {
             }
         }
         if (op.kind == OP_CONV && c.fused_into < 0 && !c.plan.w.p) {
-            int rb = 128;
             const NetOp* p = shortcut_op(net, c);
-            if (c.x_stem) {
-                if (op.w->kw * 4 * (int)e <= 64) rb = 64;
-            } else if (((size_t)cl_padded_channels(op.in.c, e) * e) % 128 ||
-                       (p && ((size_t)cl_padded_channels(p->in.c, e) * e) % 128)) {
-                rb = 64;
-            }
             try {
-                st = cl_build_plan(op.w, p ? p->w : nullptr, rb, c.x_stem, &c.plan);
+                st = cl_build_plan(op.w, p ? p->w : nullptr, step_bytes(net, *net->cl, i), c.x_stem, &c.plan);
             } catch (const std::bad_alloc&) {
                 st = fail(CADNN_ENOMEM, "out of host memory building a conv plan");
             }
@@ -402,6 +405,14 @@ std::vector<const ClVariant*> cl_candidates(const cadnn_net* net, size_t i) {
     for (const ClVariant& v : all_cl_variants())
         if (cl_variant_fits(v, net->cl->ops[i]->plan, out_pixels(op), op.out.c)) out.push_back(&v);
     return out;
+}
+
+bool cl_would_serve(const cadnn_net* net, const ClNet& cl, size_t i, const ClVariant& v) {
+    const NetOp& op = net->ops[i];
+    const NetOp* p = shortcut_op(net, *cl.ops[i]);
+    ClPlan shape;
+    return cl_plan_shape(op.w, p ? p->w : nullptr, step_bytes(net, cl, i), cl.ops[i]->x_stem, &shape) == CADNN_OK &&
+           cl_variant_fits(v, shape, out_pixels(op), op.out.c);
 }
 
 cadnn_status cl_read_buffer(cadnn_net* net, size_t i, void* host_out, size_t bytes) {

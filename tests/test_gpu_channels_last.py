@@ -187,6 +187,48 @@ def test_first_layer_reads_nothing_outside_its_windows(cad, k, stride, pad, h, w
     net.free()
 
 
+def test_a_refused_name_changes_nothing(cad):
+    """A name that no variant of the op has, or one of the other execution that does not serve the op, is refused
+    and leaves the net in the execution, and with the choices, it had."""
+    ops, shape = deep_net()
+    x, ws, bs = wl.net_tensors(ops, "refused", shape, input_relu=True)
+    xd = torch.from_numpy(x).cuda()
+    net = cad.build_net(ops, ws, bs, shape, cad.F32, use_graph=True)
+    planes = net.variants()
+    assert not planes[0].startswith("cl_")
+    want = net.run(xd)
+    for op, name in ((0, "no_such_kernel"), (0, "cl_no_such_tile"), (4, "cl_mfma_64x64")):
+        with pytest.raises(cad.CadnnError):
+            net.set_op_variant(op, name)
+        assert net.variants() == planes
+    small = [Op("conv", "a", 0, 1, 16, 16, 1, 1, 0, 0.5, True), Op("conv", "b", 1, 2, 16, 16, 3, 1, 1, 0.5, True)]
+    _, sw, sb = wl.net_tensors(small, "refused-small", (1, 16, 9, 9))
+    # (16 channels are too few for the large tile, one K step too few for two slices)
+    little = cad.build_net(small, sw, sb, (1, 16, 9, 9), cad.F32, use_graph=False)
+    before = little.variants()
+    for name in ("cl_mfma_128x128_s2", "cl_mfma_64x64_s3k2"):
+        with pytest.raises(cad.CadnnError):
+            little.set_op_variant(0, name)
+        assert little.variants() == before
+    little.free()
+    assert torch.equal(net.run(xd), want)
+    net.set_op_variant(1, "cl_mfma_64x64_s4k4")
+    tiles = net.variants()
+    want = net.run(xd)
+    # (a name of the plane layouts that the 3x3 layer has no use for: a kernel of 1x1 filters)
+    probe = cad.build_net(ops, ws, bs, shape, cad.F32, use_graph=False)
+    foreign = sorted(set(probe.op_candidates(0)) - set(probe.op_candidates(1)))
+    probe.free()
+    assert foreign
+    for name in ("no_such_kernel", foreign[0], "apart", "cl_mfma_64x64"):
+        with pytest.raises(cad.CadnnError):
+            net.set_op_variant(1, name)
+        assert net.variants() == tiles, name
+    assert torch.equal(net.run(xd), want)
+    torch.cuda.synchronize()
+    net.free()
+
+
 def test_finalize_again_after_a_pin(cad):
     """A net that a pin took channels-last is finalized a second time with a workspace of exactly the size asked
     for (smaller than the channels-last tensors, whose few channels are padded): nothing behind it is written,
