@@ -76,7 +76,7 @@ cadnn_status cl_build_plan(const cadnn_weights* w, const cadnn_weights* shortcut
 // The tile the cost rule takes, and whether a variant can run the layer.
 const ClVariant* cl_pick(int cout, const ClPlan& plan, int64_t pixels, bool f16);
 bool cl_variant_fits(const ClVariant& v, const ClPlan& plan, int64_t pixels, int cout);
-// Scratch of a split-K variant (no-op otherwise).
+// Scratch of a split-K variant (no-op otherwise), ready for launches on any stream; on failure the plan keeps what it had.
 cadnn_status cl_prepare_variant(const ClVariant& v, ClPlan* plan, int64_t pixels, int cout);
 void cl_split_scratch(const ClVariant& v, int64_t pixels, int cout, size_t* part_bytes, size_t* count_bytes);
 cadnn_status launch_cl_conv(const ClConv& c, const ClVariant& v, bool f16, hipStream_t s);

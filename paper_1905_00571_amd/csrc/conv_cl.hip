@@ -617,15 +617,17 @@ cadnn_status cl_prepare_variant(const ClVariant& v, ClPlan* plan, int64_t pixels
     if (v.sk <= 1) return CADNN_OK;
     size_t part = 0, count = 0;
     cl_split_scratch(v, pixels, cout, &part, &count);
+    // what the plan has is replaced only when all of the new is there: the variant in use keeps its scratch
+    DevBuf more_part, more_count;
     cadnn_status st = CADNN_OK;
-    if (plan->part.bytes < part) {
-        plan->part.release();
-        if ((st = plan->part.alloc(part, false)) != CADNN_OK) return st;
-    }
+    if (plan->part.bytes < part && (st = more_part.alloc(part, false)) != CADNN_OK) return st;
     if (plan->count.bytes < count) {
-        plan->count.release();
-        if ((st = plan->count.alloc(count, true)) != CADNN_OK) return st;
+        if ((st = more_count.alloc(count, true)) != CADNN_OK) return st;
+        // (the zeros are written on the null stream, which a stream of the caller's need not wait for)
+        CADNN_HIP(hipDeviceSynchronize());
     }
+    if (more_part.p) plan->part.swap(more_part);
+    if (more_count.p) plan->count.swap(more_count);
     return CADNN_OK;
 }
 

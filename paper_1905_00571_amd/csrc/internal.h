@@ -72,6 +72,7 @@ struct DevBuf {
     DevBuf(const DevBuf&) = delete;
     DevBuf& operator=(const DevBuf&) = delete;
     ~DevBuf() { release(); }
+    void swap(DevBuf& o) { std::swap(p, o.p); std::swap(bytes, o.bytes); std::swap(on_host, o.on_host); }
     void release();
     // Allocates (at least 16 bytes so that p is never NULL) and uploads `n` bytes from host.
     cadnn_status upload(const void* host, size_t n);

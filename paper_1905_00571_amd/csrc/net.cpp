@@ -1370,8 +1370,9 @@ extern "C" cadnn_status cadnn_net_set_op_variant(cadnn_net* net, int op_index, c
         if (v) {
             drop_graph(net);
             CADNN_HIP(hipDeviceSynchronize());
-            c.v = v;
-            return cl_prepare_variant(*v, &c.plan, pixels, op.out.c);
+            const cadnn_status st = cl_prepare_variant(*v, &c.plan, pixels, op.out.c);
+            if (st == CADNN_OK) c.v = v;
+            return st;
         }
         if (std::strncmp(name, "cl_", 3) == 0) return fail(CADNN_EINVAL, "cadnn_net_set_op_variant: '%s' does not serve op %d", name, op_index);
         if (op.fused_into >= 0) return CADNN_OK;            // nothing to pin on planes either: the net stays as it is

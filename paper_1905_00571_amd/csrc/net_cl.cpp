@@ -258,16 +258,20 @@ cadnn_status cl_prepare(cadnn_net* net) {
             } catch (const std::bad_alloc&) {
                 st = fail(CADNN_ENOMEM, "out of host memory building the depthwise filter table");
             }
+            if (st != CADNN_OK) c.dw.release();
         }
-        if (op.kind == OP_CONV && c.fused_into < 0 && !c.plan.w.p) {
+        if (op.kind == OP_CONV && c.fused_into < 0) {
             const NetOp* p = shortcut_op(net, c);
             try {
-                st = cl_build_plan(op.w, p ? p->w : nullptr, step_bytes(net, *net->cl, i), c.x_stem, &c.plan);
+                if (!c.plan.w.p) st = cl_build_plan(op.w, p ? p->w : nullptr, step_bytes(net, *net->cl, i), c.x_stem, &c.plan);
             } catch (const std::bad_alloc&) {
                 st = fail(CADNN_ENOMEM, "out of host memory building a conv plan");
             }
-            if (st != CADNN_OK) return st;
-            c.v = cl_pick(op.w->cout, c.plan, out_pixels(op), e == 2);
+            if (st != CADNN_OK) {
+                c.plan.w.release();             // (allocated and not filled)
+                return st;
+            }
+            if (!c.v) c.v = cl_pick(op.w->cout, c.plan, out_pixels(op), e == 2);
             st = cl_prepare_variant(*c.v, &c.plan, out_pixels(op), op.out.c);
         }
         if (st != CADNN_OK) return st;
@@ -335,7 +339,7 @@ cadnn_status cl_tune(cadnn_net* net, const void* x, void* y, hipStream_t s) {
         const NetOp& op = net->ops[i];
         ClOp& c = *net->cl->ops[i];
         if (op.kind != OP_CONV || c.fused_into >= 0) continue;
-        const ClVariant* best = nullptr;
+        const ClVariant *best = nullptr, *had = c.v;
         float best_ms = 0.0f;
         for (const ClVariant* v : cl_candidates(net, i)) {
             if ((st = cl_prepare_variant(*v, &c.plan, out_pixels(op), op.out.c)) != CADNN_OK) break;
@@ -358,7 +362,7 @@ cadnn_status cl_tune(cadnn_net* net, const void* x, void* y, hipStream_t s) {
                              op.w->kh, op.stride, op.out.n, op.out.h, op.out.w, c.plan.steps, c.plan.rb, v->name, total * 1e3f / kReps);
             if (!best || total < best_ms) { best = v; best_ms = total; }
         }
-        if (best) c.v = best;
+        c.v = best ? best : had;
     }
     (void)hipEventDestroy(e0);
     (void)hipEventDestroy(e1);

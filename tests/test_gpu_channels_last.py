@@ -187,6 +187,29 @@ def test_first_layer_reads_nothing_outside_its_windows(cad, k, stride, pad, h, w
     net.free()
 
 
+def test_split_tiles_pinned_and_run_at_once_on_another_stream(cad):
+    """The arrival counters of a split K are zero for a launch on a non-blocking stream right behind the pin, with the
+    scratch growing and the tiles changing in between."""
+    ops = [Op("conv", "a", 0, 1, 64, 64, 3, 1, 1, 0.5, True), Op("conv", "b", 1, 2, 64, 64, 3, 1, 1, 0.5, False)]
+    shape = (2, 64, 30, 31)
+    x, ws, bs = wl.net_tensors(ops, "split-stream", shape, input_relu=True)
+    ref, ins, outs = oracle.run_net(ops, x, ws, bs, dtype=np.float32)
+    bound = chain_bounds(ops, ins, outs, ws, bs, False)[-1]
+    xd = torch.from_numpy(x).cuda()
+    stream = torch.cuda.Stream()
+    torch.cuda.synchronize()
+    for names in (("cl_mfma_64x64_s3k2", "cl_mfma_64x64_s3k4"), ("cl_mfma_64x64_s4k4", "cl_mfma_64x64_s3k2"), ("cl_mfma_64x64_s3", "cl_mfma_64x64_s3k4")):
+        net = cad.build_net(ops, ws, bs, shape, cad.F32, use_graph=False)
+        with torch.cuda.stream(stream):
+            for i, name in enumerate(names):
+                net.set_op_variant(i, name)
+            got = [net.run(xd) for _ in range(3)]
+        stream.synchronize()
+        for y in got:
+            assert_within_bound(y.cpu().numpy(), ref, bound, str(names))
+        net.free()
+
+
 def test_a_refused_name_changes_nothing(cad):
     """A name that no variant of the op has, or one of the other execution that does not serve the op, is refused
     and leaves the net in the execution, and with the choices, it had."""
