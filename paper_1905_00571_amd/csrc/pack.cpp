@@ -943,6 +943,8 @@ cadnn_status get_sk_scratch(const cadnn_weights* w, const ConvVariant* v, const 
         cadnn_status st = sc->part.alloc(part_bytes, false);
         if (st == CADNN_OK) st = sc->count.alloc(count_bytes, true);
         if (st != CADNN_OK) return st;
+        // (the zeros are written on the null stream, which the launch's stream need not wait for)
+        CADNN_HIP(hipStreamSynchronize(nullptr));
         it = w->sk_scratch.emplace(k, std::move(sc)).first;
     }
     if (g_trial_plans == 0) it->second->in_use = true;
