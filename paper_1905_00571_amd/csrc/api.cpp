@@ -416,21 +416,25 @@ static const ConvVariant* heuristic_variant(const cadnn_weights* w, const ConvGe
 }
 
 // The model runs over some two hundred instantiations, which takes the host longer than a small
-// layer takes the GPU: its pick is kept on the handle, per geometry.  (A fused shortcut's own geometry is
-// not part of the key, so those picks are not kept.)
+// layer takes the GPU: its pick is kept on the handle, per geometry and distance between images (a slice of a wide
+// region can be too far apart for kernels that hold a batch behind one 32-bit offset; a pinned
+// variant is passed over there for the same reason).  A fused shortcut's own geometry is not part of the key, so
+// those picks are not kept.
 static const ConvVariant* pick_variant(const cadnn_weights* w, const ConvGeom& g) {
     const GeomKey key = g.key();
+    const std::pair<GeomKey, int64_t> spaced(key, g.xd.image);
     const bool keep = !(g.ex && g.ex->w);
     {
         std::lock_guard<std::mutex> lock(w->mu);
         auto it = w->chosen.find(key);
-        if (it != w->chosen.end()) return it->second;
-        if (keep && (it = w->modelled.find(key)) != w->modelled.end()) return it->second;
+        if (it != w->chosen.end() && variant_fits(*it->second, w, g, true)) return it->second;
+        auto kept = w->modelled.find(spaced);
+        if (keep && kept != w->modelled.end()) return kept->second;
     }
     const ConvVariant* v = heuristic_variant(w, g);
     if (keep && v) {
         std::lock_guard<std::mutex> lock(w->mu);
-        w->modelled[key] = v;
+        w->modelled[spaced] = v;
     }
     return v;
 }

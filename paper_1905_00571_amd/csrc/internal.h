@@ -465,8 +465,8 @@ struct cadnn_weights {
     mutable std::map<cadnn::PlanKey, std::shared_ptr<cadnn::ConvPlan>> plans;
     // variant pinned for a geometry by tuning or by the caller
     mutable std::map<cadnn::GeomKey, const cadnn::ConvVariant*> chosen;
-    // the cost model's pick per geometry (a pure function of the weights and the key)
-    mutable std::map<cadnn::GeomKey, const cadnn::ConvVariant*> modelled;
+    // the cost model's pick per geometry and elements between images (a pure function of the weights and these)
+    mutable std::map<std::pair<cadnn::GeomKey, int64_t>, const cadnn::ConvVariant*> modelled;
     // scratch of the split-K matrix-core variants, per (variant, layer geometry); never freed
     // or moved before the handle is (launch records and captured graphs point into it); two
     // launches of one layer that overlap in time would share it and race

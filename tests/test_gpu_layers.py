@@ -990,3 +990,53 @@ def test_big_strided_layer_reads_a_deinterleaved_copy(cad, dtype_name):
     assert_net_close(y.cpu().numpy(), refs[1][0], tol, "plain layout")
     net.free()
     plain.free()
+
+
+@pytest.mark.parametrize("pinned", [False, True])
+def test_a_pick_is_not_carried_to_images_too_far_apart(cad, pinned):
+    """One handle on a plain batch, where a kernel that runs over the whole batch behind one 32-bit offset is
+    taken (by the model, or pinned), then on the same sizes inside a region of many more channels, whose batch is
+    2 GiB and more: another kernel serves it there, with the same sums."""
+    import ctypes
+    n, c, hw, many = 32, 256, 28, 21500
+    L, check = cad.lib(), cad.binding._check
+    w = wl.pruned_weights(c, c, 1, 1, 0.8, "apart", 1)
+    h = cad.cadnn_pack_weights(w, cad.F32)
+    first = cad.cadnn_pack_weights(wl.pruned_weights(c, 8, 1, 1, 0.8, "apart", 2), cad.F32)
+    other = cad.cadnn_pack_weights(wl.pruned_weights(many, 8, 1, 1, 0.8, "apart", 3), cad.F32)
+    name = cad.cadnn_conv2d_variant_name(h, n, hw, hw, 1, 0)
+    assert name.startswith("swide_float_f4")
+    if pinned:
+        name = next(v for v in cad.cadnn_conv2d_list_variants(h, n, hw, hw, 1, 0) if v.startswith("swide_float_f4") and v != name)
+        cad.cadnn_conv2d_set_variant(h, n, hw, hw, 1, 0, name)
+    net = ctypes.c_void_p()
+    check(L.cadnn_net_create(cad.F32, n, 8, hw, hw, ctypes.byref(net)))
+    try:
+        # two layers on the input share one region of c + many channels; the layer under test reads the first's
+        check(L.cadnn_net_add_conv(net, first.handle, None, 1, 0, 1, 0, 1, -1))
+        check(L.cadnn_net_add_conv(net, other.handle, None, 1, 0, 1, 0, 2, -1))
+        check(L.cadnn_net_add_conv(net, h.handle, None, 1, 0, 0, 1, 3, -1))
+        info, nbytes = cad.OpInfo(), ctypes.c_size_t()
+        check(L.cadnn_net_op_info(net, 0, 0, ctypes.byref(info)))
+        assert info.image * 4 * n >= 1 << 31
+        check(L.cadnn_net_workspace_bytes(net, ctypes.byref(nbytes)))
+        room = torch.empty(nbytes.value, dtype=torch.uint8, device="cuda")
+        check(L.cadnn_net_finalize(net, ctypes.c_void_p(room.data_ptr()), nbytes.value, 0))
+        buf = ctypes.create_string_buffer(256)
+        check(L.cadnn_net_op_variant(net, 2, buf, 256))
+        assert not buf.value.startswith(b"swide_float_f4"), buf.value
+        x = dev(wl.activation((n, 8, hw, hw), "apart", 0, relu=True))
+        y = torch.empty(n, c, hw, hw, device="cuda")
+        check(L.cadnn_run_net(net, ctypes.c_void_p(x.data_ptr()), ctypes.c_void_p(y.data_ptr()), None))
+        torch.cuda.synchronize()
+        mid = np.empty((n, c, hw, hw), np.float32)
+        check(L.cadnn_net_read_buffer(net, 1, mid.ctypes.data_as(ctypes.c_void_p), mid.nbytes, None))
+    finally:
+        L.cadnn_net_free(net)
+    want = cad.cadnn_sparse_conv2d(h, dev(mid), 1, 0)
+    assert cad.cadnn_conv2d_variant_name(h, n, hw, hw, 1, 0) == name
+    bound = 2 * (c + 3) * 2.0 ** -24 * cond_conv(mid[:2], w, None, None, 1, 0)
+    assert (np.abs(y[:2].cpu().numpy() - want[:2].cpu().numpy()) <= bound).all()
+    assert torch.allclose(y, want, rtol=0, atol=float(4 * bound.max()))
+    for k in (h, first, other):
+        k.free()
