@@ -106,9 +106,14 @@ __global__ __launch_bounds__(256) void cl_pool_kernel(const T* __restrict__ x, C
 #pragma unroll
     for (int j = 0; j < N; ++j) { m[j] = -(T)__builtin_inff(); sum[j] = 0.0f; }
     int seen = 0;
+    // (a maximum starts from the window's first element inside the image and moves to what is greater, as on planes: a
+    // NaN in the first place stays, any other is passed over, and a k = 1 copy is one)
     auto take = [&](const V& v) __attribute__((always_inline)) {
-        if constexpr (KIND == 0) {
+        if constexpr (KIND == 0 && K > 0) {
             m = __builtin_elementwise_max(m, v);
+        } else if constexpr (KIND == 0) {
+#pragma unroll
+            for (int j = 0; j < N; ++j) m[j] = seen == 0 || v[j] > m[j] ? v[j] : m[j];
         } else {
 #pragma unroll
             for (int j = 0; j < N; ++j) sum[j] += (float)v[j];
@@ -133,6 +138,11 @@ __global__ __launch_bounds__(256) void cl_pool_kernel(const T* __restrict__ x, C
                 take(u);
                 seen += inside ? 1 : 0;
             }
+        // (the first element inside is the one at the clamped first coordinates)
+        if constexpr (KIND == 0) {
+#pragma unroll
+            for (int j = 0; j < N; ++j) m[j] = v[0][0][j] != v[0][0][j] ? v[0][0][j] : m[j];
+        }
     } else {
         for (int a = 0; a < k; ++a) {
             if (ih0 + a < 0 || ih0 + a >= xd.h) continue;

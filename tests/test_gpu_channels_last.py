@@ -187,6 +187,43 @@ def test_first_layer_reads_nothing_outside_its_windows(cad, k, stride, pad, h, w
     net.free()
 
 
+@pytest.mark.parametrize("dtype_name", ["f32", "f16"])
+@pytest.mark.parametrize("k,pad", [(1, 0), (2, 0), (2, 1), (3, 1), (3, 0), (5, 2)])
+def test_pools_and_copies_of_non_finite_values(cad, k, pad, dtype_name):
+    """Maximum pools over maps with NaN and infinities (whole windows of NaN among them), and the copy of such a
+    map into a concatenation, give what the pools on planes give: the window's first element inside the image,
+    replaced by what compares greater."""
+    dtype, npdt = (cad.F16, np.float16) if dtype_name == "f16" else (cad.F32, np.float32)
+    ops = [Op("maxpool", "pool", 0, 1, k=k, stride=1, pad=pad), Op("concat", "cat", 0, 2, srcs=(0, 0)),
+           Op("conv", "a", 1, 3, 8, 8, 1, 1, 0, 0.5, False), Op("conv", "b", 2, 4, 16, 8, 1, 1, 0, 0.5, False)]
+    n, h, w = 2, 9, 11
+    x, ws, bs = wl.net_tensors(ops, "nan-pool", (n, 8, h, w))
+    rng = np.random.default_rng(k * 7 + pad)
+    x[rng.random(x.shape) < 0.25] = np.nan
+    x[rng.random(x.shape) < 0.1] = np.inf
+    x[rng.random(x.shape) < 0.1] = -np.inf
+    x[0, 0], x[1, 3, :6, :6] = np.nan, np.nan
+    x = x.astype(npdt)
+    ho, wo = h + 2 * pad - k + 1, w + 2 * pad - k + 1
+    want = np.zeros((n, 8, ho, wo), npdt)
+    for r in range(ho):
+        for c in range(wo):
+            m = None
+            for a in range(max(r - pad, 0), min(r - pad + k, h)):
+                for b in range(max(c - pad, 0), min(c - pad + k, w)):
+                    m = x[:, :, a, b] if m is None else np.where(x[:, :, a, b] > m, x[:, :, a, b], m)
+            want[:, :, r, c] = m
+    for pin in (None, "cl_mfma_64x64_s3"):
+        net = cad.build_net(ops, ws, bs, (n, 8, h, w), dtype, use_graph=False)
+        if pin:
+            net.set_op_variant(2, pin)
+        net.run(torch.from_numpy(x).cuda())
+        torch.cuda.synchronize()
+        assert np.array_equal(net.read_buffer(1, want.shape), want, equal_nan=True), pin
+        assert np.array_equal(net.read_buffer(2, (n, 16, h, w)), np.concatenate([x, x], 1), equal_nan=True), pin
+        net.free()
+
+
 def test_split_tiles_pinned_and_run_at_once_on_another_stream(cad):
     """The arrival counters of a split K are zero for a launch on a non-blocking stream right behind the pin, with the
     scratch growing and the tiles changing in between."""
