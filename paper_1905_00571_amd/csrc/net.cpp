@@ -666,28 +666,32 @@ cadnn_status launch_one(cadnn_net* net, size_t i, const void* x, void* y, hipStr
     return fail(CADNN_EINVAL, "cadnn_net: unknown op kind");
 }
 
-// The ops in launch order: the op list's, but for the hoisted pools.
-std::vector<size_t> launch_order(const cadnn_net* net) {
-    std::vector<size_t> order;
-    for (size_t i = 0; i < net->ops.size(); ++i) {
+// The ops in launch order: the op list's, but for the hoisted pools.  f(number of the launch, op) until one fails.
+// (Walked in place: a pass, and with it cadnn_run_net_noalloc, allocates nothing for it.)
+template <class F>
+cadnn_status each_launch(const cadnn_net* net, F&& f) {
+    size_t k = 0;
+    cadnn_status st = CADNN_OK;
+    for (size_t i = 0; i < net->ops.size() && st == CADNN_OK; ++i) {
         if (!net->cl && net->ops[i].hoisted_to >= 0) continue;
-        order.push_back(i);
-        if (!net->cl) for (int h : net->ops[i].hoisted) order.push_back((size_t)h);
+        st = f(k++, i);
+        if (net->cl) continue;
+        for (size_t h = 0; h < net->ops[i].hoisted.size() && st == CADNN_OK; ++h) st = f(k++, (size_t)net->ops[i].hoisted[h]);
     }
-    return order;
+    return st;
 }
 
-cadnn_status launch_all(cadnn_net* net, const void* x, void* y, hipStream_t s) {
-    for (size_t i : launch_order(net)) {
-        cadnn_status st = launch_one(net, i, x, y, s);
-        if (st != CADNN_OK) return st;
-    }
-    return CADNN_OK;
+// Launches [first, last) of a pass.
+cadnn_status launch_range(cadnn_net* net, size_t first, size_t last, const void* x, void* y, hipStream_t s) {
+    return each_launch(net, [&](size_t k, size_t i) { return k >= first && k < last ? launch_one(net, i, x, y, s) : CADNN_OK; });
 }
+
+cadnn_status launch_all(cadnn_net* net, const void* x, void* y, hipStream_t s) { return launch_range(net, 0, SIZE_MAX, x, y, s); }
 
 void drop_graph(cadnn_net* net) {
     if (net->exec) (void)hipGraphExecDestroy(net->exec);
     net->exec = nullptr;
+    net->ranged = false;
 }
 
 // Whether launching op i reads the caller's x or writes the caller's y.
@@ -707,15 +711,19 @@ bool touches_caller(const cadnn_net* net, size_t i) {
 // neither x nor y, so that the graph serves whatever tensors a call brings.  (A graph that holds
 // their addresses has to be captured and instantiated again for every new input or output buffer:
 // 1.2 ms for ResNet-50, 0.1 ms for a three-layer block that runs in 0.03.)
-struct GraphRange { size_t first = 0, last = 0; };
-GraphRange graph_range(const cadnn_net* net, const std::vector<size_t>& order) {
+GraphRange graph_range(const cadnn_net* net) {
     GraphRange best;
-    size_t start = 0;
-    for (size_t k = 0; k <= order.size(); ++k) {
-        if (k < order.size() && !touches_caller(net, order[k])) continue;
+    size_t start = 0, launches = 0;
+    auto ends_at = [&](size_t k) {
         if (k - start > best.last - best.first) { best.first = start; best.last = k; }
         start = k + 1;
-    }
+    };
+    (void)each_launch(net, [&](size_t k, size_t i) {
+        if (touches_caller(net, i)) ends_at(k);
+        launches = k + 1;
+        return CADNN_OK;
+    });
+    ends_at(launches);
     return best;
 }
 
@@ -1039,8 +1047,7 @@ static cadnn_status plane_variant_serves(const cadnn_net* net, size_t i, const c
 
 // The net leaves the channels-last execution for the plane layouts (a variant of theirs is pinned).
 static cadnn_status leave_channels_last(cadnn_net* net) {
-    if (net->exec) (void)hipGraphExecDestroy(net->exec);
-    net->exec = nullptr;
+    drop_graph(net);
     CADNN_HIP(hipDeviceSynchronize());
     net->cl.reset();
     if (net->cl_ws.p) {         // (the plane layouts' own workspace was left as it was)
@@ -1061,8 +1068,7 @@ static cadnn_status enter_channels_last(cadnn_net* net, size_t op, const ClVaria
     if (!cl) return fail(CADNN_EUNSUPPORTED, "cadnn_net_set_op_variant: the net has no channels-last execution");
     if (cl->ops[op]->fused_into >= 0) return CADNN_OK;      // nothing to pin: the net stays as it is
     if (!cl_would_serve(net, *cl, op, v)) return fail(CADNN_EINVAL, "cadnn_net_set_op_variant: '%s' does not serve op %zu", v.name, op);
-    if (net->exec) (void)hipGraphExecDestroy(net->exec);
-    net->exec = nullptr;
+    drop_graph(net);
     CADNN_HIP(hipDeviceSynchronize());
     cadnn_status st = net->cl_ws.alloc(cl->ws_bytes, true);
     if (st != CADNN_OK) return st;
@@ -1133,8 +1139,11 @@ extern "C" cadnn_status cadnn_run_net(cadnn_net* net, const void* x, void* y, vo
         drop_graph(net);
     }
     if (!net->use_graph) return launch_all(net, x, y, s);
-    const std::vector<size_t> order = launch_order(net);
-    const GraphRange range = graph_range(net, order);
+    if (!net->ranged) {
+        net->range = graph_range(net);
+        net->ranged = true;
+    }
+    const GraphRange range = net->range;
     // (a couple of launches are cheaper one by one)
     if (range.last - range.first < 4) return launch_all(net, x, y, s);
     if (!net->exec) {
@@ -1146,7 +1155,7 @@ extern "C" cadnn_status cadnn_run_net(cadnn_net* net, const void* x, void* y, vo
         if (e != hipSuccess) {
             st = fail(CADNN_EHIP, "hipStreamBeginCapture failed: %s", hipGetErrorString(e));
         } else {
-            for (size_t k = range.first; k < range.last && st == CADNN_OK; ++k) st = launch_one(net, order[k], x, y, cs);
+            st = launch_range(net, range.first, range.last, x, y, cs);
             e = hipStreamEndCapture(cs, &graph);
             if (st == CADNN_OK && e != hipSuccess)
                 st = fail(CADNN_EHIP, "hipStreamEndCapture failed: %s", hipGetErrorString(e));
@@ -1162,16 +1171,10 @@ extern "C" cadnn_status cadnn_run_net(cadnn_net* net, const void* x, void* y, vo
         (void)hipStreamDestroy(cs);
         if (st != CADNN_OK) return st;
     }
-    for (size_t k = 0; k < range.first; ++k) {
-        cadnn_status st = launch_one(net, order[k], x, y, s);
-        if (st != CADNN_OK) return st;
-    }
+    cadnn_status st = launch_range(net, 0, range.first, x, y, s);
+    if (st != CADNN_OK) return st;
     CADNN_HIP(hipGraphLaunch(net->exec, s));
-    for (size_t k = range.last; k < order.size(); ++k) {
-        cadnn_status st = launch_one(net, order[k], x, y, s);
-        if (st != CADNN_OK) return st;
-    }
-    return CADNN_OK;
+    return launch_range(net, range.last, SIZE_MAX, x, y, s);
 }
 
 extern "C" cadnn_status cadnn_run_net_noalloc(cadnn_net* net, const void* x, void* y, void* stream) {
@@ -1239,7 +1242,8 @@ extern "C" cadnn_status cadnn_net_profile_in_order(cadnn_net* net, const void* x
     if (repeats <= 0) return fail(CADNN_EINVAL, "cadnn_net_profile_in_order: repeats must be positive");
     hipStream_t s = (hipStream_t)stream;
     const size_t nops = net->ops.size();
-    const std::vector<size_t> order = launch_order(net);
+    std::vector<size_t> order;
+    (void)each_launch(net, [&](size_t, size_t i) { order.push_back(i); return CADNN_OK; });
     std::vector<LaunchTimer> timers(order.size());
     cadnn_status st = CADNN_OK;
     for (LaunchTimer& t : timers)

@@ -95,6 +95,9 @@ struct ClNet {
     size_t in_off = 0;
 };
 
+// Launches of a pass, numbered in launch order, that are replayed as a graph.
+struct GraphRange { size_t first = 0, last = 0; };
+
 }  // namespace cadnn
 
 struct cadnn_net {
@@ -119,6 +122,8 @@ struct cadnn_net {
     std::unique_ptr<cadnn::ClNet> cl;   // set: the net runs channels-last
     cadnn::DevBuf cl_ws;                // workspace of a net that was taken there by pinning a variant
     hipGraphExec_t exec = nullptr;
+    cadnn::GraphRange range;            // of the pass as it is now (ranged), kept like the graph itself
+    bool ranged = false;
     size_t elem() const { return dtype == CADNN_F16 ? 2 : 4; }
 };
 
