@@ -6,6 +6,7 @@
 #include <cstring>
 
 #include <iterator>
+#include <new>
 
 #include "net.h"
 
@@ -471,6 +472,7 @@ void drop_channels_last(cadnn_net* net) {
 }
 
 void layout(cadnn_net* net) {
+    net->laid_out = false;
     Layout l(net);
     l.run();
     net->laid_out = true;
@@ -937,12 +939,14 @@ extern "C" cadnn_status cadnn_net_add_fc(cadnn_net* net, const cadnn_weights* w,
     return CADNN_OK;
 }
 
-extern "C" cadnn_status cadnn_net_workspace_bytes(const cadnn_net* net, size_t* bytes) {
+extern "C" cadnn_status cadnn_net_workspace_bytes(const cadnn_net* net, size_t* bytes) try {
     if (!net || !bytes) return fail(CADNN_EINVAL, "cadnn_net_workspace_bytes: NULL pointer");
     if (net->ops.empty()) return fail(CADNN_EINVAL, "cadnn_net_workspace_bytes: empty net");
     if (!net->laid_out) layout(const_cast<cadnn_net*>(net));
     *bytes = net->ws_bytes;
     return CADNN_OK;
+} catch (const std::bad_alloc&) {
+    return fail(CADNN_ENOMEM, "cadnn_net_workspace_bytes: out of host memory");
 }
 
 // (Re)does the layout if the flags that matter to it changed.
@@ -956,7 +960,7 @@ static void layout_for(cadnn_net* net, int flags) {
     }
 }
 
-extern "C" cadnn_status cadnn_net_op_info(cadnn_net* net, int op_index, int flags, cadnn_op_info* out) {
+extern "C" cadnn_status cadnn_net_op_info(cadnn_net* net, int op_index, int flags, cadnn_op_info* out) try {
     if (!net || !out) return fail(CADNN_EINVAL, "cadnn_net_op_info: NULL pointer");
     if (op_index < 0 || op_index >= (int)net->ops.size()) return fail(CADNN_EINVAL, "cadnn_net_op_info: no op %d", op_index);
     if (net->finalized) {
@@ -985,6 +989,8 @@ extern "C" cadnn_status cadnn_net_op_info(cadnn_net* net, int op_index, int flag
     out->launched_after = op.hoisted_to;
     out->input_copy = op.restaged ? (int64_t)op.x_off : -1;
     return CADNN_OK;
+} catch (const std::bad_alloc&) {
+    return fail(CADNN_ENOMEM, "cadnn_net_op_info: out of host memory");
 }
 
 // Everything the layers of a net on plane layouts need on the device.
@@ -1082,7 +1088,7 @@ static cadnn_status enter_channels_last(cadnn_net* net, size_t op, const ClVaria
     return st;
 }
 
-extern "C" cadnn_status cadnn_net_finalize(cadnn_net* net, void* ws, size_t bytes, int flags) {
+extern "C" cadnn_status cadnn_net_finalize(cadnn_net* net, void* ws, size_t bytes, int flags) try {
     if (!net) return fail(CADNN_EINVAL, "cadnn_net_finalize: NULL net");
     if (net->ops.empty()) return fail(CADNN_EINVAL, "cadnn_net_finalize: empty net");
     // (a plain layout never needs more room than the de-interleaved one that
@@ -1126,9 +1132,11 @@ extern "C" cadnn_status cadnn_net_finalize(cadnn_net* net, void* ws, size_t byte
     net->want_tune = (flags & CADNN_NET_TUNE) != 0;
     net->finalized = true;
     return CADNN_OK;
+} catch (const std::bad_alloc&) {
+    return fail(CADNN_ENOMEM, "cadnn_net_finalize: out of host memory");
 }
 
-extern "C" cadnn_status cadnn_run_net(cadnn_net* net, const void* x, void* y, void* stream) {
+extern "C" cadnn_status cadnn_run_net(cadnn_net* net, const void* x, void* y, void* stream) try {
     if (!net || !x || !y) return fail(CADNN_EINVAL, "cadnn_run_net: NULL pointer");
     if (!net->finalized) return fail(CADNN_EINVAL, "cadnn_run_net: net not finalized");
     hipStream_t s = (hipStream_t)stream;
@@ -1175,6 +1183,8 @@ extern "C" cadnn_status cadnn_run_net(cadnn_net* net, const void* x, void* y, vo
     if (st != CADNN_OK) return st;
     CADNN_HIP(hipGraphLaunch(net->exec, s));
     return launch_range(net, range.last, SIZE_MAX, x, y, s);
+} catch (const std::bad_alloc&) {
+    return fail(CADNN_ENOMEM, "cadnn_run_net: out of host memory");
 }
 
 extern "C" cadnn_status cadnn_run_net_noalloc(cadnn_net* net, const void* x, void* y, void* stream) {
@@ -1315,7 +1325,7 @@ extern "C" cadnn_status cadnn_net_op_variant(const cadnn_net* net, int op_index,
     return CADNN_OK;
 }
 
-extern "C" cadnn_status cadnn_net_op_candidates(const cadnn_net* net, int op_index, char* buf, size_t len) {
+extern "C" cadnn_status cadnn_net_op_candidates(const cadnn_net* net, int op_index, char* buf, size_t len) try {
     if (!net || !buf || len == 0) return fail(CADNN_EINVAL, "cadnn_net_op_candidates: NULL pointer");
     if (!net->finalized) return fail(CADNN_EINVAL, "cadnn_net_op_candidates: net not finalized");
     if (op_index < 0 || op_index >= (int)net->ops.size()) return fail(CADNN_EINVAL, "cadnn_net_op_candidates: no op %d", op_index);
@@ -1350,9 +1360,11 @@ extern "C" cadnn_status cadnn_net_op_candidates(const cadnn_net* net, int op_ind
     }
     ConvExtra ex;
     return conv2d_list_variants_impl(eff_w(net, op), op.xd, op.in.n, op.stride, op.pad, buf, len, out_s2d(op), shortcut_geom(net, op, &ex));
+} catch (const std::bad_alloc&) {
+    return fail(CADNN_ENOMEM, "cadnn_net_op_candidates: out of host memory");
 }
 
-extern "C" cadnn_status cadnn_net_set_op_variant(cadnn_net* net, int op_index, const char* name) {
+extern "C" cadnn_status cadnn_net_set_op_variant(cadnn_net* net, int op_index, const char* name) try {
     if (!net) return fail(CADNN_EINVAL, "cadnn_net_set_op_variant: NULL net");
     if (!net->finalized) return fail(CADNN_EINVAL, "cadnn_net_set_op_variant: net not finalized");
     if (op_index < 0 || op_index >= (int)net->ops.size()) return fail(CADNN_EINVAL, "cadnn_net_set_op_variant: no op %d", op_index);
@@ -1410,10 +1422,12 @@ extern "C" cadnn_status cadnn_net_set_op_variant(cadnn_net* net, int op_index, c
     if (st != CADNN_OK) return st;
     drop_graph(net);
     return conv2d_prepare_impl(eff_w(net, op), op.xd, op.in.n, op.stride, op.pad, out_s2d(op), shortcut_geom(net, op, &ex));
+} catch (const std::bad_alloc&) {
+    return fail(CADNN_ENOMEM, "cadnn_net_set_op_variant: out of host memory");
 }
 
 extern "C" cadnn_status cadnn_net_read_buffer(cadnn_net* net, int buf, void* host_out, size_t bytes,
-                                              void* stream) {
+                                              void* stream) try {
     if (!net || !host_out) return fail(CADNN_EINVAL, "cadnn_net_read_buffer: NULL pointer");
     if (!net->finalized) return fail(CADNN_EINVAL, "cadnn_net_read_buffer: net not finalized");
     auto it = net->producer.find(buf);
@@ -1459,6 +1473,8 @@ extern "C" cadnn_status cadnn_net_read_buffer(cadnn_net* net, int buf, void* hos
                                   (size_t)op.out.h, hipMemcpyDeviceToHost));
         }
     return CADNN_OK;
+} catch (const std::bad_alloc&) {
+    return fail(CADNN_ENOMEM, "cadnn_net_read_buffer: out of host memory");
 }
 
 extern "C" cadnn_status cadnn_net_free(cadnn_net* net) {
