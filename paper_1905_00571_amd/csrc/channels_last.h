@@ -25,9 +25,12 @@ inline int cl_padded_channels(int c, size_t elem) {
 inline ClDesc cl_desc(int c, int h, int w, int ph, int pw, int pix) {
     ClDesc d;
     d.c = c; d.h = h; d.w = w; d.ph = ph; d.pw = pw; d.pix = pix;
-    d.row = (w + 2 * pw) * pix;
+    // (a row of 2^30 elements or more: an image that no region holds, and no offset in it)
+    const int64_t row = ((int64_t)w + 2 * (int64_t)pw) * pix;
+    const bool fits = row < (1 << 30);
+    d.row = fits ? (int)row : 0;
     d.origin = ph * d.row + pw * pix;
-    d.image = (int64_t)(h + 2 * ph) * d.row;
+    d.image = fits ? (int64_t)(h + 2 * ph) * d.row : (int64_t)1 << 40;
     return d;
 }
 

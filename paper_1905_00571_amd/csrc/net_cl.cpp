@@ -89,6 +89,7 @@ std::unique_ptr<ClNet> cl_layout(const cadnn_net* net) {
         else if (o.src_inst >= 0) readers[(size_t)o.src_inst].push_back({k, false});
         if (o.res_inst >= 0) readers[(size_t)o.res_inst].push_back({k, true});
     }
+    if (net->input.n > 65535) return nullptr;           // (launch grids hold an image per y or z)
     std::unique_ptr<ClNet> cl(new ClNet());
     for (int k = 0; k < nops; ++k) cl->ops.emplace_back(new ClOp());
 

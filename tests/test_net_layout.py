@@ -302,3 +302,16 @@ def test_first_layer_steps_end_inside_the_workspace(family, n, size, first):
     last_row = ((n - 1) * wide + (out - 1) * stride + k - 1) * wide * 8
     end = start + last_row + (out - 1) * stride * 8 + (k * 8 + 15) // 16 * 16
     assert end <= nbytes, (end, nbytes)
+
+
+@pytest.mark.parametrize("n,w,stride", [(1, 160_000_000, 64), (1, 150_000_000, 64), (70_000, 8, 1)])
+def test_tensors_too_large_for_channels_last_stay_on_planes(n, w, stride):
+    """Five input channels are padded to 32 there: a row of 2^32 elements and more is not taken for a short one, and a
+    batch beyond what a launch grid holds is left to the plane layouts, which refuse it."""
+    ops = [wl.Op("conv", "a", 0, 1, 5, 256, 1, stride, 0, 0.0, True), wl.Op("conv", "b", 1, 2, 256, 8, 1, 1, 0, 0.0, False),
+           wl.Op("conv", "c", 2, 3, 8, 8, 1, 1, 0, 0.0, False)]
+    ws = [np.ones((o.cout, o.cin, 1, 1), np.float32) for o in ops]
+    infos, nbytes = cad.plan_net(ops, ws, (n, 5, 1, w), dtype=cad.F16)
+    assert all(i["plane"] > 1 for i in infos)
+    small, _ = cad.plan_net(ops, ws, (min(n, 60_000), 5, 1, min(w, 1_000_000)), dtype=cad.F16)
+    assert small[0]["plane"] == 1                   # (a size that does go channels-last)
