@@ -241,11 +241,17 @@ cadnn_status cadnn_graph_launch_floor(void* scratch32, int launches, int reps, v
 /* Dense comparator on the same ABI (implicit-GEMM convolution over the dense
  * [cout][cin][kh][kw] DEVICE weight tensor, same fused epilogue), used for the
  * dense-vs-compressed comparison the paper reports (Section 5) and as the
- * fallback for layers that are not pruned. */
+ * fallback for layers that are not pruned.  Layers with enough work bring x and w into a
+ * workspace laid out for the matrix cores first: up to 128 MiB of such workspaces are kept for
+ * later calls, of any stream and thread.  On a stream that is being captured the layer runs on the tensors as they are: slower, and with its fp32 sums taken in
+ * another order. */
 cadnn_status cadnn_dense_conv2d(const void* w_dev, const void* x, void* y, int n, int cin, int h,
                                 int wdt, int cout, int kh, int kw, int stride, int pad,
                                 const void* bias, const void* residual, int relu,
                                 cadnn_dtype dtype, void* stream);
+/* Gives the kept workspaces back to the device, once the calls that use them are through (waits
+ * for those; may be called at any time but during a stream capture). */
+cadnn_status cadnn_release_workspaces(void);
 
 /* ------------------------------------------------------------------------- *
  * Whole-network runner (Section 5 measures single-image latency of a whole

@@ -36,6 +36,7 @@ from .binding import (  # noqa: F401
     cadnn_avgpool2d,
     cadnn_global_avgpool,
     cadnn_dense_conv2d,
+    cadnn_release_workspaces,
     cadnn_run_net,
     cadnn_run_net_noalloc,
     build_net,

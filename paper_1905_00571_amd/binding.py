@@ -87,6 +87,7 @@ def lib() -> ctypes.CDLL:
         "cadnn_avgpool2d": (_i, [_vp, _vp, _i, _i, _i, _i, _i, _i, _i, _i, _vp]),
         "cadnn_global_avgpool": (_i, [_vp, _vp, _i, _i, _i, _i, _i, _vp]),
         "cadnn_dense_conv2d": (_i, [_vp, _vp, _vp] + [_i] * 9 + [_vp, _vp, _i, _i, _vp]),
+        "cadnn_release_workspaces": (_i, []),
         "cadnn_net_create": (_i, [_i, _i, _i, _i, _i, ctypes.POINTER(_vp)]),
         "cadnn_net_add_conv": (_i, [_vp, _vp, _vp, _i, _i, _i, _i, _i, _i]),
         "cadnn_net_add_depthwise": (_i, [_vp, _vp, _vp, _i, _i, _i, _i, _i]),
@@ -377,6 +378,10 @@ def cadnn_dense_conv2d(w_dev, x, stride: int = 1, pad: int = 0, bias=None, resid
                                     stride, pad, _dptr(bias), _dptr(residual), int(bool(relu)), dtype,
                                     _stream_ptr(stream)))
     return out
+
+
+def cadnn_release_workspaces() -> None:
+    _check(lib().cadnn_release_workspaces())
 
 
 class Net:

@@ -112,7 +112,8 @@ __global__ __launch_bounds__(256) void cl_arrange_kernel(const ClArrange a) {
 // them, and handed on with an event that the next user's stream waits for (8.6 us in all).  At most
 // kKeep blocks of at most kKeepBytes together are held; one that no longer fits goes back to the device, in the order
 // of the stream that takes its place.  For larger workspaces every call allocates for itself in stream
-// order.  (No captured stream comes here.)
+// order.  (No captured stream comes here.)  All of it is given back by release(), which the library calls itself when
+// an allocation of its own finds no memory.
 struct Workspace {
     char* p = nullptr;
     size_t bytes = 0;
@@ -126,7 +127,7 @@ class WorkspacePool {
         hipError_t e;
         *out = Workspace{};
         out->bytes = bytes;
-        if (bytes > kKeepBytes / 2) return hipMallocAsync((void**)&out->p, bytes, s);
+        if (bytes > kKeepBytes / 2) return allocate(&out->p, bytes, s);
         int device = 0;
         if ((e = hipGetDevice(&device)) != hipSuccess) return e;
         Workspace found, old;
@@ -156,7 +157,7 @@ class WorkspacePool {
         if (!ev && (e = hipEventCreateWithFlags(&ev, hipEventDisableTiming)) != hipSuccess) return e;
         // (room to grow: sizes that vary a little share a block)
         const size_t round = (bytes + (1u << 20) - 1) >> 20 << 20;
-        if ((e = hipMallocAsync((void**)&out->p, round, s)) != hipSuccess) {
+        if ((e = allocate(&out->p, round, s)) != hipSuccess) {
             (void)hipEventDestroy(ev);
             return e;
         }
@@ -184,7 +185,32 @@ class WorkspacePool {
         return hipFreeAsync(w.p, s);
     }
 
+    // Every kept block, when the call that had it last is through, back to the device.
+    void release() {
+        std::vector<Workspace> all;
+        {
+            std::lock_guard<std::mutex> lock(mu_);
+            all.swap(free_);
+        }
+        for (const Workspace& w : all) {
+            if (hipEventSynchronize(w.used) == hipSuccess) (void)hipFree(w.p);
+            (void)hipEventDestroy(w.used);
+        }
+        (void)hipGetLastError();
+    }
+
   private:
+    hipError_t allocate(char** p, size_t bytes, hipStream_t s) {
+        hipError_t e = hipMallocAsync((void**)p, bytes, s);
+        if (e == hipSuccess) return e;
+        release();
+        e = hipMallocAsync((void**)p, bytes, s);
+        if (e != hipSuccess) {
+            *p = nullptr;
+            (void)hipGetLastError();        // (the launches that take the call's place ask for the last error)
+        }
+        return e;
+    }
     static constexpr size_t kKeep = 8, kKeepBytes = (size_t)128 << 20;
     // (the stream is in an error state: the block is not handed on, nor freed under work that may still run)
     static hipError_t give_up(const Workspace& w, hipError_t e) {
@@ -222,6 +248,8 @@ bool dense_cl_serves(bool f16, int n, int cin, int h, int w, int cout, int kh, i
     const int64_t blocks = (hw + 63) / 64 * n * ((cout + 63) / 64);
     return ((int64_t)cin * kh * kw + 31) / 32 * ((blocks + 1023) / 1024) > 6;
 }
+
+void release_workspaces() { workspaces().release(); }
 
 cadnn_status dense_cl_conv2d(const void* w_dev, const void* x, void* y, const void* residual, int n, int cin, int h, int w,
                              int cout, int kh, int kw, int stride, int pad, const void* bias, int relu, bool f16, hipStream_t s) {

@@ -256,3 +256,8 @@ extern "C" cadnn_status cadnn_dense_conv2d(const void* w_dev, const void* x, voi
     return cadnn::dense_conv2d_impl(w_dev, x, y, n, cin, h, wdt, cout, kh, kw, stride, pad, bias,
                                     residual, relu, dtype, (hipStream_t)stream);
 }
+
+extern "C" cadnn_status cadnn_release_workspaces(void) {
+    cadnn::release_workspaces();
+    return CADNN_OK;
+}

@@ -64,6 +64,9 @@ extern thread_local LaunchTimer* g_launch_timer;
 namespace cadnn {
 
 // ---- device buffer with RAII -------------------------------------------------
+// Gives the kept workspaces of layer calls back to the device (dense_cl.hip).
+void release_workspaces();
+
 struct DevBuf {
     void* p = nullptr;
     size_t bytes = 0;

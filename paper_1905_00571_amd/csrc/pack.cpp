@@ -57,6 +57,10 @@ cadnn_status DevBuf::upload(const void* host, size_t n) {
     }
     hipError_t e = hipMalloc(&p, alloc);
     if (e != hipSuccess) {
+        release_workspaces();
+        e = hipMalloc(&p, alloc);
+    }
+    if (e != hipSuccess) {
         p = nullptr;
         return fail(CADNN_ENOMEM, "hipMalloc(%zu) failed: %s", alloc, hipGetErrorString(e));
     }
@@ -71,6 +75,10 @@ cadnn_status DevBuf::alloc(size_t n, bool zero) {
     release();
     const size_t sz = n < 16 ? 16 : n;
     hipError_t e = hipMalloc(&p, sz);
+    if (e != hipSuccess) {
+        release_workspaces();
+        e = hipMalloc(&p, sz);
+    }
     if (e != hipSuccess) {
         p = nullptr;
         return fail(CADNN_ENOMEM, "hipMalloc(%zu) failed: %s", sz, hipGetErrorString(e));

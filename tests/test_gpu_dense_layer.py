@@ -118,3 +118,30 @@ def test_dense_layer_workspaces_on_two_streams_threads_and_under_capture():
         cad.cadnn_dense_conv2d(layers[1][0], layers[1][1], 1, layers[1][2])
         torch.cuda.synchronize()
         assert bool(((y.double() - eager.double()).abs().cpu() <= bound).all())
+
+
+def test_kept_workspaces_are_given_back():
+    """Some 30 MiB a call stay for later calls; cadnn_release_workspaces returns them, also right behind a call
+    whose kernels still run, and the next call takes a new one."""
+    if not torch.cuda.is_available():
+        pytest.skip("no GPU")
+    import paper_1905_00571_amd as cad
+    x, wt = torch.randn(4, 128, 110, 110).cuda(), torch.randn(64, 128, 3, 3).cuda()
+    want = cad.cadnn_dense_conv2d(wt, x, 1, 1)
+    y = torch.empty_like(want)
+    torch.cuda.synchronize()
+    cad.cadnn_release_workspaces()
+    torch.cuda.synchronize()
+    free = torch.cuda.mem_get_info()[0]
+    for _ in range(3):
+        y.zero_()
+        cad.cadnn_dense_conv2d(wt, x, 1, 1, out=y)
+        cad.cadnn_release_workspaces()
+        torch.cuda.synchronize()
+        assert torch.equal(y, want)
+    cad.cadnn_dense_conv2d(wt, x, 1, 1, out=y)
+    torch.cuda.synchronize()
+    assert torch.cuda.mem_get_info()[0] <= free - (24 << 20)
+    cad.cadnn_release_workspaces()
+    torch.cuda.synchronize()
+    assert torch.cuda.mem_get_info()[0] >= free - (4 << 20)
