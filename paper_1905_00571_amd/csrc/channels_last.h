@@ -86,6 +86,7 @@ cadnn_status launch_cl_conv(const ClConv& c, const ClVariant& v, bool f16, hipSt
 
 // One unpruned layer on [n][c][h][w] tensors from raw weights [cout][cin][kh][kw].
 bool dense_cl_serves(bool f16, int n, int cin, int h, int w, int cout, int kh, int kw, int stride, int pad);
+// (CADNN_ENOMEM, without a text: no workspace was to be had and nothing was launched.)
 cadnn_status dense_cl_conv2d(const void* w_dev, const void* x, void* y, const void* residual, int n, int cin, int h, int w,
                              int cout, int kh, int kw, int stride, int pad, const void* bias, int relu, bool f16, hipStream_t s);
 

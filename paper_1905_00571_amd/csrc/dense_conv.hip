@@ -235,10 +235,12 @@ cadnn_status dense_conv2d_impl(const void* w_dev, const void* x, void* y, int n,
         (void)hipGetLastError();
         capture = hipStreamCaptureStatusActive;
     }
-    if (capture == hipStreamCaptureStatusNone && dense_cl_serves(dtype == CADNN_F16, n, cin, h, wdt, cout, kh, kw, stride, pad))
-        return dense_cl_conv2d(w_dev, x, y, residual, n, cin, h, wdt, cout, kh, kw, stride, pad, bias, relu, dtype == CADNN_F16, s);
+    if (capture == hipStreamCaptureStatusNone && dense_cl_serves(dtype == CADNN_F16, n, cin, h, wdt, cout, kh, kw, stride, pad)) {
+        const cadnn_status st = dense_cl_conv2d(w_dev, x, y, residual, n, cin, h, wdt, cout, kh, kw, stride, pad, bias, relu, dtype == CADNN_F16, s);
+        if (st != CADNN_ENOMEM) return st;
+    }
     // fp16 storage with whole 32-channel steps takes the 128 x 128-tile kernel where that route is not taken (a captured
-    // stream, more than 64 taps, a halo that brings the tensor to 2 GiB)
+    // stream, more than 64 taps, a halo that brings the tensor to 2 GiB, no memory for the workspace)
     if (cin % 32 == 0 && dense_wide_serves(dtype == CADNN_F16, cin, kh * kw, (int64_t)cin * h * wdt * elem * n, yd.image * elem * n,
                           (int64_t)n * hout * wout))
         return dense_wide_conv2d_raw(w_dev, x, make_desc(cin, h, wdt), y, yd, residual, yd, n, cout, kh, kw, stride, pad,

@@ -2,6 +2,8 @@
 around the 64 and 128 of a tile and the 64 bytes of a step, halos, strides, rectangular filters, K
 long enough to be split, too few channels for the channels-last route.  The bound holds for any
 order of fp32 sums of K products: (K + 3) 2^-24 (sum |w| |x| + |b| + |r|), plus one rounding to storage."""
+import ctypes
+
 import numpy as np
 import pytest
 
@@ -145,3 +147,58 @@ def test_kept_workspaces_are_given_back():
     cad.cadnn_release_workspaces()
     torch.cuda.synchronize()
     assert torch.cuda.mem_get_info()[0] >= free - (4 << 20)
+
+
+class _PoolLocation(ctypes.Structure):
+    _fields_ = [("type", ctypes.c_int), ("id", ctypes.c_int)]
+
+
+class _PoolProps(ctypes.Structure):
+    _fields_ = [("alloc_type", ctypes.c_int), ("handle_types", ctypes.c_int), ("location", _PoolLocation),
+                ("security", ctypes.c_void_p), ("max_size", ctypes.c_size_t), ("reserved", ctypes.c_ubyte * 56)]
+
+
+@pytest.mark.parametrize("dtype", ["f32", "f16"])
+def test_without_memory_for_a_workspace(dtype):
+    """A device memory pool that may hold 2 MiB: a layer whose workspace needs more runs on the tensors as they
+    are, and the next one, with memory, on its workspace again."""
+    if not torch.cuda.is_available():
+        pytest.skip("no GPU")
+    import paper_1905_00571_amd as cad
+    tt = torch.float16 if dtype == "f16" else torch.float32
+    gen = torch.Generator().manual_seed(5)
+    x = torch.randn(2, 72, 60, 61, generator=gen).to(tt).cuda()
+    wt = (torch.randn(40, 72, 3, 3, generator=gen) * 0.05).to(tt).cuda()
+    with_room = cad.cadnn_dense_conv2d(wt, x, 1, 1).clone()
+    torch.cuda.synchronize()
+    cad.cadnn_release_workspaces()
+    hip = ctypes.CDLL("libamdhip64.so")
+    hip.hipDeviceSetMemPool.argtypes = [ctypes.c_int, ctypes.c_void_p]
+    hip.hipMemPoolDestroy.argtypes = [ctypes.c_void_p]
+    before, small = ctypes.c_void_p(), ctypes.c_void_p()
+    assert hip.hipDeviceGetMemPool(ctypes.byref(before), 0) == 0
+    props = _PoolProps(alloc_type=1, handle_types=0, location=_PoolLocation(1, 0), security=None, max_size=2 << 20)
+    assert hip.hipMemPoolCreate(ctypes.byref(small), ctypes.byref(props)) == 0
+    assert hip.hipDeviceSetMemPool(0, small) == 0
+    try:
+        p = ctypes.c_void_p()
+        refused = hip.hipMallocAsync(ctypes.byref(p), ctypes.c_size_t(8 << 20), None) != 0
+        hip.hipGetLastError()
+        got = [cad.cadnn_dense_conv2d(wt, x, 1, 1).clone() for _ in range(2)]
+        torch.cuda.synchronize()
+        if not refused:
+            hip.hipFree(p)
+        cad.cadnn_release_workspaces()
+    finally:
+        assert hip.hipDeviceSetMemPool(0, before) == 0
+        hip.hipMemPoolDestroy(small)
+    assert refused, "the pool's limit is not enforced here: nothing was tested"
+    conv = torch.nn.functional.conv2d
+    size = conv(x.double().abs().cpu(), wt.double().abs().cpu(), None, 1, 1)
+    ref = conv(x.double().cpu(), wt.double().cpu(), None, 1, 1)
+    bound = (72 * 9 + 3) * 2.0 ** -24 * size
+    if dtype == "f16":
+        bound = bound + 2.0 ** -11 * ref.abs() + 2.0 ** -25
+    for y in got + [with_room]:
+        assert bool(((y.double().cpu() - ref).abs() <= bound).all())
+    assert torch.equal(cad.cadnn_dense_conv2d(wt, x, 1, 1), with_room)
