@@ -300,7 +300,8 @@ cadnn_status cadnn_net_workspace_bytes(const cadnn_net* net, size_t* bytes);
  * touch neither x nor y, which may be other tensors on every call); CADNN_NET_TUNE -- the first cadnn_run_net call
  * first runs cadnn_conv2d_tune on every convolution with the net's own buffers, the
  * op that produces its input launched before every timed launch so that the caches are
- * as they will be (that first call synchronises and takes a fraction of a second);
+ * as they will be (that first call synchronises and takes a fraction of a second; a net that would run channels-last,
+ * see below, is tuned that way and on plane layouts, and the execution with the faster whole pass stays);
  * CADNN_NET_PLAIN_LAYOUT -- keep every intermediate tensor in plain (haloed) NCHW; by
  * default the output of a convolution that is read by stride-2 convolutions is kept
  * de-interleaved by row/column parity, so those layers read it with unit stride (and a

@@ -732,8 +732,7 @@ GraphRange graph_range(const cadnn_net* net) {
 // Live tuning (CADNN_NET_TUNE, on the first run): every convolution's candidates are timed on
 // the data an ordinary pass leaves in its input region, then every group of co-launched layers
 // as a whole; a group stays only if it beats its layers launched apart.
-cadnn_status tune_net(cadnn_net* net, const void* x, void* y, hipStream_t s) {
-    if (net->cl) return cl_tune(net, x, y, s);
+cadnn_status tune_planes(cadnn_net* net, const void* x, void* y, hipStream_t s) {
     // every layer is timed on the data an ordinary pass leaves in its input region
     cadnn_status st = launch_all(net, x, y, s);
     std::vector<float> alone_us(net->ops.size(), 0.0f);
@@ -1051,6 +1050,13 @@ static cadnn_status plane_variant_serves(const cadnn_net* net, size_t i, const c
     return serves ? CADNN_OK : fail(CADNN_EINVAL, "cadnn_net_set_op_variant: '%s' does not serve op %zu", name, i);
 }
 
+// The workspace, which both executions use in their own way, for the plane layouts.
+static cadnn_status clear_and_prepare_planes(cadnn_net* net) {
+    if (net->ws_bytes) CADNN_HIP(hipMemset(net->ws, 0, net->ws_bytes));
+    CADNN_HIP(hipDeviceSynchronize());
+    return prepare_planes(net);
+}
+
 // The net leaves the channels-last execution for the plane layouts (a variant of theirs is pinned).
 static cadnn_status leave_channels_last(cadnn_net* net) {
     drop_graph(net);
@@ -1061,9 +1067,7 @@ static cadnn_status leave_channels_last(cadnn_net* net) {
         net->ws = net->planes_ws;
         return CADNN_OK;
     }
-    if (net->ws_bytes) CADNN_HIP(hipMemset(net->ws, 0, net->ws_bytes));
-    CADNN_HIP(hipDeviceSynchronize());
-    return prepare_planes(net);
+    return clear_and_prepare_planes(net);
 }
 
 // ... and the way there: a channels-last variant is pinned on a net that the rule left on planes (a saved
@@ -1136,16 +1140,8 @@ extern "C" cadnn_status cadnn_net_finalize(cadnn_net* net, void* ws, size_t byte
     return fail(CADNN_ENOMEM, "cadnn_net_finalize: out of host memory");
 }
 
-extern "C" cadnn_status cadnn_run_net(cadnn_net* net, const void* x, void* y, void* stream) try {
-    if (!net || !x || !y) return fail(CADNN_EINVAL, "cadnn_run_net: NULL pointer");
-    if (!net->finalized) return fail(CADNN_EINVAL, "cadnn_run_net: net not finalized");
-    hipStream_t s = (hipStream_t)stream;
-    if (net->want_tune) {
-        cadnn_status st = tune_net(net, x, y, s);
-        if (st != CADNN_OK) return st;
-        net->want_tune = false;
-        drop_graph(net);
-    }
+// One pass as it will be run from now on.
+static cadnn_status run_pass(cadnn_net* net, const void* x, void* y, hipStream_t s) {
     if (!net->use_graph) return launch_all(net, x, y, s);
     if (!net->ranged) {
         net->range = graph_range(net);
@@ -1183,6 +1179,72 @@ extern "C" cadnn_status cadnn_run_net(cadnn_net* net, const void* x, void* y, vo
     if (st != CADNN_OK) return st;
     CADNN_HIP(hipGraphLaunch(net->exec, s));
     return launch_range(net, range.last, SIZE_MAX, x, y, s);
+}
+
+// Milliseconds of a pass among others.
+static cadnn_status time_pass(cadnn_net* net, const void* x, void* y, hipStream_t s, float* ms) {
+    constexpr int kPasses = 10;
+    hipEvent_t e0 = nullptr, e1 = nullptr;
+    cadnn_status st = CADNN_OK;
+    if (hipEventCreate(&e0) != hipSuccess || hipEventCreate(&e1) != hipSuccess) st = fail(CADNN_EHIP, "hipEventCreate failed");
+    *ms = 0.0f;
+    for (int batch = 0; batch < 4 && st == CADNN_OK; ++batch) {         // (the first one captures and warms up)
+        if (hipEventRecord(e0, s) != hipSuccess) st = fail(CADNN_EHIP, "hipEventRecord failed");
+        for (int k = 0; k < kPasses && st == CADNN_OK; ++k) st = run_pass(net, x, y, s);
+        float t = 0.0f;
+        if (st == CADNN_OK && (hipEventRecord(e1, s) != hipSuccess || hipEventSynchronize(e1) != hipSuccess ||
+                               hipEventElapsedTime(&t, e0, e1) != hipSuccess))
+            st = fail(CADNN_EHIP, "event timing failed");
+        if (batch == 1 || (batch > 1 && t < *ms)) *ms = t;
+    }
+    *ms /= kPasses;
+    if (e0) (void)hipEventDestroy(e0);
+    if (e1) (void)hipEventDestroy(e1);
+    return st;
+}
+
+// A net that the rule (not a pin) took channels-last is tuned in both executions, and the one with the faster whole
+// pass stays: the rule is a model, and asking for tuning asks for measurements instead.
+static cadnn_status tune_net(cadnn_net* net, const void* x, void* y, hipStream_t s) {
+    if (!net->cl) return tune_planes(net, x, y, s);
+    cadnn_status st = cl_tune(net, x, y, s);
+    float cl_ms = 0.0f, planes_ms = 0.0f;
+    if (net->cl_ws.p || st != CADNN_OK) return st;
+    if ((st = time_pass(net, x, y, s, &cl_ms)) != CADNN_OK) return st;
+    drop_graph(net);
+    std::unique_ptr<ClNet> cl;
+    cl.swap(net->cl);
+    try {
+        st = clear_and_prepare_planes(net);
+        if (st == CADNN_OK) st = tune_planes(net, x, y, s);
+    } catch (const std::bad_alloc&) {
+        st = fail(CADNN_ENOMEM, "cadnn_run_net: out of host memory");
+    }
+    drop_graph(net);                                    // (groups of layers may have come apart)
+    if (st == CADNN_OK) st = time_pass(net, x, y, s, &planes_ms);
+    if (std::getenv("CADNN_TUNE_LOG"))
+        std::fprintf(stderr, "[cadnn tune] whole pass: channels-last %.1f us, planes %.1f us\n", cl_ms * 1e3f, planes_ms * 1e3f);
+    if (st == CADNN_OK && planes_ms < cl_ms) return CADNN_OK;
+    // channels-last again (also where the plane layouts cannot run the net, or found no memory)
+    drop_graph(net);
+    CADNN_HIP(hipDeviceSynchronize());
+    net->cl.swap(cl);
+    if (net->ws_bytes) CADNN_HIP(hipMemset(net->ws, 0, net->ws_bytes));
+    CADNN_HIP(hipDeviceSynchronize());
+    return st == CADNN_EHIP ? st : CADNN_OK;
+}
+
+extern "C" cadnn_status cadnn_run_net(cadnn_net* net, const void* x, void* y, void* stream) try {
+    if (!net || !x || !y) return fail(CADNN_EINVAL, "cadnn_run_net: NULL pointer");
+    if (!net->finalized) return fail(CADNN_EINVAL, "cadnn_run_net: net not finalized");
+    hipStream_t s = (hipStream_t)stream;
+    if (net->want_tune) {
+        cadnn_status st = tune_net(net, x, y, s);
+        if (st != CADNN_OK) return st;
+        net->want_tune = false;
+        drop_graph(net);
+    }
+    return run_pass(net, x, y, s);
 } catch (const std::bad_alloc&) {
     return fail(CADNN_ENOMEM, "cadnn_run_net: out of host memory");
 }

@@ -3,6 +3,8 @@ tensors) on small nets chosen for its edges: tiles that are not full, channel co
 whole K steps, first layers of few channels, strides, residuals, fused projections, in-place and copied
 concatenations, flat outputs, every tile and K split.  Buffers and outputs against the oracle with the
 propagated bound of a forward error analysis (util.chain_bounds)."""
+import re
+
 import numpy as np
 import pytest
 
@@ -146,6 +148,34 @@ def test_channels_last_tuned(cad):
         # 1e-2: the stated bar of whole nets in fp16 storage
         assert np.abs(got - ref).max() <= 1e-2 * np.abs(ref).max()
     assert all(n.startswith("cl_") or n == "fused" for n, o in zip(net.variants(), ops) if o.kind == "conv")
+    net.free()
+
+
+@pytest.mark.parametrize("family,shape", [("mobilenet_v1", (16, 3, 128, 129)), ("vgg16", (2, 3, 96, 112))])
+def test_tuning_times_both_executions(cad, family, shape, capfd, monkeypatch):
+    """A net that the rule takes channels-last is tuned on plane layouts too, and what stays is the execution whose
+    whole pass was the faster one; either computes the net, run after run, with what tuning left in the workspace."""
+    ops = wl.mobilenet_v1_ops() if family == "mobilenet_v1" else wl.vgg16_ops()[:-3]
+    if family == "vgg16":
+        ops.append(Op("avgpool", "gap", ops[-1].dst, 9))
+    x, ws, bs = wl.net_tensors(ops, "both", shape)
+    xs = x.astype(np.float16)
+    ref, _, _ = oracle.run_net(ops, xs, ws, bs, dtype=np.float16)
+    monkeypatch.setenv("CADNN_TUNE_LOG", "1")
+    plain = cad.build_net(ops, ws, bs, shape, cad.F16, use_graph=True)
+    first = next(i for i, o in enumerate(ops) if o.kind == "conv")
+    by_rule = plain.op_variant(first).startswith("cl_")
+    plain.free()
+    assert by_rule
+    net = cad.build_net(ops, ws, bs, shape, cad.F16, use_graph=True, tune=True)
+    for _ in range(3):
+        y = net.run(torch.from_numpy(xs).cuda())
+        torch.cuda.synchronize()
+        assert np.abs(y.float().cpu().numpy() - ref).max() <= 1e-2 * np.abs(ref).max()      # (whole nets in fp16 storage)
+    log = capfd.readouterr().err
+    assert "[cadnn tune] cl " in log and "[cadnn tune] cin=" in log
+    m = re.search(r"whole pass: channels-last ([\d.]+) us, planes ([\d.]+) us", log)
+    assert net.op_variant(first).startswith("cl_") == (float(m[1]) <= float(m[2]))
     net.free()
 
 
