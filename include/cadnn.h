@@ -328,10 +328,13 @@ cadnn_status cadnn_net_workspace_bytes(const cadnn_net* net, size_t* bytes);
  *     launched apart.
  *   - a window pool that rides on no launch moves up in the launch order to where its input
  *     completes (launched_after).
- * A net with enough work (a model of its launches and multiply-adds decides, unless a variant is pinned) runs with
+ * A net with enough work (a model of its launches and multiply-adds decides) runs with
  * channels-last tensors on the matrix cores instead, over zero-filled weights: there a pruned weight meets its
  * activation, so an infinity or NaN that arises in a map reaches every output channel of its windows, not only those
- * with a nonzero weight on it.  Pinning a convolution to a variant of the other kind changes the whole net over. */
+ * with a nonzero weight on it.  Pinning a convolution to a variant of the other kind (cadnn_net_set_op_variant) changes
+ * the whole net over: a net that is to keep pruned weights away from such values has one of its convolutions pinned
+ * to a variant of the compressed kernels.  Variants pinned on a weight handle (cadnn_conv2d_set_variant,
+ * cadnn_conv2d_tune) are those of plane layouts; a net that runs channels-last does not look at them. */
 #define CADNN_NET_GRAPH 1
 #define CADNN_NET_TUNE 2
 #define CADNN_NET_PLAIN_LAYOUT 4

@@ -77,7 +77,7 @@ struct CoLaunch {
 // net uses one or the other as a whole.
 struct ClOp {
     ClDesc xd, yd, rd;                       // input (an import of the caller's x included), output, residual
-    size_t x_off = 0, y_off = 0, r_off = 0;  // byte offsets in the workspace (y_off of a flat last op: the caller's y)
+    size_t x_off = 0, y_off = 0;             // byte offsets in the workspace (y_off of a flat last op: the caller's y)
     bool x_stem = false;                     // the input is the op's own packed copy of the caller's x, at x_off
     bool flat = false;                       // the output is [n][c][h][w] without padding (read by an FC layer, or y itself)
     int slice_of = -1;                       // writes its channels into that concatenation's region
