@@ -221,27 +221,129 @@ static std::vector<const ConvVariant*> candidates(const cadnn_weights* w, const 
     return out;
 }
 
-// Default choice when nothing was tuned or pinned: a model of one launch in microseconds.  Every
-// family's time is a sum of non-negative multiples of the same few quantities of a launch:
-//   1, the rounds of workgroups a CU runs one after the other, and per round the channel chunks staged, the nonzeros a
-//   wave walks and the LDS words it stages (a wave's own latency); the waves of the launch per SIMD, times the
-//   nonzeros, times the words (what all waves together issue); the levels of a split row's reduction.
-// The staging-free families have cache lines read in place of the words, the matrix-core kernels K steps.
-// The multiples are fitted per family and pixels per lane (non-negative least squares on relative errors)
-// to the tuner's times of every variant on 230 layers of 16 to 512 channels, 1x1 to 7x7, both storage types, batch 1
-// to 16, and on the layers of VGG-16, Inception-V3 and ResNet-50 in fp32 at batch 1 to 3.  Its pick takes 1.12 times
-// (nets: 1.08 times) the best variant's time in the geometric mean; a model of the staging-free families
-// alone, with the staged ones as a last resort, took 1.61 times on the single layers.
-struct VariantCost { int family, p, kind, f16; float c[9]; };
+// Default choice when nothing was tuned or pinned: a model of one launch in microseconds, over a few quantities of it:
+//   fixed: 1, and the levels of a split row's reduction;
+//   a wave's own latency: the rounds of workgroups a CU runs one after the other, and per round the channel chunks staged,
+//   the nonzeros a wave walks and the LDS words it stages;
+//   what all waves together issue: the waves of the launch per SIMD, times the nonzeros, times the words.
+// The staging-free families have cache lines read in place of the words; the matrix-core kernels K steps as their latency
+// and blocks, and blocks times steps, as what is issued (steps once more where the input channels are not whole ones).
+// A layer on plain or haloed tensors: the fixed terms plus the cube root of the sum of the cubes of the other
+// two (a launch is bound by the longer of the two, and near the crossing by both), with constants per variant,
+// fitted to the tuner's times on 8557 layers of 16 to 512 channels, 1x1 to 7x7, both storage types, batch 1 to 16, and on
+// the layers of VGG-16, Inception-V3 and ResNet-50.  100 of the 446 variants are modelled: no more of them are worth
+// having (all of them: 1.042 times the best variant's time on layers that were not fitted, in the geometric mean;
+// these: 1.043; with one set of constants per family and pixels per lane, fitted to 230 layers: 1.10, and 5 % of
+// the layers more than a fifth slower than with the choice before that, which knew the staging-free families
+// alone and took 1.66 times the best on average.  0.4 % are now).
+struct VariantCost { const char* name; float c[9]; };
 constexpr VariantCost kVariantCosts[] = {
-    {FAM_DENSE, 1, 0, 0, {4.1f, 3.92f, 1.81f, 0.357f, 0.0f, 0.0f, 0.0f, 0.0f, 0.0f}},
-    {FAM_DENSE, 1, 0, 1, {8.76f, 0.398f, 1.88f, 0.0f, 0.0f, 0.0f, 0.0f, 0.0f, 0.0f}},
-    {FAM_DIRECT, 1, 0, 0, {9.23f, 0.0f, 0.0f, 0.0486f, 0.156f, 0.0f, 0.0319f, 0.0f, 0.0f}},
-    {FAM_DIRECT, 1, 0, 1, {10.3f, 0.0f, 0.0f, 0.0414f, 0.132f, 0.0f, 0.0964f, 0.0f, 0.0f}},
-    {FAM_DIRECT, 2, 0, 0, {11.3f, 0.0f, 0.0f, 0.0691f, 0.375f, 0.0f, 0.115f, 0.0f, 0.0f}},
-    {FAM_DIRECT, 2, 0, 1, {12.0f, 0.0f, 0.0f, 0.0643f, 0.0f, 0.0f, 0.165f, 0.0f, 0.0f}},
-    {FAM_DIRECT, 4, 0, 0, {11.3f, 3.36f, 0.0f, 0.0805f, 0.0f, 0.0f, 0.268f, 0.0f, 0.0f}},
-    {FAM_DIRECT, 4, 0, 1, {16.6f, 0.0f, 0.0f, 0.0755f, 0.0f, 0.0f, 0.333f, 0.0f, 0.0f}},
+    {"dense_mfma__Float16_128x64x32_h1", {11.1f, 1.37f, 0.59f, 0.118f, 0.392f, 0.0668f, 0, 0, 0}},
+    {"dense_mfma__Float16_64x128x32_h1", {11.8f, 0.369f, 0.594f, 0.147f, 0, 0, 0, 0, 0}},
+    {"dense_mfma__Float16_64x64x32", {8.56f, 0.78f, 1.87f, 0.687f, 0.166f, 0, 0, 0, 0}},
+    {"dense_mfma__Float16_64x64x32w", {10.2f, 1.11f, 0.457f, 0.195f, 0.456f, 0.154f, 0, 0, 0}},
+    {"dense_mfma__Float16_64x64x32w_h1", {9.43f, 1.06f, 0.514f, 0.188f, 0.415f, 0.138f, 0, 0, 0}},
+    {"dense_mfma_float_64x64x32", {8.27f, 0.994f, 1.88f, 1.2f, 0, 0, 0, 0, 0}},
+    {"sconv__Float16_k7x7s1_t32p2_w4r4c4", {13.2f, 0, 0, 0.0453f, 0.278f, 0, 0, 0, 0}},
+    {"sconv_float_k7x7s1_t32p2_w4r4c4", {11.7f, 0, 0, 0.0464f, 0.278f, 0, 0, 0, 0}},
+    {"sdirect__Float16_k3x3_p1_r1k1w4", {8.9f, 0, 0.102f, 0, 0.167f, 0, 0.372f, 0, 0}},
+    {"sdirect__Float16_k3x3_p1_r1k4w4", {8.13f, 0, 0, 0.0471f, 0.298f, 0, 0.396f, 0.0226f, 0}},
+    {"sdirect__Float16_k3x3_p1_r1k8w8", {7.97f, 0, 0, 0.0303f, 0.32f, 0, 0.44f, 0.00968f, 0}},
+    {"sdirect_float_k3x3_p1_r1k1w4", {9.05f, 0, 0, 0.0541f, 0.0917f, 0, 0.429f, 0, 0}},
+    {"sdirect_float_k3x3_p1_r1k4w4", {8.25f, 0, 0, 0.0493f, 0.276f, 0, 0.463f, 0.0135f, 0}},
+    {"sdirect_float_k3x3_p1_r1k8w8", {0.0408f, 0, 0.0565f, 0.00055f, 0.303f, 0, 0.516f, 2.74f, 0}},
+    {"slinear__Float16_a2_r1k1w4u8", {5.91f, 0.0138f, 0.00137f, 0.0262f, 0.166f, 0, 0.202f, 0, 0}},
+    {"slinear__Float16_a2_r1k2w4u8", {3.36f, 0.15f, 0.0132f, 0.0202f, 0.173f, 0.00208f, 0.141f, 2.38f, 0}},
+    {"slinear__Float16_a2_r1k8w8u4", {0, 0.123f, 0, 0.0302f, 0.184f, 0.00118f, 0.0684f, 1.85f, 0}},
+    {"slinear__Float16_p1_r1k2w4u8", {5.64f, 0.443f, 0, 0.0175f, 0.0113f, 0, 0.519f, 0, 0}},
+    {"slinear__Float16_p1_r1k4w4u8", {5.68f, 0.427f, 0, 0, 0.0544f, 0, 0.521f, 0, 0}},
+    {"slinear__Float16_p1_r1k8w8u4", {5.68f, 0.271f, 0, 0, 0.0602f, 0, 0.511f, 0, 0}},
+    {"slinear__Float16_p2_r1k1w4u4", {6.01f, 0, 0.087f, 0, 0.116f, 0, 0.438f, 0, 0}},
+    {"slinear__Float16_p2_r1k4w4u4", {0.379f, 0, 0.0905f, 0, 0.137f, 0, 0.385f, 2.76f, 0}},
+    {"slinear__Float16_p2_r2k1w4u4", {6.34f, 0, 0.0837f, 0.0047f, 0.173f, 0, 0.466f, 0, 0}},
+    {"slinear__Float16_p4_r4k1w4u2", {8.79f, 0, 0.12f, 0, 0.318f, 0, 0.522f, 0, 0}},
+    {"slinear_float_a4_r1k2w4u4", {0.507f, 0.326f, 0.0726f, 0.00289f, 0.275f, 0.0353f, 0, 5.49f, 0}},
+    {"slinear_float_d1_r1k1w4u8", {4.86f, 0.181f, 0, 0.0306f, 0.256f, 0.0044f, 0.413f, 0, 0}},
+    {"slinear_float_d1_r1k4w4u8", {0.269f, 0.327f, 0.0102f, 0.0421f, 0.214f, 0.00615f, 0.21f, 2.02f, 0}},
+    {"slinear_float_g4_r1k1w4u4", {6.33f, 0.156f, 0.000232f, 0.0413f, 0.366f, 0.0386f, 0, 0, 0}},
+    {"slinear_float_g4_r1k2w4u4", {0.204f, 0.248f, 0.0726f, 0.000373f, 0.252f, 0.0367f, 0, 5.87f, 0}},
+    {"slinear_float_g4_r1k4w4u8", {4.15f, 0.292f, 0.0774f, 0, 0.315f, 0.0319f, 0, 0.901f, 0}},
+    {"slinear_float_p1_r1k16w16u4", {0.0386f, 0.429f, 0, 0, 0.12f, 0, 0.497f, 1.36f, 0}},
+    {"slinear_float_p1_r1k1w4u4", {5.97f, 0, 0, 0.0364f, 0.105f, 0, 0.415f, 0, 0}},
+    {"slinear_float_p1_r1k1w4u8", {5.92f, 0, 0, 0.0248f, 0.108f, 0, 0.475f, 0, 0}},
+    {"slinear_float_p1_r1k4w4u8", {4.52f, 0.433f, 0, 0, 0.051f, 0, 0.558f, 0.595f, 0}},
+    {"slinear_float_p2_r1k1w4u4", {6.13f, 0, 0.000437f, 0.0436f, 0.116f, 0, 0.471f, 0, 0}},
+    {"slinear_float_p4_r4k1w4u2", {8.23f, 0, 0, 0.0851f, 0.343f, 0, 0.546f, 0, 0}},
+    {"sptile__Float16_p1_r1k16w16u4", {0, 2.76f, 0, 0.0526f, 0.224f, 0.663f, 0.00326f, 0.0208f, 1.49f}},
+    {"sptile__Float16_p1_r1k2w16u4", {0.149f, 2.19f, 0, 0.0528f, 0.265f, 0.917f, 0.00433f, 0.0299f, 6.05f}},
+    {"sptile__Float16_p1_r1k4w16u4", {0.218f, 2.65f, 0, 0.0534f, 0.245f, 0.798f, 0.00341f, 0.0217f, 2.76f}},
+    {"sptile__Float16_p1_r1k8w16u4", {0.265f, 2.83f, 0, 0.054f, 0.229f, 0.731f, 0.00207f, 0.0222f, 1.81f}},
+    {"sptile__Float16_p2_r1k1w16u4", {8.88f, 0.522f, 0, 0.0605f, 0.326f, 1.18f, 0.00449f, 0.0402f, 0}},
+    {"sptile__Float16_p2_r1k2w16u4", {7.11f, 2.6f, 0, 0.0611f, 0.286f, 1.14f, 0.00641f, 0.0242f, 0.0517f}},
+    {"sptile__Float16_p2_r1k4w16u4", {0, 2.74f, 0.266f, 0.0602f, 0.258f, 1.08f, 0.00662f, 0.0147f, 3.36f}},
+    {"sptile__Float16_p2_r1k8w16u4", {0.213f, 2.59f, 0.75f, 0.0579f, 0.235f, 1.01f, 0.00975f, 0, 2.07f}},
+    {"sptile__Float16_v2_r4k1w16u4", {10.9f, 0, 0, 0.0518f, 0.35f, 1.44f, 0.00497f, 0.0896f, 0}},
+    {"sptile_float_p1_r1k1w16u4", {8.55f, 0, 0, 0.0487f, 0.154f, 0.723f, 0.00219f, 0.00281f, 0}},
+    {"sptile_float_p1_r1k2w16u4", {0, 1.99f, 0.474f, 0.0523f, 0.103f, 0.733f, 0.00445f, 0.0239f, 6.02f}},
+    {"sptile_float_p1_r1k4w16u4", {5.61f, 2.41f, 0.476f, 0.0528f, 0.0939f, 0.591f, 0.00386f, 0.026f, 0}},
+    {"sptile_float_p1_r1k8w16u4", {5.58f, 2.39f, 0.502f, 0.0528f, 0.0962f, 0.494f, 0.00318f, 0.0242f, 0.00893f}},
+    {"sptile_float_p1_r1k8w8u4", {6.48f, 1.72f, 0, 0.032f, 0.0685f, 0.501f, 0.00808f, 0.0182f, 0.0108f}},
+    {"sptile_float_p2_r1k16w16u4", {7.19f, 1.52f, 0.621f, 0.0469f, 0.0954f, 0, 0.013f, 0.0261f, 0.00486f}},
+    {"sptile_float_p2_r1k1w16u4", {9.4f, 0, 0, 0.0604f, 0.158f, 0.7f, 0.0033f, 0.021f, 0}},
+    {"sptile_float_p2_r1k2w16u4", {8.89f, 0, 0.218f, 0.0609f, 0.128f, 0.649f, 0.00341f, 0.028f, 0.0417f}},
+    {"sptile_float_p2_r1k4w16u4", {8.04f, 0.563f, 0.281f, 0.0619f, 0.12f, 0.651f, 0, 0.0211f, 0}},
+    {"sptile_float_p2_r1k8w16u4", {7.31f, 1.32f, 0.698f, 0.0527f, 0.0925f, 0, 0.0105f, 0.0278f, 0.0148f}},
+    {"sptile_float_v2_r1k1w16u4", {9.01f, 0, 0.124f, 0.0578f, 0.13f, 0.688f, 0.00317f, 0.0342f, 0}},
+    {"sptile_float_v2_r2k1w16u4", {9.86f, 0, 0, 0.0562f, 0.152f, 1.1f, 0.00276f, 0.0466f, 0}},
+    {"sptile_float_v2_r4k1w16u4", {10.3f, 0, 0, 0.0499f, 0.216f, 1.08f, 0.00576f, 0.0675f, 0}},
+    {"sptile_float_v4_r1k2w16u4", {2.06f, 3.45f, 0.548f, 0.0909f, 0.0503f, 1.19f, 0.00891f, 0.012f, 4.32f}},
+    {"sptile_float_v4_r1k4w16u4", {0.31f, 3.97f, 0.621f, 0.0907f, 0.0455f, 0.995f, 0.00901f, 0.0112f, 2.73f}},
+    {"squad__Float16_r2k8g1b16", {0.0258f, 0, 0, 0, 0, 0.0145f, 0.00759f, 2.28f, 0}},
+    {"squad_float_r4k2g2b8", {2.41f, 4.22f, 0.148f, 0, 1.22f, 0.0264f, 0.214f, 0.144f, 0}},
+    {"stile__Float16_k3x3s1_t16p4_w8g2c8f0", {6.4f, 0.405f, 1.33f, 0.0593f, 0.000166f, 1.25f, 0.0312f, 0.0176f, 0.0117f}},
+    {"stile__Float16_k3x3s1_t32p4_w8g8c8f1", {0.0651f, 1.28f, 0, 0.04f, 0.0427f, 2.18f, 0.0233f, 0.019f, 2.71f}},
+    {"stile__Float16_k3x3s1_t8p1_w16g16c4f1", {6.44f, 1.84f, 2.37f, 0.0289f, 0.0018f, 1.01f, 0.00508f, 0, 0}},
+    {"stile__Float16_k3x3s2_t32p2_w8g8c4f1", {1.16f, 0, 0, 0.0287f, 0.0622f, 1.34f, 0.015f, 0.0326f, 2.0f}},
+    {"stile__Float16_k7x7s2_t32p4_w4g4c1f1", {9.68f, 0, 0.955f, 0.0318f, 0.00509f, 0.384f, 0.0187f, 0.021f, 0}},
+    {"stile_float_k1x1s2_t32p2_w8g8c16f1", {2.27f, 0.512f, 0.121f, 0.0315f, 0.0132f, 0.293f, 0.0128f, 0.00567f, 1.15f}},
+    {"stile_float_k3x3s1_t16p4_w8g1c8f0", {4.87f, 0, 1.43f, 0.0401f, 0.00435f, 1.05f, 0.0229f, 0.0213f, 0.335f}},
+    {"stile_float_k3x3s1_t16p4_w8g2c8f0", {0.0707f, 0.596f, 1.16f, 0.055f, 0, 1.38f, 0.028f, 0.017f, 2.04f}},
+    {"stile_float_k3x3s1_t8p1_w16g16c4f1", {0.722f, 1.93f, 0, 0.0289f, 0.327f, 1.03f, 0.00507f, 0, 1.3f}},
+    {"stile_float_k3x3s1_t8p1_w8g4c16f0", {5.43f, 0.696f, 0, 0.0259f, 0.0396f, 1.34f, 0.014f, 0.0231f, 0.338f}},
+    {"stile_float_k3x3s2_t32p2_w8g8c4f1", {0, 1.37f, 1.57f, 0.0255f, 0.00836f, 1.48f, 0.0146f, 0.0284f, 1.95f}},
+    {"stile_float_k3x3s2_t8p1_w8g2c8f0", {5.63f, 0, 0, 0.0156f, 0.0559f, 0.621f, 0.012f, 0.033f, 0.00911f}},
+    {"stile_float_k7x7s2_t32p4_w4g4c1f1", {1.23f, 0, 0.00818f, 0.0313f, 0.0457f, 0.991f, 0.0154f, 0.0208f, 4.18f}},
+    {"swide__Float16_f4_r1w16", {6.86f, 1.12f, 0.852f, 0.0509f, 0.0941f, 0.325f, 0.00169f, 0.0336f, 0}},
+    {"swide__Float16_f4_r2w16", {7.2f, 1.4f, 1.44f, 0.0487f, 0.087f, 1.28f, 0.00311f, 0.025f, 0}},
+    {"swide__Float16_f4_r4w16", {8.46f, 0.571f, 2.48f, 0.0387f, 0.0713f, 1.65f, 0.00857f, 0.0331f, 0}},
+    {"swide__Float16_g4_r1w16l16", {7.09f, 0, 0.389f, 0.0616f, 0.124f, 0.812f, 0.00457f, 0.0314f, 0}},
+    {"swide__Float16_g4_r1w16l4", {6.62f, 0, 0.455f, 0.0494f, 0.129f, 0.735f, 0.00504f, 0.0271f, 0}},
+    {"swide__Float16_g4_r1w16l8", {7.17f, 0, 0.209f, 0.0618f, 0.14f, 0.83f, 0.00249f, 0.0274f, 0}},
+    {"swide__Float16_g4_r1w8l16", {6.85f, 0, 1.15f, 0.0355f, 0.0594f, 0.38f, 0.0111f, 0.0347f, 0}},
+    {"swide__Float16_g4_r1w8l4", {6.64f, 0, 1.11f, 0.033f, 0.064f, 0.253f, 0.00978f, 0.0335f, 0}},
+    {"swide__Float16_g4_r2w16l16", {7.73f, 0, 0.842f, 0.0584f, 0.12f, 1.09f, 0.00676f, 0.0428f, 0}},
+    {"swide__Float16_g4_r2w16l4", {7.29f, 0, 0.869f, 0.0461f, 0.125f, 0.774f, 0.00796f, 0.0337f, 0}},
+    {"swide__Float16_g4_r2w16l8", {8.01f, 0, 0.232f, 0.0585f, 0.14f, 0.91f, 0.00564f, 0.0429f, 0}},
+    {"swide__Float16_g4_r4w16l4", {8.53f, 0, 1.01f, 0.0342f, 0.157f, 0.94f, 0.0126f, 0.0355f, 0}},
+    {"swide_float_f4_r2w16", {6.78f, 1.54f, 1.54f, 0.0437f, 0.0665f, 1.1f, 0.0019f, 0.0421f, 0}},
+    {"swide_float_f4_r8w8", {11.0f, 0, 2.48f, 0.0316f, 0.0529f, 3.12f, 0.0104f, 0.0522f, 0}},
+    {"swide_float_g4_r1w16l16", {7.01f, 0, 0, 0.0618f, 0.117f, 0.765f, 0.00462f, 0.0313f, 0}},
+    {"swide_float_g4_r1w16l4", {6.23f, 0, 0.331f, 0.05f, 0.109f, 0.589f, 0.00392f, 0.0288f, 0}},
+    {"swide_float_g4_r1w16l8", {6.9f, 0, 0, 0.0611f, 0.124f, 0.703f, 0.00317f, 0.0284f, 0}},
+    {"swide_float_g4_r1w8l16", {6.48f, 0, 1.14f, 0.0367f, 0.0314f, 0.361f, 0.00973f, 0.0328f, 0}},
+    {"swide_float_g4_r1w8l4", {6.35f, 0, 1.21f, 0.0333f, 0.0322f, 0.184f, 0.00921f, 0.0294f, 0}},
+    {"swide_float_g4_r1w8l8", {6.64f, 0, 0.96f, 0.0366f, 0.0464f, 0.264f, 0.0102f, 0.0306f, 0}},
+    {"swide_float_g4_r2w16l16", {7.6f, 0, 0.21f, 0.0575f, 0.128f, 1.09f, 0.00761f, 0.0364f, 0}},
+    {"swide_float_g4_r2w16l4", {6.86f, 0, 0.636f, 0.0451f, 0.116f, 0.576f, 0.00704f, 0.0371f, 0}},
+    {"swide_float_g4_r2w16l8", {7.6f, 0, 0, 0.057f, 0.134f, 0.759f, 0.00716f, 0.0397f, 0}},
+    {"swide_float_g4_r4w16l4", {7.66f, 0, 0.666f, 0.0347f, 0.184f, 0.809f, 0.0117f, 0.034f, 0}},
+    {"swide_float_g4_r4w16l8", {7.79f, 0, 1.14f, 0.045f, 0.16f, 1.19f, 0.0135f, 0.0266f, 0}},
+};
+
+// Layers with something fused into them, or around de-interleaved tensors: the sum of all terms, with constants per
+// family and pixels per lane (fitted to 230 layers, and on the nets' layers 1.08 times the best).
+struct FamilyCost { int family, p, kind, f16; float c[9]; };
+constexpr FamilyCost kFamilyCosts[] = {
     {FAM_DENSE, 1, 1, 1, {11.8f, 0.846f, 0.474f, 0.0656f, 0.0f, 0.0f, 0.0f, 0.0f, 0.0f}},
     {FAM_LINEAR, 1, 0, 0, {5.93f, 0.0f, 0.0156f, 0.0183f, 0.117f, 0.0f, 0.222f, 0.0173f, 0.0f}},
     {FAM_LINEAR, 1, 0, 1, {5.76f, 0.0f, 0.0f, 0.0343f, 0.143f, 0.0f, 0.03f, 0.0f, 0.0f}},
@@ -253,32 +355,8 @@ constexpr VariantCost kVariantCosts[] = {
     {FAM_LINEAR, 4, 0, 1, {6.71f, 0.18f, 0.127f, 0.0f, 0.733f, 0.0f, 0.272f, 0.0f, 0.0f}},
     {FAM_LINEAR, 4, 1, 0, {6.22f, 0.0f, 0.0159f, 0.0245f, 0.26f, 0.0188f, 0.0f, 0.0f, 0.0f}},
     {FAM_LINEAR, 4, 1, 1, {6.08f, 0.0f, 0.0f, 0.0844f, 0.191f, 0.0143f, 0.0f, 0.0708f, 0.0f}},
-    {FAM_PTILE, 1, 0, 0, {6.99f, 1.28f, 1.19f, 0.0412f, 0.0f, 0.111f, 0.00049f, 0.0236f, 0.0464f}},
-    {FAM_PTILE, 1, 1, 0, {7.03f, 1.55f, 0.472f, 0.0452f, 0.127f, 0.107f, 0.0f, 0.0f, 0.0f}},
-    {FAM_PTILE, 1, 0, 1, {6.6f, 3.17f, 0.0f, 0.0419f, 0.128f, 0.0f, 0.00136f, 0.0267f, 0.0f}},
-    {FAM_PTILE, 1, 1, 1, {6.78f, 0.857f, 1.4f, 0.0476f, 0.263f, 0.105f, 0.0f, 0.0f, 0.277f}},
-    {FAM_PTILE, 2, 0, 0, {8.59f, 0.901f, 0.894f, 0.0436f, 0.0986f, 0.0f, 0.00271f, 0.0f, 0.0f}},
-    {FAM_PTILE, 2, 1, 0, {7.97f, 0.953f, 0.73f, 0.0547f, 0.09f, 0.0625f, 0.0f, 0.0f, 0.0f}},
-    {FAM_PTILE, 2, 0, 1, {7.21f, 2.21f, 1.85f, 0.0428f, 0.223f, 0.0f, 0.00453f, 0.0f, 0.0f}},
-    {FAM_PTILE, 2, 1, 1, {8.27f, 1.97f, 0.0381f, 0.052f, 0.25f, 0.32f, 0.00166f, 0.0f, 0.0f}},
-    {FAM_PTILE, 4, 0, 0, {8.72f, 3.53f, 1.18f, 0.0832f, 0.0286f, 0.0f, 0.0246f, 0.0f, 0.0f}},
-    {FAM_PTILE, 4, 1, 0, {7.89f, 1.67f, 1.63f, 0.0567f, 0.0f, 0.556f, 0.00774f, 0.0f, 0.0f}},
-    {FAM_PTILE, 4, 0, 1, {9.59f, 1.48f, 3.89f, 0.0743f, 0.147f, 0.0f, 0.0322f, 0.0f, 0.0f}},
-    {FAM_PTILE, 4, 1, 1, {8.39f, 0.0f, 5.39f, 0.0577f, 0.109f, 0.0f, 0.0108f, 0.00608f, 0.0f}},
     {FAM_LINEAR, 2, 2, 0, {5.85f, 0.517f, 0.0f, 0.0218f, 0.541f, 0.0217f, 0.0f, 0.0f, 0.0f}},
     {FAM_LINEAR, 4, 2, 0, {5.54f, 0.7f, 0.0f, 0.0354f, 0.286f, 0.0163f, 0.0287f, 0.342f, 0.0f}},
-    {FAM_STILE, 1, 0, 0, {5.97f, 0.729f, 1.06f, 0.0268f, 0.0f, 0.565f, 0.00592f, 0.0189f, 0.0f}},
-    {FAM_STILE, 1, 0, 1, {6.38f, 1.3f, 1.17f, 0.0268f, 0.0f, 0.198f, 0.00616f, 0.0277f, 0.0f}},
-    {FAM_STILE, 2, 0, 0, {0.0f, 0.628f, 1.32f, 0.0206f, 0.0f, 0.461f, 0.0148f, 0.0f, 1.88f}},
-    {FAM_STILE, 2, 0, 1, {0.0f, 0.0222f, 2.21f, 0.0113f, 0.0f, 0.318f, 0.0176f, 0.0f, 2.04f}},
-    {FAM_STILE, 4, 0, 0, {0.0f, 1.66f, 0.71f, 0.0455f, 5.68e-05f, 0.996f, 0.0167f, 0.0107f, 1.97f}},
-    {FAM_STILE, 4, 0, 1, {0.0f, 0.786f, 1.35f, 0.0364f, 0.0f, 1.07f, 0.0177f, 0.00839f, 2.42f}},
-    {FAM_TILE, 1, 0, 0, {5.5f, 2.13f, 1.4f, 0.0491f, 0.0128f, 2.14f, 0.0f, 0.031f, 0.0f}},
-    {FAM_TILE, 1, 0, 1, {11.4f, 0.0f, 0.0f, 0.0537f, 0.0253f, 1.96f, 0.0f, 0.128f, 0.0f}},
-    {FAM_TILE, 2, 0, 0, {5.33f, 3.03f, 1.41f, 0.0698f, 0.00986f, 2.56f, 0.0f, 0.00169f, 0.0f}},
-    {FAM_TILE, 2, 0, 1, {16.5f, 0.0f, 0.0f, 0.0566f, 0.041f, 0.0f, 0.00895f, 0.0299f, 0.0f}},
-    {FAM_TILE, 4, 0, 0, {8.05f, 0.0f, 4.19f, 0.0555f, 0.00753f, 3.71f, 0.0105f, 0.00554f, 0.0f}},
-    {FAM_TILE, 4, 0, 1, {0.0f, 10.0f, 1.25f, 0.0496f, 0.234f, 3.36f, 0.0203f, 0.01f, 0.0f}},
     {FAM_WTILE, 4, 16, 0, {8.59f, 0.0f, 1.18f, 0.0245f, 0.0662f, 0.526f, 0.00741f, 0.0f, 0.0f}},
     {FAM_WTILE, 4, 4, 0, {8.32f, 0.0f, 1.22f, 0.0204f, 0.0805f, 0.293f, 0.00506f, 0.0f, 0.0f}},
     {FAM_WTILE, 4, 64, 0, {7.92f, 0.307f, 0.717f, 0.0456f, 0.0614f, 0.592f, 0.0f, 0.0f, 0.0f}},
@@ -289,6 +367,21 @@ constexpr VariantCost kVariantCosts[] = {
     {FAM_WTILE, 4, 8, 1, {9.29f, 0.267f, 1.57f, 0.0164f, 0.0964f, 0.0f, 0.00959f, 0.0f, 0.0f}},
 };
 
+static const VariantCost* modelled_alone(const ConvVariant* v) {
+    static const std::map<const ConvVariant*, const VariantCost*> rows = [] {
+        std::map<const ConvVariant*, const VariantCost*> m;
+        for (const std::vector<ConvVariant>* all : {&all_linear_variants(), &all_quad_variants(), &all_direct_variants(), &all_tile_variants(),
+                                                    &all_dense_variants(), &all_dense_wide_variants(), &all_stile_variants(),
+                                                    &all_ptile_variants(), &all_wtile_variants()})
+            for (const ConvVariant& u : *all)
+                for (const VariantCost& c : kVariantCosts)
+                    if (std::strcmp(u.name, c.name) == 0) m[&u] = &c;
+        return m;
+    }();
+    auto it = rows.find(v);
+    return it == rows.end() ? nullptr : it->second;
+}
+
 static double variant_cost(const cadnn_weights* w, const ConvGeom& g, const ConvVariant* v) {
     auto up = [](int64_t a, int64_t b) { return (a + b - 1) / b; };
     const int taps = w->kh * w->kw, S = g.stride;
@@ -296,11 +389,15 @@ static double variant_cost(const cadnn_weights* w, const ConvGeom& g, const Conv
     // for a pruned layer (whose zeros would meet every activation), and for K split over workgroups, the measured
     // selection decides on the matrix cores
     if (dense && ((double)w->nnz < 0.25 * (double)w->cout * w->cin * taps || v->splitk > 1)) return -1.0;
-    const int kind = dense ? v->tw == 128 : v->family == FAM_PTILE ? v->tw == 16 : v->family == FAM_WTILE ? v->rw
-                     : v->family == FAM_LINEAR ? (v->quad ? 2 : v->adjacent != 0) : 0;
-    const VariantCost* m = nullptr;
-    for (const VariantCost& c : kVariantCosts)
-        if (c.family == v->family && (dense || c.p == v->p) && c.kind == kind && (c.f16 != 0) == v->is_f16) m = &c;
+    const bool alone = !g.ex && !g.xd.s2d && !g.out_s2d;
+    const float* m = nullptr;
+    if (alone) {
+        if (const VariantCost* c = modelled_alone(v)) m = c->c;
+    } else {
+        const int kind = dense ? v->tw == 128 : v->family == FAM_WTILE ? v->rw : v->family == FAM_LINEAR ? (v->quad ? 2 : v->adjacent != 0) : 0;
+        for (const FamilyCost& c : kFamilyCosts)
+            if (c.family == v->family && (dense || c.p == v->p) && c.kind == kind && (c.f16 != 0) == v->is_f16) m = c.c;
+    }
     if (!m) return -1.0;
     double x[9] = {1.0};
     if (dense) {
@@ -309,9 +406,16 @@ static double variant_cost(const cadnn_weights* w, const ConvGeom& g, const Conv
         const int64_t pixels = (int64_t)g.hout * g.wout;
         const double blocks = (double)((wide ? up(pixels * g.n, tn) : up(pixels, tn) * g.n) * up(w->cout, tm));
         const double steps = (double)(wide && w->cin % 32 == 0 ? (int64_t)w->cin / 32 * taps : up((int64_t)w->cin * taps, 32));
-        x[1] = std::max(1.0, blocks / 512.0);
-        x[2] = x[1] * steps;
         x[3] = blocks / 256.0 * steps * (tm * tn / 4096.0);
+        if (alone) {
+            x[1] = blocks / 256.0;
+            x[2] = steps;
+            x[4] = w->cin % 32 ? steps : 0.0;
+            x[5] = w->cin % 32 ? x[3] : 0.0;
+        } else {
+            x[1] = std::max(1.0, blocks / 512.0);
+            x[2] = x[1] * steps;
+        }
     } else {
         const double nnz_row = (double)w->nnz / w->cout;
         double iters = (v->quad ? 1 : v->rpw) * nnz_row / v->ks;
@@ -367,9 +471,12 @@ static double variant_cost(const cadnn_weights* w, const ConvGeom& g, const Conv
             x[8] = std::log2((double)v->ks);
         }
     }
-    double us = 0.0;
-    for (int i = 0; i < 9; ++i) us += (double)m->c[i] * x[i];
-    return us;
+    double us = 0.0, t[9];
+    for (int i = 0; i < 9; ++i) us += t[i] = (double)m[i] * x[i];
+    if (!alone) return us;
+    const double chain = dense ? t[2] + t[4] : t[1] + t[2] + t[3] + (free ? 0.0 : t[4]);
+    const double issue = dense ? t[1] + t[3] + t[5] : free ? t[4] + t[5] + t[6] : t[5] + t[6] + t[7];
+    return us - chain - issue + std::cbrt(chain * chain * chain + issue * issue * issue);
 }
 
 // Layers launched together (FAM_LINEAR only): the variants of one launch are compared by the slowest member in

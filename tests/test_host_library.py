@@ -256,3 +256,28 @@ def test_untuned_pick_is_listed_and_keeps_pruned_layers_off_the_zero_filled_matr
     assert pick in names
     if any(not nm.startswith("dense") for nm in names):
         assert not pick.startswith("dense")
+
+
+def test_untuned_choice_against_measured_times():
+    """What the cost model picks for layers whose variants have been timed (tests/golden/variant_times.txt): within
+    1.08 of the best variant in the geometric mean, no layer above 1.7."""
+    worst, logs, count = (0.0, ""), 0.0, 0
+    rng = np.random.default_rng(11)
+    path = os.path.join(os.path.dirname(__file__), "golden", "variant_times.txt")
+    lines = [l for l in open(path).read().splitlines() if not l.startswith("#")]
+    for head, times in zip(lines[::2], lines[1::2]):
+        dtype, (n, cin, cout, h, w, k, stride, pad, nnz) = head.split()[1], map(int, head.split()[2:])
+        words = times.split()
+        us = dict(zip(words[::2], map(float, words[1::2])))
+        wt = np.zeros(cout * cin * k * k, np.float32)
+        wt[rng.permutation(wt.size)[:nnz]] = 1.0
+        handle = cad.cadnn_pack_weights(wt.reshape(cout, cin, k, k), cad.F16 if dtype == "f16" else cad.F32)
+        pick = cad.cadnn_conv2d_variant_name(handle, n, h, w, stride, pad)
+        handle.free()
+        ratio = us.get(pick, 1.8 * min(us.values())) / min(us.values())
+        worst = max(worst, (ratio, head + ": " + pick))
+        logs += np.log(ratio)
+        count += 1
+    assert count == 60
+    assert np.exp(logs / count) <= 1.08, np.exp(logs / count)
+    assert worst[0] <= 1.7, worst
