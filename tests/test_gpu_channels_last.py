@@ -254,6 +254,26 @@ def test_pools_and_copies_of_non_finite_values(cad, k, pad, dtype_name):
         net.free()
 
 
+@pytest.mark.parametrize("hw", [(7, 7), (1, 1), (5, 9), (8, 8), (13, 11), (33, 40)])
+def test_global_pool_sums_are_as_exact_as_on_planes(cad, hw):
+    """The mean of a map of positive values, against 64 bits and against the pool on planes over the same map."""
+    ops = [Op("conv", "a", 0, 1, 32, 512, 1, 1, 0, 0.5, True), Op("avgpool", "gap", 1, 2)]
+    shape = (4, 32) + hw
+    x, ws, bs = wl.net_tensors(ops, "gap-sums", shape, input_relu=True)
+    net = cad.build_net(ops, ws, bs, shape, cad.F32, use_graph=False)
+    net.set_op_variant(0, "cl_mfma_64x64_s3")
+    y = net.run(torch.from_numpy(x).cuda()).cpu().numpy().reshape(4, 512).astype(np.float64)
+    torch.cuda.synchronize()
+    mid = net.read_buffer(1, (4, 512) + hw)
+    net.free()
+    planes = cad.cadnn_global_avgpool(torch.from_numpy(mid).cuda()).cpu().numpy().reshape(4, 512).astype(np.float64)
+    ref = mid.astype(np.float64).mean((2, 3))
+    off = lambda g: float(np.sqrt(((g - ref) ** 2).sum() / (ref ** 2).sum()))
+    assert off(y) <= 1.1 * off(planes) + 1e-9, (off(y), off(planes))
+    # any chain of hw / 64 + 1 additions, 7 levels and the division
+    assert (np.abs(y - ref) <= (hw[0] * hw[1] // 64 + 9) * 2.0 ** -24 * np.abs(mid).astype(np.float64).mean((2, 3))).all()
+
+
 def test_split_tiles_pinned_and_run_at_once_on_another_stream(cad):
     """The arrival counters of a split K are zero for a launch on a non-blocking stream right behind the pin, with the
     scratch growing and the tiles changing in between."""
