@@ -450,7 +450,7 @@ def main() -> int:
                 tot["mfma"] += t_mfma
                 tot["miopen"] += t_mio
                 wins += int(costs[i]["ms"] * 1e3 < min(t_mfma, t_mio))
-                by_mfma += int(names[i].startswith("dense_mfma"))
+                by_mfma += int(names[i].startswith(("dense_mfma", "cl_")))
         dense_cmp = {"layers_at_80pct_or_more": cnt, "net_faster_than_both_on": wins,
                      "of_which_the_selection_runs_on_matrix_cores": by_mfma,
                      "sum_net_us": tot["sparse"], "sum_own_mfma_dense_us": tot["mfma"],

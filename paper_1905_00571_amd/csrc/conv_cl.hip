@@ -14,14 +14,15 @@
 //   * S stage buffers.  A stage's fragments are read into registers one stage ahead of its products and its
 //     buffer is loaded again right behind the barrier that follows, between the products: one barrier and
 //     one counted wait per stage.
-//   * What bounds it is the way into LDS: 50-57 bytes per clock and CU (measured, data in L2; 29 from behind it),
-//     so a 64 x 64 x 64 step of fp16 takes 290 clocks where its products take 128.  Larger tiles reuse more
+//   * What bounds it is the way into LDS: 50-57 bytes per clock and CU (a kernel of these loads alone, data in L2; 29
+//     from behind it), so a 64 x 64 x 64 step of fp16 takes 290 clocks where its products take 128.  Larger tiles reuse more
 //     but leave CUs idle.  fp32 products take 1024 clocks a step and bound it themselves.
 //   * With one or two workgroups a CU the rest is start and end: 1200 clocks to the first loads and 1500 from the
 //     last product to the last store.  So the launch record is fetched whole, the first weights are
 //     requested before anything is computed, divisions are multiplications, and bias and residual are
-//     requested ahead of the K loop.  ResNet-50 fp16, us per pass before -> after (these and the stages above):
-//     batch 1 371 -> 320, 8 517 -> 419, 32 981 -> 851; fp32 batch 8 1132 -> 1028; MobileNet-V2 fp16 batch 16 490 -> 407.
+//     requested ahead of the K loop.  ResNet-50 fp16, us per pass before these and the stages above -> now:
+//     batch 1 371 -> 316, 8 517 -> 427, 32 981 -> 839; fp32 batch 8 1132 -> 1016; MobileNet-V2 fp16 batch 16 490 -> 353.
+//     At batch 32 the matrix pipes are busy 68 % of the busy CUs' cycles, over all of these launches; L2 hit rate 75 %.
 //   * Padding is a zero halo in memory, so no tap is ever tested.
 //   * A fused 1x1 projection shortcut (paper Section 4, layer fusion) is more K steps on a second tensor.
 //   * The epilogue goes through LDS, [pixel][channel]: residual rows come in and finished rows go out as

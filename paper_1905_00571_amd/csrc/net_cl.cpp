@@ -219,12 +219,14 @@ std::unique_ptr<ClNet> cl_layout(const cadnn_net* net) {
 // Which execution a net takes unless a variant of the other is pinned.  Both are modelled as a fixed cost
 // per launch plus multiply-adds at a rate: the compressed kernels of the plane layouts do the nonzero
 // ones at 8.5 TFLOP/s (ResNet-50, 80 % sparse, fp16 / mixed, fp32: 7-8.7 measured at batch 2 to 32), the
-// matrix cores all of them at 430 (fp16) or 80 (fp32).  Measured around the line (us, planes /
-// channels-last): ResNet-50 fp16 batch 1 417 / 321, 2 632 / 330, 8 1841 / 418, 32 6789 / 851; fp32
-// batch 2 539 / 617, 4 861 / 736, 8 1521 / 1028; VGG-16 batch 1 fp16 392 / 173, fp32 389 / 460; Inception-V3
-// fp16 batch 1 641 / 682, 2 967 / 703, fp32 batch 1 556 / 1130; MobileNet-V1 fp16 batch 1 122 / 162, 16 735 / 267;
-// MobileNet-V2 fp16 batch 2 224 / 270, 4 288 / 283, 16 613 / 407.  Near the line the plane layouts keep the
-// net: tuning gains them more (10-20 %) than it gains these kernels.
+// matrix cores all of them at 430 (fp16) or 80 (fp32).  Measured (us, planes / channels-last, untuned; * the rule
+// takes the second): ResNet-50 fp16 batch 1 379 / 313*, 2 576 / 320*, 8 1725 / 407*; fp32 batch 2 492 / 630, 4 711 / 730,
+// 6 1032 / 946*, 8 1260 / 1016*; VGG-16 batch 1 fp16 336 / 165*, fp32 322 / 450, 4 952 / 1330; Inception-V3 fp16 batch 1
+// 596 / 661, 2 926 / 676, 3 1298 / 702*, fp32 batch 1 546 / 1118, 4 1431 / 1353; MobileNet-V1 fp16 batch 1 128 / 124,
+// 4 223 / 132, 6 350 / 144*, fp32 batch 2 178 / 189, 4 258 / 212, 8 455 / 267; MobileNet-V2 fp16 batch 3 237 / 234, 8 376 / 266,
+// 12 487 / 294*, fp32 batch 6 379 / 383, 8 438 / 425.  So no net goes channels-last to its loss, and near the line the
+// plane layouts keep nets that would be up to 1.7 times as fast there (the 6 us of a depthwise launch are of an
+// older kernel: 3 to 6 now); tuning (CADNN_NET_TUNE) times both for a net that does go.
 bool cl_expected_faster(const cadnn_net* net) {
     double nonzero = 0.0, dense = 0.0;
     double cl_us = 0.0;
