@@ -36,6 +36,34 @@ inline ClDesc cl_desc(int c, int h, int w, int ph, int pw, int pix) {
 
 constexpr int kClMaxTaps = 64;
 
+// 4-byte weights are kept as three bf16 numbers whose sum they are (fp32 products on the bf16 matrix
+// pipes): bytes of an output channel's weights in a step of `rb` bytes of activations.
+constexpr int cl_weight_bytes(int rb, int elem) { return elem == 4 ? rb / 4 * 6 : rb; }
+// Where part p of the weight of k (in the step) and row r (of a block of 64 output channels) lies: by groups of
+// 16 k, parts, wave halves (k = 4 half + {0..3, 8..11} of the group), rows.
+inline __host__ __device__ int cl_split_offset(int k, int p, int r) {
+    return (((k / 16 * 3 + p) * 2 + k / 4 % 2) * 64 + r) * 16 + (k % 4 + k % 16 / 8 * 4) * 2;
+}
+// A float as the sum of three bf16, each the nearest to what the ones before it left (down to 2^-133); an infinity
+// or a NaN is the first, a value that would round to an infinity is cut off instead.
+inline __host__ __device__ void cl_split_weight(float v, uint16_t part[3]) {
+    part[1] = part[2] = 0;
+    uint32_t u = __builtin_bit_cast(uint32_t, v);
+    if ((u & 0x7f800000u) == 0x7f800000u) {
+        part[0] = (uint16_t)(u >> 16 | ((u & 0x007fffffu) ? 0x40u : 0u));
+        return;
+    }
+    for (int p = 0; p < 3; ++p) {
+        uint32_t top = (u + 0x7fffu + (u >> 16 & 1u)) & 0xffff0000u;
+        if ((top & 0x7f800000u) == 0x7f800000u) top = u & 0xffff0000u;
+        part[p] = (uint16_t)(top >> 16);
+        v -= __builtin_bit_cast(float, top);
+        u = __builtin_bit_cast(uint32_t, v);
+    }
+}
+// (offsets into the weights are 32-bit)
+constexpr size_t kClMaxWeightBytes = 0x7ffffff0u;
+
 // The weights of one layer as the matrix-core kernel reads them: K in steps of `rb` bytes per row
 // (rb / elem input channels of one filter tap, taps in order, only those that some filter uses; a
 // fused shortcut's channels follow), 64 output channels x one step side by side as [64][rb] with
@@ -50,11 +78,17 @@ struct ClPlan {
     DevBuf part, count;
 };
 
+// Bytes of the weights in this order: blocks of 64 rows, whole 128-row tiles.
+inline size_t cl_plan_bytes(int cout, const ClPlan& plan, int elem) {
+    return (size_t)((cout + 127) / 128) * 128 * (size_t)plan.steps * (size_t)cl_weight_bytes(plan.rb, elem);
+}
+
 // Tiles a layer can be run with: 64 * mi output channels x 64 * ni output pixels, s stage buffers (how far
-// the loads run ahead), sk workgroups that share a tile, each a slice of K.
+// the loads run ahead), sk workgroups that share a tile, each a slice of K, kg groups of four waves that share
+// a workgroup, each a part of its slice.
 struct ClVariant {
     const char* name;
-    int mi, ni, s, sk;
+    int mi, ni, s, sk, kg;
 };
 const std::vector<ClVariant>& all_cl_variants();
 
@@ -75,7 +109,8 @@ struct ClConv {
 // the weights on the device.
 cadnn_status cl_plan_shape(const cadnn_weights* w, const cadnn_weights* shortcut, int rb, bool stem, ClPlan* plan,
                            std::vector<int>* tap_of = nullptr);
-cadnn_status cl_build_plan(const cadnn_weights* w, const cadnn_weights* shortcut, int rb, bool stem, ClPlan* plan);
+// (`image`: where the device form is put together on the host; kept from layer to layer, its pages need not be mapped anew.)
+cadnn_status cl_build_plan(const cadnn_weights* w, const cadnn_weights* shortcut, int rb, bool stem, ClPlan* plan, std::vector<char>* image);
 // The tile the cost rule takes, and whether a variant can run the layer.
 const ClVariant* cl_pick(int cout, const ClPlan& plan, int64_t pixels, bool f16);
 bool cl_variant_fits(const ClVariant& v, const ClPlan& plan, int64_t pixels, int cout);

@@ -16,19 +16,27 @@
 //     one counted wait per stage.
 //   * What bounds it is the way into LDS: 50-57 bytes per clock and CU (a kernel of these loads alone, data in L2; 29
 //     from behind it), so a 64 x 64 x 64 step of fp16 takes 290 clocks where its products take 128.  Larger tiles reuse more
-//     but leave CUs idle.  fp32 products take 1024 clocks a step and bound it themselves.
+//     but leave CUs idle.
 //   * With one or two workgroups a CU the rest is start and end: 1200 clocks to the first loads and 1500 from the
 //     last product to the last store.  So the launch record is fetched whole, the first weights are
 //     requested before anything is computed, divisions are multiplications, and bias and residual are
-//     requested ahead of the K loop.  ResNet-50 fp16, us per pass before these and the stages above -> now:
-//     batch 1 371 -> 316, 8 517 -> 427, 32 981 -> 839; fp32 batch 8 1132 -> 1016; MobileNet-V2 fp16 batch 16 490 -> 353.
+//     requested ahead of the K loop.  ResNet-50 fp16, us per pass before these and the stages above -> behind them:
+//     batch 1 371 -> 316, 8 517 -> 427, 32 981 -> 839; MobileNet-V2 fp16 batch 16 490 -> 353.
 //     At batch 32 the matrix pipes are busy 68 % of the busy CUs' cycles, over all of these launches; L2 hit rate 75 %.
 //   * Padding is a zero halo in memory, so no tap is ever tested.
 //   * A fused 1x1 projection shortcut (paper Section 4, layer fusion) is more K steps on a second tensor.
 //   * The epilogue goes through LDS, [pixel][channel]: residual rows come in and finished rows go out as
 //     16-byte pieces of whole pixels; bias, residual and ReLU in fp32, one rounding.
-//   * fp32 storage takes v_mfma_f32_32x32x2_f32 on the same bytes: a 16-byte piece is four k of one lane,
-//     consumed by four instructions (both operands permute k the same way).
+//   * fp32 storage: a float is the sum of three bf16, exactly, and a product of two floats is six products of such parts but
+//     for 2^-25 of it.  The bf16 pipes make six in 384 clocks of a 64 x 64 x 32 step, v_mfma_f32_32x32x2_f32
+//     the one in 1024.  Weights are laid out as their parts; a wave takes its activations apart in registers, which costs as
+//     many clocks as the products and runs beside them.  ResNet-50 fp32 at 8 images 1016 -> 805 us a pass (with two groups
+//     of waves and constants of its own).  Against 64 bits the error is 0.7 to 1.0 times that of fp32 products, K = 27 to 4608
+//     (3.4e-7 against 4.1e-7 at 512): six instructions round for 16 k where eight did.  What bounds a step now (860 to 940 clocks) is the
+//     products at the clock they leave the chip (490 for zeros, 610 for random operands and taking apart), then 20 KB into LDS.
+//     Sums that are not finite are done again with fp32 products, see there.
+//   * K groups of waves in a workgroup: groups of four waves with stage buffers of their own walk parts of K side by side and exchange
+//     halves of their sums through LDS.  For workgroups that are alone on their CU.
 //   * K may be split over `sk` workgroups per tile (partial tiles at device scope, the last to arrive adds
 //     them in slice order and finishes): for layers whose tiles leave most of the chip idle.
 //   * Workgroups are numbered so that one die (workgroup id % 8) owns a contiguous run of tiles with the
@@ -47,6 +55,9 @@ constexpr uint32_t kClOutOfRange = 0x7ffffff0u;
 
 typedef _Float16 cl_h8 __attribute__((ext_vector_type(8)));
 typedef _Float16 cl_h4 __attribute__((ext_vector_type(4)));
+typedef __bf16 cl_b8 __attribute__((ext_vector_type(8)));
+typedef __bf16 cl_b2 __attribute__((ext_vector_type(2)));
+typedef float cl_f2 __attribute__((ext_vector_type(2)));
 typedef float cl_f4 __attribute__((ext_vector_type(4)));
 typedef float cl_f16v __attribute__((ext_vector_type(16)));
 typedef uint32_t cl_u4 __attribute__((ext_vector_type(4)));
@@ -71,7 +82,7 @@ struct ClArgs {
     uint32_t wspan;
     int total, hw, ow, cout, relu;
     int steps_tap, steps1, steps, ntaps, tiles_m, tiles, per_die, sk, log_sk;
-    int per_slice;              // steps of a slice of the split
+    int per_slice;              // steps of a slice: of a group of waves of a workgroup of the split
     int row_bytes;              // bytes of a step that are the pixel's own; what lies behind them is not used
     int plane;                  // PLANES: bytes from one channel to the next
     uint32_t magic_hw, magic_ow, magic_tm, magic_st;
@@ -116,16 +127,41 @@ __device__ __forceinline__ cl_u4 cl_rsrc(const void* p, uint32_t span) {
     return r;
 }
 
-// MI x NI accumulators of 32 x 32 per wave, 2 x 2 waves: a tile of 64 MI channels x 64 NI pixels; S stage buffers.
-template <typename T, int RB, int MI, int NI, int S>
+// A tile of 64 MI channels x 64 NI pixels, AM x AN accumulators of 32 x 32 for each of 4 waves; S stage buffers; KG such
+// groups of 4 waves, each with buffers and a part of K of its own.
+// 2 x 2 waves; in 4-byte storage a wave has 32 pixels, whose activations it takes apart for all of its products.
+template <typename T, int RB, int MI, int NI, int S, int KG>
 struct ClCfg {
     static constexpr int TM = 64 * MI, TN = 64 * NI;
-    static constexpr int STAGE = (TM + TN) * RB;
+    static constexpr int WN = sizeof(T) == 4 ? 2 * NI : 2;
+    static constexpr int AM = 2 * MI * WN / 4, AN = 2 * NI / WN;
+    static constexpr int WB = 64 * cl_weight_bytes(RB, sizeof(T));          // bytes of a step of 64 output channels
+    static constexpr int LA = (MI * WB + 4095) / 4096, LB = TN * RB / 4096; // loads per thread and stage
+    static constexpr int A_BYTES = LA * 4096;
+    static constexpr int STAGE = A_BYTES + TN * RB;
     static constexpr int PITCH = TM * (int)sizeof(T) + 16;
     static constexpr int cmax(int a, int b) { return a > b ? a : b; }
-    static constexpr int MAIN = cmax(S * STAGE, TN * PITCH);
-    static constexpr int LDS = MAIN + TN * 16 + TM * 4;
+    static constexpr int GROUP = S * STAGE;
+    static constexpr int KEPT = AM * AN * 16 / KG;           // sums of a thread behind the K loop
+    static constexpr int SWAP = KG == 1 ? 0 : AM * AN * 16 * 1024;      // where the groups exchange them, behind the tile
+    static constexpr int MAIN = cmax(KG * GROUP, TN * PITCH + SWAP);
+    static constexpr int LDS = MAIN + TN * 16 + TM * 4 + 16;
 };
+
+// Two floats as the sum of three pairs of bf16, exactly: each is rounded to the nearest 8 bits of what
+// the ones before it left, and 24 bits are three times 8.  (Bits below 2^-133 have no place.)  An infinity or a
+// NaN, or a value that rounds to one, leaves NaN behind, which the caller sees in the sums.
+// (Shifts, masks and subtractions run beside the matrix products; v_dot2_f32_bf16, which would take the place of two of
+// them, does not: 12 products 434 clocks, with 60 subtractions between them 470, with 60 of it 844.)
+__device__ __forceinline__ void cl_split2(float a, float b, uint32_t* p1, uint32_t* p2, uint32_t* p3) {
+    const uint32_t h1 = __builtin_bit_cast(uint32_t, __builtin_convertvector((cl_f2){a, b}, cl_b2));
+    const float ra = a - __uint_as_float(h1 << 16), rb = b - __uint_as_float(h1 & 0xffff0000u);
+    const uint32_t h2 = __builtin_bit_cast(uint32_t, __builtin_convertvector((cl_f2){ra, rb}, cl_b2));
+    const float sa = ra - __uint_as_float(h2 << 16), sb = rb - __uint_as_float(h2 & 0xffff0000u);
+    *p1 = h1;
+    *p2 = h2;
+    *p3 = __builtin_bit_cast(uint32_t, __builtin_convertvector((cl_f2){sa, sb}, cl_b2));
+}
 
 // v / d for 0 <= v < 2^31 with magic = ceil(2^32 / d): the product is at most one too large.
 __device__ __forceinline__ int cl_div(int v, uint32_t magic, int d) {
@@ -144,17 +180,20 @@ enum ClMode { CL_MAPS = 0, CL_PLANES = 1, CL_ODD_ROW = 2 };
 // wider than such a row.  Whole pieces behind it are not requested at all (that goes for every first
 // layer); the piece that is half the next pixel's loses that half in the registers, because a zero weight does not
 // undo an infinity or a NaN.  (Four more instructions a step; other layers take the kernels without them.)
-template <typename T, int RB, int MI, int NI, int S, int MODE>
-__global__ __launch_bounds__(256, MI * NI == 1 ? 4 : 2) void cl_conv_kernel(const ClArgs a) {
-    using C = ClCfg<T, RB, MI, NI, S>;
+template <typename T, int RB, int MI, int NI, int S, int KG, int MODE>
+__global__ __launch_bounds__(256 * KG, MI * NI == 1 ? 4 : 2) void cl_conv_kernel(const ClArgs a) {
+    using C = ClCfg<T, RB, MI, NI, S, KG>;
+    static_assert(KG <= 2, "two groups exchange halves of their sums");
     constexpr bool PLANES = MODE == CL_PLANES;
     static_assert(MODE != CL_ODD_ROW || sizeof(T) == 2, "a pixel of 4-byte storage is a whole piece");
     constexpr int TM = C::TM, TN = C::TN, STAGE = C::STAGE, PITCH = C::PITCH;
     constexpr int RPL = 1024 / RB;                 // rows one wave-load fills
-    constexpr int LA = TM * RB / 4096, LB = TN * RB / 4096;      // loads per thread and stage
+    constexpr int LA = C::LA, LB = C::LB;
+    constexpr bool SPLIT = sizeof(T) == 4;
+    constexpr int AM = C::AM, AN = C::AN;
+    constexpr int WB = C::WB;
     constexpr int PIECES = RB / 16;
     constexpr int EPP = 16 / (int)sizeof(T);       // elements per 16-byte piece
-    constexpr int KS = RB / 32;                    // 32-byte halves pairs: MFMA groups per stage
     extern __shared__ __attribute__((aligned(16))) char cl_smem[];
     int4* ptab = (int4*)(cl_smem + C::MAIN);       // per pixel of the tile: byte offsets in x, x2, y, residual
     float* bl = (float*)(cl_smem + C::MAIN + TN * 16);
@@ -178,21 +217,31 @@ __global__ __launch_bounds__(256, MI * NI == 1 ? 4 : 2) void cl_conv_kernel(cons
     const int m0 = mt * TM, n0 = nt * TN;
 
     const int tid = (int)threadIdx.x, lane = tid & 63;
-    const int wv = __builtin_amdgcn_readfirstlane(tid >> 6);
-    const int wm = wv >> 1, wn = wv & 1;
+    const int wave = __builtin_amdgcn_readfirstlane(tid >> 6), kg = KG == 1 ? 0 : wave >> 2, wv = wave & 3;
+    const int wm = wv / C::WN, wn = wv % C::WN;
 
     // ---- the weights of the first stage need nothing but the tile's number: on their way before all else
     constexpr int L = LA + LB;
-    const int s_first = z * a.per_slice, steps = min(a.per_slice, a.steps - s_first);
-    const uint32_t va = (uint32_t)(wv * 1024 + lane * 16);
+    // (all groups of a workgroup go through the steps of the first; what one lacks of them is zeros, fetched from out of range)
+    const int s_first = (z * KG + kg) * a.per_slice, steps = min(a.per_slice, a.steps - z * KG * a.per_slice);
+    uint32_t va = KG > 1 && s_first >= a.steps ? kClOutOfRange : (uint32_t)(lane * 16);
     const cl_u4 wr = cl_rsrc(a.w, a.wspan);
-    uint32_t wsoff[MI];
+    // (a load moves 1 KB per wave, and a 64-row block is a whole number of these; the last load of a
+    // stage has nothing left to fetch for the waves past the blocks' end)
+    uint32_t wsoff[LA];
+    uint32_t va_last = LA * 4 > MI * WB / 1024 && LA * 4 - 4 + wv >= MI * WB / 1024 ? kClOutOfRange : va;
+    auto start_weights = [&]() __attribute__((always_inline)) {
 #pragma unroll
-    for (int i = 0; i < MI; ++i) wsoff[i] = (uint32_t)((mt * MI + i) * a.steps + s_first) * (64u * RB);
-    const uint32_t lds_w = lds0 + (uint32_t)wv * 1024u;
+        for (int i = 0; i < LA; ++i) {
+            const int chunk = min(i * 4 + wv, MI * WB / 1024 - 1), block = chunk / (WB / 1024);
+            wsoff[i] = (uint32_t)((mt * MI + block) * a.steps + s_first) * (uint32_t)WB + (uint32_t)(chunk - block * (WB / 1024)) * 1024u;
+        }
+    };
+    start_weights();
+    const uint32_t lds_w = lds0 + (uint32_t)(kg * C::GROUP + wv * 1024);
     auto issue_w = [&](auto I, uint32_t buf) __attribute__((always_inline)) {
-        constexpr int i = decltype(I)::value, PER = 64 * RB / 4096;      // PER: loads of a thread per 64-row block
-        cl_dma(wr, va, wsoff[i / PER] + (uint32_t)(i % PER) * 4096u, lds_w + buf * STAGE + (uint32_t)i * 4096u);
+        constexpr int i = decltype(I)::value;
+        cl_dma(wr, i == LA - 1 ? va_last : va, wsoff[i], lds_w + buf * STAGE + (uint32_t)i * 4096u);
     };
     cl_static_for<0, LA>([&](auto I) __attribute__((always_inline)) { issue_w(I, 0u); });
 
@@ -210,6 +259,8 @@ __global__ __launch_bounds__(256, MI * NI == 1 ? 4 : 2) void cl_conv_kernel(cons
         ptab[tid] = e;
     }
     // (the bias is requested here and put in LDS behind the K loop: nothing waits for it)
+    int* const odd = (int*)(bl + TM);               // SPLIT: a sum of this workgroup's is not finite
+    if (SPLIT && tid == 0) *odd = 0;
     float my_bias = 0.0f, my_bias2 = 0.0f;
     if (tid < TM && m0 + tid < a.cout) {
         if (a.bias) my_bias = a.bias[m0 + tid];
@@ -224,22 +275,26 @@ __global__ __launch_bounds__(256, MI * NI == 1 ? 4 : 2) void cl_conv_kernel(cons
     const int sw = RB == 128 ? ((wv * RPL + lrow) >> 1) & 7 : (lrow >> 2) & 3;
     const uint32_t piece = (uint32_t)(lpos ^ sw) * 16u;
     uint32_t vb[LB];
+    cl_u4 xr;
+    auto start_sources = [&]() __attribute__((always_inline)) {
 #pragma unroll
-    for (int j = 0; j < LB; ++j) {
-        const int e = ptab[j * 4 * RPL + wv * RPL + lrow].x;
-        vb[j] = e == (int)kClOutOfRange || (int)piece >= a.row_bytes ? kClOutOfRange : (uint32_t)e + piece;
-    }
-    cl_u4 xr = cl_rsrc(a.x, a.xt.span);
+        for (int j = 0; j < LB; ++j) {
+            const int e = ptab[j * 4 * RPL + wv * RPL + lrow].x;
+            vb[j] = e == (int)kClOutOfRange || (int)piece >= a.row_bytes ? kClOutOfRange : (uint32_t)e + piece;
+        }
+        xr = cl_rsrc(a.x, a.xt.span);
+    };
+    start_sources();
 
     // ---- the residual's rows are requested up front where they fit few registers
-    constexpr int CPR = TM * (int)sizeof(T) / 16, ITEMS = TN * CPR / 256;
+    constexpr int CPR = TM * (int)sizeof(T) / 16, ITEMS = TN * CPR / (256 * KG);
     constexpr bool EARLY = ITEMS <= 8 && !PLANES;
     const __amdgpu_buffer_rsrc_t rrs = __builtin_amdgcn_make_buffer_rsrc((void*)a.res, 0, a.rt.span, 0x00020000);
     const int ec = tid % CPR, ep = tid / CPR;                    // epilogue: this thread's piece and first pixel
     const bool ec_live = m0 + ec * EPP < a.cout;
     cl_u4 resv[EARLY ? ITEMS : 1];
     auto res_load = [&](int k) __attribute__((always_inline)) {
-        const int r = ptab[ep + k * (256 / CPR)].w;
+        const int r = ptab[ep + k * (256 * KG / CPR)].w;
         const uint32_t off = (ec_live && r != (int)kClOutOfRange) ? (uint32_t)(r + m0 * (int)sizeof(T) + ec * 16) : kClOutOfRange;
         return __builtin_bit_cast(cl_u4, __builtin_amdgcn_raw_buffer_load_b128(rrs, off, 0u, 0));
     };
@@ -251,7 +306,7 @@ __global__ __launch_bounds__(256, MI * NI == 1 ? 4 : 2) void cl_conv_kernel(cons
     }
 
     // ---- the walk over this workgroup's slice of K
-    int f_left, f_tap = 0, f_todo = steps;
+    int f_left, f_tap, f_todo, f_own;
     uint32_t f_soff;
     auto enter_shortcut = [&](int at) __attribute__((always_inline)) {
         xr = cl_rsrc(a.x2, a.x2t.span);
@@ -263,17 +318,33 @@ __global__ __launch_bounds__(256, MI * NI == 1 ? 4 : 2) void cl_conv_kernel(cons
         f_left = 0x7fffffff;
         f_soff = (uint32_t)at * RB;
     };
-    if (s_first == 0) {
-        f_left = a.steps_tap;
-        f_soff = (uint32_t)a.tap_off[0];
-    } else if (s_first < a.steps1) {
-        f_tap = cl_div(s_first, a.magic_st, a.steps_tap);
-        const int at = s_first - f_tap * a.steps_tap;
-        f_left = a.steps_tap - at;
-        f_soff = (uint32_t)a.tap_off[f_tap] + (uint32_t)at * RB;
-    } else {
-        enter_shortcut(s_first - a.steps1);
-    }
+    auto past_end = [&]() __attribute__((always_inline)) {
+        va = va_last = kClOutOfRange;
+#pragma unroll
+        for (int j = 0; j < LB; ++j) vb[j] = kClOutOfRange;
+        f_left = 0x7fffffff;
+        f_soff = 0;
+    };
+    auto start_walk = [&]() __attribute__((always_inline)) {
+        f_tap = 0;
+        f_todo = steps;
+        f_own = a.steps - s_first;
+        if constexpr (KG > 1) {
+            if (f_own <= 0) return past_end();
+        }
+        if (s_first == 0) {
+            f_left = a.steps_tap;
+            f_soff = (uint32_t)a.tap_off[0];
+        } else if (s_first < a.steps1) {
+            f_tap = cl_div(s_first, a.magic_st, a.steps_tap);
+            const int at = s_first - f_tap * a.steps_tap;
+            f_left = a.steps_tap - at;
+            f_soff = (uint32_t)a.tap_off[f_tap] + (uint32_t)at * RB;
+        } else {
+            enter_shortcut(s_first - a.steps1);
+        }
+    };
+    start_walk();
     // load i of a stage: the weights' first, then the activations'
     auto issue_one = [&](auto I, uint32_t buf) __attribute__((always_inline)) {
         constexpr int i = decltype(I)::value;
@@ -282,9 +353,10 @@ __global__ __launch_bounds__(256, MI * NI == 1 ? 4 : 2) void cl_conv_kernel(cons
     };
     auto advance = [&]() __attribute__((always_inline)) {
 #pragma unroll
-        for (int i = 0; i < MI; ++i) wsoff[i] += 64u * RB;
+        for (int i = 0; i < LA; ++i) wsoff[i] += (uint32_t)WB;
         f_soff += RB;
         --f_todo;
+        if constexpr (KG > 1) { if (--f_own == 0) past_end(); }
         if (--f_left == 0 && f_todo > 0) {
             if (++f_tap < a.ntaps) {
                 f_left = a.steps_tap;
@@ -294,18 +366,21 @@ __global__ __launch_bounds__(256, MI * NI == 1 ? 4 : 2) void cl_conv_kernel(cons
             }
         }
     };
-    cl_f16v acc[MI][NI];
+    cl_f16v acc[AM][AN];
+    auto clear_sums = [&]() __attribute__((always_inline)) {
 #pragma unroll
-    for (int mi = 0; mi < MI; ++mi)
+        for (int mi = 0; mi < AM; ++mi)
 #pragma unroll
-        for (int ni = 0; ni < NI; ++ni)
+            for (int ni = 0; ni < AN; ++ni)
 #pragma unroll
-            for (int i = 0; i < 16; ++i) acc[mi][ni][i] = 0.0f;
+                for (int i = 0; i < 16; ++i) acc[mi][ni][i] = 0.0f;
+    };
+    clear_sums();
 
     // fragment addresses: row l % 32 of a 32-row block, piece 2 ks + l / 32 (permuted by the row)
     const int l31 = lane & 31, fk = lane >> 5;
     const int fs = RB == 128 ? (lane >> 1) & 7 : (lane >> 2) & 3;
-    const uint32_t fa = (uint32_t)((wm * 32 * MI + l31) * RB), fb = (uint32_t)(TM * RB + (wn * 32 * NI + l31) * RB);
+    const uint32_t fb = (uint32_t)(kg * C::GROUP + C::A_BYTES + (wn * 32 * AN + l31) * RB);
     const uint32_t fp = (uint32_t)((fk ^ fs) * 16);
 
     // A stage's fragments are read into registers one stage ahead of its products, so LDS latency and
@@ -320,105 +395,305 @@ __global__ __launch_bounds__(256, MI * NI == 1 ? 4 : 2) void cl_conv_kernel(cons
         if (behind <= 0) cl_wait<0>();
     };
     static_assert((S - 1) * L <= 63, "the wait counter counts to 63");
-    cl_u4 af[2][KS][MI], bf[2][KS][NI];
-    auto read_frags = [&](auto F, uint32_t buf) __attribute__((always_inline)) {
-        constexpr int f = decltype(F)::value;
-        const char* st = cl_smem + buf * STAGE;
-#pragma unroll
-        for (int ks = 0; ks < KS; ++ks) {
-            const uint32_t p = fp ^ (uint32_t)(ks * 32);
-#pragma unroll
-            for (int mi = 0; mi < MI; ++mi) af[f][ks][mi] = *(const cl_u4*)(st + fa + mi * 32 * RB + p);
-#pragma unroll
-            for (int ni = 0; ni < NI; ++ni) bf[f][ks][ni] = *(const cl_u4*)(st + fb + ni * 32 * RB + p);
-            if constexpr (MODE == CL_ODD_ROW) {
-                const uint32_t own = 2 * ks + fk == a.row_bytes / 16 ? 0u : ~0u;
-#pragma unroll
-                for (int ni = 0; ni < NI; ++ni) {
-                    bf[f][ks][ni][2] &= own;
-                    bf[f][ks][ni][3] &= own;
-                }
-            }
-        }
-    };
-    auto multiply = [&](auto F, auto K) __attribute__((always_inline)) {
-        constexpr int f = decltype(F)::value, ks = decltype(K)::value;
-#pragma unroll
-        for (int mi = 0; mi < MI; ++mi)
-#pragma unroll
-            for (int ni = 0; ni < NI; ++ni) {
-                if constexpr (sizeof(T) == 2) {
-                    acc[mi][ni] = __builtin_amdgcn_mfma_f32_32x32x16_f16(__builtin_bit_cast(cl_h8, af[f][ks][mi]),
-                                                                         __builtin_bit_cast(cl_h8, bf[f][ks][ni]), acc[mi][ni], 0, 0, 0);
-                } else {
-#pragma unroll
-                    for (int e = 0; e < 4; ++e)
-                        acc[mi][ni] = __builtin_amdgcn_mfma_f32_32x32x2f32(__uint_as_float(af[f][ks][mi][e]), __uint_as_float(bf[f][ks][ni][e]),
-                                                                           acc[mi][ni], 0, 0, 0);
-                }
-            }
-    };
     cl_static_for<LA, L>([&](auto I) __attribute__((always_inline)) { issue_one(I, 0u); });
     advance();
     for (int j = 1; j < S && j < steps; ++j) {
         cl_static_for<0, L>([&](auto I) __attribute__((always_inline)) { issue_one(I, (uint32_t)j); });
         advance();
     }
-    wait_loads(min(steps, S) - 1);
-    cl_barrier();
-    read_frags(std::integral_constant<int, 0>(), 0);
-    uint32_t cur = 0;                       // buffer of the stage being multiplied
-    // (FULL: stage s + S exists, known at compile time)
-    auto stage = [&](auto F, auto FULL, int s) __attribute__((always_inline)) {
-        constexpr int f = decltype(F)::value;
-        constexpr bool full = decltype(FULL)::value;
-        const uint32_t nxt = cur + 1 == S ? 0 : cur + 1;
-        const bool more = full || s + S < steps;
-        if (full || s + 1 < steps) {
-            // stages s + 2 .. s + S - 1 are in flight behind stage s + 1
-            if (more || s + S == steps) cl_wait<(S - 2) * L>();
-            else wait_loads(steps - 2 - s);
-            cl_barrier();
-            read_frags(std::integral_constant<int, f ^ 1>(), nxt);
-        }
-        // A load to LDS holds its wave for as long as the memory pipeline takes 64 addresses (16 clocks
-        // and more while the other waves' are in front); between products that time is the matrix pipe's.
-        // (The scheduler is held to the order: LDS reads, then products and loads in turn.)
-        cl_static_for<0, KS>([&](auto K) __attribute__((always_inline)) {
-            constexpr int k = decltype(K)::value;
-            __builtin_amdgcn_sched_barrier(0);
-            multiply(F, K);
-            __builtin_amdgcn_sched_barrier(0);
-            if (more) cl_static_for<k * L / KS, (k + 1) * L / KS>([&](auto I) __attribute__((always_inline)) { issue_one(I, cur); });
-        });
-        if (more) advance();
-        cur = nxt;
-    };
     typedef std::integral_constant<int, 0> Set0;
     typedef std::integral_constant<int, 1> Set1;
-    int s = 0;
-    for (; s + 1 + S < steps; s += 2) {
-        stage(Set0(), std::true_type(), s);
-        stage(Set1(), std::true_type(), s + 1);
-    }
-    for (; s < steps; s += 2) {
-        stage(Set0(), std::false_type(), s);
-        if (s + 1 < steps) stage(Set1(), std::false_type(), s + 1);
+    wait_loads(min(steps, S) - 1);
+    cl_barrier();
+    if constexpr (!SPLIT) {
+        constexpr int KS = RB / 32;                    // MFMA groups per stage
+        const uint32_t fa = (uint32_t)(kg * C::GROUP + (wm * 32 * AM + l31) * RB);
+        cl_u4 af[2][KS][AM], bf[2][KS][AN];
+        auto read_frags = [&](auto F, uint32_t buf) __attribute__((always_inline)) {
+            constexpr int f = decltype(F)::value;
+            const char* st = cl_smem + buf * STAGE;
+#pragma unroll
+            for (int ks = 0; ks < KS; ++ks) {
+                const uint32_t p = fp ^ (uint32_t)(ks * 32);
+#pragma unroll
+                for (int mi = 0; mi < AM; ++mi) af[f][ks][mi] = *(const cl_u4*)(st + fa + mi * 32 * RB + p);
+#pragma unroll
+                for (int ni = 0; ni < AN; ++ni) bf[f][ks][ni] = *(const cl_u4*)(st + fb + ni * 32 * RB + p);
+                if constexpr (MODE == CL_ODD_ROW) {
+                    const uint32_t own = 2 * ks + fk == a.row_bytes / 16 ? 0u : ~0u;
+#pragma unroll
+                    for (int ni = 0; ni < AN; ++ni) {
+                        bf[f][ks][ni][2] &= own;
+                        bf[f][ks][ni][3] &= own;
+                    }
+                }
+            }
+        };
+        auto multiply = [&](auto F, auto K) __attribute__((always_inline)) {
+            constexpr int f = decltype(F)::value, ks = decltype(K)::value;
+#pragma unroll
+            for (int mi = 0; mi < AM; ++mi)
+#pragma unroll
+                for (int ni = 0; ni < AN; ++ni) {
+                    acc[mi][ni] = __builtin_amdgcn_mfma_f32_32x32x16_f16(__builtin_bit_cast(cl_h8, af[f][ks][mi]),
+                                                                         __builtin_bit_cast(cl_h8, bf[f][ks][ni]), acc[mi][ni], 0, 0, 0);
+                }
+        };
+        read_frags(std::integral_constant<int, 0>(), 0);
+        uint32_t cur = 0;                       // buffer of the stage being multiplied
+        // (FULL: stage s + S exists, known at compile time)
+        auto stage = [&](auto F, auto FULL, int s) __attribute__((always_inline)) {
+            constexpr int f = decltype(F)::value;
+            constexpr bool full = decltype(FULL)::value;
+            const uint32_t nxt = cur + 1 == S ? 0 : cur + 1;
+            const bool more = full || s + S < steps;
+            if (full || s + 1 < steps) {
+                // stages s + 2 .. s + S - 1 are in flight behind stage s + 1
+                if (more || s + S == steps) cl_wait<(S - 2) * L>();
+                else wait_loads(steps - 2 - s);
+                cl_barrier();
+                read_frags(std::integral_constant<int, f ^ 1>(), nxt);
+            }
+            // A load to LDS holds its wave for as long as the memory pipeline takes 64 addresses (16 clocks
+            // and more while the other waves' are in front); between products that time is the matrix pipe's.
+            // (The scheduler is held to the order: LDS reads, then products and loads in turn.)
+            cl_static_for<0, KS>([&](auto K) __attribute__((always_inline)) {
+                constexpr int k = decltype(K)::value;
+                __builtin_amdgcn_sched_barrier(0);
+                multiply(F, K);
+                __builtin_amdgcn_sched_barrier(0);
+                if (more) cl_static_for<k * L / KS, (k + 1) * L / KS>([&](auto I) __attribute__((always_inline)) { issue_one(I, cur); });
+            });
+            if (more) advance();
+            cur = nxt;
+        };
+        int s = 0;
+        for (; s + 1 + S < steps; s += 2) {
+            stage(Set0(), std::true_type(), s);
+            stage(Set1(), std::true_type(), s + 1);
+        }
+        for (; s < steps; s += 2) {
+            stage(Set0(), std::false_type(), s);
+            if (s + 1 < steps) stage(Set1(), std::false_type(), s + 1);
+        }
+    } else {
+        // Fragments are read one group of 16 k ahead of their products.  The weights of a group lie as
+        // three planes of bf16, [64 channels][16 bytes] for either half of the wave: 512 bytes in a row for 32
+        // lanes.  Lane half fk takes k = 4 fk + {0..3, 8..11} of a group, as two pieces of the activations hold them.
+        constexpr int G = RB / 64;
+        const int fr = wm * 32 * AM + l31;
+        const uint32_t fa = (uint32_t)(kg * C::GROUP + (fr / 64) * WB + (fr % 64) * 16 + fk * 1024);
+        cl_u4 af[2][3][AM], bf[2][2][AN];
+        auto read_weights = [&](int f, int g, int p, int mi, const char* st) __attribute__((always_inline)) {
+            af[f][p][mi] = *(const cl_u4*)(st + fa + mi / 2 * WB + mi % 2 * 512 + (g * 3 + p) * 2048);
+        };
+        auto read_group = [&](auto F, auto GRP, uint32_t buf) __attribute__((always_inline)) {
+            constexpr int f = decltype(F)::value, g = decltype(GRP)::value;
+            const char* st = cl_smem + buf * STAGE;
+#pragma unroll
+            for (int ni = 0; ni < AN; ++ni)
+#pragma unroll
+                for (int h = 0; h < 2; ++h) bf[f][h][ni] = *(const cl_u4*)(st + fb + ni * 32 * RB + (fp ^ (uint32_t)((2 * g + h) * 32)));
+#pragma unroll
+            for (int p = 2; p >= 0; --p)
+#pragma unroll
+                for (int mi = 0; mi < AM; ++mi) read_weights(f, g, p, mi, st);
+        };
+        // x w = x1 w1 + (x1 w2 + x2 w1) + (x1 w3 + x2 w2 + x3 w1) + ...: what is left out is 2^-25 of a product at
+        // the most, and of either sign.  (`load(I)`, I < 6: called behind each product; vector and scalar arithmetic
+        // moves across, so that the next part is taken off beside the product before it)
+        static_assert(AN == 1, "a wave takes one block of pixels apart");
+        auto multiply = [&](auto F, auto&& load) __attribute__((always_inline)) {
+            constexpr int f = decltype(F)::value;
+            cl_u4 x1, x2, x3;
+#pragma unroll
+            for (int j = 0; j < 4; ++j) {
+                uint32_t p1, p2, p3;
+                cl_split2(__uint_as_float(bf[f][j / 2][0][j % 2 * 2]), __uint_as_float(bf[f][j / 2][0][j % 2 * 2 + 1]), &p1, &p2, &p3);
+                x1[j] = p1;
+                x2[j] = p2;
+                x3[j] = p3;
+            }
+            cl_static_for<0, 6>([&](auto I) __attribute__((always_inline)) {
+                constexpr int i = decltype(I)::value, p = i == 0 ? 2 : i < 3 ? 1 : 0;
+                const cl_u4 x = i == 0 || i == 1 || i == 5 ? x1 : i == 3 ? x3 : x2;
+#pragma unroll
+                for (int mi = 0; mi < AM; ++mi)
+                    acc[mi][0] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(__builtin_bit_cast(cl_b8, af[f][p][mi]), __builtin_bit_cast(cl_b8, x),
+                                                                         acc[mi][0], 0, 0, 0);
+                __builtin_amdgcn_sched_barrier(6);
+                load(I);
+                __builtin_amdgcn_sched_barrier(6);
+            });
+        };
+        read_group(Set0(), Set0(), 0);
+        uint32_t cur = 0;
+        // A stage's loads start behind its barrier and end, where it has two groups, in front of the next one, between the
+        // products of both: a load to LDS holds its wave until the memory pipeline has its addresses.
+        constexpr int HALF = G == 2 && S > 2 ? (L + 1) / 2 : L;
+        auto loads = [&](auto FROM, auto TO, auto I, uint32_t buf) __attribute__((always_inline)) {
+            constexpr int from = decltype(FROM)::value, n = decltype(TO)::value - from, i = decltype(I)::value;
+            cl_static_for<from + i * n / 6, from + (i + 1) * n / 6>([&](auto K) __attribute__((always_inline)) { issue_one(K, buf); });
+        };
+        typedef std::integral_constant<int, 0> First;
+        typedef std::integral_constant<int, HALF> Half;
+        typedef std::integral_constant<int, L> Last;
+        // (F: the set that holds the stage's first group; pending: the stage before this one has loads left)
+        auto stage = [&](auto F, auto FULL, bool pending, int s) __attribute__((always_inline)) {
+            constexpr int f = decltype(F)::value;
+            constexpr bool full = decltype(FULL)::value;
+            const uint32_t nxt = cur + 1 == S ? 0 : cur + 1;
+            const bool more = full || s + S < steps;
+            constexpr int last = G == 2 ? f ^ 1 : f;
+            if constexpr (G == 2) {
+                // (the first group has long landed; waited for behind the second's request, both would be)
+                __builtin_amdgcn_s_waitcnt(0xc07f);
+                read_group(std::integral_constant<int, last>(), Set1(), cur);
+                __builtin_amdgcn_sched_barrier(0);
+                const uint32_t before = cur == 0 ? S - 1 : cur - 1;
+                multiply(F, [&](auto I) __attribute__((always_inline)) {
+                    if (pending) loads(Half(), Last(), I, before);
+                });
+                if (pending) advance();
+                __builtin_amdgcn_sched_barrier(0);
+            }
+            if (full || s + 1 < steps) {
+                if (more || s + S == steps) cl_wait<(S - 2) * L>();
+                else wait_loads(steps - 2 - s);
+                cl_barrier();
+                read_group(std::integral_constant<int, last ^ 1>(), Set0(), nxt);
+            }
+            __builtin_amdgcn_sched_barrier(0);
+            multiply(std::integral_constant<int, last>(), [&](auto I) __attribute__((always_inline)) {
+                if (more) loads(First(), Half(), I, cur);
+            });
+            __builtin_amdgcn_sched_barrier(0);
+            if (G == 1 && more) advance();
+            cur = nxt;
+        };
+        int s = 0;
+        if constexpr (G == 2) {
+            bool pending = S < steps;
+            stage(Set0(), std::false_type(), false, 0);
+            for (s = 1; s + S < steps; ++s) stage(Set0(), std::true_type(), true, s);
+            for (; s < steps; ++s) {
+                stage(Set0(), std::false_type(), pending, s);
+                pending = false;
+            }
+        } else {
+            for (; s + 1 + S < steps; s += 2) {
+                stage(Set0(), std::true_type(), false, s);
+                stage(Set1(), std::true_type(), false, s + 1);
+            }
+            for (; s < steps; s += 2) {
+                stage(Set0(), std::false_type(), false, s);
+                if (s + 1 < steps) stage(Set1(), std::false_type(), false, s + 1);
+            }
+        }
+        // An infinity or a NaN among the operands, or parts beyond the range, leave sums that are not finite: a tile
+        // with such sums is done again with fp32 products, and they take what these give.
+        // (Channels behind the last one have weights that nobody wrote.)
+        float seen = 0.0f;
+        auto look = [&](auto ALL) __attribute__((always_inline)) {
+#pragma unroll
+            for (int mi = 0; mi < AM; ++mi)
+#pragma unroll
+                for (int ni = 0; ni < AN; ++ni)
+#pragma unroll
+                    for (int i = 0; i < 16; ++i) {
+                        const bool live = decltype(ALL)::value || m0 + wm * 32 * AM + mi * 32 + (i >> 2) * 8 + fk * 4 + (i & 3) < a.cout;
+                        seen = fmaf(live ? acc[mi][ni][i] : 0.0f, 0.0f, seen);
+                    }
+        };
+        if (m0 + TM <= a.cout) look(std::true_type());
+        else look(std::false_type());
+        if (__ballot(!(seen == 0.0f)) != 0 && lane == 0) *odd = 1;
+        __syncthreads();
+        if (__builtin_amdgcn_readfirstlane(*odd)) {
+            if (KG > 1 && s_first < a.steps) {
+                va = (uint32_t)(lane * 16);
+                va_last = LA * 4 > MI * WB / 1024 && LA * 4 - 4 + wv >= MI * WB / 1024 ? kClOutOfRange : va;
+            }
+            start_weights();
+            start_sources();
+            start_walk();
+            cl_f16v kept[AM][AN];
+#pragma unroll
+            for (int mi = 0; mi < AM; ++mi)
+#pragma unroll
+                for (int ni = 0; ni < AN; ++ni) kept[mi][ni] = acc[mi][ni];
+            clear_sums();
+            for (int s2 = 0; s2 < steps; ++s2) {
+                cl_static_for<0, L>([&](auto I) __attribute__((always_inline)) { issue_one(I, 0u); });
+                advance();
+                cl_wait<0>();
+                cl_barrier();
+                cl_static_for<0, G>([&](auto GRP) __attribute__((always_inline)) {
+                    read_group(Set0(), GRP, 0);
+#pragma unroll
+                    for (int i = 0; i < 8; ++i)
+#pragma unroll
+                        for (int mi = 0; mi < AM; ++mi) {
+                            auto part = [&](int p) __attribute__((always_inline)) {
+                                const uint32_t two = af[0][p][mi][i / 2];
+                                return __uint_as_float(i % 2 ? two & 0xffff0000u : two << 16);
+                            };
+                            const float w = part(0) + (part(1) + part(2));
+#pragma unroll
+                            for (int ni = 0; ni < AN; ++ni)
+                                acc[mi][ni] = __builtin_amdgcn_mfma_f32_32x32x2f32(w, __uint_as_float(bf[0][i / 4][ni][i % 4]), acc[mi][ni], 0, 0, 0);
+                        }
+                });
+                cl_wait<0>();
+                cl_barrier();
+            }
+#pragma unroll
+            for (int mi = 0; mi < AM; ++mi)
+#pragma unroll
+                for (int ni = 0; ni < AN; ++ni)
+#pragma unroll
+                    for (int i = 0; i < 16; ++i)
+                        if (kept[mi][ni][i] * 0.0f == 0.0f) acc[mi][ni][i] = kept[mi][ni][i];
+        }
     }
     asm volatile("s_waitcnt vmcnt(0)" ::: "memory");        // (the bias and the residual's rows)
     if (tid < TM) bl[tid] = my_bias + my_bias2;
+    // ---- the groups' sums: each keeps one half of every block's (channels 16 kg and up of its 32) and gives away the other,
+    //      the first group's part of K added first
+    constexpr int PER = 16 / KG;                    // sums of a block that a thread keeps
+    float sum[C::KEPT];
+    if constexpr (KG == 1) {
+#pragma unroll
+        for (int i = 0; i < C::KEPT; ++i) sum[i] = acc[i / 16 / AN][i / 16 % AN][i % 16];
+    } else {
+        float* const swap = (float*)(cl_smem + TN * PITCH);
+        __syncthreads();                            // the stage buffers are free: every wave is past its last read
+        auto give = [&](auto MINE) __attribute__((always_inline)) {
+            constexpr int mine = decltype(MINE)::value;
+#pragma unroll
+            for (int i = 0; i < C::KEPT; ++i) {
+                const cl_f16v& block = acc[i / PER / AN][i / PER % AN];
+                sum[i] = block[mine * PER + i % PER];
+                swap[i * 512 + tid] = block[(1 - mine) * PER + i % PER];
+            }
+        };
+        if (kg == 0) give(std::integral_constant<int, 0>());
+        else give(std::integral_constant<int, 1>());
+        __syncthreads();
+#pragma unroll
+        for (int i = 0; i < C::KEPT; ++i) {
+            const float other = swap[i * 512 + (tid ^ 256)];
+            sum[i] = kg == 0 ? sum[i] + other : other + sum[i];
+        }
+    }
     // ---- K split over workgroups: the slices of a tile meet in memory (device-scope accesses go to the level
     //      all dies share; every thread's stores are acknowledged before the arrival is counted)
     if (a.sk > 1) {
         const size_t tile_id = (size_t)nt * a.tiles_m + mt;
         float* mine = a.part + (tile_id * a.sk + z) * (size_t)(TM * TN);
 #pragma unroll
-        for (int mi = 0; mi < MI; ++mi)
-#pragma unroll
-            for (int ni = 0; ni < NI; ++ni)
-#pragma unroll
-                for (int i = 0; i < 16; ++i)
-                    __hip_atomic_store(mine + ((mi * NI + ni) * 16 + i) * 256 + tid, acc[mi][ni][i], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        for (int i = 0; i < C::KEPT; ++i)
+            __hip_atomic_store(mine + i * 256 * KG + tid, sum[i], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
         asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
         __syncthreads();
         int* flag = (int*)cl_smem;
@@ -432,56 +707,49 @@ __global__ __launch_bounds__(256, MI * NI == 1 ? 4 : 2) void cl_conv_kernel(cons
         __syncthreads();
         if (!last) return;
 #pragma unroll
-        for (int mi = 0; mi < MI; ++mi)
-#pragma unroll
-            for (int ni = 0; ni < NI; ++ni)
-#pragma unroll
-                for (int i = 0; i < 16; ++i) acc[mi][ni][i] = 0.0f;
+        for (int i = 0; i < C::KEPT; ++i) sum[i] = 0.0f;
         for (int k = 0; k < a.sk; ++k) {
             const float* src = a.part + (tile_id * a.sk + k) * (size_t)(TM * TN);
 #pragma unroll
-            for (int mi = 0; mi < MI; ++mi)
-#pragma unroll
-                for (int ni = 0; ni < NI; ++ni)
-#pragma unroll
-                    for (int i = 0; i < 16; ++i)
-                        acc[mi][ni][i] += __hip_atomic_load(src + ((mi * NI + ni) * 16 + i) * 256 + tid, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+            for (int i = 0; i < C::KEPT; ++i)
+                sum[i] += __hip_atomic_load(src + i * 256 * KG + tid, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
         }
     }
 
-    // ---- epilogue.  Lane l holds, per accumulator, pixel l % 32 and channels 8 g + 4 (l / 32) + i, g, i < 4.
-    __syncthreads();                        // the stage buffers are free: every wave is past its last read
+    // ---- epilogue.  Lane l holds, per accumulator, pixel l % 32 and channels 8 g + 4 (l / 32) + i, g, i < 4 (of two
+    //      groups, the first has those of g < 2).
+    if (KG == 1) __syncthreads();           // the stage buffers are free: every wave is past its last read
     const __amdgpu_buffer_rsrc_t yrs = __builtin_amdgcn_make_buffer_rsrc((void*)a.y, 0, a.yt.span, 0x00020000);
     if constexpr (PLANES) {
 #pragma unroll
-        for (int ni = 0; ni < NI; ++ni) {
-            const int4 e = ptab[wn * 32 * NI + ni * 32 + l31];
+        for (int ni = 0; ni < AN; ++ni) {
+            const int4 e = ptab[wn * 32 * AN + ni * 32 + l31];
 #pragma unroll
-            for (int mi = 0; mi < MI; ++mi) {
-                const int cl = wm * 32 * MI + mi * 32 + fk * 4;
-                uint32_t off[16];
-                float v[16];
+            for (int mi = 0; mi < AM; ++mi) {
+                const int cl = wm * 32 * AM + mi * 32 + kg * (32 / KG) + fk * 4;
+                uint32_t off[PER];
+                float v[PER];
 #pragma unroll
-                for (int i = 0; i < 16; ++i) {
+                for (int i = 0; i < PER; ++i) {
                     const int ch = cl + (i >> 2) * 8 + (i & 3);
                     const bool live = m0 + ch < a.cout && e.z != (int)kClOutOfRange;
                     off[i] = live ? (uint32_t)(e.z + (m0 + ch) * a.plane) : kClOutOfRange;
-                    v[i] = acc[mi][ni][i] + bl[ch];
+                    v[i] = sum[(mi * AN + ni) * PER + i] + bl[ch];
                 }
                 if (a.res) {
-                    T r[16];
+                    T r[PER];
 #pragma unroll
-                    for (int i = 0; i < 16; ++i) {
+                    for (int i = 0; i < PER; ++i) {
                         const int ch = cl + (i >> 2) * 8 + (i & 3);
                         const uint32_t ro = off[i] == kClOutOfRange ? kClOutOfRange : (uint32_t)(e.w + (m0 + ch) * a.plane);
                         if constexpr (sizeof(T) == 2) r[i] = __builtin_bit_cast(T, (uint16_t)__builtin_amdgcn_raw_buffer_load_b16(rrs, ro, 0u, 0));
                         else r[i] = __builtin_bit_cast(T, (uint32_t)__builtin_amdgcn_raw_buffer_load_b32(rrs, ro, 0u, 0));
                     }
 #pragma unroll
-                    for (int i = 0; i < 16; ++i) v[i] += (float)r[i];
+                    for (int i = 0; i < PER; ++i) v[i] += (float)r[i];
                 }
 #pragma unroll
-                for (int i = 0; i < 16; ++i) {
+                for (int i = 0; i < PER; ++i) {
                     const T o = (T)((a.relu && !(v[i] > 0.0f)) ? 0.0f : v[i]);
                     if constexpr (sizeof(T) == 2) __builtin_amdgcn_raw_buffer_store_b16(__builtin_bit_cast(uint16_t, o), yrs, off[i], 0u, 0);
                     else __builtin_amdgcn_raw_buffer_store_b32(__builtin_bit_cast(uint32_t, o), yrs, off[i], 0u, 0);
@@ -493,23 +761,23 @@ __global__ __launch_bounds__(256, MI * NI == 1 ? 4 : 2) void cl_conv_kernel(cons
     if (a.res) {
 #pragma unroll
         for (int k = 0; k < ITEMS; ++k) {
-            if constexpr (EARLY) *(cl_u4*)(cl_smem + (ep + k * (256 / CPR)) * PITCH + ec * 16) = resv[k];
-            else *(cl_u4*)(cl_smem + (ep + k * (256 / CPR)) * PITCH + ec * 16) = res_load(k);
+            if constexpr (EARLY) *(cl_u4*)(cl_smem + (ep + k * (256 * KG / CPR)) * PITCH + ec * 16) = resv[k];
+            else *(cl_u4*)(cl_smem + (ep + k * (256 * KG / CPR)) * PITCH + ec * 16) = res_load(k);
         }
         __syncthreads();
     }
 #pragma unroll
-    for (int ni = 0; ni < NI; ++ni)
+    for (int ni = 0; ni < AN; ++ni)
 #pragma unroll
-        for (int mi = 0; mi < MI; ++mi)
+        for (int mi = 0; mi < AM; ++mi)
 #pragma unroll
-            for (int g = 0; g < 4; ++g) {
-                const int ch = wm * 32 * MI + mi * 32 + g * 8 + fk * 4;
-                char* at = cl_smem + (wn * 32 * NI + ni * 32 + l31) * PITCH + ch * (int)sizeof(T);
+            for (int g = 0; g < 4 / KG; ++g) {
+                const int ch = wm * 32 * AM + mi * 32 + kg * (32 / KG) + g * 8 + fk * 4;
+                char* at = cl_smem + (wn * 32 * AN + ni * 32 + l31) * PITCH + ch * (int)sizeof(T);
                 const cl_f4 b = *(const cl_f4*)(bl + ch);
                 float v[4];
 #pragma unroll
-                for (int i = 0; i < 4; ++i) v[i] = acc[mi][ni][g * 4 + i] + b[i];
+                for (int i = 0; i < 4; ++i) v[i] = sum[(mi * AN + ni) * PER + g * 4 + i] + b[i];
                 if constexpr (sizeof(T) == 2) {
                     if (a.res) {
                         const cl_h4 r = *(const cl_h4*)at;
@@ -535,7 +803,7 @@ __global__ __launch_bounds__(256, MI * NI == 1 ? 4 : 2) void cl_conv_kernel(cons
     __syncthreads();
 #pragma unroll
     for (int k = 0; k < ITEMS; ++k) {
-        const int p = ep + k * (256 / CPR);
+        const int p = ep + k * (256 * KG / CPR);
         const int yo = ptab[p].z;
         const uint32_t off = (ec_live && yo != (int)kClOutOfRange) ? (uint32_t)(yo + m0 * (int)sizeof(T) + ec * 16) : kClOutOfRange;
         const cl_u4 v = *(const cl_u4*)(cl_smem + p * PITCH + ec * 16);
@@ -543,24 +811,25 @@ __global__ __launch_bounds__(256, MI * NI == 1 ? 4 : 2) void cl_conv_kernel(cons
     }
 }
 
-template <typename T, int RB, int MI, int NI, int S, int MODE>
+template <typename T, int RB, int MI, int NI, int S, int KG, int MODE>
 hipError_t launch_cl_tile(const ClArgs& a, hipStream_t s) {
-    using C = ClCfg<T, RB, MI, NI, S>;
+    using C = ClCfg<T, RB, MI, NI, S, KG>;
     // (more than 64 KB of dynamic LDS has to be asked for once per kernel)
     static const hipError_t attr = C::LDS <= 65536 ? hipSuccess
-                                                   : hipFuncSetAttribute((const void*)cl_conv_kernel<T, RB, MI, NI, S, MODE>,
+                                                   : hipFuncSetAttribute((const void*)cl_conv_kernel<T, RB, MI, NI, S, KG, MODE>,
                                                                          hipFuncAttributeMaxDynamicSharedMemorySize, C::LDS);
     if (attr != hipSuccess) return attr;
     const unsigned grid = (unsigned)((a.tiles + 7) / 8 * 8);
-    CADNN_LAUNCH((cl_conv_kernel<T, RB, MI, NI, S, MODE>), dim3(grid), dim3(256), (size_t)C::LDS, s, a);
+    CADNN_LAUNCH((cl_conv_kernel<T, RB, MI, NI, S, KG, MODE>), dim3(grid), dim3(256 * KG), (size_t)C::LDS, s, a);
     return hipGetLastError();
 }
 
 template <typename T, int RB, int MODE>
 hipError_t launch_cl_rb(const ClArgs& a, const ClVariant& v, hipStream_t s) {
-    if (v.mi == 2) return v.ni == 2 ? launch_cl_tile<T, RB, 2, 2, 2, MODE>(a, s) : launch_cl_tile<T, RB, 2, 1, 3, MODE>(a, s);
-    if (v.ni == 2) return launch_cl_tile<T, RB, 1, 2, 3, MODE>(a, s);
-    return v.s == 3 ? launch_cl_tile<T, RB, 1, 1, 3, MODE>(a, s) : launch_cl_tile<T, RB, 1, 1, 4, MODE>(a, s);
+    if (v.kg == 2) return v.ni == 2 ? launch_cl_tile<T, RB, 1, 2, 2, 2, MODE>(a, s) : launch_cl_tile<T, RB, 1, 1, 3, 2, MODE>(a, s);
+    if (v.mi == 2) return v.ni == 2 ? launch_cl_tile<T, RB, 2, 2, 2, 1, MODE>(a, s) : launch_cl_tile<T, RB, 2, 1, 3, 1, MODE>(a, s);
+    if (v.ni == 2) return launch_cl_tile<T, RB, 1, 2, 3, 1, MODE>(a, s);
+    return v.s == 3 ? launch_cl_tile<T, RB, 1, 1, 3, 1, MODE>(a, s) : launch_cl_tile<T, RB, 1, 1, 4, 1, MODE>(a, s);
 }
 
 template <typename T, int MODE>
@@ -584,8 +853,10 @@ ClTensorArg tensor_arg(const ClDesc& d, int n, size_t e, int stride, int r0, int
 
 const std::vector<ClVariant>& all_cl_variants() {
     static const std::vector<ClVariant> v = {
-        {"cl_mfma_128x128_s2", 2, 2, 2, 1}, {"cl_mfma_128x64_s3", 2, 1, 3, 1}, {"cl_mfma_64x128_s3", 1, 2, 3, 1}, {"cl_mfma_64x64_s3", 1, 1, 3, 1},
-        {"cl_mfma_64x64_s4", 1, 1, 4, 1}, {"cl_mfma_64x64_s3k2", 1, 1, 3, 2}, {"cl_mfma_64x64_s3k4", 1, 1, 3, 4}, {"cl_mfma_64x64_s4k4", 1, 1, 4, 4},
+        {"cl_mfma_128x128_s2", 2, 2, 2, 1, 1}, {"cl_mfma_128x64_s3", 2, 1, 3, 1, 1}, {"cl_mfma_64x128_s3", 1, 2, 3, 1, 1},
+        {"cl_mfma_64x64_s3", 1, 1, 3, 1, 1}, {"cl_mfma_64x64_s4", 1, 1, 4, 1, 1}, {"cl_mfma_64x64_s3k2", 1, 1, 3, 2, 1},
+        {"cl_mfma_64x64_s3k4", 1, 1, 3, 4, 1}, {"cl_mfma_64x64_s4k4", 1, 1, 4, 4, 1}, {"cl_mfma_64x64_s3g2", 1, 1, 3, 1, 2},
+        {"cl_mfma_64x64_s3g2k2", 1, 1, 3, 2, 2}, {"cl_mfma_64x64_s3g2k4", 1, 1, 3, 4, 2}, {"cl_mfma_64x128_s2g2", 1, 2, 2, 1, 2},
     };
     return v;
 }
@@ -600,10 +871,10 @@ bool cl_variant_fits(const ClVariant& v, const ClPlan& plan, int64_t pixels, int
     if (v.mi == 2 && cout <= 64) return false;
     if (cl_tiles(v, pixels, cout) * v.sk >= (1 << 28)) return false;
     if (pixels >= (1 << 30)) return false;      // (32-bit pixel arithmetic)
-    if (v.sk == 1) return true;
+    const int slices = v.sk * v.kg, per = (plan.steps + slices - 1) / slices;
+    if (v.sk == 1) return v.kg == 1 || plan.steps >= 2 * v.kg;
     // every slice gets at least two steps and none is empty; the scratch stays below 256 MiB
-    const int per = (plan.steps + v.sk - 1) / v.sk;
-    if (per < 2 || (v.sk - 1) * per >= plan.steps) return false;
+    if (per < 2 || (slices - 1) * per >= plan.steps) return false;
     const int64_t tiles = cl_tiles(v, pixels, cout);
     return tiles <= 512 && tiles * v.sk * v.mi * v.ni * 16384 <= (256ll << 20);
 }
@@ -636,26 +907,48 @@ cadnn_status cl_prepare_variant(const ClVariant& v, ClPlan* plan, int64_t pixels
 // a CU (LDS, and the registers the kernel is bound to), each with a start and an end that grow with the tile and
 // with how many run at once, and steps that take a fixed time while a workgroup has the CU to itself
 // (the latency of loads that run two stages ahead) and the CU's rate when it does not.  The
-// constants are fitted to the times of every variant on 387 layers (ResNet-50 at 1, 8, 16 and 32 images, MobileNet-V2
-// at 16, VGG-16 at 1, Inception-V3 at 4 in fp16, ResNet-50 at 4 and 8 in fp32): the tiles it takes are 1.7 % slower in sum than each layer's
-// best (one ResNet-50 image 0.9 %; with constants from 116 of these layers 2.5 % and 4 %: 332 -> 317 us a pass).
-// Splitting K of the larger tiles, or in eight, wins none or three of the 387.  Four stages pay where workgroups are alone or two to a CU and the K loop is long (at one ResNet-50 image:
-// 18 steps 10.9 -> 9.7 us); there is no use for more stages: six and eight measured the same.
+// constants are fitted to the times of every variant, in fp16 on 387 layers (ResNet-50 at 1, 8, 16 and 32 images, MobileNet-V2
+// at 16, VGG-16 at 1, Inception-V3 at 4), the tiles taken 1.7 % slower in sum than each layer's best; in fp32 on 190 layers (ResNet-50 at 1, 2,
+// 4, 8, VGG-16 at 1 and 2, Inception-V3 at 1 and 3, both MobileNets): 0.3 %, against 8.1 % with constants from fp32 products.
+// Two groups of waves pay in fp32 where a workgroup has the CU to itself: 128 -> 128 3x3 on 8 images of 28 x 28 19.2 -> 16.9 us,
+// 512 -> 512 3x3 on 14 x 14 (split in four as well) 20.8 -> 17.9.  In fp16 a step is bound by the way into LDS, and what
+// they gain on such a layer (7.3 -> 6.5 us launched on its own) is lost again between the launches of a graph: ResNet-50 at 8 images 426 -> 435 us a
+// pass.  Four stages pay where workgroups are alone or two to a CU and the K loop is long; there is no use for more: six and eight
+// measured the same.
+struct ClCost {
+    double matrix, bytes;           // the CU's rate: clocks of a 64 x 64 tile's step of 128 bytes, bytes a clock
+    double alone3, alone4, wider;   // a step alone on the CU, with three and four stages; how it grows with the tile
+    double narrow;                  // ... and shrinks with the step
+    double start, tile;             // of a round, of every workgroup of it and 64 x 64 tile
+    double split, slice;            // K split over workgroups
+    double group_step, group_tile, group;       // two groups of waves
+};
+
 const ClVariant* cl_pick(int cout, const ClPlan& plan, int64_t pixels, bool f16) {
+    static const ClCost cost16 = {21.5, 47, 642, 630, 0.25, 0, 367, 3370, 4960, 871, 1, 1, 0};
+    static const ClCost cost32 = {146, 27.8, 934, 1609, 1.83, 0.32, 172, 4055, 2557, 1246, 1.06, 1.08, 446};
+    const ClCost& k = f16 ? cost16 : cost32;
     const ClVariant* best = nullptr;
     double best_cost = 0.0;
     for (const ClVariant& v : all_cl_variants()) {
         if (!cl_variant_fits(v, plan, pixels, cout)) continue;
         const int64_t blocks = cl_tiles(v, pixels, cout) * v.sk;
-        const int steps = (plan.steps + v.sk - 1) / v.sk;
+        const int slices = v.sk * v.kg, steps = (plan.steps + slices - 1) / slices;
         if (v.s == 4 && (blocks > 2 * kNumCus || steps < 4)) continue;
-        const int size = v.mi * v.ni, bytes = 64 * (v.mi + v.ni) * plan.rb;
-        const int64_t per_cu = std::min<int64_t>(kLdsPerCu / (v.s * bytes), size == 1 ? 4 : 2);
-        const double rate = std::max((f16 ? 21.5 : 211.0) * size * plan.rb / 128.0, bytes / 47.0);
-        const double alone = std::max(rate, (v.s == 4 ? 630.0 : 642.0) * (1.0 + 0.25 * (size - 1)));
-        auto round = [&](int64_t n) { return n == 0 ? 0.0 : 367.0 + 3370.0 * size * (double)n + steps * std::max(alone, rate * (double)n); };
+        if (v.kg == 2 && f16) continue;
+        const int size = v.mi * v.ni, weights = cl_weight_bytes(plan.rb, f16 ? 2 : 4);
+        const int stage = (v.mi * weights * 64 + 4095) / 4096 * 4096 + 64 * v.ni * plan.rb;
+        const int lds = v.kg * v.s * stage + 64 * v.ni * 16 + 64 * v.mi * 4 + 16;
+        const int64_t per_cu = std::min<int64_t>(kLdsPerCu / lds, (size == 1 ? 4 : 2) / v.kg);
+        const double rate = std::max(k.matrix * size * v.kg * plan.rb / 128.0, 64 * (v.mi * weights + v.ni * plan.rb) * v.kg / k.bytes);
+        const double alone = std::max(rate, (v.s == 4 ? k.alone4 : k.alone3) * (1.0 + k.wider * (size - 1)) * std::pow(plan.rb / 128.0, k.narrow) *
+                                                (v.kg == 2 ? k.group_step : 1.0));
+        auto round = [&](int64_t n) {
+            return n == 0 ? 0.0 : k.start + k.tile * size * (double)n * (v.kg == 2 ? k.group_tile : 1.0) + steps * std::max(alone, rate * (double)n);
+        };
         const int64_t in_cu = (blocks + kNumCus - 1) / kNumCus;
-        const double cost = (double)(in_cu / per_cu) * round(per_cu) + round(in_cu % per_cu) + (v.sk > 1 ? 4960.0 + 871.0 * v.sk : 0.0);
+        const double cost = (double)(in_cu / per_cu) * round(per_cu) + round(in_cu % per_cu) + (v.sk > 1 ? k.split + k.slice * v.sk : 0.0) +
+                            (v.kg == 2 ? k.group : 0.0);
         if (!best || cost < best_cost) { best = &v; best_cost = cost; }
     }
     return best;
@@ -693,7 +986,7 @@ cadnn_status launch_cl_conv(const ClConv& c, const ClVariant& v, bool f16, hipSt
     a.ntaps = p.taps;
     a.row_bytes = p.stem ? p.row_bytes : p.rb;
     a.tiles = (int)cl_tiles(v, a.total, c.cout) * v.sk;
-    a.per_slice = (p.steps + v.sk - 1) / v.sk;
+    a.per_slice = (p.steps + v.sk * v.kg - 1) / (v.sk * v.kg);
     a.per_die = (a.tiles + 7) / 8;
     auto magic = [](int d) { return (uint32_t)(((1ull << 32) + (uint64_t)d - 1) / (uint64_t)d); };
     a.magic_hw = magic(a.hw);
@@ -763,37 +1056,52 @@ cadnn_status cl_plan_shape(const cadnn_weights* w, const cadnn_weights* shortcut
     return CADNN_OK;
 }
 
-cadnn_status cl_build_plan(const cadnn_weights* w, const cadnn_weights* shortcut, int rb, bool stem, ClPlan* plan) {
+cadnn_status cl_build_plan(const cadnn_weights* w, const cadnn_weights* shortcut, int rb, bool stem, ClPlan* plan, std::vector<char>* image) {
     const size_t e = w->elem();
     const int taps_all = w->kh * w->kw, kpr = rb / (int)e;
     std::vector<int> tap_index;
     const cadnn_status st = cl_plan_shape(w, shortcut, rb, stem, plan, &tap_index);
     if (st != CADNN_OK) return st;
-    const size_t blocks = (size_t)(w->cout + 127) / 128 * 2;    // (64-row blocks, whole 128-row tiles)
-    const size_t bytes = blocks * (size_t)plan->steps * 64 * (size_t)rb;
-    if (bytes >= 0x7ffffff0ull) return fail(CADNN_EUNSUPPORTED, "cadnn_net: weight matrix of 2 GiB or more");
-    std::vector<char> img(bytes, 0);
-    const int pieces = rb / 16, epp = 16 / (int)e;
-    auto put = [&](int co, int step, int k, const cadnn_weights* src, size_t j) {
-        const int r = co % 64, sw = rb == 128 ? (r >> 1) & 7 : (r >> 2) & 3;
-        const size_t at = (((size_t)(co / 64) * plan->steps + (size_t)step) * 64 + (size_t)r) * (size_t)rb +
-                          (size_t)(((k / epp) % pieces) ^ sw) * 16 + (size_t)(k % epp) * e;
-        if (e == 2) std::memcpy(&img[at], &src->vals16[j], 2);
-        else std::memcpy(&img[at], &src->vals[j], 4);
+    const size_t row_bytes = (size_t)cl_weight_bytes(rb, (int)e), bytes = cl_plan_bytes(w->cout, *plan, (int)e);
+    if (bytes >= kClMaxWeightBytes) return fail(CADNN_EUNSUPPORTED, "cadnn_net: weight matrix of 2 GiB or more");
+    image->assign(bytes, 0);
+    char* const img = image->data();
+    // where k lies in the rows of block 0 (row 0's place of it): the divisions once per k and not once per weight
+    std::vector<size_t> place;
+    auto in_step = [&](int step, int k) {
+        const size_t at = (size_t)step * 64 * row_bytes;
+        return e == 4 ? at + (size_t)cl_split_offset(k, 0, 0) : at + (size_t)k * 2;
     };
-    for (int i = 0; i < w->cout; ++i)
-        for (int32_t j = w->row_ptr[(size_t)i]; j < w->row_ptr[(size_t)i + 1]; ++j) {
-            const int k = w->col_idx[(size_t)j], ci = k / taps_all, t = k - ci * taps_all;
-            if (stem) put(w->perm[(size_t)i], t / w->kw, (t % w->kw) * 4 + ci, w, (size_t)j);
-            else put(w->perm[(size_t)i], tap_index[(size_t)t] * plan->steps_tap + ci / kpr, ci % kpr, w, (size_t)j);
-        }
-    if (shortcut)
-        for (int i = 0; i < shortcut->cout; ++i)
-            for (int32_t j = shortcut->row_ptr[(size_t)i]; j < shortcut->row_ptr[(size_t)i + 1]; ++j) {
-                const int ci = shortcut->col_idx[(size_t)j];
-                put(shortcut->perm[(size_t)i], plan->taps * plan->steps_tap + ci / kpr, ci % kpr, shortcut, (size_t)j);
+    auto put = [&](const cadnn_weights* src) {
+        for (int i = 0; i < src->cout; ++i) {
+            const int co = src->perm[(size_t)i], r = co % 64, sw = rb == 128 ? (r >> 1) & 7 : (r >> 2) & 3;
+            char* const block = img + (size_t)(co / 64) * plan->steps * 64 * row_bytes;
+            for (int32_t j = src->row_ptr[(size_t)i]; j < src->row_ptr[(size_t)i + 1]; ++j) {
+                const size_t at = place[(size_t)src->col_idx[(size_t)j]];
+                if (e == 4) {
+                    uint16_t part[3];
+                    cl_split_weight(src->vals[(size_t)j], part);
+                    uint16_t* const to = (uint16_t*)(block + at + (size_t)r * 16);
+                    for (int p = 0; p < 3; ++p) to[p * 1024] = part[p];
+                } else {
+                    // (a step is a multiple of 128 bytes, so the piece's bits of the sum are those of the place in the row)
+                    std::memcpy(block + (at ^ (size_t)(sw * 16)) + (size_t)r * (size_t)rb, &src->vals16[(size_t)j], 2);
+                }
             }
-    return plan->w.upload(img.data(), img.size());
+        }
+    };
+    place.resize((size_t)w->cin * taps_all);
+    for (int ci = 0; ci < w->cin; ++ci)
+        for (int t = 0; t < taps_all; ++t)
+            place[(size_t)ci * taps_all + t] = stem ? in_step(t / w->kw, t % w->kw * 4 + ci)
+                                                    : in_step(std::max(tap_index[(size_t)t], 0) * plan->steps_tap + ci / kpr, ci % kpr);
+    put(w);
+    if (shortcut) {
+        place.resize((size_t)shortcut->cin);
+        for (int ci = 0; ci < shortcut->cin; ++ci) place[(size_t)ci] = in_step(plan->taps * plan->steps_tap + ci / kpr, ci % kpr);
+        put(shortcut);
+    }
+    return plan->w.upload(img, bytes);
 }
 
 }  // namespace cadnn

@@ -95,13 +95,34 @@ __global__ __launch_bounds__(256) void cl_arrange_kernel(const ClArrange a) {
         if (co >= a.cout) return;
         const int row = co % 64, sw = a.pieces == 8 ? (row >> 1) & 7 : (row >> 2) & 3;
         const int64_t steps = (int64_t)a.taps * a.steps_tap;
-        for (int i = lane; i < a.taps * a.pieces; i += 64) {
-            const int t = i / a.pieces, pc = i - t * a.pieces;
-            V p;
+        if constexpr (sizeof(T) == 4) {
+            // eight k of one half of a wave: 16 bytes of each of the three parts
+            const int halves = a.kpr / 8;
+            for (int i = lane; i < a.taps * halves; i += 64) {
+                const int t = i / halves, h = i - t * halves, k0 = h / 2 * 16 + h % 2 * 4;
+                char* const block = (char*)a.wr + ((co / 64) * steps + (int64_t)t * a.steps_tap + step) * 64 * cl_weight_bytes(a.kpr * 4, 4);
+                uint16_t part[8][3];
 #pragma unroll
-            for (int j = 0; j < N; ++j) p[j] = mine[(pc * N + j) * a.taps + t];
-            const int64_t at = ((co / 64) * steps + (int64_t)t * a.steps_tap + step) * 64 + row;
-            *(V*)((T*)a.wr + at * a.kpr + (pc ^ sw) * N) = p;
+                for (int j = 0; j < 8; ++j) cl_split_weight(mine[(k0 + j / 4 * 8 + j % 4) * a.taps + t], part[j]);
+#pragma unroll
+                for (int p = 0; p < 3; ++p) {
+                    uint4 q;
+                    q.x = part[0][p] | (uint32_t)part[1][p] << 16;
+                    q.y = part[2][p] | (uint32_t)part[3][p] << 16;
+                    q.z = part[4][p] | (uint32_t)part[5][p] << 16;
+                    q.w = part[6][p] | (uint32_t)part[7][p] << 16;
+                    *(uint4*)(block + cl_split_offset(k0, p, row)) = q;
+                }
+            }
+        } else {
+            for (int i = lane; i < a.taps * a.pieces; i += 64) {
+                const int t = i / a.pieces, pc = i - t * a.pieces;
+                V p;
+#pragma unroll
+                for (int j = 0; j < N; ++j) p[j] = mine[(pc * N + j) * a.taps + t];
+                const int64_t at = ((co / 64) * steps + (int64_t)t * a.steps_tap + step) * 64 + row;
+                *(V*)((T*)a.wr + at * a.kpr + (pc ^ sw) * N) = p;
+            }
         }
     }
 }
@@ -243,7 +264,7 @@ bool dense_cl_serves(bool f16, int n, int cin, int h, int w, int cout, int kh, i
     const int64_t image = (int64_t)(h + 2 * pad) * (w + 2 * pad) * d.pix;
     if ((int64_t)d.pix * (w + 2 * pad) * (int64_t)e >= limit / 64 || image * (int64_t)e * n >= limit) return false;
     if ((int64_t)n * hw >= (1 << 30) || (int64_t)n * hw * cout * (int64_t)e >= limit) return false;
-    if (padded_rows * kh * kw * d.pix * (int64_t)e >= limit) return false;
+    if (padded_rows * kh * kw * d.pix * (f16 ? 2 : 6) >= limit) return false;      // (three 2-byte parts a 4-byte weight)
     if (f16 && cin % 32 == 0) return true;
     const int64_t blocks = (hw + 63) / 64 * n * ((cout + 63) / 64);
     return ((int64_t)cin * kh * kw + 31) / 32 * ((blocks + 1023) / 1024) > 6;
@@ -269,7 +290,7 @@ cadnn_status dense_cl_conv2d(const void* w_dev, const void* x, void* y, const vo
     const ClVariant* v = cl_pick(cout, plan, pixels, f16);
 
     const size_t x_bytes = align256((size_t)n * (size_t)xd.image * e);
-    c.w_bytes = (size_t)((cout + 127) / 128) * 128 * (size_t)plan.steps * (size_t)plan.rb;
+    c.w_bytes = cl_plan_bytes(cout, plan, (int)e);
     size_t part = 0, count = 0;
     cl_split_scratch(*v, pixels, cout, &part, &count);
     Workspace block;

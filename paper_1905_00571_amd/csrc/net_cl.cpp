@@ -211,6 +211,15 @@ std::unique_ptr<ClNet> cl_layout(const cadnn_net* net) {
             if (o.res_inst < 0 && cl->import_at < 0) cl->import_at = k;
         }
     }
+    for (int k = 0; k < nops && fits; ++k) {
+        const NetOp& o = net->ops[(size_t)k];
+        if (o.kind != OP_CONV || cl->ops[(size_t)k]->fused_into >= 0) continue;
+        const NetOp* p = shortcut_op(net, *cl->ops[(size_t)k]);
+        const int rb = step_bytes(net, *cl, (size_t)k);
+        ClPlan shape;
+        fits = cl_plan_shape(o.w, p ? p->w : nullptr, rb, cl->ops[(size_t)k]->x_stem, &shape) != CADNN_OK ||
+               cl_plan_bytes(o.w->cout, shape, (int)e) < kClMaxWeightBytes;
+    }
     if (!fits) return nullptr;
     cl->ws_bytes = off;
     return cl;
@@ -246,6 +255,7 @@ bool cl_expected_faster(const cadnn_net* net) {
 
 cadnn_status cl_prepare(cadnn_net* net) {
     const size_t e = net->elem();
+    std::vector<char> image;
     for (size_t i = 0; i < net->ops.size(); ++i) {
         const NetOp& op = net->ops[i];
         ClOp& c = *net->cl->ops[i];
@@ -266,7 +276,7 @@ cadnn_status cl_prepare(cadnn_net* net) {
         if (op.kind == OP_CONV && c.fused_into < 0) {
             const NetOp* p = shortcut_op(net, c);
             try {
-                if (!c.plan.w.p) st = cl_build_plan(op.w, p ? p->w : nullptr, step_bytes(net, *net->cl, i), c.x_stem, &c.plan);
+                if (!c.plan.w.p) st = cl_build_plan(op.w, p ? p->w : nullptr, step_bytes(net, *net->cl, i), c.x_stem, &c.plan, &image);
             } catch (const std::bad_alloc&) {
                 st = fail(CADNN_ENOMEM, "out of host memory building a conv plan");
             }

@@ -217,6 +217,40 @@ def test_first_layer_reads_nothing_outside_its_windows(cad, k, stride, pad, h, w
     net.free()
 
 
+@pytest.mark.parametrize("cin,cout,k,hw", [(8, 40, 3, 9), (64, 136, 1, 13), (96, 72, 3, 10), (160, 264, 3, 6)])
+def test_fp32_products_of_extreme_values(cad, cin, cout, k, hw):
+    """fp32 storage with every tile: infinities and NaN where 64-bit arithmetic has them (no filter has a zero), and values
+    next to the largest and far below one to the accuracy of fp32 sums of K products, (K + 3) 2^-24 (sum |w| |x| + |b|),
+    in pixels beside the others as well."""
+    rng = np.random.default_rng(cin)
+    pad, n = k // 2, 2
+    x = rng.standard_normal((n, cin, hw, hw)).astype(np.float32)
+    x[0, 1, 0, 0], x[0, cin - 1, 0, hw - 1], x[0, 0, hw - 1, 0] = np.inf, -np.inf, np.nan
+    x[1, :, : hw // 2] *= np.float32(1e-30)
+    x[1, 3, hw - 1, hw - 1], x[1, 2, hw - 1, 0] = np.finfo(np.float32).max, np.float32(-3.395e38)
+    w = (rng.choice([-1.0, 1.0], (cout, cin, k, k)) * rng.uniform(0.1, 1.0, (cout, cin, k, k)) / (cin * k * k)).astype(np.float32)
+    b = np.zeros(cout, np.float32)
+    ops = [Op("conv", "a", 0, 1, cin, cout, k, 1, pad, 0.0, False), Op("conv", "b", 1, 2, cout, 8, 1, 1, 0, 0.5, False)]
+    _, ws, bs = wl.net_tensors(ops, "extreme", x.shape)
+    ws[0], bs[0] = w, b
+    conv = torch.nn.functional.conv2d
+    ref = conv(torch.from_numpy(x).double(), torch.from_numpy(w).double(), None, 1, pad).numpy()
+    size = conv(torch.from_numpy(x).double().abs(), torch.from_numpy(w).double().abs(), None, 1, pad).numpy()
+    finite = np.isfinite(ref)
+    assert not finite.all() and np.isinf(ref).any() and np.isnan(ref).any()
+    net = cad.build_net(ops, ws, bs, x.shape, cad.F32, use_graph=False)
+    net.set_op_variant(0, "cl_mfma_64x64_s3")
+    for name in net.op_candidates(0):
+        net.set_op_variant(0, name)
+        net.run(torch.from_numpy(x).cuda())
+        torch.cuda.synchronize()
+        got = net.read_buffer(1, ref.shape)
+        assert np.array_equal(got[~finite], ref[~finite].astype(np.float32), equal_nan=True), name
+        excess = (np.abs(got.astype(np.float64) - ref) - (cin * k * k + 3) * 2.0 ** -24 * size)[finite]
+        assert excess.max() <= 0.0, f"{name}: {excess.max():.3e} above the bound"
+    net.free()
+
+
 @pytest.mark.parametrize("dtype_name", ["f32", "f16"])
 @pytest.mark.parametrize("k,pad", [(1, 0), (2, 0), (2, 1), (3, 1), (3, 0), (5, 2)])
 def test_pools_and_copies_of_non_finite_values(cad, k, pad, dtype_name):
