@@ -18,7 +18,7 @@ INCLUDE = os.path.join(ROOT, "include")
 OBJDIR = os.path.join(ROOT, "_build")
 LIB = os.path.join(HERE, "libcadnn.so")
 
-SOURCES = ["pack.cpp", "api.cpp", "net.cpp", "net_cl.cpp", "conv_tile.hip", "conv_direct.hip", "conv_linear.hip", "conv_quad.hip", "conv_stile.hip", "conv_ptile.hip", "conv_wtile.hip", "conv_depthwise.hip", "misc_kernels.hip", "dense_conv.hip", "dense_wide.hip", "conv_cl.hip", "dense_cl.hip", "channels_last_ops.hip"]
+SOURCES = ["pack.cpp", "api.cpp", "net.cpp", "net_cl.cpp", "conv_tile.hip", "conv_direct.hip", "conv_linear.hip", "conv_quad.hip", "conv_stile.hip", "conv_ptile.hip", "conv_wtile.hip", "conv_depthwise.hip", "misc_kernels.hip", "dense_conv.hip", "dense_wide.hip", "conv_cl.hip", "conv_cl_small.hip", "dense_cl.hip", "channels_last_ops.hip"]
 
 HIPCC = os.environ.get("HIPCC", "/opt/rocm/bin/hipcc")
 FLAGS = [
@@ -47,7 +47,7 @@ ASAN_LIB = os.path.join(ASAN_OBJDIR, "libcadnn_asan.so")
 def _compile(src: str, force: bool, asan: bool = False) -> str:
     path = os.path.join(CSRC, src)
     obj = os.path.join(ASAN_OBJDIR if asan else OBJDIR, src + ".o")
-    deps = [path, os.path.join(CSRC, "internal.h"), os.path.join(CSRC, "channels_last.h"), os.path.join(CSRC, "net.h"), os.path.join(INCLUDE, "cadnn.h")]
+    deps = [path, os.path.join(CSRC, "internal.h"), os.path.join(CSRC, "channels_last.h"), os.path.join(CSRC, "conv_cl.h"), os.path.join(CSRC, "net.h"), os.path.join(INCLUDE, "cadnn.h")]
     if not force and _newer(obj, deps):
         return obj
     cmd = [HIPCC, "-x", "hip", "-c", path, "-o", obj] + FLAGS + (ASAN_FLAGS if asan else [])

@@ -39,6 +39,13 @@ constexpr int kClMaxTaps = 64;
 // 4-byte weights are kept as three bf16 numbers whose sum they are (fp32 products on the bf16 matrix
 // pipes): bytes of an output channel's weights in a step of `rb` bytes of activations.
 constexpr int cl_weight_bytes(int rb, int elem) { return elem == 4 ? rb / 4 * 6 : rb; }
+// The row of an output channel in its block of 64: a 32 x 32 product leaves a lane the rows 8 g + 4 h + {0..3} of its
+// column (h the wave's half, g < 4).  These are to be 16 bytes of channels side by side each time, the other half's the next 16: in
+// 4-byte storage they are, in 2-byte storage 4 rows of g and 4 of g + 1 go together.
+inline __host__ __device__ int cl_weight_row(int co, int elem) {
+    const int c = co % 64;
+    return elem == 4 ? c : (c & ~15) | (c & 8) >> 1 | (c & 4) << 1 | (c & 3);
+}
 // Where part p of the weight of k (in the step) and row r (of a block of 64 output channels) lies: by groups of
 // 16 k, parts, wave halves (k = 4 half + {0..3, 8..11} of the group), rows.
 inline __host__ __device__ int cl_split_offset(int k, int p, int r) {
@@ -70,6 +77,8 @@ constexpr size_t kClMaxWeightBytes = 0x7ffffff0u;
 // the 16-byte pieces of a row in the order the kernel keeps them in LDS.
 struct ClPlan {
     DevBuf w;
+    int elem = 2;               // bytes of an activation
+    bool maps = true;           // y and the residual are channels-last tensors
     int rb = 0, steps = 0, steps_tap = 0, taps = 0, steps2 = 0;
     int tap_r[kClMaxTaps], tap_c[kClMaxTaps];
     bool stem = false;          // input packed 4 channels a pixel, a step is one filter row ...
@@ -89,6 +98,9 @@ inline size_t cl_plan_bytes(int cout, const ClPlan& plan, int elem) {
 struct ClVariant {
     const char* name;
     int mi, ni, s, sk, kg;
+    int bm = 0, bn = 0;         // a small tile of 16 bm x 16 bn instead, whose 8 waves share K (2-byte storage)
+    int tm() const { return bm ? 16 * bm : 64 * mi; }
+    int tn() const { return bm ? 16 * bn : 64 * ni; }
 };
 const std::vector<ClVariant>& all_cl_variants();
 

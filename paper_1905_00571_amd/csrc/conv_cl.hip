@@ -25,8 +25,11 @@
 //     At batch 32 the matrix pipes are busy 68 % of the busy CUs' cycles, over all of these launches; L2 hit rate 75 %.
 //   * Padding is a zero halo in memory, so no tap is ever tested.
 //   * A fused 1x1 projection shortcut (paper Section 4, layer fusion) is more K steps on a second tensor.
-//   * The epilogue goes through LDS, [pixel][channel]: residual rows come in and finished rows go out as
-//     16-byte pieces of whole pixels; bias, residual and ReLU in fp32, one rounding.
+//   * The epilogue works on the accumulators where they are: the rows of a block of weights are in an order that leaves a lane
+//     16-byte pieces of its pixel's channels, so residual pieces come in and finished ones go out without a pass through LDS (a
+//     barrier, a write, a barrier and a read less); bias, residual and ReLU in fp32, one rounding.  The first loads wait for nothing but
+//     their own addresses.  fp16 with the pass / without, us: ResNet-50 batch 1 316 / 312, 8 426 / 418, 32 837 / 801 (256 -> 1024 1x1 on
+//     14 x 14 14.2 / 11.5), MobileNet-V2 batch 16 352 / 340; results the same to the bit.
 //   * fp32 storage: a float is the sum of three bf16, exactly, and a product of two floats is six products of such parts but
 //     for 2^-25 of it.  The bf16 pipes make six in 384 clocks of a 64 x 64 x 32 step, v_mfma_f32_32x32x2_f32
 //     the one in 1024.  Weights are laid out as their parts; a wave takes its activations apart in registers, which costs as
@@ -45,49 +48,19 @@
 #include <cstring>
 #include <type_traits>
 
-#include "channels_last.h"
+#include "conv_cl.h"
 
 namespace cadnn {
 
 namespace {
 
-constexpr uint32_t kClOutOfRange = 0x7ffffff0u;
-
 typedef _Float16 cl_h8 __attribute__((ext_vector_type(8)));
 typedef _Float16 cl_h4 __attribute__((ext_vector_type(4)));
 typedef __bf16 cl_b8 __attribute__((ext_vector_type(8)));
-typedef __bf16 cl_b2 __attribute__((ext_vector_type(2)));
-typedef float cl_f2 __attribute__((ext_vector_type(2)));
 typedef float cl_f4 __attribute__((ext_vector_type(4)));
 typedef float cl_f16v __attribute__((ext_vector_type(16)));
 typedef uint32_t cl_u4 __attribute__((ext_vector_type(4)));
 typedef uint32_t cl_u2 __attribute__((ext_vector_type(2)));
-
-// Offsets and pitches in bytes.
-struct ClTensorArg {
-    uint32_t span;              // bytes behind the base pointer
-    int img, row, col, org;     // per image, per OUTPUT row and column (strides included), first
-};
-struct ClArgs {
-    const char* w;
-    const char* x;
-    const char* x2;
-    char* y;
-    const char* res;
-    const float* bias;
-    const float* bias2;
-    float* part;
-    int* count;
-    ClTensorArg xt, x2t, yt, rt;
-    uint32_t wspan;
-    int total, hw, ow, cout, relu;
-    int steps_tap, steps1, steps, ntaps, tiles_m, tiles, per_die, sk, log_sk;
-    int per_slice;              // steps of a slice: of a group of waves of a workgroup of the split
-    int row_bytes;              // bytes of a step that are the pixel's own; what lies behind them is not used
-    int plane;                  // PLANES: bytes from one channel to the next
-    uint32_t magic_hw, magic_ow, magic_tm, magic_st;
-    int tap_off[kClMaxTaps];
-};
 
 template <int I, int N, class F>
 __device__ __forceinline__ void cl_static_for(F&& f) {
@@ -111,10 +84,15 @@ __device__ __forceinline__ void cl_barrier() {
     asm volatile("" ::: "memory");
 }
 
-// 16 bytes per lane from memory to LDS (lane l: lds + 16 l).  The wait for it is the caller's.
+// 16 (4) bytes per lane from memory to LDS (lane l: lds + 16 l, 4 l).  The wait for it is the caller's.
 __device__ __forceinline__ void cl_dma(cl_u4 rsrc, uint32_t voff, uint32_t soff, uint32_t lds) {
     asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tbuffer_load_dwordx4 %1, %2, %3 offen lds"
                  :: "s"(lds), "v"(voff), "s"(rsrc), "s"(soff) : "memory");
+}
+
+__device__ __forceinline__ void cl_dma4(cl_u4 rsrc, uint32_t voff, uint32_t lds) {
+    asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tbuffer_load_dword %1, %2, 0 offen lds"
+                 :: "s"(lds), "v"(voff), "s"(rsrc) : "memory");
 }
 
 __device__ __forceinline__ cl_u4 cl_rsrc(const void* p, uint32_t span) {
@@ -139,35 +117,12 @@ struct ClCfg {
     static constexpr int LA = (MI * WB + 4095) / 4096, LB = TN * RB / 4096; // loads per thread and stage
     static constexpr int A_BYTES = LA * 4096;
     static constexpr int STAGE = A_BYTES + TN * RB;
-    static constexpr int PITCH = TM * (int)sizeof(T) + 16;
     static constexpr int cmax(int a, int b) { return a > b ? a : b; }
     static constexpr int GROUP = S * STAGE;
     static constexpr int KEPT = AM * AN * 16 / KG;           // sums of a thread behind the K loop
-    static constexpr int SWAP = KG == 1 ? 0 : AM * AN * 16 * 1024;      // where the groups exchange them, behind the tile
-    static constexpr int MAIN = cmax(KG * GROUP, TN * PITCH + SWAP);
-    static constexpr int LDS = MAIN + TN * 16 + TM * 4 + 16;
+    static constexpr int MAIN = cmax(KG * GROUP, KG == 1 ? 0 : AM * AN * 16 * 1024);       // (the groups exchange sums there)
+    static constexpr int LDS = MAIN + TN * 16 + TM * 8 + 16;
 };
-
-// Two floats as the sum of three pairs of bf16, exactly: each is rounded to the nearest 8 bits of what
-// the ones before it left, and 24 bits are three times 8.  (Bits below 2^-133 have no place.)  An infinity or a
-// NaN, or a value that rounds to one, leaves NaN behind, which the caller sees in the sums.
-// (Shifts, masks and subtractions run beside the matrix products; v_dot2_f32_bf16, which would take the place of two of
-// them, does not: 12 products 434 clocks, with 60 subtractions between them 470, with 60 of it 844.)
-__device__ __forceinline__ void cl_split2(float a, float b, uint32_t* p1, uint32_t* p2, uint32_t* p3) {
-    const uint32_t h1 = __builtin_bit_cast(uint32_t, __builtin_convertvector((cl_f2){a, b}, cl_b2));
-    const float ra = a - __uint_as_float(h1 << 16), rb = b - __uint_as_float(h1 & 0xffff0000u);
-    const uint32_t h2 = __builtin_bit_cast(uint32_t, __builtin_convertvector((cl_f2){ra, rb}, cl_b2));
-    const float sa = ra - __uint_as_float(h2 << 16), sb = rb - __uint_as_float(h2 & 0xffff0000u);
-    *p1 = h1;
-    *p2 = h2;
-    *p3 = __builtin_bit_cast(uint32_t, __builtin_convertvector((cl_f2){sa, sb}, cl_b2));
-}
-
-// v / d for 0 <= v < 2^31 with magic = ceil(2^32 / d): the product is at most one too large.
-__device__ __forceinline__ int cl_div(int v, uint32_t magic, int d) {
-    const int q = (int)__umulhi((uint32_t)v, magic);
-    return d == 1 ? v : q - (q * d > v ? 1 : 0);
-}
 
 // What a launch is, beside a layer between channels-last tensors.
 enum ClMode { CL_MAPS = 0, CL_PLANES = 1, CL_ODD_ROW = 2 };
@@ -186,7 +141,7 @@ __global__ __launch_bounds__(256 * KG, MI * NI == 1 ? 4 : 2) void cl_conv_kernel
     static_assert(KG <= 2, "two groups exchange halves of their sums");
     constexpr bool PLANES = MODE == CL_PLANES;
     static_assert(MODE != CL_ODD_ROW || sizeof(T) == 2, "a pixel of 4-byte storage is a whole piece");
-    constexpr int TM = C::TM, TN = C::TN, STAGE = C::STAGE, PITCH = C::PITCH;
+    constexpr int TM = C::TM, TN = C::TN, STAGE = C::STAGE;
     constexpr int RPL = 1024 / RB;                 // rows one wave-load fills
     constexpr int LA = C::LA, LB = C::LB;
     constexpr bool SPLIT = sizeof(T) == 4;
@@ -245,27 +200,32 @@ __global__ __launch_bounds__(256 * KG, MI * NI == 1 ? 4 : 2) void cl_conv_kernel
     };
     cl_static_for<0, LA>([&](auto I) __attribute__((always_inline)) { issue_w(I, 0u); });
 
+    // the biases go to LDS the same way (out of range: 0)
+    if (kg == 0 && wv < TM / 32) {
+        const bool second = wv >= TM / 64;
+        const int chunk = second ? wv - TM / 64 : wv;
+        const float* const src = second ? a.bias2 : a.bias;
+        cl_dma4(cl_rsrc(src, src ? (uint32_t)a.cout * 4u : 0u), (uint32_t)(m0 + chunk * 64 + lane) * 4u,
+                lds0 + (uint32_t)(C::MAIN + TN * 16 + wv * 256));
+    }
+    // (what the first loads need; a 32-bit product takes as long as four other instructions)
+    int img = 0, oh = 0, ow = 0;
     if (tid < TN) {
         const int Q = n0 + tid;
         int4 e = make_int4((int)kClOutOfRange, (int)kClOutOfRange, (int)kClOutOfRange, (int)kClOutOfRange);
         if (Q < a.total) {
-            const int img = cl_div(Q, a.magic_hw, a.hw), q = Q - img * a.hw;
-            const int oh = cl_div(q, a.magic_ow, a.ow), ow = q - oh * a.ow;
+            img = cl_div(Q, a.magic_hw, a.hw);
+            const int q = Q - img * a.hw;
+            oh = cl_div(q, a.magic_ow, a.ow);
+            ow = q - oh * a.ow;
             e.x = img * a.xt.img + oh * a.xt.row + ow * a.xt.col + a.xt.org;
-            e.y = img * a.x2t.img + oh * a.x2t.row + ow * a.x2t.col + a.x2t.org;
-            e.z = img * a.yt.img + oh * a.yt.row + ow * a.yt.col + a.yt.org;
-            e.w = img * a.rt.img + oh * a.rt.row + ow * a.rt.col + a.rt.org;
+            if (a.steps > a.steps1) e.y = img * a.x2t.img + oh * a.x2t.row + ow * a.x2t.col + a.x2t.org;
+            if (a.res) e.w = img * a.rt.img + oh * a.rt.row + ow * a.rt.col + a.rt.org;
         }
         ptab[tid] = e;
     }
-    // (the bias is requested here and put in LDS behind the K loop: nothing waits for it)
-    int* const odd = (int*)(bl + TM);               // SPLIT: a sum of this workgroup's is not finite
+    int* const odd = (int*)(bl + 2 * TM);           // SPLIT: a sum of this workgroup's is not finite
     if (SPLIT && tid == 0) *odd = 0;
-    float my_bias = 0.0f, my_bias2 = 0.0f;
-    if (tid < TM && m0 + tid < a.cout) {
-        if (a.bias) my_bias = a.bias[m0 + tid];
-        if (a.bias2) my_bias2 = a.bias2[m0 + tid];
-    }
     // (no wait for memory here, as __syncthreads would have: only the table in LDS is awaited)
     __builtin_amdgcn_s_waitcnt(0xc07f);
     cl_barrier();
@@ -286,22 +246,29 @@ __global__ __launch_bounds__(256 * KG, MI * NI == 1 ? 4 : 2) void cl_conv_kernel
     };
     start_sources();
 
-    // ---- the residual's rows are requested up front where they fit few registers
-    constexpr int CPR = TM * (int)sizeof(T) / 16, ITEMS = TN * CPR / (256 * KG);
+    // ---- the residual's pieces are requested up front where they fit few registers.  (A lane has, of a block of 32 channels and its
+    //      pixel, the pieces 2 p + l / 32: the rows of a block of weights are in an order that makes it so.)
+    constexpr int PER = 16 / KG, NP = PER / EPP, ITEMS = AM * AN * NP;      // sums of a block that a thread keeps, pieces, pieces in all
     constexpr bool EARLY = ITEMS <= 8 && !PLANES;
+    const int l31 = lane & 31, fk = lane >> 5;
     const __amdgpu_buffer_rsrc_t rrs = __builtin_amdgcn_make_buffer_rsrc((void*)a.res, 0, a.rt.span, 0x00020000);
-    const int ec = tid % CPR, ep = tid / CPR;                    // epilogue: this thread's piece and first pixel
-    const bool ec_live = m0 + ec * EPP < a.cout;
+    auto piece_channel = [&](int mi, int p) __attribute__((always_inline)) {
+        return m0 + wm * 32 * AM + mi * 32 + kg * 16 + (p * 2 + fk) * EPP;
+    };
     cl_u4 resv[EARLY ? ITEMS : 1];
-    auto res_load = [&](int k) __attribute__((always_inline)) {
-        const int r = ptab[ep + k * (256 * KG / CPR)].w;
-        const uint32_t off = (ec_live && r != (int)kClOutOfRange) ? (uint32_t)(r + m0 * (int)sizeof(T) + ec * 16) : kClOutOfRange;
+    auto res_load = [&](int at, int mi, int p) __attribute__((always_inline)) {
+        const int ch = piece_channel(mi, p);
+        const uint32_t off = (ch < a.cout && at != (int)kClOutOfRange) ? (uint32_t)(at + ch * (int)sizeof(T)) : kClOutOfRange;
         return __builtin_bit_cast(cl_u4, __builtin_amdgcn_raw_buffer_load_b128(rrs, off, 0u, 0));
     };
     if constexpr (EARLY) {
         if (a.res) {
 #pragma unroll
-            for (int k = 0; k < ITEMS; ++k) resv[k] = res_load(k);
+            for (int ni = 0; ni < AN; ++ni) {
+                const int at = ptab[wn * 32 * AN + ni * 32 + l31].w;
+#pragma unroll
+                for (int k = 0; k < AM * NP; ++k) resv[ni * AM * NP + k] = res_load(at, k / NP, k % NP);
+            }
         }
     }
 
@@ -378,7 +345,6 @@ __global__ __launch_bounds__(256 * KG, MI * NI == 1 ? 4 : 2) void cl_conv_kernel
     clear_sums();
 
     // fragment addresses: row l % 32 of a 32-row block, piece 2 ks + l / 32 (permuted by the row)
-    const int l31 = lane & 31, fk = lane >> 5;
     const int fs = RB == 128 ? (lane >> 1) & 7 : (lane >> 2) & 3;
     const uint32_t fb = (uint32_t)(kg * C::GROUP + C::A_BYTES + (wn * 32 * AN + l31) * RB);
     const uint32_t fp = (uint32_t)((fk ^ fs) * 16);
@@ -401,6 +367,8 @@ __global__ __launch_bounds__(256 * KG, MI * NI == 1 ? 4 : 2) void cl_conv_kernel
         cl_static_for<0, L>([&](auto I) __attribute__((always_inline)) { issue_one(I, (uint32_t)j); });
         advance();
     }
+    if (tid < TN && n0 + tid < a.total)             // (read behind the K loop)
+        ptab[tid].z = img * a.yt.img + oh * a.yt.row + ow * a.yt.col + a.yt.org;
     typedef std::integral_constant<int, 0> Set0;
     typedef std::integral_constant<int, 1> Set1;
     wait_loads(min(steps, S) - 1);
@@ -656,17 +624,15 @@ __global__ __launch_bounds__(256 * KG, MI * NI == 1 ? 4 : 2) void cl_conv_kernel
                         if (kept[mi][ni][i] * 0.0f == 0.0f) acc[mi][ni][i] = kept[mi][ni][i];
         }
     }
-    asm volatile("s_waitcnt vmcnt(0)" ::: "memory");        // (the bias and the residual's rows)
-    if (tid < TM) bl[tid] = my_bias + my_bias2;
+    asm volatile("s_waitcnt vmcnt(0)" ::: "memory");        // (the residual's pieces)
     // ---- the groups' sums: each keeps one half of every block's (channels 16 kg and up of its 32) and gives away the other,
     //      the first group's part of K added first
-    constexpr int PER = 16 / KG;                    // sums of a block that a thread keeps
     float sum[C::KEPT];
     if constexpr (KG == 1) {
 #pragma unroll
         for (int i = 0; i < C::KEPT; ++i) sum[i] = acc[i / 16 / AN][i / 16 % AN][i % 16];
     } else {
-        float* const swap = (float*)(cl_smem + TN * PITCH);
+        float* const swap = (float*)cl_smem;
         __syncthreads();                            // the stage buffers are free: every wave is past its last read
         auto give = [&](auto MINE) __attribute__((always_inline)) {
             constexpr int mine = decltype(MINE)::value;
@@ -716,34 +682,37 @@ __global__ __launch_bounds__(256 * KG, MI * NI == 1 ? 4 : 2) void cl_conv_kernel
         }
     }
 
-    // ---- epilogue.  Lane l holds, per accumulator, pixel l % 32 and channels 8 g + 4 (l / 32) + i, g, i < 4 (of two
-    //      groups, the first has those of g < 2).
-    if (KG == 1) __syncthreads();           // the stage buffers are free: every wave is past its last read
+    // ---- epilogue, straight from the accumulators: bias, residual and ReLU in fp32, one rounding.  (PLANES: a store takes 32
+    //      pixels of a channel.)
     const __amdgpu_buffer_rsrc_t yrs = __builtin_amdgcn_make_buffer_rsrc((void*)a.y, 0, a.yt.span, 0x00020000);
-    if constexpr (PLANES) {
 #pragma unroll
-        for (int ni = 0; ni < AN; ++ni) {
-            const int4 e = ptab[wn * 32 * AN + ni * 32 + l31];
+    for (int ni = 0; ni < AN; ++ni) {
+        const int4 e = ptab[wn * 32 * AN + ni * 32 + l31];
 #pragma unroll
-            for (int mi = 0; mi < AM; ++mi) {
-                const int cl = wm * 32 * AM + mi * 32 + kg * (32 / KG) + fk * 4;
+        for (int mi = 0; mi < AM; ++mi) {
+            float v[PER];
+#pragma unroll
+            for (int p = 0; p < NP; ++p)
+#pragma unroll
+                for (int j = 0; j < EPP; j += 4) {
+                    const float* const at = bl + piece_channel(mi, p) - m0 + j;
+                    const cl_f4 b1 = *(const cl_f4*)at, b2 = *(const cl_f4*)(at + TM);
+#pragma unroll
+                    for (int i = 0; i < 4; ++i) v[p * EPP + j + i] = sum[(mi * AN + ni) * PER + p * EPP + j + i] + (b1[i] + b2[i]);
+                }
+            if constexpr (PLANES) {
                 uint32_t off[PER];
-                float v[PER];
 #pragma unroll
                 for (int i = 0; i < PER; ++i) {
-                    const int ch = cl + (i >> 2) * 8 + (i & 3);
-                    const bool live = m0 + ch < a.cout && e.z != (int)kClOutOfRange;
-                    off[i] = live ? (uint32_t)(e.z + (m0 + ch) * a.plane) : kClOutOfRange;
-                    v[i] = sum[(mi * AN + ni) * PER + i] + bl[ch];
+                    const int ch = piece_channel(mi, i / EPP) + i % EPP;
+                    off[i] = ch < a.cout && e.z != (int)kClOutOfRange ? (uint32_t)(e.z + ch * a.plane) : kClOutOfRange;
                 }
                 if (a.res) {
                     T r[PER];
 #pragma unroll
                     for (int i = 0; i < PER; ++i) {
-                        const int ch = cl + (i >> 2) * 8 + (i & 3);
-                        const uint32_t ro = off[i] == kClOutOfRange ? kClOutOfRange : (uint32_t)(e.w + (m0 + ch) * a.plane);
-                        if constexpr (sizeof(T) == 2) r[i] = __builtin_bit_cast(T, (uint16_t)__builtin_amdgcn_raw_buffer_load_b16(rrs, ro, 0u, 0));
-                        else r[i] = __builtin_bit_cast(T, (uint32_t)__builtin_amdgcn_raw_buffer_load_b32(rrs, ro, 0u, 0));
+                        if constexpr (sizeof(T) == 2) r[i] = __builtin_bit_cast(T, (uint16_t)__builtin_amdgcn_raw_buffer_load_b16(rrs, off[i], 0u, 0));
+                        else r[i] = __builtin_bit_cast(T, (uint32_t)__builtin_amdgcn_raw_buffer_load_b32(rrs, off[i], 0u, 0));
                     }
 #pragma unroll
                     for (int i = 0; i < PER; ++i) v[i] += (float)r[i];
@@ -754,60 +723,54 @@ __global__ __launch_bounds__(256 * KG, MI * NI == 1 ? 4 : 2) void cl_conv_kernel
                     if constexpr (sizeof(T) == 2) __builtin_amdgcn_raw_buffer_store_b16(__builtin_bit_cast(uint16_t, o), yrs, off[i], 0u, 0);
                     else __builtin_amdgcn_raw_buffer_store_b32(__builtin_bit_cast(uint32_t, o), yrs, off[i], 0u, 0);
                 }
-            }
-        }
-        return;
-    }
-    if (a.res) {
+            } else {
+                typedef T Piece __attribute__((ext_vector_type(EPP)));
+                if (a.res) {
 #pragma unroll
-        for (int k = 0; k < ITEMS; ++k) {
-            if constexpr (EARLY) *(cl_u4*)(cl_smem + (ep + k * (256 * KG / CPR)) * PITCH + ec * 16) = resv[k];
-            else *(cl_u4*)(cl_smem + (ep + k * (256 * KG / CPR)) * PITCH + ec * 16) = res_load(k);
-        }
-        __syncthreads();
-    }
+                    for (int p = 0; p < NP; ++p) {
+                        cl_u4 q;
+                        if constexpr (EARLY) q = resv[(ni * AM + mi) * NP + p];
+                        else q = res_load(e.w, mi, p);
+                        const Piece r = __builtin_bit_cast(Piece, q);
 #pragma unroll
-    for (int ni = 0; ni < AN; ++ni)
-#pragma unroll
-        for (int mi = 0; mi < AM; ++mi)
-#pragma unroll
-            for (int g = 0; g < 4 / KG; ++g) {
-                const int ch = wm * 32 * AM + mi * 32 + kg * (32 / KG) + g * 8 + fk * 4;
-                char* at = cl_smem + (wn * 32 * AN + ni * 32 + l31) * PITCH + ch * (int)sizeof(T);
-                const cl_f4 b = *(const cl_f4*)(bl + ch);
-                float v[4];
-#pragma unroll
-                for (int i = 0; i < 4; ++i) v[i] = sum[(mi * AN + ni) * PER + g * 4 + i] + b[i];
-                if constexpr (sizeof(T) == 2) {
-                    if (a.res) {
-                        const cl_h4 r = *(const cl_h4*)at;
-#pragma unroll
-                        for (int i = 0; i < 4; ++i) v[i] += (float)r[i];
+                        for (int j = 0; j < EPP; ++j) v[p * EPP + j] += (float)r[j];
                     }
-                    cl_h4 o;
+                }
+                cl_u4 o[NP];
 #pragma unroll
-                    for (int i = 0; i < 4; ++i) o[i] = (_Float16)((a.relu && !(v[i] > 0.0f)) ? 0.0f : v[i]);
-                    *(cl_h4*)at = o;
+                for (int p = 0; p < NP; ++p) {
+                    Piece q;
+#pragma unroll
+                    for (int j = 0; j < EPP; ++j) q[j] = (T)((a.relu && !(v[p * EPP + j] > 0.0f)) ? 0.0f : v[p * EPP + j]);
+                    o[p] = __builtin_bit_cast(cl_u4, q);
+                }
+                auto store = [&](cl_u4 q, int at, int p) __attribute__((always_inline)) {
+                    const int ch = piece_channel(mi, p);
+                    const uint32_t off = ch < a.cout && at != (int)kClOutOfRange ? (uint32_t)(at + ch * (int)sizeof(T)) : kClOutOfRange;
+                    __builtin_amdgcn_raw_buffer_store_b128(q, yrs, off, 0u, 0);
+                };
+                if constexpr (NP == 1) {
+                    store(o[0], e.z, 0);
                 } else {
-                    if (a.res) {
-                        const cl_f4 r = *(const cl_f4*)at;
+                    // neighbouring lanes exchange a piece, so that a store takes 64 bytes side by side of one pixel, not 32 of two
+                    auto other = [](uint32_t q) __attribute__((always_inline)) { return (uint32_t)__builtin_amdgcn_mov_dpp((int)q, 0xb1, 0xf, 0xf, true); };
+                    const bool odd_lane = (lane & 1) != 0;
+                    const int theirs = (int)other((uint32_t)e.z), even = odd_lane ? theirs : e.z, odd_at = odd_lane ? e.z : theirs;
 #pragma unroll
-                        for (int i = 0; i < 4; ++i) v[i] += r[i];
+                    for (int p = 0; p < NP; p += 2) {
+                        cl_u4 first, second;
+#pragma unroll
+                        for (int j = 0; j < 4; ++j) {
+                            const uint32_t got = other(odd_lane ? o[p][j] : o[p + 1][j]);
+                            first[j] = odd_lane ? got : o[p][j];
+                            second[j] = odd_lane ? o[p + 1][j] : got;
+                        }
+                        store(first, even, p + (odd_lane ? 1 : 0));
+                        store(second, odd_at, p + (odd_lane ? 1 : 0));
                     }
-                    cl_f4 o;
-#pragma unroll
-                    for (int i = 0; i < 4; ++i) o[i] = (a.relu && !(v[i] > 0.0f)) ? 0.0f : v[i];
-                    *(cl_f4*)at = o;
                 }
             }
-    __syncthreads();
-#pragma unroll
-    for (int k = 0; k < ITEMS; ++k) {
-        const int p = ep + k * (256 * KG / CPR);
-        const int yo = ptab[p].z;
-        const uint32_t off = (ec_live && yo != (int)kClOutOfRange) ? (uint32_t)(yo + m0 * (int)sizeof(T) + ec * 16) : kClOutOfRange;
-        const cl_u4 v = *(const cl_u4*)(cl_smem + p * PITCH + ec * 16);
-        __builtin_amdgcn_raw_buffer_store_b128(v, yrs, off, 0u, 0);
+        }
     }
 }
 
@@ -857,6 +820,8 @@ const std::vector<ClVariant>& all_cl_variants() {
         {"cl_mfma_64x64_s3", 1, 1, 3, 1, 1}, {"cl_mfma_64x64_s4", 1, 1, 4, 1, 1}, {"cl_mfma_64x64_s3k2", 1, 1, 3, 2, 1},
         {"cl_mfma_64x64_s3k4", 1, 1, 3, 4, 1}, {"cl_mfma_64x64_s4k4", 1, 1, 4, 4, 1}, {"cl_mfma_64x64_s3g2", 1, 1, 3, 1, 2},
         {"cl_mfma_64x64_s3g2k2", 1, 1, 3, 2, 2}, {"cl_mfma_64x64_s3g2k4", 1, 1, 3, 4, 2}, {"cl_mfma_64x128_s2g2", 1, 2, 2, 1, 2},
+        {"cl_mfma_16x16_w8", 0, 0, 0, 1, 1, 1, 1}, {"cl_mfma_16x32_w8", 0, 0, 0, 1, 1, 1, 2}, {"cl_mfma_32x16_w8", 0, 0, 0, 1, 1, 2, 1},
+        {"cl_mfma_32x32_w8", 0, 0, 0, 1, 1, 2, 2},
     };
     return v;
 }
@@ -864,13 +829,14 @@ const std::vector<ClVariant>& all_cl_variants() {
 constexpr int64_t kNumCus = 256, kLdsPerCu = 160 * 1024;
 
 static int64_t cl_tiles(const ClVariant& v, int64_t pixels, int cout) {
-    return ((pixels + 64 * v.ni - 1) / (64 * v.ni)) * ((cout + 64 * v.mi - 1) / (64 * v.mi));
+    return ((pixels + v.tn() - 1) / v.tn()) * ((cout + v.tm() - 1) / v.tm());
 }
 
 bool cl_variant_fits(const ClVariant& v, const ClPlan& plan, int64_t pixels, int cout) {
     if (v.mi == 2 && cout <= 64) return false;
     if (cl_tiles(v, pixels, cout) * v.sk >= (1 << 28)) return false;
     if (pixels >= (1 << 30)) return false;      // (32-bit pixel arithmetic)
+    if (v.bm) return plan.elem == 2 && plan.maps && !plan.stem;
     const int slices = v.sk * v.kg, per = (plan.steps + slices - 1) / slices;
     if (v.sk == 1) return v.kg == 1 || plan.steps >= 2 * v.kg;
     // every slice gets at least two steps and none is empty; the scratch stays below 256 MiB
@@ -909,11 +875,16 @@ cadnn_status cl_prepare_variant(const ClVariant& v, ClPlan* plan, int64_t pixels
 // (the latency of loads that run two stages ahead) and the CU's rate when it does not.  The
 // constants are fitted to the times of every variant, in fp16 on 387 layers (ResNet-50 at 1, 8, 16 and 32 images, MobileNet-V2
 // at 16, VGG-16 at 1, Inception-V3 at 4), the tiles taken 1.7 % slower in sum than each layer's best; in fp32 on 190 layers (ResNet-50 at 1, 2,
-// 4, 8, VGG-16 at 1 and 2, Inception-V3 at 1 and 3, both MobileNets): 0.3 %, against 8.1 % with constants from fp32 products.
+// 4, 8, VGG-16 at 1 and 2, Inception-V3 at 1 and 3, both MobileNets): 0.3 %, against 8.1 % with constants from fp32 products
+// (steps of 64 bytes excepted, where a second group costs more than those times say: 16 -> 58 7x7 on 28 x 28 as a call 17.7 us split
+// in four, 20.2 in two of two groups).
 // Two groups of waves pay in fp32 where a workgroup has the CU to itself: 128 -> 128 3x3 on 8 images of 28 x 28 19.2 -> 16.9 us,
 // 512 -> 512 3x3 on 14 x 14 (split in four as well) 20.8 -> 17.9.  In fp16 a step is bound by the way into LDS, and what
 // they gain on such a layer (7.3 -> 6.5 us launched on its own) is lost again between the launches of a graph: ResNet-50 at 8 images 426 -> 435 us a
-// pass.  Four stages pay where workgroups are alone or two to a CU and the K loop is long; there is no use for more: six and eight
+// pass.  Small tiles (conv_cl_small.hip) are a start, a launch that grows with the workgroups, and their operands at 18 bytes a clock;
+// in graphs of equal layers at one image, us a layer, best large tile / best small one: 256 -> 256 3x3 on 14 x 14 8.6 / 7.0, 1024 -> 256
+// 1x1 5.5 / 4.0, 128 -> 128 3x3 on 28 x 28 7.2 / 6.4, 2048 -> 512 1x1 on 7 x 7 7.4 / 6.2; 256 -> 1024 1x1 5.9 / 6.7, 64 -> 256 1x1 on
+// 56 x 56 4.3 / 8.8; at 4 images 1024 -> 256 5.7 / 5.4, 256 -> 256 3x3 9.1 / 10.7.  Four stages pay where workgroups are alone or two to a CU and the K loop is long; there is no use for more: six and eight
 // measured the same.
 struct ClCost {
     double matrix, bytes;           // the CU's rate: clocks of a 64 x 64 tile's step of 128 bytes, bytes a clock
@@ -921,24 +892,30 @@ struct ClCost {
     double narrow;                  // ... and shrinks with the step
     double start, tile;             // of a round, of every workgroup of it and 64 x 64 tile
     double split, slice;            // K split over workgroups
-    double group_step, group_tile, group;       // two groups of waves
+    double group_step, group_tile, group, group64;      // two groups of waves; of steps of 128 and of 64 bytes
 };
 
 const ClVariant* cl_pick(int cout, const ClPlan& plan, int64_t pixels, bool f16) {
-    static const ClCost cost16 = {21.5, 47, 642, 630, 0.25, 0, 367, 3370, 4960, 871, 1, 1, 0};
-    static const ClCost cost32 = {146, 27.8, 934, 1609, 1.83, 0.32, 172, 4055, 2557, 1246, 1.06, 1.08, 446};
+    static const ClCost cost16 = {21.5, 47, 642, 630, 0.25, 0, 367, 3370, 4960, 871, 1, 1, 0, 0};
+    static const ClCost cost32 = {146, 27.8, 934, 1609, 1.83, 0.32, 172, 4055, 2557, 1246, 1.06, 1.08, 446, 2000};
     const ClCost& k = f16 ? cost16 : cost32;
     const ClVariant* best = nullptr;
     double best_cost = 0.0;
     for (const ClVariant& v : all_cl_variants()) {
         if (!cl_variant_fits(v, plan, pixels, cout)) continue;
         const int64_t blocks = cl_tiles(v, pixels, cout) * v.sk;
+        if (v.bm) {
+            const double bytes = (double)plan.steps * plan.rb * (v.tm() + v.tn());      // a workgroup's operands
+            const double cost = 3170.0 + 12.0 * (double)blocks + (double)((blocks + kNumCus - 1) / kNumCus) * bytes / 18.0;
+            if (!best || cost < best_cost) { best = &v; best_cost = cost; }
+            continue;
+        }
         const int slices = v.sk * v.kg, steps = (plan.steps + slices - 1) / slices;
         if (v.s == 4 && (blocks > 2 * kNumCus || steps < 4)) continue;
         if (v.kg == 2 && f16) continue;
         const int size = v.mi * v.ni, weights = cl_weight_bytes(plan.rb, f16 ? 2 : 4);
         const int stage = (v.mi * weights * 64 + 4095) / 4096 * 4096 + 64 * v.ni * plan.rb;
-        const int lds = v.kg * v.s * stage + 64 * v.ni * 16 + 64 * v.mi * 4 + 16;
+        const int lds = v.kg * v.s * stage + 64 * v.ni * 16 + 64 * v.mi * 8 + 16;
         const int64_t per_cu = std::min<int64_t>(kLdsPerCu / lds, (size == 1 ? 4 : 2) / v.kg);
         const double rate = std::max(k.matrix * size * v.kg * plan.rb / 128.0, 64 * (v.mi * weights + v.ni * plan.rb) * v.kg / k.bytes);
         const double alone = std::max(rate, (v.s == 4 ? k.alone4 : k.alone3) * (1.0 + k.wider * (size - 1)) * std::pow(plan.rb / 128.0, k.narrow) *
@@ -948,7 +925,7 @@ const ClVariant* cl_pick(int cout, const ClPlan& plan, int64_t pixels, bool f16)
         };
         const int64_t in_cu = (blocks + kNumCus - 1) / kNumCus;
         const double cost = (double)(in_cu / per_cu) * round(per_cu) + round(in_cu % per_cu) + (v.sk > 1 ? k.split + k.slice * v.sk : 0.0) +
-                            (v.kg == 2 ? k.group : 0.0);
+                            (v.kg == 2 ? (plan.rb == 64 ? k.group64 : k.group) : 0.0);
         if (!best || cost < best_cost) { best = &v; best_cost = cost; }
     }
     return best;
@@ -980,7 +957,7 @@ cadnn_status launch_cl_conv(const ClConv& c, const ClVariant& v, bool f16, hipSt
     a.steps_tap = p.steps_tap;
     a.steps1 = p.taps * p.steps_tap;
     a.steps = p.steps;
-    a.tiles_m = (c.cout + 64 * v.mi - 1) / (64 * v.mi);
+    a.tiles_m = (c.cout + v.tm() - 1) / v.tm();
     a.sk = v.sk;
     a.log_sk = v.sk == 4 ? 2 : v.sk == 2 ? 1 : 0;
     a.ntaps = p.taps;
@@ -998,7 +975,9 @@ cadnn_status launch_cl_conv(const ClConv& c, const ClVariant& v, bool f16, hipSt
     for (int t = 0; t < p.taps; ++t)
         a.tap_off[t] = (int)(((int64_t)p.tap_r[t] * c.xd.row + (int64_t)p.tap_c[t] * c.xd.pix) * (int64_t)e);
     hipError_t err;
-    if (c.planes) {
+    if (v.bm) {
+        err = launch_cl_small(a, v, p.rb, s);
+    } else if (c.planes) {
         // one pixel of one channel after the other; images follow each other
         a.yt.img = (int)((int64_t)c.cout * a.hw * (int64_t)e);
         a.yt.row = (int)(a.ow * e);
@@ -1022,6 +1001,7 @@ cadnn_status cl_plan_shape(const cadnn_weights* w, const cadnn_weights* shortcut
     const size_t e = w->elem();
     const int taps_all = w->kh * w->kw, kpr = rb / (int)e;      // k per step
     plan->rb = rb;
+    plan->elem = (int)e;
     plan->stem = stem;
     plan->taps = 0;
     std::vector<int> tap_index((size_t)taps_all, -1);
@@ -1074,7 +1054,7 @@ cadnn_status cl_build_plan(const cadnn_weights* w, const cadnn_weights* shortcut
     };
     auto put = [&](const cadnn_weights* src) {
         for (int i = 0; i < src->cout; ++i) {
-            const int co = src->perm[(size_t)i], r = co % 64, sw = rb == 128 ? (r >> 1) & 7 : (r >> 2) & 3;
+            const int co = src->perm[(size_t)i], r = cl_weight_row(co, (int)e), sw = rb == 128 ? (r >> 1) & 7 : (r >> 2) & 3;
             char* const block = img + (size_t)(co / 64) * plan->steps * 64 * row_bytes;
             for (int32_t j = src->row_ptr[(size_t)i]; j < src->row_ptr[(size_t)i + 1]; ++j) {
                 const size_t at = place[(size_t)src->col_idx[(size_t)j]];

@@ -11,7 +11,7 @@
 #include <mutex>
 #include <vector>
 
-#include "channels_last.h"
+#include "conv_cl.h"
 
 namespace cadnn {
 
@@ -93,7 +93,7 @@ __global__ __launch_bounds__(256) void cl_arrange_kernel(const ClArrange a) {
         }
         __syncthreads();
         if (co >= a.cout) return;
-        const int row = co % 64, sw = a.pieces == 8 ? (row >> 1) & 7 : (row >> 2) & 3;
+        const int row = cl_weight_row(co, (int)sizeof(T)), sw = a.pieces == 8 ? (row >> 1) & 7 : (row >> 2) & 3;
         const int64_t steps = (int64_t)a.taps * a.steps_tap;
         if constexpr (sizeof(T) == 4) {
             // eight k of one half of a wave: 16 bytes of each of the three parts
@@ -101,18 +101,30 @@ __global__ __launch_bounds__(256) void cl_arrange_kernel(const ClArrange a) {
             for (int i = lane; i < a.taps * halves; i += 64) {
                 const int t = i / halves, h = i - t * halves, k0 = h / 2 * 16 + h % 2 * 4;
                 char* const block = (char*)a.wr + ((co / 64) * steps + (int64_t)t * a.steps_tap + step) * 64 * cl_weight_bytes(a.kpr * 4, 4);
-                uint16_t part[8][3];
+                float v[8];
+                bool large = false;
 #pragma unroll
-                for (int j = 0; j < 8; ++j) cl_split_weight(mine[(k0 + j / 4 * 8 + j % 4) * a.taps + t], part[j]);
-#pragma unroll
-                for (int p = 0; p < 3; ++p) {
-                    uint4 q;
-                    q.x = part[0][p] | (uint32_t)part[1][p] << 16;
-                    q.y = part[2][p] | (uint32_t)part[3][p] << 16;
-                    q.z = part[4][p] | (uint32_t)part[5][p] << 16;
-                    q.w = part[6][p] | (uint32_t)part[7][p] << 16;
-                    *(uint4*)(block + cl_split_offset(k0, p, row)) = q;
+                for (int j = 0; j < 8; ++j) {
+                    v[j] = mine[(k0 + j / 4 * 8 + j % 4) * a.taps + t];
+                    large |= (__float_as_uint(v[j]) & 0x7fffffffu) >= 0x7f7f8000u;      // rounds to an infinity, or is none or a NaN
                 }
+                uint32_t part[3][4];
+                if (large) {
+#pragma unroll
+                    for (int j = 0; j < 4; ++j) {
+                        uint16_t lo[3], hi[3];
+                        cl_split_weight(v[2 * j], lo);
+                        cl_split_weight(v[2 * j + 1], hi);
+#pragma unroll
+                        for (int p = 0; p < 3; ++p) part[p][j] = lo[p] | (uint32_t)hi[p] << 16;
+                    }
+                } else {
+#pragma unroll
+                    for (int j = 0; j < 4; ++j) cl_split2(v[2 * j], v[2 * j + 1], &part[0][j], &part[1][j], &part[2][j]);
+                }
+#pragma unroll
+                for (int p = 0; p < 3; ++p)
+                    *(uint4*)(block + cl_split_offset(k0, p, row)) = make_uint4(part[p][0], part[p][1], part[p][2], part[p][3]);
             }
         } else {
             for (int i = lane; i < a.taps * a.pieces; i += 64) {
@@ -276,6 +288,8 @@ cadnn_status dense_cl_conv2d(const void* w_dev, const void* x, void* y, const vo
                              int cout, int kh, int kw, int stride, int pad, const void* bias, int relu, bool f16, hipStream_t s) {
     const size_t e = f16 ? 2 : 4;
     ClPlan plan;
+    plan.elem = (int)e;
+    plan.maps = false;
     const ClDesc xd = cl_desc(cin, h, w, pad, pad, cl_padded_channels(cin, e));
     plan.rb = ((size_t)xd.pix * e) % 128 ? 64 : 128;
     const int kpr = plan.rb / (int)e, pieces = plan.rb / 16;

@@ -217,6 +217,56 @@ def test_first_layer_reads_nothing_outside_its_windows(cad, k, stride, pad, h, w
     net.free()
 
 
+@pytest.mark.parametrize("n,cin,cout,k,stride,h,w", [(1, 8, 8, 1, 1, 3, 5),          # one step: seven waves have nothing of K
+                                                     (1, 40, 24, 3, 1, 4, 4),         # rows of 64 bytes, one whole block of pixels
+                                                     (2, 96, 72, 3, 2, 9, 7),         # an odd number of half steps, pixels across images
+                                                     (1, 64, 136, 1, 1, 17, 1),       # a pixel more than a block
+                                                     (3, 160, 40, 5, 1, 6, 6),        # parts of K that end inside a tap
+                                                     (1, 520, 16, 3, 1, 7, 7)])
+def test_small_tiles(cad, n, cin, cout, k, stride, h, w):
+    """The variants whose waves share K, at the ends of their tiles and of K, with a residual and a fused projection: within
+    fp32 sums of K products and one rounding to fp16 of 64-bit arithmetic."""
+    ops = [Op("conv", "in", 0, 1, cin, cin, 1, 1, 0, 0.0, False), Op("conv", "p", 1, 2, cin, cout, 1, stride, 0, 0.0, False),
+           Op("conv", "a", 1, 3, cin, cout, k, stride, k // 2, 0.0, True, 2), Op("conv", "b", 3, 4, cout, cout, 1, 1, 0, 0.0, True, 3),
+           Op("conv", "out", 4, 5, cout, 8, 1, 1, 0, 0.5, False)]
+    x, ws, bs = wl.net_tensors(ops, "small", (n, cin, h, w))
+    x = x.astype(np.float16)
+    net = cad.build_net(ops, ws, bs, x.shape, cad.F16, use_graph=False)
+    net.set_op_variant(0, "cl_mfma_64x64_s3")
+    names = [v for v in net.op_candidates(2) if v.endswith("_w8")]
+    assert len(names) == 4
+    conv = torch.nn.functional.conv2d
+
+    def layer(i, t):
+        wt = torch.from_numpy(ws[i].astype(np.float16)).double().reshape(ops[i].cout, ops[i].cin, ops[i].k, ops[i].k)
+        both = [conv(a, b, c, ops[i].stride, ops[i].pad) for a, b, c in
+                ((t, wt, torch.from_numpy(bs[i]).double()), (t.abs(), wt.abs(), torch.from_numpy(np.abs(bs[i])).double()))]
+        return both[0].numpy(), both[1].numpy(), ops[i].cin * ops[i].k ** 2
+
+    def check(got, ref, size, terms, what):
+        bound = (terms + 3) * 2.0 ** -24 * size + 2.0 ** -11 * np.abs(ref) + 2.0 ** -25
+        excess = (np.abs(got.astype(np.float64) - ref) - bound).max()
+        assert excess <= 0.0, f"{what}: {excess:.3e} above the bound"
+
+    for name in names:
+        for op in (0, 2, 3):
+            net.set_op_variant(op, name)
+        net.run(torch.from_numpy(x).cuda())
+        torch.cuda.synchronize()
+        assert net.op_variant(1) == "fused" and net.op_variant(2) == name
+        ho, wo = (wl.conv_out_size(s, k, stride, k // 2) for s in (h, w))
+        mid = net.read_buffer(1, (n, cin, h, w))
+        a, b = net.read_buffer(3, (n, cout, ho, wo)), net.read_buffer(4, (n, cout, ho, wo))
+        ref, size, terms = layer(0, torch.from_numpy(x).double())
+        check(mid, ref, size, terms, name + " in")
+        (ref, size, terms), (ref2, size2, terms2) = layer(2, torch.from_numpy(mid).double()), layer(1, torch.from_numpy(mid).double())
+        check(a, np.maximum(ref + ref2, 0.0), size + size2, terms + terms2, name + " a")
+        ref, size, terms = layer(3, torch.from_numpy(a).double())
+        r = a.astype(np.float64)
+        check(b, np.maximum(ref + r, 0.0), size + np.abs(r), terms, name + " b")
+    net.free()
+
+
 @pytest.mark.parametrize("cin,cout,k,hw", [(8, 40, 3, 9), (64, 136, 1, 13), (96, 72, 3, 10), (160, 264, 3, 6)])
 def test_fp32_products_of_extreme_values(cad, cin, cout, k, hw):
     """fp32 storage with every tile: infinities and NaN where 64-bit arithmetic has them (no filter has a zero), and values
