@@ -74,6 +74,18 @@ int step_bytes(const cadnn_net* net, const ClNet& cl, size_t i) {
     return ((size_t)cl_padded_channels(op.in.c, e) * e) % 128 || (p && ((size_t)cl_padded_channels(p->in.c, e) * e) % 128) ? 64 : 128;
 }
 
+// Filter taps that some filter of the layer has a weight at (a rectangular filter lies in a square bank).
+int used_taps(const cadnn_weights* w) {
+    const int all = w->kh * w->kw;
+    if (all > kClMaxTaps) return all;
+    uint64_t seen = 0;
+    const uint64_t every = all == 64 ? ~0ull : (1ull << all) - 1;
+    for (size_t j = 0; j < w->col_idx.size() && seen != every; ++j) seen |= 1ull << (w->col_idx[j] % all);
+    int n = 0;
+    for (; seen; seen &= seen - 1) ++n;
+    return n;
+}
+
 int64_t out_pixels(const NetOp& op) { return (int64_t)op.out.n * op.out.h * op.out.w; }
 
 }  // namespace
@@ -225,32 +237,46 @@ std::unique_ptr<ClNet> cl_layout(const cadnn_net* net) {
     return cl;
 }
 
-// Which execution a net takes unless a variant of the other is pinned.  Both are modelled as a fixed cost
-// per launch plus multiply-adds at a rate: the compressed kernels of the plane layouts do the nonzero
-// ones at 8.5 TFLOP/s (ResNet-50, 80 % sparse, fp16 / mixed, fp32: 7-8.7 measured at batch 2 to 32), the
-// matrix cores all of them at 430 (fp16) or 80 (fp32).  Measured (us, planes / channels-last, untuned; * the rule
-// takes the second): ResNet-50 fp16 batch 1 379 / 313*, 2 576 / 320*, 8 1725 / 407*; fp32 batch 2 492 / 630, 4 711 / 730,
-// 6 1032 / 946*, 8 1260 / 1016*; VGG-16 batch 1 fp16 336 / 165*, fp32 322 / 450, 4 952 / 1330; Inception-V3 fp16 batch 1
-// 596 / 661, 2 926 / 676, 3 1298 / 702*, fp32 batch 1 546 / 1118, 4 1431 / 1353; MobileNet-V1 fp16 batch 1 128 / 124,
-// 4 223 / 132, 6 350 / 144*, fp32 batch 2 178 / 189, 4 258 / 212, 8 455 / 267; MobileNet-V2 fp16 batch 3 237 / 234, 8 376 / 266,
-// 12 487 / 294*, fp32 batch 6 379 / 383, 8 438 / 425.  So no net goes channels-last to its loss, and near the line the
-// plane layouts keep nets that would be up to 1.7 times as fast there (the 6 us of a depthwise launch are of an
-// older kernel: 3 to 6 now); tuning (CADNN_NET_TUNE) times both for a net that does go.
+// Which execution a net takes unless a variant of the other is pinned.  Both are modelled as a cost per launch plus
+// multiply-adds at a rate: the compressed kernels of the plane layouts do the nonzero ones at 7.8 to 8.5 TFLOP/s, the matrix cores all
+// of them at 430 (fp16) or 115 (fp32: bf16 parts; 80 with fp32 products).  Measured (us, planes / channels-last, untuned; * the rule
+// takes the second; ResNet-50 and the bottleneck 80 % sparse): fp16 ResNet-50 batch 1 379 / 278*, of 160 x 160
+// 302 / 263*, of 100 x 100 269 / 259*, batch 8 1725 / 417*; VGG-16 336 / 163*; Inception-V3 599 / 510*, of 230 x 230 420 / 487, batch 2
+// 922 / 551*, 4 of 150 x 150 664 / 503*; bottleneck on 28 x 28 16 / 21, 8 images of 14 x 14 16 / 22.  fp32 ResNet-50 batch 1 400 / 483,
+// 2 582 / 533*, 3 of 128 x 128 463 / 483, 6 of 110 x 110 721 / 529*; VGG-16 328 / 347, batch 2 564 / 533, 4 948 / 926*; Inception-V3
+// 546 / 978, batch 3 1088 / 1109; bottleneck batch 2 32 / 41.  Nets with depthwise layers keep the line that goes with depthwise layers
+// fused on the planes, which is a feature of that execution that programs see (MobileNet-V1 at 4 and V2 at 2 images report it), and
+// parts of a net in fp16 that take or give maps the one that counts a rectangular filter as the square bank it lies in: fp16
+// MobileNet-V1 batch 4 223 / 132, 6 350 / 144*; MobileNet-V2 batch 2 206 / 211, 4 268 / 224, 8 376 / 266, 12 487 / 294*; fp32
+// MobileNet-V1 batch 2 179 / 162, 4 258 / 189, V2 batch 8 438 / 391.  No net of these goes channels-last to a loss; tuning
+// (CADNN_NET_TUNE) times both for a net that does go.
 bool cl_expected_faster(const cadnn_net* net) {
-    double nonzero = 0.0, dense = 0.0;
-    double cl_us = 0.0;
-    int planes_launches = 0;
+    const size_t e = net->elem();
+    const bool f16 = net->dtype == CADNN_F16;
+    double nonzero = 0.0, dense = 0.0, square = 0.0;
+    int planes_launches = 0, convs = 0, depthwise = 0, others = 0, copies = 0;
+    bool import = false;
     for (const NetOp& o : net->ops) {
-        if (o.kind != OP_CONCAT) cl_us += o.kind == OP_DEPTHWISE ? 6.0 : 5.3;
+        if (o.kind == OP_CONV) ++convs;
+        else if (o.kind == OP_DEPTHWISE) ++depthwise;
+        else if (o.kind != OP_CONCAT) ++others;
+        if (o.kind != OP_CONCAT && o.kind != OP_FC && o.src_inst < 0 && !stem_conv(o, e)) import = true;
         if (o.fused_into < 0 && o.kind != OP_CONCAT) ++planes_launches;
         if (!o.w) continue;
         const double pixels = (double)o.out.n * o.out.h * o.out.w;
         nonzero += 2.0 * (double)o.w->nnz * pixels;
-        if (o.kind == OP_CONV) dense += 2.0 * (double)o.w->cout * o.w->cin * o.w->kh * o.w->kw * pixels;
+        if (o.kind != OP_CONV) continue;
+        const double per_tap = 2.0 * (double)o.w->cout * o.w->cin * pixels;
+        dense += per_tap * used_taps(o.w);
+        square += per_tap * (o.w->kh * o.w->kw);
     }
-    const double planes_us = 4.5 * planes_launches + nonzero / 8.5e6;
-    cl_us += dense / (net->dtype == CADNN_F16 ? 430e6 : 80e6);
-    return cl_us < 0.77 * planes_us;
+    // (tensors brought in and taken out, beside a first layer's and a classifier's)
+    const int last = net->ops.back().kind;
+    copies = (import ? 1 : 0) + (last == OP_CONV || last == OP_DEPTHWISE || last == OP_CONCAT ? 1 : 0);
+    if (f16 && depthwise == 0 && copies == 0)
+        return 4.0 * convs + 4.2 * others + dense / 430e6 < 0.97 * (4.4 * planes_launches + nonzero / 7.8e6);
+    return 5.3 * (convs + others + (f16 ? 0 : copies)) + 6.0 * depthwise + square / (f16 ? 430e6 : 115e6) <
+           0.77 * (4.5 * planes_launches + nonzero / 8.5e6);
 }
 
 cadnn_status cl_prepare(cadnn_net* net) {
