@@ -54,19 +54,22 @@ inline __host__ __device__ int cl_split_offset(int k, int p, int r) {
 // A float as the sum of three bf16, each the nearest to what the ones before it left (down to 2^-133); an infinity
 // or a NaN is the first, a value that would round to an infinity is cut off instead.
 inline __host__ __device__ void cl_split_weight(float v, uint16_t part[3]) {
-    part[1] = part[2] = 0;
-    uint32_t u = __builtin_bit_cast(uint32_t, v);
-    if ((u & 0x7f800000u) == 0x7f800000u) {
-        part[0] = (uint16_t)(u >> 16 | ((u & 0x007fffffu) ? 0x40u : 0u));
-        return;
+    const uint32_t u = __builtin_bit_cast(uint32_t, v);
+    uint32_t top = (u + 0x7fffu + (u >> 16 & 1u)) & 0xffff0000u;
+    if ((u & 0x7fffffffu) >= 0x7f7f8000u) {         // rounds to an infinity, or is none or a NaN
+        if ((u & 0x7f800000u) == 0x7f800000u) {
+            part[0] = (uint16_t)(u >> 16 | ((u & 0x007fffffu) ? 0x40u : 0u));
+            part[1] = part[2] = 0;
+            return;
+        }
+        top = u & 0xffff0000u;
     }
-    for (int p = 0; p < 3; ++p) {
-        uint32_t top = (u + 0x7fffu + (u >> 16 & 1u)) & 0xffff0000u;
-        if ((top & 0x7f800000u) == 0x7f800000u) top = u & 0xffff0000u;
-        part[p] = (uint16_t)(top >> 16);
-        v -= __builtin_bit_cast(float, top);
-        u = __builtin_bit_cast(uint32_t, v);
-    }
+    const float rest = v - __builtin_bit_cast(float, top);
+    const uint32_t r = __builtin_bit_cast(uint32_t, rest), mid = (r + 0x7fffu + (r >> 16 & 1u)) & 0xffff0000u;
+    part[0] = (uint16_t)(top >> 16);
+    part[1] = (uint16_t)(mid >> 16);
+    // (8 bits are left: nothing is cut off above 2^-133)
+    part[2] = (uint16_t)(__builtin_bit_cast(uint32_t, rest - __builtin_bit_cast(float, mid)) >> 16);
 }
 // (offsets into the weights are 32-bit)
 constexpr size_t kClMaxWeightBytes = 0x7ffffff0u;

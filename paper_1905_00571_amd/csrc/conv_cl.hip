@@ -1048,13 +1048,17 @@ cadnn_status cl_build_plan(const cadnn_weights* w, const cadnn_weights* shortcut
     char* const img = image->data();
     // where k lies in the rows of block 0 (row 0's place of it): the divisions once per k and not once per weight
     std::vector<size_t> place;
+    std::vector<int> row_of;
     auto in_step = [&](int step, int k) {
         const size_t at = (size_t)step * 64 * row_bytes;
         return e == 4 ? at + (size_t)cl_split_offset(k, 0, 0) : at + (size_t)k * 2;
     };
     auto put = [&](const cadnn_weights* src) {
-        for (int i = 0; i < src->cout; ++i) {
-            const int co = src->perm[(size_t)i], r = cl_weight_row(co, (int)e), sw = rb == 128 ? (r >> 1) & 7 : (r >> 2) & 3;
+        // (in the order of channels: a block of 64 is put together while it is in the cache)
+        row_of.resize((size_t)src->cout);
+        for (int i = 0; i < src->cout; ++i) row_of[(size_t)src->perm[(size_t)i]] = i;
+        for (int co = 0; co < src->cout; ++co) {
+            const int i = row_of[(size_t)co], r = cl_weight_row(co, (int)e), sw = rb == 128 ? (r >> 1) & 7 : (r >> 2) & 3;
             char* const block = img + (size_t)(co / 64) * plan->steps * 64 * row_bytes;
             for (int32_t j = src->row_ptr[(size_t)i]; j < src->row_ptr[(size_t)i + 1]; ++j) {
                 const size_t at = place[(size_t)src->col_idx[(size_t)j]];
