@@ -17,8 +17,8 @@
 //   * What bounds it is the way into LDS: 50-57 bytes per clock and CU (a kernel of these loads alone, data in L2; 29
 //     from behind it), so a 64 x 64 x 64 step of fp16 takes 290 clocks where its products take 128.  Larger tiles reuse more
 //     but leave CUs idle.
-//   * With one or two workgroups a CU the rest is start and end: 1200 clocks to the first loads and 1500 from the
-//     last product to the last store.  So the launch record is fetched whole, the first weights are
+//   * With one or two workgroups a CU the rest is start and end: 1200 clocks to the first loads and 1500 (with a
+//     pass through LDS, which is gone) from the last product to the last store.  So the launch record is fetched whole, the first weights are
 //     requested before anything is computed, divisions are multiplications, and bias and residual are
 //     requested ahead of the K loop.  ResNet-50 fp16, us per pass before these and the stages above -> behind them:
 //     batch 1 371 -> 316, 8 517 -> 427, 32 981 -> 839; MobileNet-V2 fp16 batch 16 490 -> 353.
@@ -34,7 +34,7 @@
 //     for 2^-25 of it.  The bf16 pipes make six in 384 clocks of a 64 x 64 x 32 step, v_mfma_f32_32x32x2_f32
 //     the one in 1024.  Weights are laid out as their parts; a wave takes its activations apart in registers, which costs as
 //     many clocks as the products and runs beside them.  ResNet-50 fp32 at 8 images 1016 -> 805 us a pass (with two groups
-//     of waves and constants of its own).  Against 64 bits the error is 0.7 to 1.0 times that of fp32 products, K = 27 to 4608
+//     of waves and constants of its own).  Against 64 bits the error is 0.7 to 1.01 times that of fp32 products, K = 27 to 4608
 //     (3.4e-7 against 4.1e-7 at 512): six instructions round for 16 k where eight did.  What bounds a step now (860 to 940 clocks) is the
 //     products at the clock they leave the chip (490 for zeros, 610 for random operands and taking apart), then 20 KB into LDS.
 //     Sums that are not finite are done again with fp32 products, see there.
