@@ -287,6 +287,10 @@ __global__ __launch_bounds__(256 * KG, MI * NI == 1 ? 4 : 2) void cl_conv_kernel
     };
     auto past_end = [&]() __attribute__((always_inline)) {
         va = va_last = kClOutOfRange;
+        // (the scalar offsets go back to the start, from where the steps left stay inside the span: the range that an offset
+        // is checked against is the span less the scalar offset, and that is not to be negative)
+#pragma unroll
+        for (int i = 0; i < LA; ++i) wsoff[i] = 0;
 #pragma unroll
         for (int j = 0; j < LB; ++j) vb[j] = kClOutOfRange;
         f_left = 0x7fffffff;

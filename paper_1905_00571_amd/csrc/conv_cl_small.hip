@@ -83,7 +83,7 @@ __global__ __launch_bounds__(64 * kWaves) void cl_small_kernel(const ClArgs a) {
         xv[nb] = p.live ? (uint32_t)offset(a.xt, p) + (uint32_t)q * 16u : kClOutOfRange;
         xv2[nb] = a.steps > a.steps1 && p.live ? (uint32_t)offset(a.x2t, p) + (uint32_t)q * 16u : kClOutOfRange;
     }
-    // ---- the walk over K.  Past the end of the wave's part nothing is fetched (a span of 0: zeros).
+    // ---- the walk over K.  Past the end of the wave's part nothing is fetched (a span and an offset of 0: zeros).
     int left, tap = 0, todo = count;
     uint32_t x_soff;
     bool second = false;
@@ -105,12 +105,14 @@ __global__ __launch_bounds__(64 * kWaves) void cl_small_kernel(const ClArgs a) {
         const bool live = todo > 0;
         const auto wr = rsrc(a.w, live ? a.wspan : 0u);
         const auto xr = rsrc(second ? a.x2 : a.x, live ? (second ? a.x2t.span : a.xt.span) : 0u);
+        // (an offset is checked against the span less the scalar offset, which is not to be negative)
+        const uint32_t ws = live ? w_soff : 0u, xs = live ? x_soff : 0u;
 #pragma unroll
         for (int mb = 0; mb < BM; ++mb)
-            af[d][mb] = __builtin_bit_cast(cs_u4, __builtin_amdgcn_raw_buffer_load_b128(wr, HALVES == 2 ? wv0[mb] ^ (uint32_t)(half * 64) : wv0[mb], w_soff, 0));
+            af[d][mb] = __builtin_bit_cast(cs_u4, __builtin_amdgcn_raw_buffer_load_b128(wr, HALVES == 2 ? wv0[mb] ^ (uint32_t)(half * 64) : wv0[mb], ws, 0));
 #pragma unroll
         for (int nb = 0; nb < BN; ++nb)
-            bf[d][nb] = __builtin_bit_cast(cs_u4, __builtin_amdgcn_raw_buffer_load_b128(xr, second ? xv2[nb] : xv[nb], x_soff, 0));
+            bf[d][nb] = __builtin_bit_cast(cs_u4, __builtin_amdgcn_raw_buffer_load_b128(xr, second ? xv2[nb] : xv[nb], xs, 0));
         --todo;
         x_soff += 64u;
         if (HALVES == 1 || half == 1) w_soff += 64u * RB;

@@ -267,6 +267,29 @@ def test_small_tiles(cad, n, cin, cout, k, stride, h, w):
     net.free()
 
 
+@pytest.mark.parametrize("cin,cout,k", [(32, 128, 3), (16, 256, 3), (160, 128, 1), (352, 256, 1), (480, 128, 1), (416, 384, 1)])
+def test_steps_that_the_groups_of_a_split_do_not_share_evenly(cad, cin, cout, k):
+    """fp32 storage with every tile, where the last part of K is shorter than the others and the last block of channels ends
+    with the weights: what is requested behind the end comes back as zeros.  (K + 3) 2^-24 (sum |w| |x| + |b|)."""
+    ops = [Op("conv", "a", 0, 1, cin, cout, k, 1, k // 2, 0.0, False), Op("conv", "b", 1, 2, cout, 8, 1, 1, 0, 0.5, False)]
+    x, ws, bs = wl.net_tensors(ops, f"uneven-{cin}-{cout}", (2, cin, 6, 7))
+    wt = torch.from_numpy(ws[0]).double().reshape(cout, cin, k, k)
+    conv = torch.nn.functional.conv2d
+    ref = conv(torch.from_numpy(x).double(), wt, torch.from_numpy(bs[0]).double(), 1, k // 2).numpy()
+    size = conv(torch.from_numpy(x).double().abs(), wt.abs(), torch.from_numpy(np.abs(bs[0])).double(), 1, k // 2).numpy()
+    net = cad.build_net(ops, ws, bs, x.shape, cad.F32, use_graph=False)
+    net.set_op_variant(0, "cl_mfma_64x64_s3")
+    names = net.op_candidates(0)
+    assert "cl_mfma_64x64_s3g2" in names and "cl_mfma_64x128_s2g2" in names
+    for name in names:
+        net.set_op_variant(0, name)
+        net.run(torch.from_numpy(x).cuda())
+        torch.cuda.synchronize()
+        excess = np.abs(net.read_buffer(1, ref.shape).astype(np.float64) - ref) - (cin * k * k + 3) * 2.0 ** -24 * size
+        assert excess.max() <= 0.0, f"{name}: {excess.max():.3e} above the bound"
+    net.free()
+
+
 @pytest.mark.parametrize("cin,cout,k,hw", [(8, 40, 3, 9), (64, 136, 1, 13), (96, 72, 3, 10), (160, 264, 3, 6)])
 def test_fp32_products_of_extreme_values(cad, cin, cout, k, hw):
     """fp32 storage with every tile: infinities and NaN where 64-bit arithmetic has them (no filter has a zero), and values
