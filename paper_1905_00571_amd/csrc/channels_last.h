@@ -36,7 +36,7 @@ inline ClDesc cl_desc(int c, int h, int w, int ph, int pw, int pix) {
 
 constexpr int kClMaxTaps = 64;
 
-// 4-byte weights are kept as three bf16 numbers whose sum they are (fp32 products on the bf16 matrix
+// 4-byte weights are kept as three bf16 numbers whose sum they are but for a scale (fp32 products on the bf16 matrix
 // pipes): bytes of an output channel's weights in a step of `rb` bytes of activations.
 constexpr int cl_weight_bytes(int rb, int elem) { return elem == 4 ? rb / 4 * 6 : rb; }
 // The row of an output channel in its block of 64: a 32 x 32 product leaves a lane the rows 8 g + 4 h + {0..3} of its
@@ -51,25 +51,36 @@ inline __host__ __device__ int cl_weight_row(int co, int elem) {
 inline __host__ __device__ int cl_split_offset(int k, int p, int r) {
     return (((k / 16 * 3 + p) * 2 + k / 4 % 2) * 64 + r) * 16 + (k % 4 + k % 16 / 8 * 4) * 2;
 }
-// A float as the sum of three bf16, each the nearest to what the ones before it left (down to 2^-133); an infinity
-// or a NaN is the first, a value that would round to an infinity is cut off instead.
+// Weights and activations are taken apart scaled by 2^24: the last bit of any float, 2^-149, is then 2^-125, which a bf16 has room for as a
+// normal number (bf16 ends at 2^-133: unscaled, operands below 2^-109 would lose bits).
+constexpr float kClPartScale = 0x1p24f, kClPartUnscale = 0x1p-24f, kClSumUnscale = 0x1p-48f;
+// The first part of a weight that has no scaled parts; the other two then hold the upper and the lower half of the float.
+constexpr uint16_t kClWholeWeight = 0x7fff;
+// A float, scaled, as the sum of three bf16, each the nearest to what the ones before it left.  An infinity, a NaN, or
+// a value that scaled rounds to an infinity is kept whole instead behind a NaN, which the kernel sees in the sums.
 inline __host__ __device__ void cl_split_weight(float v, uint16_t part[3]) {
-    const uint32_t u = __builtin_bit_cast(uint32_t, v);
-    uint32_t top = (u + 0x7fffu + (u >> 16 & 1u)) & 0xffff0000u;
-    if ((u & 0x7fffffffu) >= 0x7f7f8000u) {         // rounds to an infinity, or is none or a NaN
-        if ((u & 0x7f800000u) == 0x7f800000u) {
-            part[0] = (uint16_t)(u >> 16 | ((u & 0x007fffffu) ? 0x40u : 0u));
-            part[1] = part[2] = 0;
-            return;
-        }
-        top = u & 0xffff0000u;
+    const float s = v * kClPartScale;
+    const uint32_t u = __builtin_bit_cast(uint32_t, s);
+    if ((u & 0x7fffffffu) >= 0x7f7f8000u) {
+        const uint32_t bits = __builtin_bit_cast(uint32_t, v);
+        part[0] = kClWholeWeight;
+        part[1] = (uint16_t)(bits >> 16);
+        part[2] = (uint16_t)bits;
+        return;
     }
-    const float rest = v - __builtin_bit_cast(float, top);
+    const uint32_t top = (u + 0x7fffu + (u >> 16 & 1u)) & 0xffff0000u;
+    const float rest = s - __builtin_bit_cast(float, top);
     const uint32_t r = __builtin_bit_cast(uint32_t, rest), mid = (r + 0x7fffu + (r >> 16 & 1u)) & 0xffff0000u;
     part[0] = (uint16_t)(top >> 16);
     part[1] = (uint16_t)(mid >> 16);
-    // (8 bits are left: nothing is cut off above 2^-133)
+    // (8 bits are left: nothing is cut off)
     part[2] = (uint16_t)(__builtin_bit_cast(uint32_t, rest - __builtin_bit_cast(float, mid)) >> 16);
+}
+// ... and the float again.
+inline __host__ __device__ float cl_join_weight(uint16_t p0, uint16_t p1, uint16_t p2) {
+    if (p0 == kClWholeWeight) return __builtin_bit_cast(float, (uint32_t)p1 << 16 | p2);
+    const float rest = __builtin_bit_cast(float, (uint32_t)p1 << 16) + __builtin_bit_cast(float, (uint32_t)p2 << 16);
+    return (__builtin_bit_cast(float, (uint32_t)p0 << 16) + rest) * kClPartUnscale;
 }
 // (offsets into the weights are 32-bit)
 constexpr size_t kClMaxWeightBytes = 0x7ffffff0u;

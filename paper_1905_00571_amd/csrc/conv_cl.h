@@ -44,12 +44,14 @@ __device__ __forceinline__ int cl_div(int v, uint32_t magic, int d) {
 typedef __bf16 cl_b2 __attribute__((ext_vector_type(2)));
 typedef float cl_f2 __attribute__((ext_vector_type(2)));
 
-// Two floats as the sum of three pairs of bf16, exactly: each is rounded to the nearest 8 bits of what
-// the ones before it left, and 24 bits are three times 8.  (Bits below 2^-133 have no place.)  An infinity or a
-// NaN, or a value that rounds to one, leaves NaN behind, which the caller sees in the sums.
+// Two floats, scaled, as the sum of three pairs of bf16, exactly: each is rounded to the nearest 8 bits of what
+// the ones before it left, and 24 bits are three times 8, down to the smallest subnormal.  An infinity or a
+// NaN, or a value that scaled rounds to one (2^104 and more), leaves NaN behind, which the caller sees in the sums.
 // (Shifts, masks and subtractions run beside the matrix products; v_dot2_f32_bf16, which would take the place of two of
 // them, does not: 12 products 434 clocks, with 60 subtractions between them 470, with 60 of it 844.)
 __device__ __forceinline__ void cl_split2(float a, float b, uint32_t* p1, uint32_t* p2, uint32_t* p3) {
+    a *= kClPartScale;
+    b *= kClPartScale;
     const uint32_t h1 = __builtin_bit_cast(uint32_t, __builtin_convertvector((cl_f2){a, b}, cl_b2));
     const float ra = a - __uint_as_float(h1 << 16), rb = b - __uint_as_float(h1 & 0xffff0000u);
     const uint32_t h2 = __builtin_bit_cast(uint32_t, __builtin_convertvector((cl_f2){ra, rb}, cl_b2));

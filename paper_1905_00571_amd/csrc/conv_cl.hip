@@ -30,8 +30,8 @@
 //     barrier, a write, a barrier and a read less); bias, residual and ReLU in fp32, one rounding.  The first loads wait for nothing but
 //     their own addresses.  fp16 with the pass / without, us: ResNet-50 batch 1 316 / 312, 8 426 / 418, 32 837 / 801 (256 -> 1024 1x1 on
 //     14 x 14 14.2 / 11.5), MobileNet-V2 batch 16 352 / 340; results the same to the bit.
-//   * fp32 storage: a float is the sum of three bf16, exactly, and a product of two floats is six products of such parts but
-//     for 2^-25 of it.  The bf16 pipes make six in 384 clocks of a 64 x 64 x 32 step, v_mfma_f32_32x32x2_f32
+//   * fp32 storage: a float scaled by 2^24 is the sum of three bf16, exactly and whatever its size, and a product of two floats is six products of
+//     such parts but for 2^-24 of it at the most (2^-28 on average for normally distributed ones).  The bf16 pipes make six in 384 clocks of a 64 x 64 x 32 step, v_mfma_f32_32x32x2_f32
 //     the one in 1024.  Weights are laid out as their parts; a wave takes its activations apart in registers, which costs as
 //     many clocks as the products and runs beside them.  ResNet-50 fp32 at 8 images 1016 -> 805 us a pass (with two groups
 //     of waves and constants of its own).  Against 64 bits the error is 0.7 to 1.01 times that of fp32 products, K = 27 to 4608
@@ -471,8 +471,8 @@ __global__ __launch_bounds__(256 * KG, MI * NI == 1 ? 4 : 2) void cl_conv_kernel
 #pragma unroll
                 for (int mi = 0; mi < AM; ++mi) read_weights(f, g, p, mi, st);
         };
-        // x w = x1 w1 + (x1 w2 + x2 w1) + (x1 w3 + x2 w2 + x3 w1) + ...: what is left out is 2^-25 of a product at
-        // the most, and of either sign.  (`load(I)`, I < 6: called behind each product; vector and scalar arithmetic
+        // x w = x1 w1 + (x1 w2 + x2 w1) + (x1 w3 + x2 w2 + x3 w1) + ...: what is left out, x2 w3 + x3 w2, is 2^-24 of a product at
+        // the most (operands just above a power of two whose second parts are largest), and of either sign.  (`load(I)`, I < 6: called behind each product; vector and scalar arithmetic
         // moves across, so that the next part is taken off beside the product before it)
         static_assert(AN == 1, "a wave takes one block of pixels apart");
         auto multiply = [&](auto F, auto&& load) __attribute__((always_inline)) {
@@ -562,8 +562,8 @@ __global__ __launch_bounds__(256 * KG, MI * NI == 1 ? 4 : 2) void cl_conv_kernel
                 if (s + 1 < steps) stage(Set1(), std::false_type(), false, s + 1);
             }
         }
-        // An infinity or a NaN among the operands, or parts beyond the range, leave sums that are not finite: a tile
-        // with such sums is done again with fp32 products, and they take what these give.
+        // An infinity or a NaN among the operands, or operands or sums whose scale takes them beyond the range (2^104, 2^80), leave
+        // sums that are not finite: a tile with such sums is done again with fp32 products, and they take what these give.
         // (Channels behind the last one have weights that nobody wrote.)
         float seen = 0.0f;
         auto look = [&](auto ALL) __attribute__((always_inline)) {
@@ -606,11 +606,8 @@ __global__ __launch_bounds__(256 * KG, MI * NI == 1 ? 4 : 2) void cl_conv_kernel
                     for (int i = 0; i < 8; ++i)
 #pragma unroll
                         for (int mi = 0; mi < AM; ++mi) {
-                            auto part = [&](int p) __attribute__((always_inline)) {
-                                const uint32_t two = af[0][p][mi][i / 2];
-                                return __uint_as_float(i % 2 ? two & 0xffff0000u : two << 16);
-                            };
-                            const float w = part(0) + (part(1) + part(2));
+                            auto part = [&](int p) __attribute__((always_inline)) { return (uint16_t)(af[0][p][mi][i / 2] >> (i % 2 * 16)); };
+                            const float w = cl_join_weight(part(0), part(1), part(2));
 #pragma unroll
                             for (int ni = 0; ni < AN; ++ni)
                                 acc[mi][ni] = __builtin_amdgcn_mfma_f32_32x32x2f32(w, __uint_as_float(bf[0][i / 4][ni][i % 4]), acc[mi][ni], 0, 0, 0);
@@ -625,7 +622,14 @@ __global__ __launch_bounds__(256 * KG, MI * NI == 1 ? 4 : 2) void cl_conv_kernel
                 for (int ni = 0; ni < AN; ++ni)
 #pragma unroll
                     for (int i = 0; i < 16; ++i)
-                        if (kept[mi][ni][i] * 0.0f == 0.0f) acc[mi][ni][i] = kept[mi][ni][i];
+                        if (kept[mi][ni][i] * 0.0f == 0.0f) acc[mi][ni][i] = kept[mi][ni][i] * kClSumUnscale;
+        } else {
+#pragma unroll
+            for (int mi = 0; mi < AM; ++mi)
+#pragma unroll
+                for (int ni = 0; ni < AN; ++ni)
+#pragma unroll
+                    for (int i = 0; i < 16; ++i) acc[mi][ni][i] *= kClSumUnscale;
         }
     }
     asm volatile("s_waitcnt vmcnt(0)" ::: "memory");        // (the residual's pieces)

@@ -106,7 +106,7 @@ __global__ __launch_bounds__(256) void cl_arrange_kernel(const ClArrange a) {
 #pragma unroll
                 for (int j = 0; j < 8; ++j) {
                     v[j] = mine[(k0 + j / 4 * 8 + j % 4) * a.taps + t];
-                    large |= (__float_as_uint(v[j]) & 0x7fffffffu) >= 0x7f7f8000u;      // rounds to an infinity, or is none or a NaN
+                    large |= (__float_as_uint(v[j] * kClPartScale) & 0x7fffffffu) >= 0x7f7f8000u;       // has no scaled parts
                 }
                 uint32_t part[3][4];
                 if (large) {

@@ -324,6 +324,46 @@ def test_fp32_products_of_extreme_values(cad, cin, cout, k, hw):
     net.free()
 
 
+@pytest.mark.parametrize("cin,cout,k", [(16, 40, 3), (64, 72, 1)])
+@pytest.mark.parametrize("x_exp,w_exp", [(-120, 100), (-147, 95), (95, -120), (95, -147), (-60, -60), (0, 0)])
+def test_fp32_products_of_operands_of_every_magnitude(cad, cin, cout, k, x_exp, w_exp):
+    """fp32 storage with every tile: tiny and subnormal activations under large weights, and the other way round, some
+    of them among ordinary ones, count with all of their bits: (K + 3) 2^-24 (sum |w| |x| + |b|).  The last
+    pixels hold the operands whose product is furthest from that of its leading parts, all of one sign."""
+    rng = np.random.default_rng(1000 + cin + x_exp)
+    hw, pad, n = 9, k // 2, 2
+    x = np.ldexp(rng.standard_normal((n, cin, hw, hw)), x_exp).astype(np.float32)
+    w = np.ldexp(rng.choice([-1.0, 1.0], (cout, cin, k, k)) * rng.uniform(0.1, 1.0, (cout, cin, k, k)), w_exp).astype(np.float32)
+    if x_exp == -120:
+        x[0, :, :4] = np.ldexp(rng.standard_normal((cin, 4, hw)), 0)                # whole rows of ordinary ones
+    if x_exp == 0:
+        x[1], w[8:] = 1.0 + 2.0 ** -8 - 2.0 ** -17, 1.0 + 2.0 ** -8 - 2.0 ** -17
+    if w_exp == -120:
+        w[:, : cin // 2] = 0.0
+    ops = [Op("conv", "a", 0, 1, cin, cout, k, 1, pad, 0.0, False), Op("conv", "b", 1, 2, cout, 8, 1, 1, 0, 0.5, False)]
+    _, ws, bs = wl.net_tensors(ops, "magnitudes", x.shape)
+    ws[0], bs[0] = w, np.zeros(cout, np.float32)
+    conv = torch.nn.functional.conv2d
+    ref = conv(torch.from_numpy(x).double(), torch.from_numpy(w).double(), None, 1, pad)
+    size = conv(torch.from_numpy(x).double().abs(), torch.from_numpy(w).double().abs(), None, 1, pad)
+    # (a sum that ends below the normal numbers is rounded to a multiple of 2^-149)
+    bound = (cin * k * k + 3) * 2.0 ** -24 * size + 2.0 ** -149
+
+    def check(got, what):
+        excess = ((torch.as_tensor(got).double().cpu() - ref).abs() - bound).max().item()
+        assert excess <= 0.0, f"{what}: {excess:.3e} above the bound"
+
+    net = cad.build_net(ops, ws, bs, x.shape, cad.F32, use_graph=False)
+    net.set_op_variant(0, "cl_mfma_64x64_s3")
+    for name in net.op_candidates(0):
+        net.set_op_variant(0, name)
+        net.run(torch.from_numpy(x).cuda())
+        torch.cuda.synchronize()
+        check(net.read_buffer(1, tuple(ref.shape)), name)
+    net.free()
+    check(cad.cadnn_dense_conv2d(torch.from_numpy(w).cuda(), torch.from_numpy(x).cuda(), 1, pad), "layer call")
+
+
 @pytest.mark.parametrize("dtype_name", ["f32", "f16"])
 @pytest.mark.parametrize("k,pad", [(1, 0), (2, 0), (2, 1), (3, 1), (3, 0), (5, 2)])
 def test_pools_and_copies_of_non_finite_values(cad, k, pad, dtype_name):
