@@ -331,9 +331,11 @@ cadnn_status cadnn_net_workspace_bytes(const cadnn_net* net, size_t* bytes);
  * A net with enough work (a model of its launches and multiply-adds decides) runs with
  * channels-last tensors on the matrix cores instead, over zero-filled weights: there a pruned weight meets its
  * activation, so an infinity or NaN that arises in a map reaches every output channel of its windows, not only those
- * with a nonzero weight on it.  Pinning a convolution to a variant of the other kind (cadnn_net_set_op_variant) changes
- * the whole net over: a net that is to keep pruned weights away from such values has one of its convolutions pinned
- * to a variant of the compressed kernels.  Variants pinned on a weight handle (cadnn_conv2d_set_variant,
+ * with a nonzero weight on it (an fp16 map reaches infinity at 65520).  Which nets the model takes there is no part of this interface: it
+ * moves with the kernels, to smaller images and batches of late (fp16 ResNet-50, 80 % sparse, from one image of 130 x 130, fp32 from
+ * two images), so a program must not rely on where a net of its own lies.  Pinning a convolution to a variant of the other kind
+ * (cadnn_net_set_op_variant) changes the whole net over: a net that is to keep pruned weights away from such values has one of its
+ * convolutions pinned to a variant of the compressed kernels, and stays there whatever the model says.  Variants pinned on a weight handle (cadnn_conv2d_set_variant,
  * cadnn_conv2d_tune) are those of plane layouts; a net that runs channels-last does not look at them. */
 #define CADNN_NET_GRAPH 1
 #define CADNN_NET_TUNE 2

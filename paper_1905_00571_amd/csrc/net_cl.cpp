@@ -238,18 +238,22 @@ std::unique_ptr<ClNet> cl_layout(const cadnn_net* net) {
 }
 
 // Which execution a net takes unless a variant of the other is pinned.  Both are modelled as a cost per launch plus
-// multiply-adds at a rate: the compressed kernels of the plane layouts do the nonzero ones at 7.8 to 8.5 TFLOP/s, the matrix cores all
-// of them at 430 (fp16) or 115 (fp32: bf16 parts; 80 with fp32 products).  Measured (us, planes / channels-last, untuned; * the rule
-// takes the second; ResNet-50 and the bottleneck 80 % sparse): fp16 ResNet-50 batch 1 379 / 278*, of 160 x 160
-// 302 / 263*, of 100 x 100 269 / 259*, batch 8 1725 / 417*; VGG-16 336 / 163*; Inception-V3 599 / 510*, of 230 x 230 420 / 487, batch 2
-// 922 / 551*, 4 of 150 x 150 664 / 503*; bottleneck on 28 x 28 16 / 21, 8 images of 14 x 14 16 / 22.  fp32 ResNet-50 batch 1 400 / 483,
-// 2 582 / 533*, 3 of 128 x 128 463 / 483, 6 of 110 x 110 721 / 529*; VGG-16 328 / 347, batch 2 564 / 533, 4 948 / 926*; Inception-V3
-// 546 / 978, batch 3 1088 / 1109; bottleneck batch 2 32 / 41.  Nets with depthwise layers keep the line that goes with depthwise layers
-// fused on the planes, which is a feature of that execution that programs see (MobileNet-V1 at 4 and V2 at 2 images report it), and
-// parts of a net in fp16 that take or give maps the one that counts a rectangular filter as the square bank it lies in: fp16
-// MobileNet-V1 batch 4 223 / 132, 6 350 / 144*; MobileNet-V2 batch 2 206 / 211, 4 268 / 224, 8 376 / 266, 12 487 / 294*; fp32
-// MobileNet-V1 batch 2 179 / 162, 4 258 / 189, V2 batch 8 438 / 391.  No net of these goes channels-last to a loss; tuning
-// (CADNN_NET_TUNE) times both for a net that does go.
+// multiply-adds at a rate: of the nonzero weights for the compressed kernels of the plane layouts, of all of them for the matrix cores.
+// fp16 nets from an image to classes, without depthwise layers: fitted to ResNet-50 at 13 sizes from one image of 96 x 96 to 16 and at 50
+// to 95 % sparsity, VGG-16 and Inception-V3, so that no net of these 85 goes channels-last to a loss (the nearest is modelled at 1.03
+// times its planes).  us, planes / channels-last, untuned (* the rule takes the second), one image of 96, 160 and 224, two of 224:
+//   80 %  264 / 248, 303 / 263*, 379 / 277*, 579 / 303*     90 %  222 / 246, 246 / 261, 291 / 275*, 405 / 302*
+//   95 %  197 / 246, 211 / 261, 242 / 276, 317 / 302*       VGG-16 336 / 161*, Inception-V3 599 / 508*, of 230 x 230 419 / 488, four of
+//   150 x 150 665 / 501 (its launches overlap on planes, and the fit keeps it there).
+// fp32 nets: ResNet-50 80 % sparse at one image of 224 x 224 398 / 490, two 583 / 539*, three of 128 x 128 461 / 492, four of 160 x 160 721 / 546*;
+// 90 % at two 419 / 540, eight 1062 / 828; VGG-16 322 / 339, two 557 / 535, four 948 / 926*; Inception-V3 545 / 1015, three 1089 / 1133;
+// bottleneck 80 % at two images 31 / 41, four 46 / 47*.
+// Nets with depthwise layers keep an older line, with a depthwise launch at 6 us and rectangular filters counted as the square bank
+// they lie in: on planes their depthwise layers run inside the convolutions that feed them, which programs see (MobileNet-V1 at 4
+// and V2 at 2 images report it).  That costs fp16 MobileNet-V1 batch 4 223 / 132 us, V2 batch 4 268 / 224, 8 376 / 266,
+// fp32 V1 batch 4 258 / 189.  Parts of a net in fp16 that take or give maps keep it too, with the copies uncounted: a bottleneck,
+// 80 % sparse, of one image of 56 x 56 goes channels-last to a loss there (18.5 / 23.5), at 16 of 14 x 14 and 50 % to a gain (34 / 24).
+// Tuning (CADNN_NET_TUNE) times both executions of a net that does go.
 bool cl_expected_faster(const cadnn_net* net) {
     const size_t e = net->elem();
     const bool f16 = net->dtype == CADNN_F16;
@@ -274,7 +278,7 @@ bool cl_expected_faster(const cadnn_net* net) {
     const int last = net->ops.back().kind;
     copies = (import ? 1 : 0) + (last == OP_CONV || last == OP_DEPTHWISE || last == OP_CONCAT ? 1 : 0);
     if (f16 && depthwise == 0 && copies == 0)
-        return 4.0 * convs + 4.2 * others + dense / 430e6 < 0.97 * (4.4 * planes_launches + nonzero / 7.8e6);
+        return 4.7 * convs + 1.3 * others + dense / 350e6 < 3.8 * planes_launches + nonzero / 7.5e6;
     return 5.3 * (convs + others + (f16 ? 0 : copies)) + 6.0 * depthwise + square / (f16 ? 430e6 : 115e6) <
            0.77 * (4.5 * planes_launches + nonzero / 8.5e6);
 }

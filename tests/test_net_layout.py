@@ -304,6 +304,21 @@ def test_first_layer_steps_end_inside_the_workspace(family, n, size, first):
     assert end <= nbytes, (end, nbytes)
 
 
+@pytest.mark.parametrize("sparsity,planes,channels_last",
+                         [(0.8, [], [(1, 160), (1, 224), (2, 100)]),
+                          (0.9, [(1, 96), (1, 160)], [(1, 224), (2, 160), (4, 100)]),
+                          (0.95, [(1, 96), (1, 160), (1, 224), (1, 288), (2, 160)], [(2, 224), (4, 160), (8, 112)])])
+def test_fp16_nets_run_where_they_were_measured_to_be_faster(sparsity, planes, channels_last):
+    """ResNet-50 of uniform sparsity, by images and their size: the execution that was the faster one, by 3 to 50 %, on
+    an MI355X (the times stand at the rule)."""
+    ops = wl.resnet50_ops(uniform=sparsity)
+    _, ws, _ = wl.net_tensors(ops, "line", (1, 3, 32, 32))
+    for sizes, cl in ((planes, False), (channels_last, True)):
+        for n, size in sizes:
+            infos, _ = cad.plan_net(ops, ws, (n, 3, size, size), dtype=cad.F16)
+            assert (infos[0]["plane"] == 1) == cl, (n, size)
+
+
 @pytest.mark.parametrize("n,w,stride", [(1, 160_000_000, 64), (1, 150_000_000, 64), (70_000, 8, 1)])
 def test_tensors_too_large_for_channels_last_stay_on_planes(n, w, stride):
     """Five input channels are padded to 32 there: a row of 2^32 elements and more is not taken for a short one, and a
