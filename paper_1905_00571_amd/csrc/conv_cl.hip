@@ -287,8 +287,8 @@ __global__ __launch_bounds__(256 * KG, MI * NI == 1 ? 4 : 2) void cl_conv_kernel
     };
     auto past_end = [&]() __attribute__((always_inline)) {
         va = va_last = kClOutOfRange;
-        // (the scalar offsets go back to the start, from where the steps left stay inside the span: the range that an offset
-        // is checked against is the span less the scalar offset, and that is not to be negative)
+        // (the scalar offsets go back to the start, from where the steps left stay inside the span: what an offset is checked
+        // against, the span or the span less the scalar offset, is then never negative)
 #pragma unroll
         for (int i = 0; i < LA; ++i) wsoff[i] = 0;
 #pragma unroll

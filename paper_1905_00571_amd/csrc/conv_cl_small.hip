@@ -105,7 +105,7 @@ __global__ __launch_bounds__(64 * kWaves) void cl_small_kernel(const ClArgs a) {
         const bool live = todo > 0;
         const auto wr = rsrc(a.w, live ? a.wspan : 0u);
         const auto xr = rsrc(second ? a.x2 : a.x, live ? (second ? a.x2t.span : a.xt.span) : 0u);
-        // (an offset is checked against the span less the scalar offset, which is not to be negative)
+        // (what an offset is checked against, the span or the span less the scalar offset, is never negative)
         const uint32_t ws = live ? w_soff : 0u, xs = live ? x_soff : 0u;
 #pragma unroll
         for (int mb = 0; mb < BM; ++mb)
