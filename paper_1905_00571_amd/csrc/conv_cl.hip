@@ -797,7 +797,11 @@ hipError_t launch_cl_tile(const ClArgs& a, hipStream_t s) {
 
 template <typename T, int RB, int MODE>
 hipError_t launch_cl_rb(const ClArgs& a, const ClVariant& v, hipStream_t s) {
-    if (v.kg == 2) return v.ni == 2 ? launch_cl_tile<T, RB, 1, 2, 2, 2, MODE>(a, s) : launch_cl_tile<T, RB, 1, 1, 3, 2, MODE>(a, s);
+    if (v.kg == 2) {
+        // (layer calls take the cost rule's pick, which is never one of these in 2-byte storage)
+        if constexpr (sizeof(T) == 2 && MODE == CL_PLANES) return hipErrorInvalidValue;
+        else return v.ni == 2 ? launch_cl_tile<T, RB, 1, 2, 2, 2, MODE>(a, s) : launch_cl_tile<T, RB, 1, 1, 3, 2, MODE>(a, s);
+    }
     if (v.mi == 2) return v.ni == 2 ? launch_cl_tile<T, RB, 2, 2, 2, 1, MODE>(a, s) : launch_cl_tile<T, RB, 2, 1, 3, 1, MODE>(a, s);
     if (v.ni == 2) return launch_cl_tile<T, RB, 1, 2, 3, 1, MODE>(a, s);
     return v.s == 3 ? launch_cl_tile<T, RB, 1, 1, 3, 1, MODE>(a, s) : launch_cl_tile<T, RB, 1, 1, 4, 1, MODE>(a, s);
@@ -889,7 +893,7 @@ cadnn_status cl_prepare_variant(const ClVariant& v, ClPlan* plan, int64_t pixels
 // Two groups of waves pay in fp32 where a workgroup has the CU to itself: 128 -> 128 3x3 on 8 images of 28 x 28 19.2 -> 16.9 us,
 // 512 -> 512 3x3 on 14 x 14 (split in four as well) 20.8 -> 17.9.  In fp16 a step is bound by the way into LDS, and what
 // they gain on such a layer (7.3 -> 6.5 us launched on its own) is lost again between the launches of a graph: ResNet-50 at 8 images 426 -> 435 us a
-// pass.  Small tiles (conv_cl_small.hip) are a start, a launch that grows with the workgroups, and their operands at 18 bytes a clock;
+// pass.  So in 2-byte storage neither this rule nor tuning, which times layers alone, takes them; a pin does.  Small tiles (conv_cl_small.hip) are a start, a launch that grows with the workgroups, and their operands at 18 bytes a clock;
 // in graphs of equal layers at one image, us a layer, best large tile / best small one: 256 -> 256 3x3 on 14 x 14 8.6 / 7.0, 1024 -> 256
 // 1x1 5.5 / 4.0, 128 -> 128 3x3 on 28 x 28 7.2 / 6.4, 2048 -> 512 1x1 on 7 x 7 7.4 / 6.2; 256 -> 1024 1x1 5.9 / 6.7, 64 -> 256 1x1 on
 // 56 x 56 4.3 / 8.8; at 4 images 1024 -> 256 5.7 / 5.4, 256 -> 256 3x3 9.1 / 10.7.  Four stages pay where workgroups are alone or two to a CU and the K loop is long; there is no use for more: six and eight
@@ -918,9 +922,9 @@ const ClVariant* cl_pick(int cout, const ClPlan& plan, int64_t pixels, bool f16)
             if (!best || cost < best_cost) { best = &v; best_cost = cost; }
             continue;
         }
+        if (v.kg == 2 && f16) continue;
         const int slices = v.sk * v.kg, steps = (plan.steps + slices - 1) / slices;
         if (v.s == 4 && (blocks > 2 * kNumCus || steps < 4)) continue;
-        if (v.kg == 2 && f16) continue;
         const int size = v.mi * v.ni, weights = cl_weight_bytes(plan.rb, f16 ? 2 : 4);
         const int stage = (v.mi * weights * 64 + 4095) / 4096 * 4096 + 64 * v.ni * plan.rb;
         const int lds = v.kg * v.s * stage + 64 * v.ni * 16 + 64 * v.mi * 8 + 16;

@@ -385,6 +385,8 @@ cadnn_status cl_tune(cadnn_net* net, const void* x, void* y, hipStream_t s) {
         const ClVariant *best = nullptr, *had = c.v;
         float best_ms = 0.0f;
         for (const ClVariant* v : cl_candidates(net, i)) {
+            // (two wave groups in 2-byte storage win a layer timed alone and lose the net, see the cost rule)
+            if (v->kg == 2 && net->dtype == CADNN_F16) continue;
             if ((st = cl_prepare_variant(*v, &c.plan, out_pixels(op), op.out.c)) != CADNN_OK) break;
             c.v = v;
             float total = 0.0f;

@@ -151,6 +151,26 @@ def test_channels_last_tuned(cad):
     net.free()
 
 
+def test_tuning_in_2_byte_storage_leaves_out_two_wave_groups(cad, capfd, monkeypatch):
+    """They win a layer timed alone, which is what tuning measures, and lose the net: offered for a pin, never tuned to."""
+    ops = [Op("conv", f"c{i}", i, i + 1, 256, 256, 3, 1, 1, 0.8, True) for i in range(2)]
+    x, ws, bs = wl.net_tensors(ops, "tune-groups", (2, 256, 14, 14))
+    monkeypatch.setenv("CADNN_TUNE_LOG", "1")
+    for dtype, tuned in ((cad.F16, False), (cad.F32, True)):
+        net = cad.build_net(ops, ws, bs, x.shape, dtype, use_graph=False, tune=True)
+        net.set_op_variant(0, "cl_mfma_64x64_s3")
+        xd = torch.from_numpy(x).cuda()
+        net.run(xd.half() if dtype == cad.F16 else xd)
+        torch.cuda.synchronize()
+        names = net.op_candidates(0)
+        assert "cl_mfma_64x64_s3g2" in names
+        timed = [line for line in capfd.readouterr().err.splitlines() if line.startswith("[cadnn tune] cl ")]
+        assert timed and any("s3g2" in line for line in timed) == tuned
+        net.set_op_variant(0, "cl_mfma_64x64_s3g2")
+        assert net.op_variant(0) == "cl_mfma_64x64_s3g2"
+        net.free()
+
+
 @pytest.mark.parametrize("family,shape", [("mobilenet_v1", (16, 3, 128, 129)), ("vgg16", (2, 3, 96, 112))])
 def test_tuning_times_both_executions(cad, family, shape, capfd, monkeypatch):
     """A net that the rule takes channels-last is tuned on plane layouts too, and what stays is the execution whose
