@@ -92,20 +92,24 @@ __global__ __launch_bounds__(256) void cl_arrange_kernel(const ClArrange a) {
             }
         }
         __syncthreads();
-        if (co >= a.cout) return;
-        const int row = cl_weight_row(co, (int)sizeof(T)), sw = a.pieces == 8 ? (row >> 1) & 7 : (row >> 2) & 3;
         const int64_t steps = (int64_t)a.taps * a.steps_tap;
         if constexpr (sizeof(T) == 4) {
-            // eight k of one half of a wave: 16 bytes of each of the three parts
-            const int halves = a.kpr / 8;
-            for (int i = lane; i < a.taps * halves; i += 64) {
-                const int t = i / halves, h = i - t * halves, k0 = h / 2 * 16 + h % 2 * 4;
-                char* const block = (char*)a.wr + ((co / 64) * steps + (int64_t)t * a.steps_tap + step) * 64 * cl_weight_bytes(a.kpr * 4, 4);
+            // Eight k of one half of a wave: 16 bytes of each of the three parts.  The four filters of the workgroup are four rows side by
+            // side, so four lanes write 64 bytes of a part.  (A wave for its own filter, 16 bytes at a time in lines 1 KB apart: us of the
+            // launch 5.2 -> 4.1 for 16 -> 58 7x7, 5.6 -> 4.2 for 107 -> 68 1x1 on 102 x 102, 12.8 -> 9.8 for 512 -> 512 3x3; 4-byte weights
+            // as they are took 3.9, 4.0, 10.0.)
+            const int log_halves = a.kpr == 32 ? 2 : 1;
+            for (int i = tid; i < a.taps << (log_halves + 2); i += 256) {
+                const int at = i >> 2, t = at >> log_halves, h = at - (t << log_halves), k0 = h / 2 * 16 + h % 2 * 4;
+                const int r = i & 3, filter = co - wv + r;
+                if (filter >= a.cout) continue;
+                const T* const from = lds + r * all + k0 * a.taps + t;
+                char* const block = (char*)a.wr + ((filter / 64) * steps + (int64_t)t * a.steps_tap + step) * 64 * cl_weight_bytes(a.kpr * 4, 4);
                 float v[8];
                 bool large = false;
 #pragma unroll
                 for (int j = 0; j < 8; ++j) {
-                    v[j] = mine[(k0 + j / 4 * 8 + j % 4) * a.taps + t];
+                    v[j] = from[(j / 4 * 8 + j % 4) * a.taps];
                     large |= (__float_as_uint(v[j] * kClPartScale) & 0x7fffffffu) >= 0x7f7f8000u;       // has no scaled parts
                 }
                 uint32_t part[3][4];
@@ -124,9 +128,11 @@ __global__ __launch_bounds__(256) void cl_arrange_kernel(const ClArrange a) {
                 }
 #pragma unroll
                 for (int p = 0; p < 3; ++p)
-                    *(uint4*)(block + cl_split_offset(k0, p, row)) = make_uint4(part[p][0], part[p][1], part[p][2], part[p][3]);
+                    *(uint4*)(block + cl_split_offset(k0, p, filter % 64)) = make_uint4(part[p][0], part[p][1], part[p][2], part[p][3]);
             }
         } else {
+            if (co >= a.cout) return;
+            const int row = cl_weight_row(co, (int)sizeof(T)), sw = a.pieces == 8 ? (row >> 1) & 7 : (row >> 2) & 3;
             for (int i = lane; i < a.taps * a.pieces; i += 64) {
                 const int t = i / a.pieces, pc = i - t * a.pieces;
                 V p;
