@@ -242,7 +242,7 @@ cadnn_status cadnn_graph_launch_floor(void* scratch32, int launches, int reps, v
  * [cout][cin][kh][kw] DEVICE weight tensor, same fused epilogue), used for the
  * dense-vs-compressed comparison the paper reports (Section 5) and as the
  * fallback for layers that are not pruned.  Layers with enough work bring x and w into a
- * workspace laid out for the matrix cores first: up to 128 MiB of such workspaces are kept for
+ * workspace laid out for the matrix cores first: up to 192 MiB of such workspaces are kept for
  * later calls, of any stream and thread.  Where none is to be had, and on a stream that is being
  * captured, the layer runs on the tensors as they are: slower, and with its fp32 sums taken in
  * another order. */

@@ -149,7 +149,8 @@ __global__ __launch_bounds__(256) void cl_arrange_kernel(const ClArrange a) {
 // them 16 to 18; and 50 us where every call is waited for, the pool giving its memory back each time), more than
 // the kernels of most layers, so blocks are kept: taken under the lock, owned by one call until it returns
 // them, and handed on with an event that the next user's stream waits for (8.6 us in all).  At most
-// kKeep blocks of at most kKeepBytes together are held; one that no longer fits goes back to the device, in the order
+// kKeep blocks of at most kKeepBytes together are held, of at most half of that each (96 MiB: 64 MiB of 4-byte weights, which
+// take 6 bytes here); one that no longer fits goes back to the device, in the order
 // of the stream that takes its place.  For larger workspaces every call allocates for itself in stream
 // order.  (No captured stream comes here.)  All of it is given back by release(), which the library calls itself when
 // an allocation of its own finds no memory.
@@ -250,7 +251,7 @@ class WorkspacePool {
         }
         return e;
     }
-    static constexpr size_t kKeep = 8, kKeepBytes = (size_t)128 << 20;
+    static constexpr size_t kKeep = 8, kKeepBytes = (size_t)192 << 20;
     // (the stream is in an error state: the block is not handed on, nor freed under work that may still run)
     static hipError_t give_up(const Workspace& w, hipError_t e) {
         (void)hipEventDestroy(w.used);

@@ -149,6 +149,25 @@ def test_kept_workspaces_are_given_back():
     assert torch.cuda.mem_get_info()[0] >= free - (4 << 20)
 
 
+def test_workspaces_of_large_fp32_weights_are_kept():
+    """56 MiB of weights take 84 at the 6 bytes of their device form: held for the next call like 64 MiB of others."""
+    if not torch.cuda.is_available():
+        pytest.skip("no GPU")
+    import paper_1905_00571_amd as cad
+    x, wt = torch.randn(1, 1600, 7, 7).cuda(), (torch.randn(1024, 1600, 3, 3) * 0.01).cuda()
+    y = cad.cadnn_dense_conv2d(wt, x, 1, 1)
+    torch.cuda.synchronize()
+    cad.cadnn_release_workspaces()
+    torch.cuda.synchronize()
+    free = torch.cuda.mem_get_info()[0]
+    cad.cadnn_dense_conv2d(wt, x, 1, 1, out=y)
+    torch.cuda.synchronize()
+    assert torch.cuda.mem_get_info()[0] <= free - (80 << 20)
+    cad.cadnn_release_workspaces()
+    torch.cuda.synchronize()
+    assert torch.cuda.mem_get_info()[0] >= free - (4 << 20)
+
+
 class _PoolLocation(ctypes.Structure):
     _fields_ = [("type", ctypes.c_int), ("id", ctypes.c_int)]
 
