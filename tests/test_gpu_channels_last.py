@@ -344,6 +344,76 @@ def test_fp32_products_of_extreme_values(cad, cin, cout, k, hw):
     net.free()
 
 
+def assert_fp32_sums(got, ref, size, terms, what):
+    """Infinities and NaN where 64-bit arithmetic has them, else within (terms + 3) 2^-24 size."""
+    finite = np.isfinite(ref)
+    assert np.array_equal(got[~finite], ref[~finite].astype(np.float32), equal_nan=True), what
+    excess = np.abs(got[finite].astype(np.float64) - ref[finite]) - (terms + 3) * 2.0 ** -24 * size[finite]
+    assert excess.max() <= 0.0, f"{what}: {excess.max():.3e} above the bound"
+
+
+@pytest.mark.parametrize("where", ["main", "shortcut"])
+@pytest.mark.parametrize("cin,csc,cout,k", [(96, 64, 72, 3), (40, 24, 136, 1), (64, 160, 40, 3)])
+def test_repeat_with_fp32_products_across_a_fused_projection(cad, cin, csc, cout, k, where):
+    """An infinity in the layer's own input, or in the input of the stride-2 projection that is more of its K: every tile,
+    two wave groups and splits that begin inside the projection among them, gives what 64-bit arithmetic gives on the maps."""
+    ops = [Op("conv", "m", 0, 1, 8, cin, 1, 1, 0, 0.0, False), Op("conv", "q", 0, 2, 8, csc, 1, 1, 0, 0.0, False),
+           Op("conv", "p", 2, 3, csc, cout, 1, 2, 0, 0.0, False), Op("conv", "a", 1, 4, cin, cout, k, 2, k // 2, 0.0, False, 3),
+           Op("conv", "out", 4, 5, cout, 8, 1, 1, 0, 0.5, False)]
+    n, h, w = 2, 11, 9
+    x, ws, bs = wl.net_tensors(ops, f"repeat-{cin}", (n, 8, h, w))
+    x, ws = x.copy(), [None if t is None else t.copy() for t in ws]
+    x[0, 3, 4, 4], x[1, 3, 0, 0], x[1, 3, h - 1, w - 1] = 1e30, -1e30, 1e30
+    for i in (0, 1):
+        ws[i][:, 3] = 1e-30
+    ws[0 if where == "main" else 1][5, 3] = 1e30           # (that channel of that map overflows)
+    net = cad.build_net(ops, ws, bs, x.shape, cad.F32, use_graph=False)
+    net.set_op_variant(0, "cl_mfma_64x64_s3")
+    names = net.op_candidates(3)
+    assert net.op_variant(2) == "fused" and "cl_mfma_64x64_s3g2" in names
+    conv = torch.nn.functional.conv2d
+    for name in names:
+        net.set_op_variant(3, name)
+        net.run(torch.from_numpy(x).cuda())
+        torch.cuda.synchronize()
+        maps = [net.read_buffer(1, (n, cin, h, w)), net.read_buffer(2, (n, csc, h, w))]
+        assert [bool(np.isinf(m).any()) for m in maps] == [where == "main", where == "shortcut"]
+        ref, size = 0.0, 0.0
+        for m, i in ((maps[0], 3), (maps[1], 2)):
+            t, wt, b = torch.from_numpy(m).double(), torch.from_numpy(ws[i]).double(), torch.from_numpy(bs[i]).double()
+            wt = wt.reshape(cout, -1, ops[i].k, ops[i].k)
+            ref = ref + conv(t, wt, b, 2, ops[i].pad).numpy()
+            size = size + conv(t.abs(), wt.abs(), b.abs(), 2, ops[i].pad).numpy()
+        assert not np.isfinite(ref).all() and np.isfinite(ref).any()
+        assert_fp32_sums(net.read_buffer(4, ref.shape), ref, size, cin * k * k + csc, name)
+    net.free()
+
+
+@pytest.mark.parametrize("k,stride,pad,h,w", [(3, 2, 0, 19, 23), (7, 2, 3, 21, 20), (5, 1, 0, 11, 9)])
+def test_repeat_with_fp32_products_in_a_first_layer(cad, k, stride, pad, h, w):
+    """... and in a packed first layer, whose steps are wider than its filter rows."""
+    ops = [Op("conv", "stem", 0, 1, 3, 40, k, stride, pad, 0.0, False), Op("conv", "next", 1, 2, 40, 8, 1, 1, 0, 0.5, False)]
+    x, ws, bs = wl.net_tensors(ops, f"stem-repeat-{k}", (2, 3, h, w))
+    x = x.copy()
+    x[0, 1, 0, 0], x[0, 2, h - 1, w - 1], x[0, 0, h // 2, 0], x[1, 0, h // 2, w // 2] = np.inf, -np.inf, np.nan, 3e38
+    wt = torch.from_numpy(ws[0]).double().reshape(40, 3, k, k)
+    conv = torch.nn.functional.conv2d
+    ref = conv(torch.from_numpy(x).double(), wt, torch.from_numpy(bs[0]).double(), stride, pad).numpy()
+    size = conv(torch.from_numpy(x).double().abs(), wt.abs(), torch.from_numpy(np.abs(bs[0])).double(), stride, pad).numpy()
+    ref[np.abs(ref) > np.finfo(np.float32).max] = np.nan
+    sure = np.isfinite(ref)
+    net = cad.build_net(ops, ws, bs, x.shape, cad.F32, use_graph=False)
+    net.set_op_variant(0, "cl_mfma_64x64_s3")
+    for name in net.op_candidates(0):
+        net.set_op_variant(0, name)
+        net.run(torch.from_numpy(x).cuda())
+        torch.cuda.synchronize()
+        got = net.read_buffer(1, ref.shape)
+        assert not np.isfinite(got[~sure]).any(), name
+        assert_fp32_sums(got[sure], ref[sure], size[sure], 3 * k * k, name)
+    net.free()
+
+
 @pytest.mark.parametrize("cin,cout,k", [(16, 40, 3), (64, 72, 1)])
 @pytest.mark.parametrize("x_exp,w_exp", [(-120, 100), (-147, 95), (95, -120), (95, -147), (-60, -60), (0, 0)])
 def test_fp32_products_of_operands_of_every_magnitude(cad, cin, cout, k, x_exp, w_exp):

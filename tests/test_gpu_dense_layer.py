@@ -55,6 +55,34 @@ def test_dense_layer_against_64_bits(case, dtype):
     assert got.shape == ref.shape and excess <= 0.0, f"{case} {dtype}: {excess:.3e} above the bound"
 
 
+@pytest.mark.parametrize("cin,cout,h,w,k,stride", [(33, 40, 9, 11, 3, 1), (64, 130, 12, 10, 3, 2), (512, 70, 7, 7, 3, 1), (160, 1, 15, 13, 5, 1)])
+def test_dense_layer_of_non_finite_values_in_a_used_workspace(cin, cout, h, w, k, stride):
+    """fp32: infinities and NaN come out where 64-bit arithmetic has them and nowhere else, in a workspace where the call
+    before left NaN (the rows behind the last filter are not written, and must not count)."""
+    if not torch.cuda.is_available():
+        pytest.skip("no GPU")
+    import paper_1905_00571_amd as cad
+    gen = torch.Generator().manual_seed(cin + cout)
+    x = torch.randn(2, cin, h, w, generator=gen)
+    wt = torch.randn(cout, cin, k, k, generator=gen) * (2.0 / (cin * k * k)) ** 0.5
+    b = torch.randn(cout, generator=gen)
+    wide = (cout + 127) // 128 * 128
+    conv = torch.nn.functional.conv2d
+    for bad in (False, True):
+        if bad:
+            x[0, 1, 0, 0], x[0, cin - 1, h - 1, w - 1], x[1, 0, h // 2, w // 2] = float("inf"), float("-inf"), float("nan")
+        cad.cadnn_release_workspaces()
+        cad.cadnn_dense_conv2d(torch.full((wide, cin, k, k), float("nan")).cuda(), torch.full_like(x, float("nan")).cuda(), stride, k // 2)
+        got = cad.cadnn_dense_conv2d(wt.cuda(), x.cuda(), stride, k // 2, b.cuda()).cpu()
+        ref = conv(x.double(), wt.double(), b.double(), stride, k // 2)
+        size = conv(x.double().abs(), wt.double().abs(), b.double().abs(), stride, k // 2)
+        finite = torch.isfinite(ref)
+        assert bool(finite.all()) != bad
+        assert torch.equal(torch.nan_to_num(got[~finite], 1.0, 2.0, 3.0), torch.nan_to_num(ref[~finite].float(), 1.0, 2.0, 3.0))
+        excess = ((got.double() - ref).abs() - (cin * k * k + 3) * 2.0 ** -24 * size)[finite].max().item()
+        assert excess <= 0.0, f"{excess:.3e} above the bound"
+
+
 def test_dense_layer_repeats_and_follows_new_weights():
     """Nothing of a call is kept for the next: new weights and inputs in the same tensors."""
     if not torch.cuda.is_available():
