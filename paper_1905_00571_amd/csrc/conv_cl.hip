@@ -33,11 +33,14 @@
 //   * fp32 storage: a float scaled by 2^24 is the sum of three bf16, exactly and whatever its size, and a product of two floats is six products of
 //     such parts but for 2^-24 of it at the most (2^-28 on average for normally distributed ones).  The bf16 pipes make six in 384 clocks of a 64 x 64 x 32 step, v_mfma_f32_32x32x2_f32
 //     the one in 1024.  Weights are laid out as their parts; a wave takes its activations apart in registers, which costs as
-//     many clocks as the products and runs beside them.  ResNet-50 fp32 at 8 images 1016 -> 805 us a pass (with two groups
-//     of waves and constants of its own).  Against 64 bits the error is 0.7 to 1.01 times that of fp32 products, K = 27 to 4608
-//     (3.4e-7 against 4.1e-7 at 512): six instructions round for 16 k where eight did.  What bounds a step now (860 to 940 clocks) is the
+//     many clocks as the products and runs beside them.  ResNet-50 fp32 at 8 images 1016 -> 830 us a pass (with two groups
+//     of waves and constants of its own).  The products of the leading parts have sums of their own, so that a sum is rounded once for 16 k (all six in
+//     one: six times, where fp32 products round once a nonzero, 1.6 to 3 of 16 in a pruned layer).  Against 64 bits, six products with two
+//     sums / with one / fp32 products: unpruned K = 576 0.8e-7 / 1.8e-7 / 4.3e-7, 4608 1.4e-7 / 3.7e-7 / 6.1e-7; ResNet-50 of mixed sparsity, the
+//     whole net, 1.02e-7 / 1.96e-7 / 1.11e-7.  What bounds a step now (860 to 940 clocks) is the
 //     products at the clock they leave the chip (490 for zeros, 610 for random operands and taking apart), then 20 KB into LDS.
-//     Sums that are not finite are done again with fp32 products, see there.
+//     Sums that are not finite are done again with fp32 products, without overlap: a layer with an infinity in every tile takes two to three
+//     times as long (512 -> 512 3x3 on 8 images of 14 x 14 86 -> 235 us).
 //   * K groups of waves in a workgroup: groups of four waves with stage buffers of their own walk parts of K side by side and exchange
 //     halves of their sums through LDS.  For workgroups that are alone on their CU.
 //   * K may be split over `sk` workgroups per tile (partial tiles at device scope, the last to arrive adds
@@ -337,14 +340,17 @@ __global__ __launch_bounds__(256 * KG, MI * NI == 1 ? 4 : 2) void cl_conv_kernel
             }
         }
     };
-    cl_f16v acc[AM][AN];
+    cl_f16v acc[AM][AN], low[SPLIT ? AM : 1][SPLIT ? AN : 1];
     auto clear_sums = [&]() __attribute__((always_inline)) {
 #pragma unroll
         for (int mi = 0; mi < AM; ++mi)
 #pragma unroll
             for (int ni = 0; ni < AN; ++ni)
 #pragma unroll
-                for (int i = 0; i < 16; ++i) acc[mi][ni][i] = 0.0f;
+                for (int i = 0; i < 16; ++i) {
+                    acc[mi][ni][i] = 0.0f;
+                    if constexpr (SPLIT) low[mi][ni][i] = 0.0f;
+                }
     };
     clear_sums();
 
@@ -455,27 +461,39 @@ __global__ __launch_bounds__(256 * KG, MI * NI == 1 ? 4 : 2) void cl_conv_kernel
         constexpr int G = RB / 64;
         const int fr = wm * 32 * AM + l31;
         const uint32_t fa = (uint32_t)(kg * C::GROUP + (fr / 64) * WB + (fr % 64) * 16 + fk * 1024);
-        cl_u4 af[2][3][AM], bf[2][2][AN];
-        auto read_weights = [&](int f, int g, int p, int mi, const char* st) __attribute__((always_inline)) {
-            af[f][p][mi] = *(const cl_u4*)(st + fa + mi / 2 * WB + mi % 2 * 512 + (g * 3 + p) * 2048);
+        // (The largest tile has registers for one set of weights: a part is read again for the next group behind its last product.)
+        constexpr int SETS = AM == 4 ? 1 : 2;
+        cl_u4 af[SETS][3][AM], bf[2][2][AN];
+        auto read_weights = [&](auto F, auto GRP, auto P, uint32_t buf) __attribute__((always_inline)) {
+            constexpr int f = decltype(F)::value % SETS, g = decltype(GRP)::value, p = decltype(P)::value;
+            const char* st = cl_smem + buf * STAGE;
+#pragma unroll
+            for (int mi = 0; mi < AM; ++mi) af[f][p][mi] = *(const cl_u4*)(st + fa + mi / 2 * WB + mi % 2 * 512 + (g * 3 + p) * 2048);
         };
-        auto read_group = [&](auto F, auto GRP, uint32_t buf) __attribute__((always_inline)) {
+        auto read_pixels = [&](auto F, auto GRP, uint32_t buf) __attribute__((always_inline)) {
             constexpr int f = decltype(F)::value, g = decltype(GRP)::value;
             const char* st = cl_smem + buf * STAGE;
 #pragma unroll
             for (int ni = 0; ni < AN; ++ni)
 #pragma unroll
                 for (int h = 0; h < 2; ++h) bf[f][h][ni] = *(const cl_u4*)(st + fb + ni * 32 * RB + (fp ^ (uint32_t)((2 * g + h) * 32)));
-#pragma unroll
-            for (int p = 2; p >= 0; --p)
-#pragma unroll
-                for (int mi = 0; mi < AM; ++mi) read_weights(f, g, p, mi, st);
         };
+        auto read_all_weights = [&](auto F, auto GRP, uint32_t buf) __attribute__((always_inline)) {
+            cl_static_for<0, 3>([&](auto I) __attribute__((always_inline)) {
+                read_weights(F, GRP, std::integral_constant<int, 2 - decltype(I)::value>(), buf);
+            });
+        };
+        auto read_group = [&](auto F, auto GRP, uint32_t buf) __attribute__((always_inline)) {
+            read_pixels(F, GRP, buf);
+            if constexpr (SETS == 2) read_all_weights(F, GRP, buf);
+        };
+        // (the last product, of the leading parts, has its own sum: the others' are 2^-8 of it and less, and so are their roundings)
         // x w = x1 w1 + (x1 w2 + x2 w1) + (x1 w3 + x2 w2 + x3 w1) + ...: what is left out, x2 w3 + x3 w2, is 2^-24 of a product at
         // the most (operands just above a power of two whose second parts are largest), and of either sign.  (`load(I)`, I < 6: called behind each product; vector and scalar arithmetic
-        // moves across, so that the next part is taken off beside the product before it)
+        // moves across, so that the next part is taken off beside the product before it; one set of weights: that of group GRP
+        // of buffer `buf` follows, if there is one)
         static_assert(AN == 1, "a wave takes one block of pixels apart");
-        auto multiply = [&](auto F, auto&& load) __attribute__((always_inline)) {
+        auto multiply = [&](auto F, auto GRP, bool follows, uint32_t buf, auto&& load) __attribute__((always_inline)) {
             constexpr int f = decltype(F)::value;
             cl_u4 x1, x2, x3;
 #pragma unroll
@@ -490,15 +508,20 @@ __global__ __launch_bounds__(256 * KG, MI * NI == 1 ? 4 : 2) void cl_conv_kernel
                 constexpr int i = decltype(I)::value, p = i == 0 ? 2 : i < 3 ? 1 : 0;
                 const cl_u4 x = i == 0 || i == 1 || i == 5 ? x1 : i == 3 ? x3 : x2;
 #pragma unroll
-                for (int mi = 0; mi < AM; ++mi)
-                    acc[mi][0] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(__builtin_bit_cast(cl_b8, af[f][p][mi]), __builtin_bit_cast(cl_b8, x),
-                                                                         acc[mi][0], 0, 0, 0);
+                for (int mi = 0; mi < AM; ++mi) {
+                    cl_f16v& to = i == 5 ? acc[mi][0] : low[mi][0];
+                    to = __builtin_amdgcn_mfma_f32_32x32x16_bf16(__builtin_bit_cast(cl_b8, af[f % SETS][p][mi]), __builtin_bit_cast(cl_b8, x), to, 0, 0, 0);
+                }
                 __builtin_amdgcn_sched_barrier(6);
+                if constexpr (SETS == 1 && (i == 0 || i == 2 || i == 5)) {
+                    if (follows) read_weights(F, GRP, std::integral_constant<int, p>(), buf);
+                }
                 load(I);
                 __builtin_amdgcn_sched_barrier(6);
             });
         };
         read_group(Set0(), Set0(), 0);
+        if constexpr (SETS == 1) read_all_weights(Set0(), Set0(), 0);
         uint32_t cur = 0;
         // A stage's loads start behind its barrier and end, where it has two groups, in front of the next one, between the
         // products of both: a load to LDS holds its wave until the memory pipeline has its addresses.
@@ -519,11 +542,11 @@ __global__ __launch_bounds__(256 * KG, MI * NI == 1 ? 4 : 2) void cl_conv_kernel
             constexpr int last = G == 2 ? f ^ 1 : f;
             if constexpr (G == 2) {
                 // (the first group has long landed; waited for behind the second's request, both would be)
-                __builtin_amdgcn_s_waitcnt(0xc07f);
+                if constexpr (SETS == 2) __builtin_amdgcn_s_waitcnt(0xc07f);
                 read_group(std::integral_constant<int, last>(), Set1(), cur);
                 __builtin_amdgcn_sched_barrier(0);
                 const uint32_t before = cur == 0 ? S - 1 : cur - 1;
-                multiply(F, [&](auto I) __attribute__((always_inline)) {
+                multiply(F, Set1(), true, cur, [&](auto I) __attribute__((always_inline)) {
                     if (pending) loads(Half(), Last(), I, before);
                 });
                 if (pending) advance();
@@ -536,7 +559,7 @@ __global__ __launch_bounds__(256 * KG, MI * NI == 1 ? 4 : 2) void cl_conv_kernel
                 read_group(std::integral_constant<int, last ^ 1>(), Set0(), nxt);
             }
             __builtin_amdgcn_sched_barrier(0);
-            multiply(std::integral_constant<int, last>(), [&](auto I) __attribute__((always_inline)) {
+            multiply(std::integral_constant<int, last>(), Set0(), full || s + 1 < steps, nxt, [&](auto I) __attribute__((always_inline)) {
                 if (more) loads(First(), Half(), I, cur);
             });
             __builtin_amdgcn_sched_barrier(0);
@@ -565,6 +588,12 @@ __global__ __launch_bounds__(256 * KG, MI * NI == 1 ? 4 : 2) void cl_conv_kernel
         // An infinity or a NaN among the operands, or operands or sums whose scale takes them beyond the range (2^104, 2^80), leave
         // sums that are not finite: a tile with such sums is done again with fp32 products, and they take what these give.
         // (Channels behind the last one have weights that nobody wrote.)
+#pragma unroll
+        for (int mi = 0; mi < AM; ++mi)
+#pragma unroll
+            for (int ni = 0; ni < AN; ++ni)
+#pragma unroll
+                for (int i = 0; i < 16; ++i) acc[mi][ni][i] += low[mi][ni][i];
         float seen = 0.0f;
         auto look = [&](auto ALL) __attribute__((always_inline)) {
 #pragma unroll
@@ -601,7 +630,8 @@ __global__ __launch_bounds__(256 * KG, MI * NI == 1 ? 4 : 2) void cl_conv_kernel
                 cl_wait<0>();
                 cl_barrier();
                 cl_static_for<0, G>([&](auto GRP) __attribute__((always_inline)) {
-                    read_group(Set0(), GRP, 0);
+                    read_pixels(Set0(), GRP, 0);
+                    read_all_weights(Set0(), GRP, 0);
 #pragma unroll
                     for (int i = 0; i < 8; ++i)
 #pragma unroll

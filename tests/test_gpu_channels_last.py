@@ -344,6 +344,34 @@ def test_fp32_products_of_extreme_values(cad, cin, cout, k, hw):
     net.free()
 
 
+@pytest.mark.parametrize("cin,cout,k,sparsity", [(64, 64, 1, 0.9), (512, 128, 1, 0.9), (256, 64, 3, 0.8), (64, 64, 3, 0.95), (96, 64, 3, 0.0)])
+def test_fp32_sums_are_as_exact_as_a_chain_over_the_nonzeros(cad, cin, cout, k, sparsity):
+    """fp32 storage with every tile, against 64 bits: no further off (2-norm) than products and sums of the stored weights alone, one
+    after the other in fp32, for zeros add no rounding there.  (1.15: the two are random walks of different steps.)"""
+    pad, n, hw = k // 2, 1, 12
+    ops = [Op("conv", "a", 0, 1, cin, cout, k, 1, pad, sparsity, False), Op("conv", "b", 1, 2, cout, 8, 1, 1, 0, 0.5, False)]
+    x, ws, bs = wl.net_tensors(ops, f"exact-{cin}-{k}", (n, cin, hw, hw), input_relu=True)
+    bs[0] = np.zeros(cout, np.float32)
+    w = ws[0].reshape(cout, cin, k, k)
+    padded = np.pad(x, ((0, 0), (0, 0), (pad, pad), (pad, pad)))
+    chain, ref = np.zeros((n, cout, hw, hw), np.float32), np.zeros((n, cout, hw, hw))
+    for co in range(cout):
+        for ci, r, c in np.argwhere(w[co]):
+            part = padded[:, ci, r:r + hw, c:c + hw]
+            chain[:, co] += w[co, ci, r, c] * part
+            ref[:, co] += np.float64(w[co, ci, r, c]) * part.astype(np.float64)
+    off = lambda y: float(np.sqrt(((y - ref) ** 2).sum() / (ref ** 2).sum()))
+    net = cad.build_net(ops, ws, bs, x.shape, cad.F32, use_graph=False)
+    net.set_op_variant(0, "cl_mfma_64x64_s3")
+    for name in net.op_candidates(0):
+        net.set_op_variant(0, name)
+        net.run(torch.from_numpy(x).cuda())
+        torch.cuda.synchronize()
+        got = off(net.read_buffer(1, ref.shape))
+        assert got <= 1.15 * off(chain), f"{name}: {got:.3e}, a chain {off(chain):.3e}"
+    net.free()
+
+
 def assert_fp32_sums(got, ref, size, terms, what):
     """Infinities and NaN where 64-bit arithmetic has them, else within (terms + 3) 2^-24 size."""
     finite = np.isfinite(ref)
