@@ -91,10 +91,12 @@ def kernel_of(variant: str) -> str:
     """The __global__ function a variant name is an instantiation of."""
     if variant.startswith("dense_mfma") and not variant.endswith("_64x64x32"):
         return "dense_wide_kernel"
+    if variant.startswith("cl_mfma") and variant.endswith("_w8"):
+        return "cl_small_kernel"
     return KERNEL_OF_PREFIX.get(variant.split("_")[0], variant)
 
 
-MFMA_KERNELS = ("dense_conv_kernel", "dense_wide_kernel", "cl_conv_kernel")
+MFMA_KERNELS = ("dense_conv_kernel", "dense_wide_kernel", "cl_conv_kernel", "cl_small_kernel")
 
 
 def main() -> int:

@@ -22,7 +22,7 @@
 //     requested before anything is computed, divisions are multiplications, and bias and residual are
 //     requested ahead of the K loop.  ResNet-50 fp16, us per pass before these and the stages above -> behind them:
 //     batch 1 371 -> 316, 8 517 -> 427, 32 981 -> 839; MobileNet-V2 fp16 batch 16 490 -> 353.
-//     At batch 32 the matrix pipes are busy 68 % of the busy CUs' cycles, over all of these launches; L2 hit rate 75 %.
+//     At batch 32 the four matrix pipes of a CU are busy 18 % of the busy CUs' cycles, over all of these launches; L2 hit rate 76 %.
 //   * Padding is a zero halo in memory, so no tap is ever tested.
 //   * A fused 1x1 projection shortcut (paper Section 4, layer fusion) is more K steps on a second tensor.
 //   * The epilogue works on the accumulators where they are: the rows of a block of weights are in an order that leaves a lane
@@ -917,16 +917,20 @@ cadnn_status cl_prepare_variant(const ClVariant& v, ClPlan* plan, int64_t pixels
 // (the latency of loads that run two stages ahead) and the CU's rate when it does not.  The
 // constants are fitted to the times of every variant, in fp16 on 387 layers (ResNet-50 at 1, 8, 16 and 32 images, MobileNet-V2
 // at 16, VGG-16 at 1, Inception-V3 at 4), the tiles taken 1.7 % slower in sum than each layer's best; in fp32 on 190 layers (ResNet-50 at 1, 2,
-// 4, 8, VGG-16 at 1 and 2, Inception-V3 at 1 and 3, both MobileNets): 0.3 %, against 8.1 % with constants from fp32 products
-// (steps of 64 bytes excepted, where a second group costs more than those times say: 16 -> 58 7x7 on 28 x 28 as a call 17.7 us split
-// in four, 20.2 in two of two groups).
+// 4, 8, VGG-16 at 1 and 2, Inception-V3 at 1 and 3, both MobileNets): 0.3 %, against 8.1 % with constants from fp32 products.
+// Timed inside the pass, with the kernels as they are now: 3.5 % on 516 fp16 layers (ResNet-50 at 1 to 8 images, MobileNet-V2 at 4 and 16,
+// Inception-V3 at 1 and 2, VGG-16), 1.9 % on 254 fp32 ones (ResNet-50 at 2, 4 and 8, VGG-16 at 4, Inception-V3 at 3).  Four stages in fp32 are
+// the best of 3 of those 254 and this rule never takes them: a pin and tuning do.  Steps of 64 bytes with two groups have a constant from one
+// layer, as they cost more alone than inside a net: 16 -> 58 7x7 on 28 x 28 as a call 17.7 us split in four, 20.2 in two of two groups.
 // Two groups of waves pay in fp32 where a workgroup has the CU to itself: 128 -> 128 3x3 on 8 images of 28 x 28 19.2 -> 16.9 us,
 // 512 -> 512 3x3 on 14 x 14 (split in four as well) 20.8 -> 17.9.  In fp16 a step is bound by the way into LDS, and what
 // they gain on such a layer (7.3 -> 6.5 us launched on its own) is lost again between the launches of a graph: ResNet-50 at 8 images 426 -> 435 us a
-// pass.  So in 2-byte storage neither this rule nor tuning, which times layers alone, takes them; a pin does.  Small tiles (conv_cl_small.hip) are a start, a launch that grows with the workgroups, and their operands at 18 bytes a clock;
+// pass.  So in 2-byte storage neither this rule nor tuning, which times layers alone, takes them; a pin does.
+// Small tiles (conv_cl_small.hip) are a start, a launch that grows with the workgroups, and their operands at 18 bytes a clock;
 // in graphs of equal layers at one image, us a layer, best large tile / best small one: 256 -> 256 3x3 on 14 x 14 8.6 / 7.0, 1024 -> 256
 // 1x1 5.5 / 4.0, 128 -> 128 3x3 on 28 x 28 7.2 / 6.4, 2048 -> 512 1x1 on 7 x 7 7.4 / 6.2; 256 -> 1024 1x1 5.9 / 6.7, 64 -> 256 1x1 on
-// 56 x 56 4.3 / 8.8; at 4 images 1024 -> 256 5.7 / 5.4, 256 -> 256 3x3 9.1 / 10.7.  Four stages pay where workgroups are alone or two to a CU and the K loop is long; there is no use for more: six and eight
+// 56 x 56 4.3 / 8.8; at 4 images 1024 -> 256 5.7 / 5.4, 256 -> 256 3x3 9.1 / 10.7.  Of the 516 layers 269 take one, 3.3 % slower in sum than
+// the best (the others 3.7 %).  Four stages pay where workgroups are alone or two to a CU and the K loop is long; there is no use for more: six and eight
 // measured the same.
 struct ClCost {
     double matrix, bytes;           // the CU's rate: clocks of a 64 x 64 tile's step of 128 bytes, bytes a clock

@@ -201,7 +201,8 @@ hipError_t launch_small_rb(const ClArgs& a, const ClVariant& v, hipStream_t s) {
 hipError_t launch_cl_small(const ClArgs& args, const ClVariant& v, int rb, hipStream_t s) {
     ClArgs a = args;
     a.per_slice = (a.steps * (rb / 64) + kWaves - 1) / kWaves;
-    // A die fetches its tiles' operands from behind its L2: where the weights are the larger one, it owns output channels.
+    // A die fetches its tiles' operands from behind its L2: where the weights are the larger one, it owns output channels.  (ResNet-50
+    // fp16 at one image, always pixels / this: 280.3 / 278.4 us a pass, runs of either within 0.4 %.)
     a.pixels_first = a.wspan > a.xt.span;
     if (a.pixels_first) {
         a.tiles_m = (a.total + v.tn() - 1) / v.tn();
